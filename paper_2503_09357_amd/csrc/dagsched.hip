@@ -36,6 +36,7 @@
 #include "kernel_contended.h"
 #include "kernel_general.h"
 #include "kernel_ring.h"
+#include "kernel_schedule.h"
 #include "kernel_search.h"
 #include "kernel_static.h"
 #include "kernel_util.h"
@@ -43,12 +44,11 @@
 using namespace dagsched_dev;
 
 // Scratch of dagsched_schedule_static, the entry point for callers that cannot allocate: one order-list row and one
-// end-time row of kStaticMaxNodes int32 each, then the small output block of the one-candidate evaluation.  The
+// end-time row of kStaticMaxNodes int32 each.  The
 // array's name is a host-side stand-in only; host code uses the device address that hipGetSymbolAddress returns for
 // the current device (every GPU holds a copy of its own), kept per device in g_scratch.
 constexpr int kStaticMaxNodes = DAGSCHED_STATIC_MAX_NODES;
-constexpr size_t kScratchOut = 2 * sizeof(int32_t) * (size_t)kStaticMaxNodes;
-constexpr size_t kScratchBytes = kScratchOut + 32 + 8 * DAGSCHED_MAX_DEVICES;
+constexpr size_t kScratchBytes = 2 * sizeof(int32_t) * (size_t)kStaticMaxNodes;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -122,9 +122,13 @@ struct dagsched {
   uint8_t *d_st_machine = nullptr;
   int32_t *d_st_off = nullptr;
   int64_t *d_st_base = nullptr;
-  // search helpers: machine counts of a base schedule; one row of general-kernel workspace and outputs
-  int32_t *ws_cnt = nullptr, *ws_sched_list = nullptr, *ws_sched_end = nullptr;
-  unsigned char *ws_sched_out = nullptr;
+  // search helpers: machine counts of a base schedule
+  int32_t *ws_cnt = nullptr;
+  // start and end times of one schedule: rows of scratch, where the end times live, ring slots, LDS of the workgroup
+  int32_t *ws_sched_list = nullptr, *ws_sched_end = nullptr;
+  int32_t *d_red_ptr = nullptr, *d_red_idx = nullptr;   // predecessor CSR without the implied edges
+  bool sched_lds_cells = false;
+  int32_t n_red = 0, sched_slots = 0, sched_lds = 0;
   // candidate-minor input staging
   int32_t *ws_tp = nullptr, *ws_tr = nullptr, *ws_te = nullptr;
   // evaluation with channel contention: edge tables and one workspace row per resident workgroup
@@ -228,8 +232,8 @@ bool dev_alloc(T **dst, size_t n) {
 void free_handle(dagsched *h) {
   if (!h) return;
   void *bufs[] = {h->d_pred_ptr, h->d_pred_idx, h->d_dur, h->d_comm, h->d_mem, h->d_weight, h->d_limit, h->ws_list, h->ws_end, h->d_rec,
-                  h->d_comm_scaled, h->d_nparts, h->ws_list16, h->ws_pib, h->ws_cnt, h->ws_sched_list, h->ws_sched_end,
-                  h->ws_sched_out, h->d_fb_count, h->d_fb_list, h->ws_meta, h->ws_tp, h->ws_tr, h->d_no_channel, h->d_edges,
+                  h->d_comm_scaled, h->d_nparts, h->ws_list16, h->ws_pib, h->ws_cnt, h->ws_sched_list, h->ws_sched_end, h->d_red_ptr, h->d_red_idx,
+                  h->d_fb_count, h->d_fb_list, h->ws_meta, h->ws_tp, h->ws_tr, h->d_no_channel, h->d_edges,
                   h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_base, h->ws_te, h->d_pred_eid, h->d_edge_src, h->d_edge_dst, h->d_succ_ptr,
                   h->wc_list, h->wc_end, h->wc_tlist, h->wc_tend, h->wc_ccnt, h->wc_coff, h->wc_echan};
   for (void *b : bufs)
@@ -293,8 +297,52 @@ struct RingPlan {
   LdsLayout lds_ingest{};
 };
 
+// Predecessors of every operation without the edges that other paths imply.  An edge (u, v) is left out when B has another path u -> w1 -> ... -> wk -> v
+// whose intermediate durations sum to at least the largest channel delay: then s_v >= e_wk >= ... >= e_u +
+// sum D^o_wi >= e_u + delta(u, v) whatever the candidate, so eqs. (11)-(13) for (u, v) are implied (and a cycle
+// through (u, v) also runs through that path).  Fewer parts mean fewer relaxer trips on the critical path, and
+// a pipeline's operations keep a single predecessor each (the forward -> backward edge of a stage is implied by
+// the path through the next stage), which selects a lighter kind of kernel.  Bounded search: six hops, 512
+// visits (four hops do for the plain pipelines, six for the bidirectional one with its transfer operations).
+using PredLists = std::vector<std::vector<int32_t>>;
+PredLists reduce_preds(const dagsched_desc_t *d, const std::vector<int32_t> &pred_ptr, const std::vector<int32_t> &pred_idx) {
+  const int N = d->n_nodes, P = d->n_devices;
+  int64_t max_comm = 0;
+  for (int a = 0; a < P; ++a)
+    for (int b = 0; b < P; ++b)
+      if (a != b) max_comm = std::max<int64_t>(max_comm, d->comm[a * P + b]);
+  PredLists op_preds(N);
+  struct Item { int32_t node, hops; int64_t sum; };
+  std::vector<Item> stack;
+  auto implied = [&](int32_t u, int32_t v) {
+    stack.clear();
+    stack.push_back({u, 0, 0});
+    int visits = 0;
+    while (!stack.empty()) {
+      const Item it = stack.back();
+      stack.pop_back();
+      if (++visits > 512) return false;
+      for (int32_t k = d->row_ptr[it.node]; k < d->row_ptr[it.node + 1]; ++k) {
+        const int32_t y = d->col_idx[k];
+        if (y == v) {
+          if (it.hops >= 1 && it.sum >= max_comm) return true;
+        } else if (it.hops + 1 < 6) {
+          stack.push_back({y, it.hops + 1, it.sum + d->dur[y]});
+        }
+      }
+    }
+    return false;
+  };
+  for (int v = 0; v < N; ++v) {
+    const int deg = pred_ptr[v + 1] - pred_ptr[v];
+    for (int k = pred_ptr[v]; k < pred_ptr[v + 1]; ++k)
+      if (deg < 2 || !implied(pred_idx[k], v)) op_preds[v].push_back(pred_idx[k]);
+  }
+  return op_preds;
+}
+
 RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_ptr, const std::vector<int32_t> &pred_idx,
-                   int64_t sum_dur, int lds_max, int n_cu) {
+                   const PredLists &reduced, int64_t sum_dur, int lds_max, int n_cu) {
   RingPlan plan;
   const int N = d->n_nodes, P = d->n_devices, Pseg = next_pow2(P);
   int64_t g = 0, max_comm = 0;
@@ -334,42 +382,7 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   plan.scale = (int32_t)g;
 
   constexpr int PR = 4;                                // DAG predecessors per op part
-  // Predecessor lists of the ops.  An edge (u, v) is left out when B has another path u -> w1 -> ... -> wk -> v
-  // whose intermediate durations sum to at least the largest channel delay: then s_v >= e_wk >= ... >= e_u +
-  // sum D^o_wi >= e_u + delta(u, v) whatever the candidate, so eqs. (11)-(13) for (u, v) are implied (and a cycle
-  // through (u, v) also runs through that path).  Fewer parts mean fewer relaxer trips on the critical path, and
-  // a pipeline's operations keep a single predecessor each (the forward -> backward edge of a stage is implied by
-  // the path through the next stage), which selects a lighter kind of kernel.  Bounded search: six hops, 512
-  // visits (four hops do for the plain pipelines, six for the bidirectional one with its transfer operations).
-  std::vector<std::vector<int32_t>> op_preds(N);
-  {
-    struct Item { int32_t node, hops; int64_t sum; };
-    std::vector<Item> stack;
-    auto implied = [&](int32_t u, int32_t v) {
-      stack.clear();
-      stack.push_back({u, 0, 0});
-      int visits = 0;
-      while (!stack.empty()) {
-        const Item it = stack.back();
-        stack.pop_back();
-        if (++visits > 512) return false;
-        for (int32_t k = d->row_ptr[it.node]; k < d->row_ptr[it.node + 1]; ++k) {
-          const int32_t y = d->col_idx[k];
-          if (y == v) {
-            if (it.hops >= 1 && it.sum >= max_comm) return true;
-          } else if (it.hops + 1 < 6) {
-            stack.push_back({y, it.hops + 1, it.sum + d->dur[y]});
-          }
-        }
-      }
-      return false;
-    };
-    for (int v = 0; v < N; ++v) {
-      const int deg = pred_ptr[v + 1] - pred_ptr[v];
-      for (int k = pred_ptr[v]; k < pred_ptr[v + 1]; ++k)
-        if (deg < 2 || !implied(pred_idx[k], v)) op_preds[v].push_back(pred_idx[k]);
-    }
-  }
+  std::vector<std::vector<int32_t>> op_preds = reduced;   // (sorted below)
   // shared operator records, part i of node v at [i * plane + v]
   const uint32_t dummy = (uint32_t)N;
   int max_parts = 1;
@@ -769,6 +782,15 @@ bool allow_large_lds(const void *kernel, int device, int bytes) {
   return true;
 }
 
+using ScheduleKernel = void (*)(ScheduleParams);
+ScheduleKernel schedule_kernel_for(const dagsched *h) {   // lanes per machine: as many as a wavefront has, at most eight
+  const bool l = h->sched_lds_cells;
+  return h->Pseg <= 8    ? (l ? schedule_kernel<8, true> : schedule_kernel<8, false>)
+         : h->Pseg == 16 ? (l ? schedule_kernel<4, true> : schedule_kernel<4, false>)
+         : h->Pseg == 32 ? (l ? schedule_kernel<2, true> : schedule_kernel<2, false>)
+                         : (l ? schedule_kernel<1, true> : schedule_kernel<1, false>);
+}
+
 size_t channel_flag_lds(int32_t n_nodes) {               // mask words + one byte per node
   return (size_t)DAGSCHED_MAX_DEVICES * sizeof(uint64_t) + (size_t)n_nodes;
 }
@@ -950,16 +972,17 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
 
   RingPlan plan;
   StaticPlan splan;
+  const PredLists reduced = reduce_preds(desc, pred_ptr, pred_idx);
   const bool force_general = desc->shape && desc->shape->kernel == 1;
   if (!force_general && desc->shared_placement && !(desc->shape && desc->shape->ignore_shared_placement))
     splan = plan_static(desc, pred_ptr, pred_idx, sum_dur, lds_max, n_cu);
-  if (!force_general && !splan.ok) plan = plan_ring(desc, pred_ptr, pred_idx, sum_dur, lds_max, n_cu);
+  if (!force_general && !splan.ok) plan = plan_ring(desc, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
   const bool need_general = splan.ok || !plan.ok || !plan.exact;
 
   bool ok = upload(&h->d_mem, desc->mem_delta, (size_t)h->N) &&
             (!desc->weight || upload(&h->d_weight, desc->weight, (size_t)h->N)) &&
             (!desc->mem_limit || upload(&h->d_limit, desc->mem_limit, (size_t)h->P));
-  // the general kernel's view of the problem is always resident: dagsched_schedule runs it on one candidate
+  // the plain view of the problem is always resident: dagsched_schedule reads it
   ok = ok && upload(&h->d_pred_ptr, pred_ptr.data(), (size_t)h->N + 1) &&
        upload(&h->d_pred_idx, pred_idx.data(), (size_t)h->E) &&
        upload(&h->d_dur, desc->dur, (size_t)h->N) &&
@@ -969,8 +992,22 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
                          (channel_flag_lds(h->N) <= 48 * 1024 ||
                           allow_large_lds((const void *)channel_flag_kernel, h->device, (int)channel_flag_lds(h->N))))) &&
        dev_alloc(&h->ws_cnt, (size_t)DAGSCHED_MAX_DEVICES) &&
-       dev_alloc(&h->ws_sched_list, (size_t)h->row_stride) && dev_alloc(&h->ws_sched_end, (size_t)h->row_stride) &&
-       dev_alloc(&h->ws_sched_out, (size_t)(32 + 8 * DAGSCHED_MAX_DEVICES));
+       dev_alloc(&h->ws_sched_list, (size_t)h->row_stride) && dev_alloc(&h->ws_sched_end, (size_t)h->row_stride);
+  std::vector<int32_t> red_ptr((size_t)h->N + 1, 0), red_idx;
+  for (int32_t v = 0; v < h->N; ++v) {
+    red_idx.insert(red_idx.end(), reduced[v].begin(), reduced[v].end());
+    red_ptr[v + 1] = (int32_t)red_idx.size();
+  }
+  h->n_red = (int32_t)red_idx.size();
+  ok = ok && upload(&h->d_red_ptr, red_ptr.data(), red_ptr.size()) && upload(&h->d_red_idx, red_idx.data(), red_idx.size());
+  // one schedule: the deepest rings that fit beside the end times; end times in the L2 when not even shallow ones do
+  for (const auto &[slots, lds_cells] : {std::pair<int, bool>{32, true}, {16, true}, {32, false}}) {
+    ScheduleParams sp{};
+    sp.N = h->N; sp.P = h->P; sp.slots = slots;
+    h->sched_lds_cells = lds_cells; h->sched_slots = slots; h->sched_lds = (int32_t)schedule_lds(&sp, lds_cells);
+    if (h->sched_lds <= lds_max) break;
+  }
+  ok = ok && h->sched_lds <= lds_max && (h->sched_lds <= 48 * 1024 || allow_large_lds((const void *)schedule_kernel_for(h), h->device, h->sched_lds));
   if (ok && need_general) {
     h->gen_G = kWave / h->Pseg;
     const int64_t lds_need = (int64_t)h->gen_G * h->N * 4;
@@ -1023,7 +1060,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       fsh.window_cells = -1;
       dagsched_desc_t fd = *desc;
       fd.shape = &fsh;
-      const RingPlan fp = plan_ring(&fd, pred_ptr, pred_idx, sum_dur, lds_max, n_cu);
+      const RingPlan fp = plan_ring(&fd, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
       // (same records, part counts and delays: both plans divide by the same common factor and drop the same edges)
       if (fp.ok && fp.exact && fp.cell32 && !fp.lds.wide && fp.scale == plan.scale && fp.rec_plane == plan.rec_plane &&
           fp.id_bits == plan.id_bits && fp.rec.size() == plan.rec.size()) {
@@ -1037,7 +1074,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
         // too large for that: the misses of the window go to the 16-bit kernel with a cell per operation (its own range
         // stops to a second list and the general kernel)
         fsh.state_bits = 0;
-        const RingPlan gp = plan_ring(&fd, pred_ptr, pred_idx, sum_dur, lds_max, n_cu);
+        const RingPlan gp = plan_ring(&fd, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
         if (gp.ok && !gp.cell32 && !gp.win_log2 && !gp.lds.wide && gp.scale == plan.scale && gp.rec_plane == plan.rec_plane &&
             gp.id_bits == plan.id_bits && gp.rec.size() == plan.rec.size()) {
           h->fb_G = gp.G; h->fb_slots = gp.ring; h->fb_feeders = gp.feeders; h->fb_block = gp.block; h->fb_lds = gp.lds; h->fb_kind = gp.kind;
@@ -1213,28 +1250,19 @@ int dagsched_select(dagsched_t *h, int32_t n_cand, const int32_t *makespan, cons
 }
 
 namespace {
-// One candidate through the int32 kernel with its order list and end times in the given workspace rows (row_stride
-// int32 each; the kernel writes every entry it later reads, so the rows need no clearing), its outputs in `o`
-// (32 + 8 * DAGSCHED_MAX_DEVICES bytes), then start = end - duration.
-int launch_schedule(dagsched_t *h, int32_t *list_row, int32_t *end_row, unsigned char *o, const int32_t *placement,
-                    const int32_t *rank, int32_t *start, int32_t *end, int32_t *flag, hipStream_t stream) {
-  GeneralParams p;
-  p.N = h->N; p.P = h->P; p.Pseg = h->Pseg; p.G = 1; p.C = 1;
-  p.row_stride = h->row_stride;
-  p.pred_ptr = h->d_pred_ptr; p.pred_idx = h->d_pred_idx; p.dur = h->d_dur; p.comm = h->d_comm; p.mem_delta = h->d_mem;
-  p.weight = h->d_weight; p.mem_limit = h->d_limit;
-  p.sum_dur = h->sum_dur;
+// list_row, end_row: N int32 of scratch each (the kernel writes every entry it later reads, so they need no clearing)
+int launch_schedule(dagsched_t *h, int32_t *list_row, int32_t *end_row, const int32_t *placement, const int32_t *rank,
+                    int32_t *start, int32_t *end, int32_t *flag, hipStream_t stream) {
+  ScheduleParams p{};
+  p.N = h->N; p.P = h->P; p.Pseg = h->Pseg; p.n_red = h->n_red; p.slots = h->sched_slots;
+  p.pred_ptr = h->d_pred_ptr; p.pred_idx = h->d_pred_idx; p.red_ptr = h->d_red_ptr; p.red_idx = h->d_red_idx; p.dur = h->d_dur; p.comm = h->d_comm;
+  p.no_channel = h->d_no_channel;
+  p.mem_delta = h->d_mem; p.weight = h->d_weight; p.mem_limit = h->d_limit;
   p.placement = placement; p.rank = rank;
-  p.ws_list = list_row; p.ws_end = end_row;
-  p.cand_list = nullptr; p.cand_count = nullptr;
-  p.out.makespan = (int32_t *)o; p.out.flags = (int32_t *)(o + 4); p.out.bubble = (int64_t *)(o + 8);
-  p.out.peak_mem = (int64_t *)(o + 16); p.out.peak_stride_c = h->P; p.out.peak_stride_j = 1;
-  hipLaunchKernelGGL(relax_general_kernel<false>, dim3(1), dim3(kWave), 0, stream, p);
-  if (h->d_no_channel)
-    hipLaunchKernelGGL(channel_flag_kernel, dim3(1), dim3(1024), channel_flag_lds(h->N), stream, h->N, h->E, h->P,
-                       h->d_edges, h->d_no_channel, placement, p.out);
-  hipLaunchKernelGGL(schedule_out_kernel, dim3((unsigned)std::min(256, (h->N + 255) / 256)), dim3(256), 0, stream, h->N,
-                     h->d_dur, end_row, (const int32_t *)(o + 4), start, end, flag);
+  p.list = list_row; p.cells = end_row;
+  p.start = start; p.end = end; p.flag = flag;
+  const uint32_t lds = schedule_lds(&p, h->sched_lds_cells);
+  hipLaunchKernelGGL(schedule_kernel_for(h), dim3(1), dim3(kScheduleThreads), lds, stream, p);
   if (!hip_ok(hipGetLastError(), "kernel launch")) return DAGSCHED_EHIP;
   return DAGSCHED_OK;
 }
@@ -1243,8 +1271,7 @@ int launch_schedule(dagsched_t *h, int32_t *list_row, int32_t *end_row, unsigned
 int dagsched_schedule(dagsched_t *h, const int32_t *placement, const int32_t *rank, int32_t *start, int32_t *end,
                       int32_t *flag, void *hip_stream) {
   if (!h || !placement || !rank || !start || !end || !flag) return DAGSCHED_EINVAL;
-  return launch_schedule(h, h->ws_sched_list, h->ws_sched_end, h->ws_sched_out, placement, rank, start, end, flag,
-                         (hipStream_t)hip_stream);
+  return launch_schedule(h, h->ws_sched_list, h->ws_sched_end, placement, rank, start, end, flag, (hipStream_t)hip_stream);
 }
 
 int dagsched_schedule_static(dagsched_t *h, const int32_t *placement, const int32_t *rank, int32_t *start, int32_t *end,
@@ -1255,7 +1282,7 @@ int dagsched_schedule_static(dagsched_t *h, const int32_t *placement, const int3
   if (!ptr) return DAGSCHED_EHIP;                          // (dagsched_create resolves it; a handle implies it is there)
   // rows of row_stride <= kStaticMaxNodes entries each (N rounded up to 32, and kStaticMaxNodes is a multiple of 32)
   int32_t *list_row = (int32_t *)ptr, *end_row = list_row + kStaticMaxNodes;
-  return launch_schedule(h, list_row, end_row, ptr + kScratchOut, placement, rank, start, end, flag, (hipStream_t)hip_stream);
+  return launch_schedule(h, list_row, end_row, placement, rank, start, end, flag, (hipStream_t)hip_stream);
 }
 
 int dagsched_coarsen(int32_t n_nodes, int32_t n_edges, const int32_t *row_ptr, const int32_t *col_idx,
@@ -1380,7 +1407,7 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
   StaticPlan splan;
   if (!force_general && cleaned.shared_placement && !(cleaned.shape && cleaned.shape->ignore_shared_placement))
     splan = plan_static(&cleaned, pred_ptr, pred_idx, sum_dur, lds_bytes, n_cu);
-  if (!force_general && !splan.ok) plan = plan_ring(&cleaned, pred_ptr, pred_idx, sum_dur, lds_bytes, n_cu);
+  if (!force_general && !splan.ok) plan = plan_ring(&cleaned, pred_ptr, pred_idx, reduce_preds(&cleaned, pred_ptr, pred_idx), sum_dur, lds_bytes, n_cu);
   if (splan.ok || !plan.ok || !plan.exact) {
     h.gen_G = kWave / h.Pseg;
     const int64_t lds_need = (int64_t)h.gen_G * h.N * 4;

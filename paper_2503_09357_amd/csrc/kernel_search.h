@@ -1,6 +1,5 @@
 // Helpers for a planner that searches with the evaluator in its loop (the part a MIP solver plays in
-// Sec. IV-V): a one-move neighbourhood of a base schedule, the choice of the best feasible candidate,
-// and the start/end times of one schedule for a Gantt chart (cf. the charts of Sec. V).
+// Sec. IV-V): a one-move neighbourhood of a base schedule and the choice of the best feasible candidate.
 #pragma once
 
 #include "device_common.h"
@@ -107,21 +106,6 @@ __global__ __launch_bounds__(1024) void select_kernel(int32_t C, const int32_t *
     best[0] = (key == ~0ull) ? -1 : (int32_t)(uint32_t)key;
     best[1] = (key == ~0ull) ? -1 : (int32_t)(key >> 32);
   }
-}
-
-// start / end times of one evaluated schedule from the end-time array the general kernel left in its
-// workspace; -1 everywhere when the schedule carries a flag.
-__global__ __launch_bounds__(256) void schedule_out_kernel(int32_t N, const int32_t *__restrict__ dur,
-                                                            const int32_t *__restrict__ end_ws,
-                                                            const int32_t *__restrict__ flag_in, int32_t *__restrict__ start,
-                                                            int32_t *__restrict__ end, int32_t *__restrict__ flag_out) {
-  const int flag = *flag_in;
-  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < N; i += gridDim.x * blockDim.x) {
-    const int32_t e = end_ws[i];
-    start[i] = flag ? -1 : e - dur[i];
-    end[i] = flag ? -1 : e;
-  }
-  if (blockIdx.x == 0 && threadIdx.x == 0) *flag_out = flag;
 }
 
 }  // namespace dagsched_dev

@@ -1,0 +1,46 @@
+"""Start and end times of one schedule against the oracle where the kernel's split changes: lanes per machine (8 down to
+1), end times in LDS and in the L2, both ring depths, operations of many parts (more than the ring holds)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2503_09357_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n,p,fanin,window", [
+    (1, 1, 1, None), (2, 64, 1, None), (700, 1, 5, 30), (513, 8, 40, None), (514, 9, 33, 200), (640, 16, 17, 100), (641, 17, 9, 90),
+    (1300, 32, 8, 60), (1301, 33, 5, 60), (3000, 64, 12, 300), (19400, 64, 4, 400), (24000, 5, 3, 200), (28500, 31, 4, 500), (50001, 12, 4, 300)])
+def test_schedule_at_the_edges_of_its_splits(gpu_lib, n, p, fanin, window):
+    import torch
+    rng = np.random.default_rng(n)
+    print("[schedule] n=%d p=%d fanin=%d" % (n, p, fanin), flush=True)
+    w = W.random_instance(rng, n, p, 1, max_fanin=fanin, max_dur=60000 if n < 20000 else 9000, max_comm=4000, frac_arbitrary=0.0, frac_bad=0.0) \
+        if window is None else None
+    if w is None:
+        rp, ci = W.random_dag(rng, n, fanin, window=window)
+        pl, rk = W.list_schedules(rp, ci, p, 1, n)
+        w = W.Workload("window", p, rp, ci, rng.integers(0, 20000, n).astype(np.int32), rng.integers(0, 3000, (p, p)).astype(np.int32),
+                       rng.integers(-3, 4, n).astype(np.int64), pl, rk)
+    if n == 3000:                                            # the last of a topological order gets 1500 predecessors
+        src, dst = W.edges_from_csr(w.row_ptr, w.col_idx)
+        order = np.lexsort((w.rank[0],))
+        last = [v for v in range(n) if w.row_ptr[v] == w.row_ptr[v + 1]][-1]
+        more = np.array([v for v in order if v != last][:1500])
+        rp, ci = W.csr_from_edges(n, np.concatenate([src, more]), np.concatenate([dst, np.full(len(more), last)]))
+        pl, rk = W.list_schedules(rp, ci, p, 1, n)
+        w = W.Workload("one wide operation", p, rp, ci, w.dur, w.comm, w.mem_delta, pl, rk)
+    prob = oracle.Problem.of(w)
+    dev = torch.device("cuda", 0)
+    with gpu_lib.Evaluator.for_workload(w, max_candidates=1, shared_placement=None) as ev:
+        rk2 = w.rank[0].copy()                               # the second order is a cycle wherever it can be one
+        same = np.nonzero(w.placement[0] == w.placement[0, 0])[0]
+        rk2[same] = len(same) - 1 - rk2[same]
+        for rk in (w.rank[0], rk2):
+            s, e, f = (t.cpu().numpy() for t in ev.schedule(torch.from_numpy(w.placement[0]).to(dev), torch.from_numpy(rk).to(dev)))
+            flag, so, eo, _, _ = prob.schedule(w.placement[0], rk)
+            assert int(f[0]) == flag
+            assert (s == so).all() and (e == eo).all() if flag == 0 else (s == -1).all() and (e == -1).all()
