@@ -1331,54 +1331,63 @@ int dagsched_coarsen(int32_t n_nodes, int32_t n_edges, const int32_t *row_ptr, c
 
   CoarsenParams p{};
   p.n = n; p.n_edges = E; p.words = (n + 63) / 64; p.target = params->target_nodes;
-  p.edge_dur_max = params->edge_dur_max; p.edge_mem_max = params->edge_mem_max;
-  p.nonedge_dur_max = params->nonedge_dur_max; p.nonedge_mem_max = params->nonedge_mem_max;
-  std::vector<int64_t> dur64(dur, dur + n), req64(n, 0);
-  if (mem_req) req64.assign(mem_req, mem_req + n);
-  const size_t matrix = (size_t)n * (size_t)p.words;
-  std::vector<void *> owned;
-  auto alloc = [&](auto **dst, size_t count) {
-    if (!dev_alloc(dst, count)) return false;
-    owned.push_back((void *)*dst);
-    return true;
-  };
-  int32_t *d_row_ptr = nullptr, *d_col_idx = nullptr;
-  bool ok = alloc(&d_row_ptr, (size_t)n + 1) && alloc(&d_col_idx, (size_t)E) && alloc(&p.succ, matrix) && alloc(&p.pred, matrix) && alloc(&p.kept, matrix) &&
-            alloc(&p.dur, (size_t)n) && alloc(&p.mem, (size_t)n) && alloc(&p.req, (size_t)n) && alloc(&p.alive, (size_t)n) &&
-            alloc(&p.parent, (size_t)n) && alloc(&p.outdeg, (size_t)n) && alloc(&p.indeg, (size_t)n) && alloc(&p.only, (size_t)n) &&
-            alloc(&p.depth, (size_t)n) && alloc(&p.left, (size_t)n) && alloc(&p.index_of, (size_t)n) && alloc(&p.node_map, (size_t)n) &&
-            alloc(&p.c_row_ptr, (size_t)n + 1) && alloc(&p.c_col_idx, (size_t)E) && alloc(&p.c_dur, (size_t)n) &&
-            alloc(&p.c_mem, (size_t)n) && alloc(&p.c_req, (size_t)n) && alloc(&p.counts, 3);
-  p.row_ptr = d_row_ptr; p.col_idx = d_col_idx;
-  auto h2d = [&](void *dst, const void *src, size_t bytes) {
-    return bytes == 0 || hip_ok(hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice), "hipMemcpy");
-  };
-  ok = ok && h2d(d_row_ptr, row_ptr, sizeof(int32_t) * ((size_t)n + 1)) && h2d(d_col_idx, col_idx, sizeof(int32_t) * (size_t)E) &&
-       h2d(p.dur, dur64.data(), sizeof(int64_t) * (size_t)n) && h2d(p.mem, mem_delta, sizeof(int64_t) * (size_t)n) &&
-       h2d(p.req, req64.data(), sizeof(int64_t) * (size_t)n) &&
-       hip_ok(hipMemset(p.succ, 0, matrix * sizeof(unsigned long long)), "hipMemset") &&
-       hip_ok(hipMemset(p.pred, 0, matrix * sizeof(unsigned long long)), "hipMemset") &&
-       hip_ok(hipMemset(p.kept, 0, matrix * sizeof(unsigned long long)), "hipMemset");
-  int32_t counts[3] = {0, 0, 0};
-  std::vector<int64_t> out_dur(n);
+  // (no sum is negative: every negative threshold means the same)
+  p.edge_dur_max = std::max<int64_t>(-1, params->edge_dur_max); p.edge_mem_max = std::max<int64_t>(-1, params->edge_mem_max);
+  p.nonedge_dur_max = std::max<int64_t>(-1, params->nonedge_dur_max); p.nonedge_mem_max = std::max<int64_t>(-1, params->nonedge_mem_max);
+  p.at = coarsen_layout(n);
+  const bool in_lds = n <= kCoarsenLdsNodes;
+  // One block of device memory: what goes in, what comes out, and the work arrays when they are not in LDS.  Either
+  // part crosses in one copy from or to a host image of it (every copy of a few bytes costs as much as a large one).
+  size_t bytes = 0;
+  auto place = [&](size_t count, size_t size) { const size_t o = bytes; bytes += (count * size + 15) / 16 * 16; return o; };
+  const size_t N1 = (size_t)n, E1 = (size_t)E;
+  const size_t i_mem = place(N1, 8), i_req = place(mem_req ? N1 : 0, 8), i_row = place(N1 + 1, 4), i_dur = place(N1, 4), i_col = place(E1, 4);
+  const size_t in_bytes = bytes;
+  const size_t o_counts = place(4, 4), o_mem = place(N1, 8), o_req = place(N1, 8), o_dur = place(N1, 4), o_map = place(N1, 4),
+               o_row = place(N1 + 1, 4), o_col = place(E1, 4);
+  const size_t out_bytes = bytes - in_bytes;
+  const size_t o_arena = place(in_lds ? 0 : p.at.total, 1);
+  std::vector<unsigned char> image(std::max(in_bytes, out_bytes));
+  auto put = [&](size_t at, const void *src, size_t size) { if (size) memcpy(image.data() + at, src, size); };
+  put(i_mem, mem_delta, 8 * N1);
+  if (mem_req) put(i_req, mem_req, 8 * N1);
+  put(i_row, row_ptr, 4 * (N1 + 1)); put(i_dur, dur, 4 * N1); put(i_col, col_idx, 4 * E1);
+  unsigned char *dev = nullptr;
+  bool ok = dev_alloc(&dev, bytes) && hip_ok(hipMemcpy(dev, image.data(), in_bytes, hipMemcpyHostToDevice), "hipMemcpy");
   if (ok) {
-    hipLaunchKernelGGL(coarsen_kernel, dim3(1), dim3(1024), 0, (hipStream_t)nullptr, p);
-    ok = hip_ok(hipGetLastError(), "kernel launch") && hip_ok(hipDeviceSynchronize(), "hipDeviceSynchronize");
+    p.row_ptr = (const int32_t *)(dev + i_row); p.col_idx = (const int32_t *)(dev + i_col); p.dur = (const int32_t *)(dev + i_dur);
+    p.mem = (const int64_t *)(dev + i_mem); p.req = mem_req ? (const int64_t *)(dev + i_req) : nullptr;
+    p.counts = (int32_t *)(dev + o_counts); p.node_map = (int32_t *)(dev + o_map);
+    p.c_row_ptr = (int32_t *)(dev + o_row); p.c_col_idx = (int32_t *)(dev + o_col); p.c_dur = (int32_t *)(dev + o_dur);
+    p.c_mem = (int64_t *)(dev + o_mem); p.c_req = (int64_t *)(dev + o_req);
+    p.arena = dev + o_arena;
+    if (in_lds) {
+      const bool small = n <= 256;
+      const void *kernel = small ? (const void *)coarsen_lds_kernel<4> : (const void *)coarsen_lds_kernel<8>;
+      const size_t lds = coarsen_lds_bytes(small ? 4 : 8);
+      ok = lds <= 48 * 1024 || allow_large_lds(kernel, hip_device, (int)lds);
+      if (ok && small) hipLaunchKernelGGL(coarsen_lds_kernel<4>, dim3(1), dim3(256), lds, (hipStream_t)nullptr, p);
+      if (ok && !small) hipLaunchKernelGGL(coarsen_lds_kernel<8>, dim3(1), dim3(512), lds, (hipStream_t)nullptr, p);
+    } else {
+      ok = hip_ok(hipMemset(p.arena, 0, p.at.dur), "hipMemset");   // the three matrices
+      if (ok) hipLaunchKernelGGL(coarsen_kernel, dim3(1), dim3(1024), 0, (hipStream_t)nullptr, p);
+    }
+    ok = ok && hip_ok(hipGetLastError(), "kernel launch") && hip_ok(hipMemcpy(image.data(), dev + in_bytes, out_bytes, hipMemcpyDeviceToHost), "hipMemcpy");
   }
-  auto d2h = [&](void *dst, const void *src, size_t bytes) {
-    return bytes == 0 || hip_ok(hipMemcpy(dst, src, bytes, hipMemcpyDeviceToHost), "hipMemcpy");
-  };
-  ok = ok && d2h(counts, p.counts, sizeof(counts));
-  const size_t k = ok ? (size_t)counts[0] : 0;
-  int32_t coarse_edges = 0;
-  ok = ok && d2h(node_map, p.node_map, sizeof(int32_t) * (size_t)n) && d2h(c_row_ptr, p.c_row_ptr, sizeof(int32_t) * (k + 1));
-  if (ok) coarse_edges = c_row_ptr[k];
-  ok = ok && d2h(c_col_idx, p.c_col_idx, sizeof(int32_t) * (size_t)coarse_edges) && d2h(out_dur.data(), p.c_dur, sizeof(int64_t) * k) &&
-       d2h(c_mem_delta, p.c_mem, sizeof(int64_t) * k) && d2h(c_mem_req, p.c_req, sizeof(int64_t) * k);
   const bool oom = !ok && strstr(g_hip_error, "memory") != nullptr;
-  for (void *b : owned) (void)hipFree(b);
+  if (dev) (void)hipFree(dev);
   if (!ok) return oom ? DAGSCHED_ENOMEM : DAGSCHED_EHIP;
-  for (size_t i = 0; i < k; ++i) c_dur[i] = (int32_t)out_dur[i];
+  auto out = [&](size_t at) { return image.data() + (at - in_bytes); };
+  int32_t counts[3];
+  memcpy(counts, out(o_counts), sizeof(counts));
+  const size_t k = (size_t)counts[0];
+  memcpy(node_map, out(o_map), 4 * N1);
+  memcpy(c_row_ptr, out(o_row), 4 * (k + 1));
+  const int32_t coarse_edges = c_row_ptr[k];
+  if (coarse_edges) memcpy(c_col_idx, out(o_col), 4 * (size_t)coarse_edges);
+  memcpy(c_dur, out(o_dur), 4 * k);
+  memcpy(c_mem_delta, out(o_mem), 8 * k);
+  memcpy(c_mem_req, out(o_req), 8 * k);
   result->n_coarse = counts[0]; result->n_coarse_edges = coarse_edges;
   result->merges_edge = counts[1]; result->merges_nonedge = counts[2];
   return DAGSCHED_OK;
