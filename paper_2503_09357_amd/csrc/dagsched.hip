@@ -39,6 +39,7 @@
 #include "kernel_schedule.h"
 #include "kernel_search.h"
 #include "kernel_static.h"
+#include "kernel_transfers.h"
 #include "kernel_util.h"
 
 using namespace dagsched_dev;
@@ -137,6 +138,11 @@ struct dagsched {
   int32_t *wc_list = nullptr, *wc_end = nullptr, *wc_tlist = nullptr, *wc_tend = nullptr, *wc_ccnt = nullptr, *wc_coff = nullptr, *wc_echan = nullptr;
   int32_t wc_grid = 0;
   int64_t row_e = 0, row_c = 0;
+  // ... its fast path (transfers ranked as they are produced): total == 0 when the problem does not fit it
+  TransferParams tr{};
+  int32_t tr_grid = 0;
+  uint4 *d_out = nullptr, *wc_stream = nullptr;
+  int32_t *d_col_idx = nullptr, *d_tr_count = nullptr, *d_tr_list = nullptr;
 };
 
 namespace {
@@ -235,7 +241,8 @@ void free_handle(dagsched *h) {
                   h->d_comm_scaled, h->d_nparts, h->ws_list16, h->ws_pib, h->ws_cnt, h->ws_sched_list, h->ws_sched_end, h->d_red_ptr, h->d_red_idx,
                   h->d_fb_count, h->d_fb_list, h->ws_meta, h->ws_tp, h->ws_tr, h->d_no_channel, h->d_edges,
                   h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_base, h->ws_te, h->d_pred_eid, h->d_edge_src, h->d_edge_dst, h->d_succ_ptr,
-                  h->wc_list, h->wc_end, h->wc_tlist, h->wc_tend, h->wc_ccnt, h->wc_coff, h->wc_echan};
+                  h->wc_list, h->wc_end, h->wc_tlist, h->wc_tend, h->wc_ccnt, h->wc_coff, h->wc_echan,
+                  h->d_out, h->wc_stream, h->d_col_idx, h->d_tr_count, h->d_tr_list};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   delete h;
@@ -1120,6 +1127,32 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
          dev_alloc(&h->wc_echan, g * (size_t)h->row_e) &&
          dev_alloc(&h->wc_ccnt, g * (size_t)h->row_c) && dev_alloc(&h->wc_coff, g * (size_t)h->row_c) &&
          (h->layout != DAGSCHED_CAND_MINOR || dev_alloc(&h->ws_te, maxc * (size_t)std::max(E, 1)));
+    int32_t max_in = 0;
+    for (int32_t v = 0; v < h->N; ++v) max_in = std::max(max_in, pred_ptr[v + 1] - pred_ptr[v]);
+    TransferParams &tp = h->tr;
+    tp.N = h->N; tp.E = E; tp.P = h->P; tp.Pseg = h->Pseg; tp.log_pseg = ilog2(h->Pseg);
+    if (ok && max_in <= 255 && transfer_plan(&tp, kTransferThreads, h->max_cand, n_cu, (uint32_t)lds_max)) {   // (a byte counts an operation's messages)
+      std::vector<uint4> outs((size_t)h->N);
+      for (int32_t v = 0; v < h->N; ++v) {
+        uint32_t x[4] = {0, 0, 0, 0};
+        const int32_t lo = desc->row_ptr[v], deg = desc->row_ptr[v + 1] - lo;
+        for (int32_t e = 0; e < std::min(deg, 4); ++e) x[e] = (uint32_t)desc->col_idx[lo + e];
+        outs[v] = make_uint4((uint32_t)lo, (uint32_t)deg, x[0] | (x[1] << 16), x[2] | (x[3] << 16));
+      }
+      tp.row_items = ((int64_t)h->N + E + 7) / 8 * 8;
+      const int64_t groups = ((int64_t)h->max_cand + tp.G - 1) / tp.G;
+      h->tr_grid = (int32_t)std::min<int64_t>(groups, (int64_t)n_cu * std::max(1, std::min(2, lds_max / (int)tp.total)));
+      const int32_t zero[2] = {0, 0};
+      ok = upload(&h->d_out, outs.data(), outs.size()) && upload(&h->d_col_idx, desc->col_idx, (size_t)E) &&
+           upload(&h->d_tr_count, zero, 2) && dev_alloc(&h->d_tr_list, maxc) &&
+           dev_alloc(&h->wc_stream, (size_t)h->tr_grid * (size_t)tp.G * (size_t)tp.row_items) &&
+           allow_large_lds((const void *)transfer_kernel, h->device, (int)tp.total);
+      tp.out = h->d_out; tp.col_idx = h->d_col_idx; tp.dur = h->d_dur; tp.comm = h->d_comm;
+      tp.mem_delta = h->d_mem; tp.weight = h->d_weight; tp.mem_limit = h->d_limit; tp.sum_dur = h->sum_dur;
+      tp.stream = h->wc_stream; tp.fb_count = h->d_tr_count; tp.fb_list = h->d_tr_list;
+    } else {
+      tp.total = 0;
+    }
   }
   if (!ok) {
     const bool oom = strstr(g_hip_error, "memory") != nullptr;
@@ -1169,6 +1202,14 @@ int dagsched_evaluate_contended(dagsched_t *h, int32_t n_cand, const int32_t *pl
   p.ws_ccnt = h->wc_ccnt; p.ws_coff = h->wc_coff; p.ws_echan = h->wc_echan;
   p.row_n = h->row_stride; p.row_e = h->row_e; p.row_c = h->row_c;
   p.out = make_out(h, n_cand, makespan, bubble, peak_mem, flags);
+  p.cand_list = nullptr; p.cand_count = nullptr; p.ticket = nullptr;
+  if (h->tr.total) {                                    // first the candidates whose orders follow the producers, then what is left
+    TransferParams q = h->tr;
+    q.C = n_cand; q.placement = pl; q.rank = rk; q.edge_rank = er; q.out_ptrs = p.out;
+    const int64_t groups = ((int64_t)n_cand + q.G - 1) / q.G;
+    hipLaunchKernelGGL(transfer_kernel, dim3((unsigned)std::min<int64_t>(groups, h->tr_grid)), dim3(kTransferThreads), q.total, stream, q);
+    p.cand_list = h->d_tr_list; p.cand_count = h->d_tr_count; p.ticket = h->d_tr_count + 1;
+  }
   hipLaunchKernelGGL(relax_contended_kernel, dim3((unsigned)std::min(n_cand, h->wc_grid)), dim3((unsigned)contended_threads(h->P)), contended_lds(h->P), stream, p);
   if (h->d_no_channel)
     hipLaunchKernelGGL(channel_flag_kernel, dim3((unsigned)n_cand), dim3(n_cand < 2048 ? 1024 : 256), channel_flag_lds(N), stream, N, E,

@@ -1,4 +1,6 @@
-// Evaluation with channel contention (Sec. III, eqs. (11)-(15)), a placement per candidate.
+// Evaluation with channel contention (Sec. III, eqs. (11)-(15)), a placement per candidate, any order of the transfers.
+// (kernel_transfers.h is the fast path for orders that follow the producers; this kernel takes the candidates it leaves and
+// the problems that do not fit it.)
 //
 // The message of an edge (u, x) of B whose ends sit on different machines a, b is a transfer that occupies the
 // channel (a, b) for comm[a][b] time units: it starts once u has ended and the transfer before it on the channel
@@ -17,7 +19,7 @@
 // only when its bell has rung since it last looked (or right after it completed a transfer).  A round in which
 // nothing completes although something is left is a deadlock: a cycle through operations and transfers.
 // A workgroup takes one candidate after the other; its order lists, end times and channel tables live in a
-// workspace row of its own (indexed by the workgroup, not by the candidate), read and written at the L2.
+// workspace row of its own (indexed by the workgroup, not by the candidate).
 #pragma once
 
 #include "device_common.h"
@@ -53,6 +55,8 @@ struct ContendedParams {
   int32_t *ws_ccnt, *ws_coff;           // [grid][row_c] transfers per channel; start of the channel in ws_tlist
   int32_t *ws_echan;                    // [grid][row_e] channel a * P + b of edge k under this candidate, -1 inside a machine
   int64_t row_n, row_e, row_c;
+  const int32_t *cand_list;             // not NULL: evaluate cand_list[0 .. *cand_count) and leave *cand_count = 0 behind
+  int32_t *cand_count, *ticket;
   OutPtrs out;
 };
 
@@ -69,18 +73,20 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
   int32_t *ccnt = p.ws_ccnt + (int64_t)blockIdx.x * p.row_c, *coff = p.ws_coff + (int64_t)blockIdx.x * p.row_c;
   int32_t *echan = p.ws_echan + (int64_t)blockIdx.x * p.row_e;
 
-  for (int64_t c = blockIdx.x; c < p.C; c += gridDim.x) {
+  const int64_t n_todo = p.cand_list ? (int64_t)*p.cand_count : (int64_t)p.C;
+  for (int64_t item = blockIdx.x; item < n_todo; item += gridDim.x) {
+    const int64_t c = p.cand_list ? (int64_t)p.cand_list[item] : item;
     const int32_t *pl = p.placement + c * N, *rk = p.rank + c * N, *er = p.edge_rank + c * E;
     if (t < kWave) s_cnt[t] = 0;
     if (t == 0) { s_flag = 0; s_z = 0; }
-    for (int ch = t; ch < PP; ch += T) st_agent(&ccnt[ch], 0);
+    for (int ch = t; ch < PP; ch += T) st_group(&ccnt[ch], 0);
     __syncthreads();
     // x in range (eq. (6)), operations per machine
     for (int v = t; v < N; v += T) {
       const int32_t pi = pl[v];
       if ((uint32_t)pi >= (uint32_t)P) atomicOr(&s_flag, kBitBadPlacement);
       else atomicAdd(&s_cnt[pi], 1);
-      st_agent(&end[v], -1);
+      st_group(&end[v], -1);
     }
     __syncthreads();
     bool bad = s_flag != 0;                                 // the same for every thread
@@ -95,26 +101,26 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
       for (int v = t; v < N; v += T) {
         const int32_t pi = pl[v], r = rk[v];
         if ((uint32_t)r >= (uint32_t)s_cnt[pi]) atomicOr(&s_flag, kBitBadRank);
-        else st_agent(&list[s_off[pi] + r], v);
+        else st_group(&list[s_off[pi] + r], v);
       }
       // transfers per channel
       for (int k = t; k < E; k += T) {
         const int32_t a = pl[p.edge_src[k]], b = pl[p.edge_dst[k]];
         if (a != b) atomicAdd(&ccnt[a * P + b], 1);
-        st_agent(&echan[k], a != b ? a * P + b : -1);
-        st_agent(&tend[k], -1);
+        st_group(&echan[k], a != b ? a * P + b : -1);
+        st_group(&tend[k], -1);
       }
       __syncthreads();
       for (int v = t; v < N; v += T) {
         const int32_t pi = pl[v], r = rk[v];
-        if ((uint32_t)r < (uint32_t)s_cnt[pi] && ld_agent(&list[s_off[pi] + r]) != v) atomicOr(&s_flag, kBitBadRank);
+        if ((uint32_t)r < (uint32_t)s_cnt[pi] && ld_group(&list[s_off[pi] + r]) != v) atomicOr(&s_flag, kBitBadRank);
       }
       // start of every channel in the transfer list: each thread sums a block of consecutive channels, thread 0 scans
       const int per = (PP + T - 1) / T;
       int mine = 0;
       for (int i = 0; i < per; ++i) {
         const int ch = t * per + i;
-        if (ch < PP) mine += ld_agent(&ccnt[ch]);
+        if (ch < PP) mine += ld_group(&ccnt[ch]);
       }
       s_part[t] = mine;
       __syncthreads();
@@ -127,7 +133,7 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
         int at = s_part[t];
         for (int i = 0; i < per; ++i) {
           const int ch = t * per + i;
-          if (ch < PP) { st_agent(&coff[ch], at); at += ld_agent(&ccnt[ch]); }
+          if (ch < PP) { st_group(&coff[ch], at); at += ld_group(&ccnt[ch]); }
         }
       }
       __syncthreads();
@@ -137,8 +143,8 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
         if (a == b) continue;
         const int ch = a * P + b;
         const int32_t r = er[k];
-        if ((uint32_t)r >= (uint32_t)ld_agent(&ccnt[ch])) atomicOr(&s_flag, kBitBadRank);
-        else st_agent(&tlist[ld_agent(&coff[ch]) + r], k);
+        if ((uint32_t)r >= (uint32_t)ld_group(&ccnt[ch])) atomicOr(&s_flag, kBitBadRank);
+        else st_group(&tlist[ld_group(&coff[ch]) + r], k);
       }
       __syncthreads();
       for (int k = t; k < E; k += T) {
@@ -146,7 +152,7 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
         if (a == b) continue;
         const int ch = a * P + b;
         const int32_t r = er[k];
-        if ((uint32_t)r < (uint32_t)ld_agent(&ccnt[ch]) && ld_agent(&tlist[ld_agent(&coff[ch]) + r]) != k) atomicOr(&s_flag, kBitBadRank);
+        if ((uint32_t)r < (uint32_t)ld_group(&ccnt[ch]) && ld_group(&tlist[ld_group(&coff[ch]) + r]) != k) atomicOr(&s_flag, kBitBadRank);
       }
       __syncthreads();
       bad = s_flag != 0;
@@ -166,7 +172,7 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
         poll = (pl[u] == t) ? &end[u] : &tend[p.pred_eid[q]];   // eq. (12)
       };
       auto next_op = [&]() {
-        v = ld_agent(&list[k]);
+        v = ld_group(&list[k]);
         q = p.pred_ptr[v]; qend = p.pred_ptr[v + 1];
         acc = free_at;
         if (q < qend) next_edge();
@@ -183,9 +189,9 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
         c_at[i] = c_end[i] = c_free[i] = c_u[i] = 0;
         c_seen[i] = -1;
         if (ch < PP) {
-          c_at[i] = ld_agent(&coff[ch]);
-          c_end[i] = c_at[i] + ld_agent(&ccnt[ch]);
-          if (c_at[i] < c_end[i]) c_u[i] = p.edge_src[ld_agent(&tlist[c_at[i]])];
+          c_at[i] = ld_group(&coff[ch]);
+          c_end[i] = c_at[i] + ld_group(&ccnt[ch]);
+          if (c_at[i] < c_end[i]) c_u[i] = p.edge_src[ld_group(&tlist[c_at[i]])];
         }
       }
       __syncthreads();
@@ -194,7 +200,7 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
         bool progressed = false;
         if (k < kend) {
           while (q < qend) {                                  // in-edges deliver in any order; they are waited for in turn
-            const int32_t at = ld_agent(poll);
+            const int32_t at = ld_group(poll);
             if (at < 0) break;
             acc = max(acc, at);
             ++q;
@@ -203,15 +209,15 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
           }
           if (q == qend) {
             const int32_t e = acc + p.dur[v];                 // eq. (3); acc >= free_at: one operation at a time, eq. (7)
-            st_agent(&end[v], e);
+            st_group(&end[v], e);
             free_at = e;
             level += p.mem_delta[v];                          // eq. (19)
             peak = max(peak, level);
             if (p.weight) base += p.weight[v];                // eq. (16)
-            // (the end time must have arrived at the L2 before a bell is rung: the wavefront waits for its stores)
+            // (the end time must be out before a bell is rung: the wavefront waits for its stores)
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             for (int kq = p.succ_ptr[v]; kq < p.succ_ptr[v + 1]; ++kq) {   // the channels v feeds hear of it
-              const int ch = ld_agent(&echan[kq]);
+              const int ch = ld_group(&echan[kq]);
               if (ch >= 0) atomicAdd(&s_bell[ch], 1);
             }
             ++k;
@@ -226,13 +232,13 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
           if (c_at[i] < c_end[i]) {
             const int32_t bell = *(volatile int32_t *)&s_bell[t + i * T];
             if (bell != c_seen[i]) {
-              const int32_t eu = ld_agent(&end[c_u[i]]);
+              const int32_t eu = ld_group(&end[c_u[i]]);
               if (eu >= 0) {                                   // eq. (13); the channel is free from c_free on, eqs. (14)-(15)
                 const int32_t d = max(c_free[i], eu) + p.comm[t + i * T];   // eq. (11)
-                st_agent(&tend[ld_agent(&tlist[c_at[i]])], d);
+                st_group(&tend[ld_group(&tlist[c_at[i]])], d);
                 c_free[i] = d;
                 ++c_at[i];
-                if (c_at[i] < c_end[i]) c_u[i] = p.edge_src[ld_agent(&tlist[c_at[i]])];
+                if (c_at[i] < c_end[i]) c_u[i] = p.edge_src[ld_group(&tlist[c_at[i]])];
                 c_seen[i] = -1;                                // the next head's producer may have ended long ago
                 progressed = true;
               } else {
@@ -265,6 +271,10 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
       p.out.flags[c] = flag;
     }
     __syncthreads();                                         // the shared words are reset for the next candidate
+  }
+  if (p.cand_list && t == 0 && atomicAdd(p.ticket, 1) == (int32_t)gridDim.x - 1) {   // everybody has read the count
+    *p.cand_count = 0;
+    *p.ticket = 0;
   }
 }
 
