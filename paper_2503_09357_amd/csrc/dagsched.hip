@@ -141,8 +141,11 @@ struct dagsched {
   // ... its fast path (transfers ranked as they are produced): total == 0 when the problem does not fit it
   TransferParams tr{};
   int32_t tr_grid = 0;
-  uint4 *d_out = nullptr, *wc_stream = nullptr;
-  int32_t *d_col_idx = nullptr, *d_tr_count = nullptr, *d_tr_list = nullptr;
+  uint32_t *d_in_degree = nullptr;
+  uint2 *d_item = nullptr;
+  uint16_t *wc_stream = nullptr;
+  uint32_t *d_first = nullptr;
+  int32_t *d_tr_count = nullptr, *d_tr_list = nullptr;
 };
 
 namespace {
@@ -242,7 +245,7 @@ void free_handle(dagsched *h) {
                   h->d_fb_count, h->d_fb_list, h->ws_meta, h->ws_tp, h->ws_tr, h->d_no_channel, h->d_edges,
                   h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_base, h->ws_te, h->d_pred_eid, h->d_edge_src, h->d_edge_dst, h->d_succ_ptr,
                   h->wc_list, h->wc_end, h->wc_tlist, h->wc_tend, h->wc_ccnt, h->wc_coff, h->wc_echan,
-                  h->d_out, h->wc_stream, h->d_col_idx, h->d_tr_count, h->d_tr_list};
+                  h->d_item, h->d_in_degree, h->wc_stream, h->d_first, h->d_tr_count, h->d_tr_list};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   delete h;
@@ -789,6 +792,11 @@ bool allow_large_lds(const void *kernel, int device, int bytes) {
   return true;
 }
 
+using TransferKernel = void (*)(TransferParams);
+TransferKernel transfer_kernel_for(int lanes_per_machine) {
+  return lanes_per_machine == 4 ? transfer_kernel<4> : lanes_per_machine == 2 ? transfer_kernel<2> : transfer_kernel<1>;
+}
+
 using ScheduleKernel = void (*)(ScheduleParams);
 ScheduleKernel schedule_kernel_for(const dagsched *h) {   // lanes per machine: as many as a wavefront has, at most eight
   const bool l = h->sched_lds_cells;
@@ -1131,23 +1139,36 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     for (int32_t v = 0; v < h->N; ++v) max_in = std::max(max_in, pred_ptr[v + 1] - pred_ptr[v]);
     TransferParams &tp = h->tr;
     tp.N = h->N; tp.E = E; tp.P = h->P; tp.Pseg = h->Pseg; tp.log_pseg = ilog2(h->Pseg);
-    if (ok && max_in <= 255 && transfer_plan(&tp, kTransferThreads, h->max_cand, n_cu, (uint32_t)lds_max)) {   // (a byte counts an operation's messages)
-      std::vector<uint4> outs((size_t)h->N);
+    if (ok && max_in <= 255 && transfer_plan(&tp, h->max_cand, n_cu, (uint32_t)lds_max)) {   // (a byte counts an operation's messages)
+      const int R = tp.R;
+      const int64_t n_items = transfer_items(desc->row_ptr, h->N, R);
+      std::vector<uint32_t> first((size_t)h->N);
+      std::vector<uint2> item((size_t)n_items * R, make_uint2((uint32_t)h->N * 0x10001u, 0u));
+      uint32_t at = 0;
       for (int32_t v = 0; v < h->N; ++v) {
-        uint32_t x[4] = {0, 0, 0, 0};
         const int32_t lo = desc->row_ptr[v], deg = desc->row_ptr[v + 1] - lo;
-        for (int32_t e = 0; e < std::min(deg, 4); ++e) x[e] = (uint32_t)desc->col_idx[lo + e];
-        outs[v] = make_uint4((uint32_t)lo, (uint32_t)deg, x[0] | (x[1] << 16), x[2] | (x[3] << 16));
+        const uint32_t n = (uint32_t)std::max(1, (deg + R - 1) / R);
+        first[v] = at | (n << 16);
+        // (every lane of the operation's first item names the operation)
+        for (int r = 0; r < R; ++r) item[(size_t)at * R + r].x = (uint32_t)v | ((uint32_t)h->N << 16);
+        for (int32_t e = 0; e < deg; ++e) {
+          uint2 &x = item[(size_t)at * R + e];
+          x = make_uint2((x.x & 0xFFFFu) | ((uint32_t)desc->col_idx[lo + e] << 16), (uint32_t)(lo + e));
+        }
+        at += n;
       }
-      tp.row_items = ((int64_t)h->N + E + 7) / 8 * 8;
+      tp.row_items = (n_items + 63) / 64 * 64;
+      std::vector<uint32_t> in_degree(((size_t)h->N + 3) / 4, 0u);
+      for (int32_t v = 0; v < h->N; ++v) in_degree[v / 4] |= (uint32_t)(pred_ptr[v + 1] - pred_ptr[v]) << (v % 4 * 8);
       const int64_t groups = ((int64_t)h->max_cand + tp.G - 1) / tp.G;
-      h->tr_grid = (int32_t)std::min<int64_t>(groups, (int64_t)n_cu * std::max(1, std::min(2, lds_max / (int)tp.total)));
+      h->tr_grid = (int32_t)std::min<int64_t>(groups, (int64_t)n_cu * (tp.threads == 512 ? 2 : 1));
       const int32_t zero[2] = {0, 0};
-      ok = upload(&h->d_out, outs.data(), outs.size()) && upload(&h->d_col_idx, desc->col_idx, (size_t)E) &&
+      ok = upload(&h->d_first, first.data(), first.size()) && upload(&h->d_item, item.data(), item.size()) &&
+           upload(&h->d_in_degree, in_degree.data(), in_degree.size()) &&
            upload(&h->d_tr_count, zero, 2) && dev_alloc(&h->d_tr_list, maxc) &&
            dev_alloc(&h->wc_stream, (size_t)h->tr_grid * (size_t)tp.G * (size_t)tp.row_items) &&
-           allow_large_lds((const void *)transfer_kernel, h->device, (int)tp.total);
-      tp.out = h->d_out; tp.col_idx = h->d_col_idx; tp.dur = h->d_dur; tp.comm = h->d_comm;
+           allow_large_lds((const void *)transfer_kernel_for(tp.R), h->device, (int)tp.total);
+      tp.first = h->d_first; tp.item = h->d_item; tp.in_degree = h->d_in_degree; tp.dur = h->d_dur; tp.comm = h->d_comm;
       tp.mem_delta = h->d_mem; tp.weight = h->d_weight; tp.mem_limit = h->d_limit; tp.sum_dur = h->sum_dur;
       tp.stream = h->wc_stream; tp.fb_count = h->d_tr_count; tp.fb_list = h->d_tr_list;
     } else {
@@ -1207,7 +1228,7 @@ int dagsched_evaluate_contended(dagsched_t *h, int32_t n_cand, const int32_t *pl
     TransferParams q = h->tr;
     q.C = n_cand; q.placement = pl; q.rank = rk; q.edge_rank = er; q.out_ptrs = p.out;
     const int64_t groups = ((int64_t)n_cand + q.G - 1) / q.G;
-    hipLaunchKernelGGL(transfer_kernel, dim3((unsigned)std::min<int64_t>(groups, h->tr_grid)), dim3(kTransferThreads), q.total, stream, q);
+    hipLaunchKernelGGL(transfer_kernel_for(q.R), dim3((unsigned)std::min<int64_t>(groups, h->tr_grid)), dim3((unsigned)q.threads), q.total, stream, q);
     p.cand_list = h->d_tr_list; p.cand_count = h->d_tr_count; p.ticket = h->d_tr_count + 1;
   }
   hipLaunchKernelGGL(relax_contended_kernel, dim3((unsigned)std::min(n_cand, h->wc_grid)), dim3((unsigned)contended_threads(h->P)), contended_lds(h->P), stream, p);

@@ -1,0 +1,50 @@
+"""Evaluation with channel contention against the oracle where its fast path changes shape: one, two and four lanes per
+machine, one to many candidates per workgroup, deep and shallow rings, operations with many outputs, and what it leaves to
+the other kernel (orders that do not follow the producers, more than 255 inputs, more than 65000 operations and edges)."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import test_gpu_channels as T
+from paper_2503_09357_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _star(rng, n, fan, inward):
+    """A chain of n operations plus `fan` edges into the last or out of the first one."""
+    src, dst = list(range(n - 1)), list(range(1, n))
+    for k in range(1, fan + 1):
+        src.append(k if inward else 0)
+        dst.append(n - 1 if inward else k + 1)
+    return W.csr_from_edges(n, src, dst)
+
+
+@pytest.mark.parametrize("n,p,c,kind", [
+    (5, 1, 3, "random"), (300, 2, 700, "random"), (301, 4, 1500, "dense"), (257, 8, 3000, "sparse"), (900, 16, 520, "dense"),
+    (1000, 17, 300, "random"), (640, 32, 1030, "dense"), (700, 33, 90, "sparse"), (800, 64, 300, "dense"), (4000, 64, 40, "random"),
+    (16000, 7, 9, "random"), (25000, 5, 3, "sparse"), (150, 5, 40, "out"), (300, 5, 40, "in"), (420, 9, 20, "in255"), (20000, 6, 3, "large")])
+def test_shapes_of_the_fast_path(gpu_lib, n, p, c, kind):
+    rng = np.random.default_rng(n)
+    if kind in ("out", "in", "in255"):
+        rp, ci = _star(rng, n, {"out": 120, "in": 280, "in255": 254}[kind], kind != "out")
+    else:
+        rp, ci = W.random_dag(rng, n, {"dense": 6, "random": 3, "sparse": 1, "large": 6}[kind], window=400)
+    pl, rk = W.list_schedules(rp, ci, p, c, n)
+    for i in range(0, c, 7):                                 # some cycles and some malformed candidates
+        j = np.nonzero(pl[i] == pl[i, 0])[0]
+        rk[i, j] = rk[i, j][::-1].copy()
+    if c > 5:
+        rk[3, n // 2] = -1
+        pl[5, n // 3] = p
+    w = W.Workload("transfers n=%d p=%d %s" % (n, p, kind), p, rp, ci, rng.integers(0, 9, n).astype(np.int32),
+                   rng.integers(0, 90, (p, p)).astype(np.int32), rng.integers(-5, 6, n).astype(np.int64), pl, rk)
+    if n % 2:
+        w.weight, w.mem_limit = rng.integers(0, 9, n).astype(np.int64), np.full(p, 5 * n // p + 20, np.int64)
+    er = W.fcfs_edge_ranks(rp, ci, p, pl, rk)
+    some = np.arange(c) % 5 == 1                             # orders that do not follow the producers, and bad ones
+    er[some] = T._shuffle_some_channels(rng, W.Workload("", p, rp, ci, w.dur, w.comm, w.mem_delta, pl[some], rk[some]), er[some])
+    if c > 9:
+        er[8] = er[8] + 1
+    T._parity(gpu_lib, w, er, layout=n % 2, repeats=2)
