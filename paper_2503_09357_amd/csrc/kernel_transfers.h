@@ -272,6 +272,7 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
     const int ql = lane_on ? ml : 0, g = ql >> p.log_pseg, j = ql & (Pseg - 1);
     const bool ok = lane_on && g < ng && flagw[g] == 0 && j < P;
     const uint32_t n_items = ok ? items[ql] : 0u;
+    __syncthreads();                                         // (everyone has read the flags before an accountant adds one)
     const int ring_mask = p.slots - 1;
     const uint32_t acc0 = (uint32_t)g * p.acc_stride >> 2;   // LDS address / 4 of this candidate's arrival times, and of its channels
     const uint32_t free0 = (p.o_free + (uint32_t)g * p.free_stride) >> 2;
