@@ -237,7 +237,7 @@ int dagsched_schedule(dagsched_t *h, const int32_t *placement, const int32_t *ra
 /*
  * dagsched_schedule for callers that cannot allocate or have no workspace to give: code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same results and same asynchrony as
- * dagsched_schedule, but the per-call scratch (one order-list row, one end-time row, a small output block) lives in
+ * dagsched_schedule, but the per-call scratch (one order-list row, one end-time row) lives in
  * a static device array of the library instead of the handle's workspace: 256 KiB that every GPU a handle
  * was made on holds until the process ends.  The call allocates and frees nothing.  Problems with more than
  * DAGSCHED_STATIC_MAX_NODES operations are refused with DAGSCHED_ESCRATCH (nothing is enqueued).  All calls on
