@@ -1162,15 +1162,16 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       for (int32_t v = 0; v < h->N; ++v) in_degree[v / 4] |= (uint32_t)(pred_ptr[v + 1] - pred_ptr[v]) << (v % 4 * 8);
       const int64_t groups = ((int64_t)h->max_cand + tp.G - 1) / tp.G;
       h->tr_grid = (int32_t)std::min<int64_t>(groups, (int64_t)n_cu * (tp.threads == 512 ? 2 : 1));
-      const int32_t zero[2] = {0, 0};
+      const int32_t zero[3] = {0, 0, 0};
       ok = upload(&h->d_first, first.data(), first.size()) && upload(&h->d_item, item.data(), item.size()) &&
            upload(&h->d_in_degree, in_degree.data(), in_degree.size()) &&
-           upload(&h->d_tr_count, zero, 2) && dev_alloc(&h->d_tr_list, maxc) &&
+           upload(&h->d_tr_count, zero, 3) && dev_alloc(&h->d_tr_list, maxc) &&
            dev_alloc(&h->wc_stream, (size_t)h->tr_grid * (size_t)tp.G * (size_t)tp.row_items) &&
            allow_large_lds((const void *)transfer_kernel_for(tp.R), h->device, (int)tp.total);
       tp.first = h->d_first; tp.item = h->d_item; tp.in_degree = h->d_in_degree; tp.dur = h->d_dur; tp.comm = h->d_comm;
       tp.mem_delta = h->d_mem; tp.weight = h->d_weight; tp.mem_limit = h->d_limit; tp.sum_dur = h->sum_dur;
-      tp.stream = h->wc_stream; tp.fb_count = h->d_tr_count; tp.fb_list = h->d_tr_list;
+      tp.stream = h->wc_stream; tp.fb_count = h->d_tr_count; tp.ticket = h->d_tr_count + 1; tp.fb_todo = h->d_tr_count + 2;
+      tp.fb_list = h->d_tr_list;
     } else {
       tp.total = 0;
     }
@@ -1223,13 +1224,13 @@ int dagsched_evaluate_contended(dagsched_t *h, int32_t n_cand, const int32_t *pl
   p.ws_ccnt = h->wc_ccnt; p.ws_coff = h->wc_coff; p.ws_echan = h->wc_echan;
   p.row_n = h->row_stride; p.row_e = h->row_e; p.row_c = h->row_c;
   p.out = make_out(h, n_cand, makespan, bubble, peak_mem, flags);
-  p.cand_list = nullptr; p.cand_count = nullptr; p.ticket = nullptr;
+  p.cand_list = nullptr; p.cand_count = nullptr;
   if (h->tr.total) {                                    // first the candidates whose orders follow the producers, then what is left
     TransferParams q = h->tr;
     q.C = n_cand; q.placement = pl; q.rank = rk; q.edge_rank = er; q.out_ptrs = p.out;
     const int64_t groups = ((int64_t)n_cand + q.G - 1) / q.G;
     hipLaunchKernelGGL(transfer_kernel_for(q.R), dim3((unsigned)std::min<int64_t>(groups, h->tr_grid)), dim3((unsigned)q.threads), q.total, stream, q);
-    p.cand_list = h->d_tr_list; p.cand_count = h->d_tr_count; p.ticket = h->d_tr_count + 1;
+    p.cand_list = h->d_tr_list; p.cand_count = h->d_tr_count + 2;
   }
   hipLaunchKernelGGL(relax_contended_kernel, dim3((unsigned)std::min(n_cand, h->wc_grid)), dim3((unsigned)contended_threads(h->P)), contended_lds(h->P), stream, p);
   if (h->d_no_channel)

@@ -55,8 +55,8 @@ struct ContendedParams {
   int32_t *ws_ccnt, *ws_coff;           // [grid][row_c] transfers per channel; start of the channel in ws_tlist
   int32_t *ws_echan;                    // [grid][row_e] channel a * P + b of edge k under this candidate, -1 inside a machine
   int64_t row_n, row_e, row_c;
-  const int32_t *cand_list;             // not NULL: evaluate cand_list[0 .. *cand_count) and leave *cand_count = 0 behind
-  int32_t *cand_count, *ticket;
+  const int32_t *cand_list;             // not NULL: evaluate cand_list[0 .. *cand_count)
+  const int32_t *cand_count;
   OutPtrs out;
 };
 
@@ -271,10 +271,6 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
       p.out.flags[c] = flag;
     }
     __syncthreads();                                         // the shared words are reset for the next candidate
-  }
-  if (p.cand_list && t == 0 && atomicAdd(p.ticket, 1) == (int32_t)gridDim.x - 1) {   // everybody has read the count
-    *p.cand_count = 0;
-    *p.ticket = 0;
   }
 }
 
