@@ -22,7 +22,11 @@
 //             other kernel.
 //   HELPERS   the other waves: look the items up and put them into rings in LDS, 16 bytes a lane, ahead of the relaxer.
 // They never meet at a barrier before the end.  Item i of a lane goes to ring slot i mod slots; the last half word of the entry is
-// i, written last, which tells the relaxer that it is there; the relaxer tells how many it has taken every four steps.
+// i + slots, written last, which tells the relaxer that it is there (what the slot held before is less); the relaxer tells how
+// many it has taken, plus slots, every four steps.  The R lanes of a machine have to stay in step: the delays of messages that
+// share a channel are laid out for lanes that read the channel's time in the same step.  An LDS access of a wavefront need
+// not be one moment for all its lanes, so what a lane reads of another wavefront's writing is never acted upon alone: an
+// item is taken when the least of its lanes' tags says so, and a helper goes as far as the least of the lanes' counts.
 //
 // What bounds it is the chain of dependent steps (MoE graph: a candidate's longest path of operations and messages),
 // each an LDS round trip and about 40 instructions of a lone wavefront.  MoE graph, 512 candidates, two workgroups of one
@@ -70,7 +74,7 @@ inline int64_t transfer_items(const int32_t *row_ptr, int n, int R) {
 // Shape for a problem, or false when it does not fit (the other kernel then does everything).
 inline bool transfer_plan(TransferParams *p, int64_t n_cand, int n_cu, uint32_t lds_max) {
   const uint32_t N = (uint32_t)p->N, E = (uint32_t)p->E, P = (uint32_t)p->P;
-  if ((uint64_t)N + E > 65000u) return false;            // item numbers and ranks are 16-bit
+  if ((uint64_t)N + E > 65000u) return false;            // item numbers and tags are 16-bit
   auto up = [](uint32_t x, uint32_t a) { return (x + a - 1) / a * a; };
   p->acc_stride = up(4 * (N + 1), 16);
   p->free_stride = up(4 * P * P, 16);
@@ -108,7 +112,7 @@ inline bool transfer_plan(TransferParams *p, int64_t n_cand, int n_cu, uint32_t 
 }
 
 // R: lanes per machine.  Ring entry of a lane: x = own operation | receiver << 16 (as LDS addresses of arrival times / 4),
-// y = duration, z = delay (negative: no message), w = channel (likewise) | number of the item << 16.
+// y = duration, z = delay (negative: no message), w = channel (likewise) | tag << 16.
 template <int R>
 __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferParams p) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -120,7 +124,7 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
   int32_t *const off = mcount + 64;                          // [64] list position of the machine's first operation
   uint32_t *const item0 = (uint32_t *)(off + 64);            // [64] the lane's first item, and its number of items
   uint32_t *const items = item0 + 64;
-  uint32_t *const taken = items + 64;                        // [64] items the relaxer has taken from the ring
+  uint32_t *const taken = items + 64;                        // [64] tag of the item the relaxer takes next
   int32_t *const flagw = (int32_t *)(taken + 64);            // [64] (G used)
   uint32_t *const seenw = (uint32_t *)(flagw + 64);          // [accountants][64] transfers so far, by receiving machine
   int32_t *const misc = (int32_t *)(seenw + 64 * p.accountants);            // [0] 1: the relaxer is through
@@ -261,9 +265,9 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
     // nothing has arrived anywhere; entry N of every candidate (the operation of items without one) stays 0
     for (int i = tid; i < (int)(G * p.acc_stride / 4); i += T) ((uint32_t *)lds)[i] = 0;
     for (int i = tid; i < (int)(G * p.free_stride / 4); i += T) ((uint32_t *)(lds + p.o_free))[i] = 0;
-    // (no slot holds the item that is looked for in it first)
-    for (int i = tid; i < p.slots * kWave; i += T) ((u32x4_t *)(lds + p.o_ring))[i] = u32x4_t{0u, 0u, 0u, 0xFFFF0000u};
-    if (tid < 64) taken[tid] = 0;
+    // (a tag below every one that is looked for)
+    for (int i = tid; i < p.slots * kWave; i += T) ((u32x4_t *)(lds + p.o_ring))[i] = u32x4_t{0u, 0u, 0u, 0u};
+    if (tid < 64) taken[tid] = (uint32_t)p.slots;
     if (tid == 0) misc[0] = 0;
     __syncthreads();
 
@@ -277,6 +281,12 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
     const int ring_mask = p.slots - 1;
     const uint32_t acc0 = (uint32_t)g * p.acc_stride >> 2;   // LDS address / 4 of this candidate's arrival times, and of its channels
     const uint32_t free0 = (p.o_free + (uint32_t)g * p.free_stride) >> 2;
+    // least of a machine's lanes, in each of them (all lanes of the wavefront take part)
+    auto least = [](uint32_t x) {
+      if (R >= 2) x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true));   // lane ^ 1
+      if (R >= 4) x = min(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true));   // lane ^ 2
+      return x;
+    };
     uint32_t x_acc = 0;
     bool cyclic = false;
     if (wave == 0) {
@@ -285,10 +295,11 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
       const uint32_t cnt_k = p.o_cnt + (uint32_t)g * p.cnt_stride - acc0;   // LDS address of a count = index of the arrival time + this
       const uint32_t none = (acc0 + (uint32_t)N) * 0x10001u;
       const uint64_t segmask = ((Pseg * R == kWave) ? ~0ull : ((1ull << (Pseg * R)) - 1ull)) << (g * Pseg * R);
-      uint32_t t = 0;
+      uint32_t t = (uint32_t)p.slots;                        // tag of the next item
+      const uint32_t t_end = n_items + (uint32_t)p.slots;
       uint64_t have = 0;                                     // lanes that hold an item
       bool dead = false;
-      u32x4_t w = {none, 0u, kNoMessage, free0}, nw = {0u, 0u, 0u, 0xFFFF0000u};   // the item at work, and the content of ring slot t
+      u32x4_t w = {none, 0u, kNoMessage, free0}, nw = {0u, 0u, 0u, 0u};   // the item at work, and the content of the next one's ring slot
       // arrival time and open messages of the item's operation; when its channel is free
       uint32_t arr = 0, cnt = 0, ch0 = 0;
       lds_vu32_t *const taken_p = (lds_vu32_t *)(ldsb + (uint32_t)((unsigned char *)taken - lds) + (uint32_t)lane * 4u);
@@ -303,7 +314,14 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
           const bool ran = lane_bit(ran_m);
           const uint32_t d = max(e, ch0) + w.z;              // eqs. (11), (13)-(15)
           x_acc = ran ? e : x_acc;
-          const uint64_t take_m = (ran_m | ~have) & __ballot((nw.w >> 16) == (t & 0xFFFFu));
+          uint64_t there;                                    // machines whose next item is there in all their lanes
+          if (R == 4) {                                      // (missing in any lane of the four: one scalar instruction; two moves cost 1 % of a step)
+            asm("s_wqm_b64 %0, %1" : "=s"(there) : "s"(__ballot((nw.w >> 16) != (t & 0xFFFFu))) : "scc");
+            there = ~there;
+          } else {
+            there = __ballot((least(nw.w) >> 16) == (t & 0xFFFFu));
+          }
+          const uint64_t take_m = (ran_m | ~have) & there;
           const bool take = lane_bit(take_m);
           have = (have & ~ran_m) | take_m;
           moved |= ran_m | take_m;
@@ -318,21 +336,22 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
           const uint32_t own = w.x & 0xFFFFu;
           cnt = *(lds_cu8_t *)(uintptr_t)(own + cnt_k);
           arr = *(lds_vu32_t *)(uintptr_t)(own << 2);
-          ch0 = *(lds_vu32_t *)(uintptr_t)lo16_x4(w.w);
-          t += take ? 1u : 0u;
+          uint64_t carry;
+          asm("v_addc_co_u32 %0, %1, %2, 0, %3" : "=v"(t), "=&s"(carry) : "v"(t), "s"(take_m));   // t + 1 where taken
           nw = *(lds_vu32x4_t *)(ring_lane + ((t & (uint32_t)ring_mask) << 10));
+          ch0 = *(lds_vu32_t *)(uintptr_t)lo16_x4(w.w);      // (needed last: read before the entry it costs 8 us of 592)
           if (sub == 3 || sub == 7) *taken_p = t;
           __builtin_amdgcn_sched_barrier(0);                 // (all reads are on their way before the first is waited for)
         }
         const bool held = lane_bit(have);
-        bool through = dead || (!held && t == n_items);
+        bool through = dead || (!held && t == t_end);
         const uint64_t open = __ballot(!through);
         if (open == 0) break;
         // every unfinished machine of a candidate holds an item and none of them moved in eight steps: a cycle
         const uint64_t stuck = (__ballot(held) | ~open) & ~moved;
         if (!through && (stuck & segmask) == segmask) { dead = cyclic = true; }
       }
-      if (done_turns == max_turns && !(dead || (!lane_bit(have) && t == n_items))) flagw[g] = kBitInternal;   // never expected
+      if (done_turns == max_turns && !(dead || (!lane_bit(have) && t == t_end))) flagw[g] = kBitInternal;   // never expected
       *(lds_vu32_t *)(ldsb + (uint32_t)((unsigned char *)misc - lds)) = 1u;
       __builtin_amdgcn_s_setprio(0);
     } else if (wave <= p.accountants) {
@@ -433,7 +452,7 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
       lds_vu32_t *const done_p = (lds_vu32_t *)(ldsb + (uint32_t)((unsigned char *)misc - lds));
       uint32_t f = (uint32_t)h;                              // the lane's next item that is this wavefront's
       while (__ballot(f < n_items) != 0 && !*done_p) {       // (the relaxer always ends, and says so)
-        const uint32_t upto = min(n_items, *taken_p + (uint32_t)p.slots);
+        const uint32_t upto = min(n_items, least(*taken_p));
         if (__ballot(f < upto) == 0) { __builtin_amdgcn_s_sleep(2); continue; }
         // (messages of one item on one channel: the second one starts when the first is through, which is what twice the
         // delay says.  Three items at a time: each is three lookups, one behind the other)
@@ -469,11 +488,11 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
             }
             if (at >= upto) continue;
             const uint32_t chan = to[u] >= 0 ? (uint32_t)(j * P + to[u]) + free0 : free0;
-            // (the number of the item last: it says that the rest is there)
-            const u32x4_t val = {q[u].x + bias_x, dur[u], to[u] >= 0 ? delay[u] * times : kNoMessage, chan | (~at << 16)};
+            // (the tag last: it says that the rest is there; until then the one before it)
+            const u32x4_t val = {q[u].x + bias_x, dur[u], to[u] >= 0 ? delay[u] * times : kNoMessage, chan | (at << 16)};
             lds_byte_t *const sp = ldsb + p.o_ring + ((at & (uint32_t)ring_mask) << 10) + (uint32_t)lane * 16u;
             *(lds_vu32x4_t *)sp = val;
-            *(lds_vu32_t *)(sp + 12) = chan | (at << 16);
+            *(lds_vu32_t *)(sp + 12) = chan | ((at + (uint32_t)p.slots) << 16);
           }
 #pragma unroll
           for (int u = 0; u < kI; ++u) f += f < upto ? (uint32_t)nh : 0u;

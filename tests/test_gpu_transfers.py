@@ -48,3 +48,19 @@ def test_shapes_of_the_fast_path(gpu_lib, n, p, c, kind):
     if c > 9:
         er[8] = er[8] + 1
     T._parity(gpu_lib, w, er, layout=n % 2, repeats=2)
+
+
+@pytest.mark.parametrize("p,c", [(1, 70), (3, 2100), (9, 600), (16, 40), (17, 300), (32, 40), (32, 600), (40, 40)])
+def test_messages_of_one_operation_share_a_channel(gpu_lib, p, c):
+    """Seven messages per operation, most of them over the same channel, and channels that everything waits for: the lanes
+    of a machine send them side by side, with delays laid out for lanes that stay in step."""
+    rng = np.random.default_rng(100 * p + c)
+    n, fan = 420, 7
+    src = np.repeat(np.arange(n - fan), fan)
+    dst = src + np.tile(np.arange(1, fan + 1), n - fan)
+    rp, ci = W.csr_from_edges(n, src, dst)
+    where = np.unique([0, p // 2, p - 1])[rng.integers(0, len({0, p // 2, p - 1}), n)].astype(np.int32)
+    pl, rk = W.list_schedules(rp, ci, p, c, n, fixed_placement=where)
+    w = W.Workload("shared channels p=%d" % p, p, rp, ci, rng.integers(0, 4, n).astype(np.int32),
+                   rng.integers(20, 90, (p, p)).astype(np.int32), rng.integers(-5, 6, n).astype(np.int64), pl, rk)
+    T._parity(gpu_lib, w, W.fcfs_edge_ranks(rp, ci, p, pl, rk), repeats=3)
