@@ -362,7 +362,7 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
       auto begin = [&](int g_at, int m_at) {
         for (;; m_at += p.accountants) {
           while (m_at >= P) { m_at -= P; ++g_at; }
-          if (g_at >= ng || !(__builtin_amdgcn_readfirstlane(flagw[g_at]) & (kBitBadPlacement | kBitBadRank))) break;
+          if (g_at >= ng || !(__builtin_amdgcn_readfirstlane(flagw[g_at]) & (kBitBadPlacement | kBitBadRank | kBitOrder))) break;
         }
         return Turn{g_at, m_at, 0u, g_at < ng ? (uint32_t)__builtin_amdgcn_readfirstlane((int)items[g_at * Pseg + m_at]) * R : 0u};
       };
@@ -434,6 +434,15 @@ __global__ __launch_bounds__(kTransferThreads) void transfer_kernel(TransferPara
           if (lane == 0) {
             p.out_ptrs.peak_mem[(c0 + t0.g) * p.out_ptrs.peak_stride_c + m * p.out_ptrs.peak_stride_j] = top;
             if (bits) atomicOr(&flagw[t0.g], bits);
+          }
+          if (bits & kBitOrder) {
+            // The other kernel's candidate: its counts get a bit that no message takes away (bit 7 where it is not set already,
+            // which is enough of them), so that its machines come to a halt, which the relaxer takes for a cycle.  (A look at the
+            // flag by the relaxer cost 1 % of every batch, by the helpers 2 %; this test at every turn instead of at a stream's
+            // last one, 1 to 3 %.)
+            lds_byte_t *const cnt_b = ldsb + p.o_cnt + (uint32_t)t0.g * p.cnt_stride;
+            for (int i = lane; i < (N + 4) / 4; i += kWave)
+              __hip_atomic_fetch_or((DAGSCHED_LDS uint32_t *)cnt_b + i, 0x80808080u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
           }
         }
 #undef DAGSCHED_WAVE64

@@ -64,3 +64,20 @@ def test_messages_of_one_operation_share_a_channel(gpu_lib, p, c):
     w = W.Workload("shared channels p=%d" % p, p, rp, ci, rng.integers(0, 4, n).astype(np.int32),
                    rng.integers(20, 90, (p, p)).astype(np.int32), rng.integers(-5, 6, n).astype(np.int64), pl, rk)
     T._parity(gpu_lib, w, W.fcfs_edge_ranks(rp, ci, p, pl, rk), repeats=3)
+
+
+@pytest.mark.parametrize("p,c,fan_in", [(2, 17000, 0), (4, 9000, 0), (8, 4200, 0), (3, 9000, 150), (16, 40, 0), (32, 40, 200)])
+def test_orders_left_to_the_other_kernel_beside_others(gpu_lib, p, c, fan_in):
+    """Candidates whose orders do not follow the producers share a wavefront with candidates whose orders do: theirs are
+    brought to a halt (also past operations with more than 127 inputs), the others run on."""
+    rng = np.random.default_rng(p + c)
+    n = 40 + 2 * fan_in
+    rp, ci = _star(rng, n, fan_in, True) if fan_in else W.random_dag(rng, n, 4)
+    pl, rk = W.list_schedules(rp, ci, p, c, n)
+    w = W.Workload("mixed orders p=%d" % p, p, rp, ci, rng.integers(0, 9, n).astype(np.int32), rng.integers(0, 30, (p, p)).astype(np.int32),
+                   rng.integers(-5, 6, n).astype(np.int64), pl, rk)
+    er = W.fcfs_edge_ranks(rp, ci, p, pl, rk)
+    some = np.arange(c) % 11 == 3
+    some[c // 2:c // 2 + 64] = True                          # a whole workgroup's
+    er[some] = T._shuffle_some_channels(rng, W.Workload("", p, rp, ci, w.dur, w.comm, w.mem_delta, pl[some], rk[some]), er[some], every=1)
+    T._parity(gpu_lib, w, er, repeats=2)
