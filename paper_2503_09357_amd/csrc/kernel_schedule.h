@@ -25,6 +25,7 @@
 
 namespace dagsched_dev {
 
+constexpr int kBitNoChannel = 32;                          // (the evaluations leave this flag to a pass of its own)
 constexpr int kScheduleHelpers = 8;                        // wavefronts
 constexpr int kScheduleThreads = (2 + kScheduleHelpers) * kWave;   // relaxer, accountant, helpers
 
@@ -337,7 +338,8 @@ __global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(SchedulePara
   }
 
   // ---------------------------------------------------------------- outputs
-  const int flag = flag_from_bits(bits);
+  // (looked for only where placement and ranks are well-formed, and then nothing was relaxed: the only bit there is)
+  const int flag = bits & kBitNoChannel ? DAGSCHED_FLAG_NO_CHANNEL : flag_from_bits(bits);
 #pragma unroll 4
   for (int v = tid; v < N; v += T) {
     const int32_t e = flag ? -1 : LDSC ? (int32_t)cellw[v] : ld_group(&p.cells[v]);

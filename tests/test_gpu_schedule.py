@@ -44,3 +44,52 @@ def test_schedule_at_the_edges_of_its_splits(gpu_lib, n, p, fanin, window):
             flag, so, eo, _, _ = prob.schedule(w.placement[0], rk)
             assert int(f[0]) == flag
             assert (s == so).all() and (e == eo).all() if flag == 0 else (s == -1).all() and (e == -1).all()
+
+
+@pytest.mark.parametrize("n,p", [(1, 1), (300, 1), (514, 9), (700, 64), (19400, 64), (24000, 5)])
+def test_schedule_with_limits_and_missing_channels(gpu_lib, n, p):
+    """Memory limits that are just met, exceeded by one on the last machine in use, exceeded together with a cycle and with
+    a channel that is not there; end times in LDS and in the L2."""
+    import dataclasses
+
+    import torch
+    rng = np.random.default_rng(n + p)
+    print("[schedule limits] n=%d p=%d" % (n, p), flush=True)
+    rp, ci = W.random_dag(rng, n, 3, window=200)
+    pl, rk = W.list_schedules(rp, ci, p, 1, n)
+    w = W.Workload("limits", p, rp, ci, rng.integers(0, 300, n).astype(np.int32), rng.integers(0, 90, (p, p)).astype(np.int32),
+                   rng.integers(-3, 4, n).astype(np.int64), pl, rk, weight=rng.integers(0, 20, n).astype(np.int64),
+                   mem_limit=np.full(p, 1 << 40, np.int64))
+    peak = oracle.Problem.of(w).evaluate(pl, rk, 0, 1)[2][0]
+    last = int(pl.max())
+    rk2 = rk[0].copy()                                       # every machine's order reversed
+    for j in range(p):
+        idx = np.nonzero(pl[0] == j)[0]
+        rk2[idx] = len(idx) - 1 - rk2[idx]
+    src, dst = W.edges_from_csr(rp, ci)
+    a, b = pl[0][src], pl[0][dst]
+    comm = w.comm.copy()
+    if (a != b).any():
+        k = np.nonzero(a != b)[0][-1]
+        comm[a[k], b[k]] = oracle.NO_CHANNEL
+    short = peak.copy()
+    short[last] -= 1
+    seen = set()
+    for limit in (peak, short):
+        for cm in (w.comm, comm):
+            v = dataclasses.replace(w, mem_limit=limit, comm=cm)
+            prob = oracle.Problem.of(v)
+            with gpu_lib.Evaluator.for_workload(v, max_candidates=1, shared_placement=None) as ev:
+                for r in (rk[0], rk2):
+                    flag = int(prob.evaluate(pl, r[None], 0, 1)[3][0])
+                    s, e, f = (t.cpu().numpy() for t in ev.schedule(*(torch.from_numpy(x).to("cuda:0") for x in (pl[0], r))))
+                    assert int(f[0]) == flag
+                    seen.add(flag)
+                    if flag:
+                        assert (s == -1).all() and (e == -1).all()
+                    else:
+                        _, so, eo, _, _ = prob.schedule(pl[0], r)
+                        assert (s == so).all() and (e == eo).all()
+    assert {0, oracle.FLAG_OVER_MEMORY} <= seen
+    assert n == 1 or oracle.FLAG_CYCLIC in seen
+    assert p == 1 or oracle.FLAG_NO_CHANNEL in seen
