@@ -106,7 +106,7 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
       // transfers per channel
       for (int k = t; k < E; k += T) {
         const int32_t a = pl[p.edge_src[k]], b = pl[p.edge_dst[k]];
-        if (a != b) atomicAdd(&ccnt[a * P + b], 1);
+        if (a != b) __hip_atomic_fetch_add(&ccnt[a * P + b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
         st_group(&echan[k], a != b ? a * P + b : -1);
         st_group(&tend[k], -1);
       }
@@ -214,7 +214,9 @@ __global__ __launch_bounds__(kContendedThreads) __attribute__((amdgpu_waves_per_
             level += p.mem_delta[v];                          // eq. (19)
             peak = max(peak, level);
             if (p.weight) base += p.weight[v];                // eq. (16)
-            // (the end time must be out before a bell is rung: the wavefront waits for its stores)
+            // A lane that sees a bell finds the end time.  At this scope the fence makes the compiler keep the order but waits for
+            // nothing: the wavefronts of a workgroup share one vector cache, which takes accesses in the order in which they are
+            // issued, and whoever sees the bell issues its load after this store.
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
             for (int kq = p.succ_ptr[v]; kq < p.succ_ptr[v + 1]; ++kq) {   // the channels v feeds hear of it
               const int ch = ld_group(&echan[kq]);

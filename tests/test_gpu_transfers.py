@@ -81,3 +81,26 @@ def test_orders_left_to_the_other_kernel_beside_others(gpu_lib, p, c, fan_in):
     some[c // 2:c // 2 + 64] = True                          # a whole workgroup's
     er[some] = T._shuffle_some_channels(rng, W.Workload("", p, rp, ci, w.dur, w.comm, w.mem_delta, pl[some], rk[some]), er[some], every=1)
     T._parity(gpu_lib, w, er, repeats=2)
+
+
+@pytest.mark.parametrize("p,c", [(64, 2200), (3, 8500)])
+def test_several_candidates_per_workgroup_of_the_other_kernel(gpu_lib, p, c):
+    """More candidates with orders of their own than the other kernel has workgroups (1024 with 64 machines, 4096 with few,
+    on 256 CUs): its rows of scratch are used again, while what the candidate before read of them may still be cached."""
+    rng = np.random.default_rng(p)
+    n = 40
+    rp, ci = W.random_dag(rng, n, 6)
+    pl, rk = W.list_schedules(rp, ci, p, c, n)
+    src = W.edges_from_csr(rp, ci)[0]
+    w = W.Workload("rows p=%d" % p, p, rp, ci, rng.integers(0, 9, n).astype(np.int32), rng.integers(0, 30, (p, p)).astype(np.int32),
+                   rng.integers(-5, 6, n).astype(np.int64), pl, rk)
+    er = W.fcfs_edge_ranks(rp, ci, p, pl, rk)
+    if p > 3:
+        er = T._shuffle_some_channels(rng, w, er, every=1)
+    else:                                                    # (those would all be cycles) two messages of one operation trade places
+        for i in range(c):
+            key = np.where(pl[i, src] != pl[i, ci], src * p + pl[i, ci], -1 - np.arange(len(src)))
+            k = [np.nonzero(key == x)[0] for x in np.unique(key[key >= 0])]
+            k = max(k, key=len)[:2]
+            er[i, k] = er[i, k[::-1]]
+    T._parity(gpu_lib, w, er, repeats=2)
