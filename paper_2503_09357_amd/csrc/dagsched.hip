@@ -86,6 +86,7 @@ struct dagsched {
   int32_t N = 0, E = 0, P = 0, Pseg = 0, max_cand = 0, layout = 0, device = 0;
   int64_t sum_dur = 0;
   int32_t variant = 0;
+  unsigned char *problem_tables = nullptr, *channel_tables = nullptr;   // blocks that hold the description (Tables)
   // general kernel
   int32_t gen_G = 0, gen_lds = 0;
   bool gen_lds_state = false;
@@ -233,6 +234,25 @@ bool upload(T **dst, const T *src, size_t n) {
   return hip_ok(hipMemcpy(*dst, src, n * sizeof(T), hipMemcpyHostToDevice), "hipMemcpy");
 }
 
+// Constant tables of a handle, gathered on the host and sent in one copy to one block (an allocation and a copy for
+// each table cost some 10 us, several dozen of them more than the planning of a small problem).
+struct Tables {
+  std::vector<unsigned char> image;
+  std::vector<std::pair<void **, size_t>> parts;
+  template <typename T>
+  void add(T **dst, const std::common_type_t<T> *src, size_t n) {   // 256-byte aligned, as an allocation of its own would be
+    const size_t at = (image.size() + 255) / 256 * 256;
+    image.resize(at + std::max<size_t>(n, 1) * sizeof(T));
+    if (n) memcpy(image.data() + at, src, n * sizeof(T));
+    parts.push_back({(void **)dst, at});
+  }
+  bool send(unsigned char **block) {
+    if (!upload(block, image.data(), image.size())) return false;
+    for (auto &[dst, at] : parts) *dst = *block + at;
+    return true;
+  }
+};
+
 template <typename T>
 bool dev_alloc(T **dst, size_t n) {
   return hip_ok(hipMalloc((void **)dst, std::max<size_t>(n, 1) * sizeof(T)), "hipMalloc workspace");
@@ -240,12 +260,12 @@ bool dev_alloc(T **dst, size_t n) {
 
 void free_handle(dagsched *h) {
   if (!h) return;
-  void *bufs[] = {h->d_pred_ptr, h->d_pred_idx, h->d_dur, h->d_comm, h->d_mem, h->d_weight, h->d_limit, h->ws_list, h->ws_end, h->d_rec,
-                  h->d_comm_scaled, h->d_nparts, h->ws_list16, h->ws_pib, h->ws_cnt, h->ws_sched_list, h->ws_sched_end, h->d_red_ptr, h->d_red_idx,
-                  h->d_fb_count, h->d_fb_list, h->ws_meta, h->ws_tp, h->ws_tr, h->d_no_channel, h->d_edges,
-                  h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_base, h->ws_te, h->d_pred_eid, h->d_edge_src, h->d_edge_dst, h->d_succ_ptr,
+  void *bufs[] = {h->problem_tables, h->channel_tables, h->ws_list, h->ws_end, h->d_rec,
+                  h->d_comm_scaled, h->d_nparts, h->ws_list16, h->ws_pib, h->ws_cnt, h->ws_sched_list, h->ws_sched_end,
+                  h->d_fb_count, h->d_fb_list, h->ws_meta, h->ws_tp, h->ws_tr,
+                  h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_base, h->ws_te,
                   h->wc_list, h->wc_end, h->wc_tlist, h->wc_tend, h->wc_ccnt, h->wc_coff, h->wc_echan,
-                  h->d_item, h->d_in_degree, h->wc_stream, h->d_first, h->d_tr_count, h->d_tr_list};
+                  h->wc_stream, h->d_tr_list};
   for (void *b : bufs)
     if (b) (void)hipFree(b);
   delete h;
@@ -314,14 +334,21 @@ struct RingPlan {
 // a pipeline's operations keep a single predecessor each (the forward -> backward edge of a stage is implied by
 // the path through the next stage), which selects a lighter kind of kernel.  Bounded search: six hops, 512
 // visits (four hops do for the plain pipelines, six for the bidirectional one with its transfer operations).
-using PredLists = std::vector<std::vector<int32_t>>;
+struct PredLists {                                      // a CSR: the lists are copied and uploaded as they are
+  std::vector<int32_t> ptr, idx;
+  struct Range { const int32_t *first, *last; const int32_t *begin() const { return first; } const int32_t *end() const { return last; } };
+  int size(int v) const { return ptr[v + 1] - ptr[v]; }
+  Range operator[](int v) const { return {idx.data() + ptr[v], idx.data() + ptr[v + 1]}; }
+};
 PredLists reduce_preds(const dagsched_desc_t *d, const std::vector<int32_t> &pred_ptr, const std::vector<int32_t> &pred_idx) {
   const int N = d->n_nodes, P = d->n_devices;
   int64_t max_comm = 0;
   for (int a = 0; a < P; ++a)
     for (int b = 0; b < P; ++b)
       if (a != b) max_comm = std::max<int64_t>(max_comm, d->comm[a * P + b]);
-  PredLists op_preds(N);
+  PredLists lists;
+  lists.ptr.assign((size_t)N + 1, 0);
+  lists.idx.reserve(pred_idx.size());
   struct Item { int32_t node, hops; int64_t sum; };
   std::vector<Item> stack;
   auto implied = [&](int32_t u, int32_t v) {
@@ -346,9 +373,10 @@ PredLists reduce_preds(const dagsched_desc_t *d, const std::vector<int32_t> &pre
   for (int v = 0; v < N; ++v) {
     const int deg = pred_ptr[v + 1] - pred_ptr[v];
     for (int k = pred_ptr[v]; k < pred_ptr[v + 1]; ++k)
-      if (deg < 2 || !implied(pred_idx[k], v)) op_preds[v].push_back(pred_idx[k]);
+      if (deg < 2 || !implied(pred_idx[k], v)) lists.idx.push_back(pred_idx[k]);
+    lists.ptr[v + 1] = (int32_t)lists.idx.size();
   }
-  return op_preds;
+  return lists;
 }
 
 RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_ptr, const std::vector<int32_t> &pred_idx,
@@ -392,33 +420,33 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   plan.scale = (int32_t)g;
 
   constexpr int PR = 4;                                // DAG predecessors per op part
-  std::vector<std::vector<int32_t>> op_preds = reduced;   // (sorted below)
+  PredLists op_preds = reduced;                        // (sorted below)
   // shared operator records, part i of node v at [i * plane + v]
   const uint32_t dummy = (uint32_t)N;
   int max_parts = 1;
-  for (int v = 0; v < N; ++v) max_parts = std::max(max_parts, ((int)op_preds[v].size() + PR - 1) / PR);
+  for (int v = 0; v < N; ++v) max_parts = std::max(max_parts, (op_preds.size(v) + PR - 1) / PR);
   if (max_parts > 16) return plan;                     // very wide fan-in: leave it to the general kernel
   {                                                    // the kernel counts a lane's op parts in 16 bits
     int64_t total_parts = 0;
-    for (int v = 0; v < N; ++v) total_parts += std::max(1, ((int)op_preds[v].size() + PR - 1) / PR);
+    for (int v = 0; v < N; ++v) total_parts += std::max(1, (op_preds.size(v) + PR - 1) / PR);
     if (total_parts >= 65536) return plan;
   }
   // kernel kind: 2 when no operation has more than two DAG predecessors, 1 when none has more than four (every
   // operation is a single part), 0 otherwise (or when the caller's shape asks for four predecessors per op)
-  size_t max_deg = 0;
-  for (int v = 0; v < N; ++v) max_deg = std::max(max_deg, op_preds[v].size());
+  int max_deg = 0;
+  for (int v = 0; v < N; ++v) max_deg = std::max(max_deg, op_preds.size(v));
   plan.kind = (d->shape && d->shape->preds_per_op == 4) ? 0 : max_deg <= 1 ? 3 : max_deg <= 2 ? 2 : max_parts == 1 ? 1 : 0;
   if (d->shape && d->shape->preds_per_op == 2 && plan.kind == 3) plan.kind = 2;   // (the caller asks for the two-predecessor kind)
   const int plane = N;
   std::vector<uint4> rec((size_t)max_parts * plane, make_uint4(dummy | (dummy << 16), dummy | (dummy << 16), 0, 0));
   for (int v = 0; v < N; ++v) {
-    const int deg = (int)op_preds[v].size();
+    const int deg = op_preds.size(v);
     const int parts = std::max(1, (deg + PR - 1) / PR);
     // A part waits for its own predecessors and for the parts before it, so the operation ends one trip
     // later for every part that follows the one holding its last predecessor.  Predecessors that end late
     // on the critical path of B alone go last, and the first part takes the remainder.
-    std::vector<int32_t> &ps = op_preds[v];
-    std::stable_sort(ps.begin(), ps.end(), [&](int32_t a, int32_t b) { return fin[a] < fin[b]; });
+    int32_t *const ps = op_preds.idx.data() + op_preds.ptr[v];
+    std::stable_sort(ps, ps + deg, [&](int32_t a, int32_t b) { return fin[a] < fin[b]; });
     const int first = deg - PR * (parts - 1);
     for (int part = 0; part < parts; ++part) {
       uint32_t u[4] = {dummy, dummy, dummy, dummy};
@@ -442,12 +470,12 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   plan.id_bits = 16 - part_bits;
   if (N > (1 << plan.id_bits)) return plan;            // ids and part counts do not fit: general kernel
   for (int v = 0; v < N; ++v) {                        // 0xFFFF marks an unwritten list slot during ingest
-    const int parts = std::max(1, ((int)op_preds[v].size() + PR - 1) / PR);
+    const int parts = std::max(1, (op_preds.size(v) + PR - 1) / PR);
     if (((uint32_t)v | ((uint32_t)(parts - 1) << plan.id_bits)) == 0xFFFFu) return plan;
   }
   if (max_parts > 1) {
     plan.nparts.resize(N);
-    for (int v = 0; v < N; ++v) plan.nparts[v] = (uint8_t)std::max(1, ((int)op_preds[v].size() + PR - 1) / PR);
+    for (int v = 0; v < N; ++v) plan.nparts[v] = (uint8_t)std::max(1, (op_preds.size(v) + PR - 1) / PR);
   }
   plan.comm_scaled.resize((size_t)P * P);
   for (int i = 0; i < P * P; ++i) plan.comm_scaled[i] = (i / P != i % P) ? (int32_t)(d->comm[i] / g) : 0;
@@ -994,27 +1022,27 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   if (!force_general && !splan.ok) plan = plan_ring(desc, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
   const bool need_general = splan.ok || !plan.ok || !plan.exact;
 
-  bool ok = upload(&h->d_mem, desc->mem_delta, (size_t)h->N) &&
-            (!desc->weight || upload(&h->d_weight, desc->weight, (size_t)h->N)) &&
-            (!desc->mem_limit || upload(&h->d_limit, desc->mem_limit, (size_t)h->P));
   // the plain view of the problem is always resident: dagsched_schedule reads it
-  ok = ok && upload(&h->d_pred_ptr, pred_ptr.data(), (size_t)h->N + 1) &&
-       upload(&h->d_pred_idx, pred_idx.data(), (size_t)h->E) &&
-       upload(&h->d_dur, desc->dur, (size_t)h->N) &&
-       upload(&h->d_comm, desc->comm, (size_t)h->P * h->P) &&
-       (!any_missing || (upload(&h->d_no_channel, no_channel.data(), no_channel.size()) &&
-                         upload(&h->d_edges, edges.data(), edges.size()) &&
-                         (channel_flag_lds(h->N) <= 48 * 1024 ||
-                          allow_large_lds((const void *)channel_flag_kernel, h->device, (int)channel_flag_lds(h->N))))) &&
+  Tables tables;
+  tables.add(&h->d_mem, desc->mem_delta, (size_t)h->N);
+  if (desc->weight) tables.add(&h->d_weight, desc->weight, (size_t)h->N);
+  if (desc->mem_limit) tables.add(&h->d_limit, desc->mem_limit, (size_t)h->P);
+  tables.add(&h->d_pred_ptr, pred_ptr.data(), (size_t)h->N + 1);
+  tables.add(&h->d_pred_idx, pred_idx.data(), (size_t)h->E);
+  tables.add(&h->d_red_ptr, reduced.ptr.data(), reduced.ptr.size());
+  tables.add(&h->d_red_idx, reduced.idx.data(), reduced.idx.size());
+  tables.add(&h->d_dur, desc->dur, (size_t)h->N);
+  tables.add(&h->d_comm, desc->comm, (size_t)h->P * h->P);
+  if (any_missing) {
+    tables.add(&h->d_no_channel, no_channel.data(), no_channel.size());
+    tables.add(&h->d_edges, edges.data(), edges.size());
+  }
+  h->n_red = (int32_t)reduced.idx.size();
+  bool ok = tables.send(&h->problem_tables) &&
+       (!any_missing || channel_flag_lds(h->N) <= 48 * 1024 ||
+        allow_large_lds((const void *)channel_flag_kernel, h->device, (int)channel_flag_lds(h->N))) &&
        dev_alloc(&h->ws_cnt, (size_t)DAGSCHED_MAX_DEVICES) &&
        dev_alloc(&h->ws_sched_list, (size_t)h->row_stride) && dev_alloc(&h->ws_sched_end, (size_t)h->row_stride);
-  std::vector<int32_t> red_ptr((size_t)h->N + 1, 0), red_idx;
-  for (int32_t v = 0; v < h->N; ++v) {
-    red_idx.insert(red_idx.end(), reduced[v].begin(), reduced[v].end());
-    red_ptr[v + 1] = (int32_t)red_idx.size();
-  }
-  h->n_red = (int32_t)red_idx.size();
-  ok = ok && upload(&h->d_red_ptr, red_ptr.data(), red_ptr.size()) && upload(&h->d_red_idx, red_idx.data(), red_idx.size());
   // one schedule: the deepest rings that fit beside the end times; end times in the L2 when not even shallow ones do
   for (const auto &[slots, lds_cells] : {std::pair<int, bool>{32, true}, {16, true}, {32, false}}) {
     ScheduleParams sp{};
@@ -1128,9 +1156,12 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     h->row_e = ((int64_t)std::max(E, 1) + 31) / 32 * 32;
     h->row_c = ((int64_t)h->P * h->P + 1 + 31) / 32 * 32;
     const size_t g = (size_t)h->wc_grid;
-    ok = upload(&h->d_pred_eid, peid.data(), (size_t)E) && upload(&h->d_edge_src, esrc.data(), (size_t)E) &&
-         upload(&h->d_edge_dst, edst.data(), (size_t)E) && upload(&h->d_succ_ptr, desc->row_ptr, (size_t)h->N + 1) &&
-         dev_alloc(&h->wc_list, g * (size_t)h->row_stride) && dev_alloc(&h->wc_end, g * (size_t)h->row_stride) &&
+    Tables channels;
+    channels.add(&h->d_pred_eid, peid.data(), (size_t)E);
+    channels.add(&h->d_edge_src, esrc.data(), (size_t)E);
+    channels.add(&h->d_edge_dst, edst.data(), (size_t)E);
+    channels.add(&h->d_succ_ptr, desc->row_ptr, (size_t)h->N + 1);
+    ok = dev_alloc(&h->wc_list, g * (size_t)h->row_stride) && dev_alloc(&h->wc_end, g * (size_t)h->row_stride) &&
          dev_alloc(&h->wc_tlist, g * (size_t)h->row_e) && dev_alloc(&h->wc_tend, g * (size_t)h->row_e) &&
          dev_alloc(&h->wc_echan, g * (size_t)h->row_e) &&
          dev_alloc(&h->wc_ccnt, g * (size_t)h->row_c) && dev_alloc(&h->wc_coff, g * (size_t)h->row_c) &&
@@ -1163,9 +1194,11 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       const int64_t groups = ((int64_t)h->max_cand + tp.G - 1) / tp.G;
       h->tr_grid = (int32_t)std::min<int64_t>(groups, (int64_t)n_cu * (tp.threads == 512 ? 2 : 1));
       const int32_t zero[3] = {0, 0, 0};
-      ok = upload(&h->d_first, first.data(), first.size()) && upload(&h->d_item, item.data(), item.size()) &&
-           upload(&h->d_in_degree, in_degree.data(), in_degree.size()) &&
-           upload(&h->d_tr_count, zero, 3) && dev_alloc(&h->d_tr_list, maxc) &&
+      channels.add(&h->d_first, first.data(), first.size());
+      channels.add(&h->d_item, item.data(), item.size());
+      channels.add(&h->d_in_degree, in_degree.data(), in_degree.size());
+      channels.add(&h->d_tr_count, zero, 3);
+      ok = channels.send(&h->channel_tables) && dev_alloc(&h->d_tr_list, maxc) &&
            dev_alloc(&h->wc_stream, (size_t)h->tr_grid * (size_t)tp.G * (size_t)tp.row_items) &&
            allow_large_lds((const void *)transfer_kernel_for(tp.R), h->device, (int)tp.total);
       tp.first = h->d_first; tp.item = h->d_item; tp.in_degree = h->d_in_degree; tp.dur = h->d_dur; tp.comm = h->d_comm;
@@ -1174,6 +1207,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       tp.fb_list = h->d_tr_list;
     } else {
       tp.total = 0;
+      ok = ok && channels.send(&h->channel_tables);
     }
   }
   if (!ok) {

@@ -104,3 +104,17 @@ def test_several_candidates_per_workgroup_of_the_other_kernel(gpu_lib, p, c):
             k = max(k, key=len)[:2]
             er[i, k] = er[i, k[::-1]]
     T._parity(gpu_lib, w, er, repeats=2)
+
+
+@pytest.mark.parametrize("n,p", [(1, 1), (70, 3)])
+def test_operations_without_edges(gpu_lib, n, p):
+    """Tables of no entries among the others, some channels missing, limits."""
+    rng = np.random.default_rng(n)
+    rp, ci = W.csr_from_edges(n, [], [])
+    pl, rk = W.list_schedules(rp, ci, p, 20, n)
+    comm = rng.integers(0, 9, (p, p)).astype(np.int32)
+    if p > 1:
+        comm[0, 1] = -1
+    w = W.Workload("no edges", p, rp, ci, rng.integers(0, 9, n).astype(np.int32), comm, rng.integers(-5, 6, n).astype(np.int64), pl, rk,
+                   weight=rng.integers(0, 9, n).astype(np.int64), mem_limit=np.full(p, 5 * n // p + 20, np.int64))
+    T._parity(gpu_lib, w, W.fcfs_edge_ranks(rp, ci, p, pl, rk))
