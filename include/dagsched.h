@@ -343,6 +343,23 @@ int dagsched_plan(const dagsched_desc_t *desc, int32_t lds_bytes, int32_t n_cu, 
 int dagsched_last_fallbacks(dagsched_t *h, void *hip_stream, int32_t *count);
 
 /*
+ * What the handle's LAST dagsched_evaluate_contended ran with, for tests and tuning: the shape of the fast path for
+ * candidates whose channel orders follow their producers (all 0 when the problem does not fit it) and how many
+ * candidates it left to the general kernel (0 before the first call).  Synchronises hip_stream, the stream that call was
+ * enqueued on.  DAGSCHED_EINVAL for a handle made without contention.
+ */
+typedef struct {
+  int32_t cand_per_block;    /* candidates of a workgroup */
+  int32_t lanes_per_machine; /* messages a machine sends per step: 1, 2 or 4 */
+  int32_t ring_slots;        /* 16 or 32 */
+  int32_t block_threads;
+  int32_t ingest_teams;      /* candidates of a workgroup that are read side by side */
+  int32_t left_over;
+} dagsched_contended_info_t;
+
+int dagsched_contended_info(dagsched_t *h, void *hip_stream, dagsched_contended_info_t *info);
+
+/*
  * Timing aid: evaluate `reps` times back to back on hip_stream between two HIP events recorded on
  * that same stream and return the mean milliseconds per evaluate in *ms_per_eval.  Synchronises
  * hip_stream.  Same pointer contract as dagsched_evaluate.

@@ -1577,6 +1577,18 @@ int dagsched_last_fallbacks(dagsched_t *h, void *hip_stream, int32_t *count) {
   return DAGSCHED_OK;
 }
 
+int dagsched_contended_info(dagsched_t *h, void *hip_stream, dagsched_contended_info_t *info) {
+  if (!h || !info || !h->contention) return DAGSCHED_EINVAL;
+  memset(info, 0, sizeof(*info));
+  if (!h->tr.total) return DAGSCHED_OK;
+  info->cand_per_block = h->tr.G; info->lanes_per_machine = h->tr.R; info->ring_slots = h->tr.slots;
+  info->block_threads = h->tr.threads; info->ingest_teams = h->tr.teams;
+  if (!hip_ok(hipMemcpyAsync(&info->left_over, h->tr.fb_todo, sizeof(int32_t), hipMemcpyDeviceToHost, (hipStream_t)hip_stream), "hipMemcpyAsync") ||
+      !hip_ok(hipStreamSynchronize((hipStream_t)hip_stream), "hipStreamSynchronize"))
+    return DAGSCHED_EHIP;
+  return DAGSCHED_OK;
+}
+
 const char *dagsched_strerror(int code) {
   static thread_local char buf[320];
   switch (code) {

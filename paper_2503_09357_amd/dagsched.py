@@ -21,7 +21,7 @@ CAND_MAJOR, CAND_MINOR = 0, 1
 MAX_DEVICES, MAX_NODES = 64, 65535
 
 EXPORTS = ("dagsched_validate", "dagsched_create", "dagsched_evaluate", "dagsched_evaluate_contended", "dagsched_destroy",
-           "dagsched_strerror", "dagsched_get_info", "dagsched_plan", "dagsched_last_fallbacks", "dagsched_time_evaluate", "dagsched_propose",
+           "dagsched_strerror", "dagsched_get_info", "dagsched_plan", "dagsched_last_fallbacks", "dagsched_contended_info", "dagsched_time_evaluate", "dagsched_propose",
            "dagsched_propose_orders", "dagsched_select", "dagsched_schedule", "dagsched_schedule_static", "dagsched_coarsen")
 
 
@@ -78,6 +78,10 @@ class Info(ctypes.Structure):
                 ("window_log2", ctypes.c_int8)]
 
 
+class ContendedInfo(ctypes.Structure):
+    _fields_ = [(k, ctypes.c_int32) for k in ("cand_per_block", "lanes_per_machine", "ring_slots", "block_threads", "ingest_teams", "left_over")]
+
+
 class CoarsenParams(ctypes.Structure):
     _fields_ = [("target_nodes", ctypes.c_int32), ("edge_dur_max", ctypes.c_int64), ("edge_mem_max", ctypes.c_int64),
                 ("nonedge_dur_max", ctypes.c_int64), ("nonedge_mem_max", ctypes.c_int64)]
@@ -128,6 +132,8 @@ def load(import_torch_first: bool = True):
     lib.dagsched_plan.argtypes = [ctypes.POINTER(Desc), i32, i32, ctypes.POINTER(Info)]
     lib.dagsched_last_fallbacks.restype = ctypes.c_int
     lib.dagsched_last_fallbacks.argtypes = [vp, vp, ctypes.POINTER(ctypes.c_int32)]
+    lib.dagsched_contended_info.restype = ctypes.c_int
+    lib.dagsched_contended_info.argtypes = [vp, vp, ctypes.POINTER(ContendedInfo)]
     lib.dagsched_propose.restype = ctypes.c_int
     lib.dagsched_propose.argtypes = [vp, i32, vp, vp, vp, vp, vp, vp]
     lib.dagsched_propose_orders.restype = ctypes.c_int
@@ -340,6 +346,15 @@ class Evaluator:
         n = ctypes.c_int32()
         _check(load().dagsched_last_fallbacks(self._h, s.cuda_stream, ctypes.byref(n)))
         return int(n.value)
+
+    def contended_info(self, stream=None) -> dict:
+        """Shape of the contended evaluation's fast path, and the candidates that the last evaluate_contended left to the
+        general kernel (synchronises the stream)."""
+        import torch
+        s = torch.cuda.current_stream(self.hip_device) if stream is None else stream
+        i = ContendedInfo()
+        _check(load().dagsched_contended_info(self._h, s.cuda_stream, ctypes.byref(i)))
+        return {k: getattr(i, k) for k, _ in ContendedInfo._fields_}
 
     def _n_cand(self, placement, rank) -> int:
         import torch

@@ -1,11 +1,13 @@
 """Evaluation with channel contention against the oracle where its fast path changes shape: one, two and four lanes per
-machine, one to many candidates per workgroup, deep and shallow rings, operations with many outputs, and what it leaves to
-the other kernel (orders that do not follow the producers, more than 255 inputs, more than 65000 operations and edges)."""
+machine, one to 64 candidates per workgroup, deep and shallow rings, operations with many outputs, and what it leaves to
+the other kernel (orders that do not follow the producers, more than 255 inputs, more than 65000 operations and edges).
+The shapes and the number of candidates left over are asserted, not assumed."""
 from __future__ import annotations
 
 import numpy as np
 import pytest
 
+import oracle
 import test_gpu_channels as T
 from paper_2503_09357_amd import workloads as W
 
@@ -118,3 +120,38 @@ def test_operations_without_edges(gpu_lib, n, p):
     w = W.Workload("no edges", p, rp, ci, rng.integers(0, 9, n).astype(np.int32), comm, rng.integers(-5, 6, n).astype(np.int64), pl, rk,
                    weight=rng.integers(0, 9, n).astype(np.int64), mem_limit=np.full(p, 5 * n // p + 20, np.int64))
     T._parity(gpu_lib, w, W.fcfs_edge_ranks(rp, ci, p, pl, rk))
+
+
+@pytest.mark.parametrize("n,p,reach,most,shape", [       # shape: candidates, lanes, slots, threads, teams
+    (40, 1, 1, 33000, (64, 1, 32, 512, 8)), (200, 1, 1, 17000, (64, 1, 32, 1024, 16)), (41, 2, 1, 16500, (32, 1, 32, 512, 8)),
+    (60, 4, 1, 8300, (16, 1, 32, 512, 8)), (61, 4, 2, 4200, (8, 2, 32, 512, 8)), (60, 8, 1, 4200, (8, 1, 32, 512, 8)),
+    (700, 4, 1, 8300, (16, 1, 16, 512, 8)), (1000, 4, 1, 4200, (16, 1, 32, 1024, 16)), (1500, 8, 1, 4200, (8, 1, 16, 512, 8)),
+    (2500, 8, 2, 2100, (4, 2, 16, 512, 4)), (5000, 4, 2, 1100, (4, 4, 32, 1024, 4)), (90, 16, 2, 30, (1, 4, 32, 512, 1)), (90, 33, 2, 30, (1, 1, 32, 512, 1))])
+def test_small_batches_on_handles_for_large_ones(gpu_lib, n, p, reach, most, shape):
+    """1, one less and one more than a workgroup's candidates, and several workgroups' on a handle made for many more."""
+    import torch
+    rng = np.random.default_rng(n + p)
+    G = shape[0]
+    c = 3 * G + 2
+    step = np.arange(n)
+    src, dst = np.concatenate([step[:n - r - 1] for r in range(1, reach + 1)]), np.concatenate([step[r + 1:] for r in range(1, reach + 1)])
+    rp, ci = W.csr_from_edges(n, src, dst)
+    pl, rk = W.list_schedules(rp, ci, p, c, n)
+    if p > 1:
+        pl[2, 0] = p
+    w = W.Workload("G=%d" % G, p, rp, ci, rng.integers(0, 9, n).astype(np.int32), rng.integers(0, 30, (p, p)).astype(np.int32),
+                   rng.integers(-5, 6, n).astype(np.int64), pl, rk, weight=rng.integers(0, 9, n).astype(np.int64),
+                   mem_limit=np.full(p, 6 * n // p + 30, np.int64))
+    fcfs = W.fcfs_edge_ranks(rp, ci, p, pl, rk)
+    er = T._shuffle_some_channels(rng, w, fcfs.copy(), every=5)
+    strange = (er != fcfs).any(axis=1) & (pl < p).all(axis=1)
+    dev = torch.device("cuda", 0)
+    print("[transfers] n=%d p=%d shape=%s" % (n, p, shape), flush=True)
+    with gpu_lib.Evaluator.for_workload(w, max_candidates=most, contention=True, shared_placement=None) as ev:
+        for size in (1, max(1, G - 1), G + 1, c):
+            want = oracle.Problem.of(w).evaluate_contended(pl[:size], rk[:size], er[:size], 0, threads=8)
+            got = ev.evaluate_contended(*(torch.from_numpy(a[:size]).to(dev) for a in (pl, rk, er)))
+            info = ev.contended_info()
+            assert all((a.cpu().numpy() == b).all() for a, b in zip(got, want)), size
+            assert tuple(info[k] for k in ("cand_per_block", "lanes_per_machine", "ring_slots", "block_threads", "ingest_teams")) == shape
+            assert info["left_over"] == strange[:size].sum()
