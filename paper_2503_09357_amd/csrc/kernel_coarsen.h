@@ -24,7 +24,7 @@
 // a thread per operation and a wavefront per 64 of them, with rows short enough to be read whole: a row of B' is a
 // ballot per 64 columns, an edge merge takes three barriers and a non-edge merge none.  Larger graphs (coarsen_kernel)
 // work in the L2.
-// The paper's scale, 200 operations to 40: 285 us (326 us for the whole call with its allocation and copies) against
+// The paper's scale, 200 operations to 40: 271 us (321 us for the whole call with its allocation and copies) against
 // 7400 us for the kernel that worked in the L2 and searched all pairs for every merge; the MoE graph (11712 operations,
 // 700 merges, in the L2) 0.2 s against 11 s.  What is left of the small one is instructions of a lone wavefront: about
 // 1000 cycles per partner looked for, two per merge.

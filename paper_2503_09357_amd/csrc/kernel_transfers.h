@@ -3,7 +3,7 @@
 //
 // Every transfer of a channel (a, b) is produced by an operation of machine a, and machine a runs its operations one
 // after the other.  Where the transfers of every channel are ranked in the order in which machine a produces them (first
-// come, first served, and every order that does not put a transfer behind one that is produced later), a transfer can be
+// come, first served; the messages of one operation over the same channel by the index of their edge), a transfer can be
 // completed the moment its producer has ended:
 //   d_k = max(e_u, free(a, b)) + comm[a][b],  free(a, b) = d_k       (eqs. (11), (13)-(15))
 // so nothing ever waits for a channel (an edge inside a machine is a message over a channel of its own without delay).
@@ -30,9 +30,13 @@
 //
 // What bounds it is the chain of dependent steps (MoE graph: a candidate's longest path of operations and messages),
 // each an LDS round trip and about 40 instructions of a lone wavefront.  MoE graph, 512 candidates, two workgroups of one
-// candidate per CU: 609 us, 3500 steps of 298 cycles each; with one lane per machine 4377 steps (of 280), with a barrier
-// every 17 steps 755 us, with the messages written to memory at ingest (262 KB a candidate) 860 us.  The kernel before took
-// 17235 us.  Zero-bubble pipeline, 2048 candidates: 1030 -> 77 us.
+// candidate per CU: 609 us, which is the slowest candidate (601 us) and the second launch; 33 us of ingest and 3664 steps of
+// 306 cycles at 2.27 GHz (494 us) on the average, 38 us and 4216 steps (563 us) at most.  In about one step of eight
+// some machine waits for the helpers.  With one lane per machine 4377 steps (of 280), with a barrier every 17 steps 755 us,
+// with the messages written to memory at ingest (262 KB a candidate) 860 us.  The kernel before took 17235 us.  Zero-bubble
+// pipeline, 2048 candidates: 1030 -> 77 us (9 us of ingest, 302 steps of 312 cycles, then the accountants' last 16 us).
+// A candidate that is left to the other kernel costs the ingest and the accountants' first streams: MoE graph, all channels'
+// orders reversed 1199 us with the other kernel alone, 1236 us with this one in front of it.
 #pragma once
 
 #include "device_common.h"
@@ -84,7 +88,7 @@ inline bool transfer_plan(TransferParams *p, int64_t n_cand, int n_cu, uint32_t 
   p->s_part = p->s_list + up(2 * N, 16);
   p->team_stride = p->s_part + 64;
   // Two lanes per machine where operations send more than one message: the MoE graph (2.2 out-edges per operation) then
-  // takes 2810 steps instead of 4377, a pipeline (1.25) as many as before with half the candidates in a wavefront.
+  // takes 3664 steps instead of 4377, a pipeline (1.25) as many as before with half the candidates in a wavefront.
   p->R = 2 * (uint64_t)E > 3 * (uint64_t)N && p->Pseg <= kWave / 2 ? 2 : 1;
   for (int G = kWave / (p->Pseg * p->R); G >= 1; G >>= 1) {
     for (int slots : {32, 16}) {
