@@ -35,12 +35,14 @@
 #include "kernel_coarsen.h"
 #include "kernel_contended.h"
 #include "kernel_general.h"
+#include "kernel_pipeline.h"
 #include "kernel_ring.h"
 #include "kernel_schedule.h"
 #include "kernel_search.h"
 #include "kernel_static.h"
 #include "kernel_transfers.h"
 #include "kernel_util.h"
+#include "share_cells.h"
 
 using namespace dagsched_dev;
 
@@ -124,6 +126,8 @@ struct dagsched {
   uint8_t *d_st_machine = nullptr;
   int32_t *d_st_off = nullptr;
   int64_t *d_st_base = nullptr;
+  // ... its form for pipelines (pl.total == 0: not in use); the tables above serve both
+  PipelineParams pl{};
   // search helpers: machine counts of a base schedule
   int32_t *ws_cnt = nullptr;
   // start and end times of one schedule: rows of scratch, where the end times live, ring slots, LDS of the workgroup
@@ -716,7 +720,7 @@ int static_threads(int relaxers) {                       // relaxers, accountant
 // and how many relaxing wavefronts share a workgroup.  Not taken (ok = false) when an operation has more than four
 // distinct DAG predecessors, a time does not fit the op format or 16 bits, or the LDS is too small.
 struct StaticPlan {
-  bool ok = false;
+  bool ok = false, fits_format = false;                // fits_format: predecessors and times are what the kernel takes
   int G = 0, W = 0, preds = 4, scale = 1, wgs = 1;      // wgs: workgroups that fit a CU
   uint32_t o_mem = 0, o_mach = 0, o_cand = 0, cand_stride = 0, o_list = 0, o_book = 0, total = 0;
   std::vector<uint4> ops;
@@ -772,6 +776,7 @@ StaticPlan plan_static(const dagsched_desc_t *d, const std::vector<int32_t> &pre
     plan.base.assign(P, 0);
     for (int v = 0; v < N; ++v) plan.base[pi[v]] += d->weight[v];
   }
+  plan.fits_format = true;
   // LDS: op table, memory adjustments, then per candidate the cells (N + 3, padded) and the list (N + 4 entries), then bookkeeping
   plan.G = kWave / Pseg;
   const uint32_t cells = align_up((uint32_t)((N + 4) / 2) * 4u, 4u), list = (uint32_t)((N + 5) / 2) * 4u;
@@ -803,6 +808,91 @@ StaticPlan plan_static(const dagsched_desc_t *d, const std::vector<int32_t> &pre
   plan.o_book = plan.o_cand + (uint32_t)(plan.G * plan.W) * plan.cand_stride;
   plan.total = plan.o_book + 1024u + 512u * (uint32_t)plan.W;
   plan.ok = true;
+  return plan;
+}
+
+// Plan of the pipeline kernel, the leaner form of the shared-placement kernel for graphs whose operations wait for at most
+// one end time each.  base: what plan_static says about times and predecessors (its limits hold here as well).
+struct PipelinePlan {
+  bool ok = false;
+  int T = 0;                                             // bits of an end time in a cell
+  PipelineParams p{};
+  int wgs = 1;
+  std::vector<uint4> ops;
+};
+
+int pipeline_threads(int relaxers) { return std::max(256, 2 * relaxers * kWave); }
+
+PipelinePlan plan_pipeline(const dagsched_desc_t *d, const StaticPlan &base, const PredLists &reduced, int64_t sum_dur, int lds_max, int n_cu) {
+  PipelinePlan plan;
+  const int N = d->n_nodes, P = d->n_devices, Pseg = next_pow2(P);
+  const int32_t *pi = d->shared_placement;
+  if (!base.fits_format) return plan;
+  // one predecessor on the operation's own machine is a matter of the order; what is left is read
+  std::vector<int32_t> local((size_t)N), before((size_t)N, -1), read_ptr((size_t)N + 1, 0), read_idx, count((size_t)P, 0);
+  for (int v = 0; v < N; ++v) local[v] = count[pi[v]]++;
+  int64_t max_delay = 0;
+  for (int v = 0; v < N; ++v) {
+    int32_t other = -1;
+    for (int32_t u : reduced[v]) {
+      if (pi[u] == pi[v] && (before[v] < 0 || before[v] == u)) before[v] = u;
+      else if (other < 0 || other == u) other = u;
+      else return plan;
+    }
+    if (other >= 0) {
+      read_idx.push_back(other);
+      if (pi[other] != pi[v]) max_delay = std::max<int64_t>(max_delay, d->comm[pi[other] * P + pi[v]] / base.scale);
+    }
+    read_ptr[v + 1] = (int32_t)read_idx.size();
+  }
+  const int64_t bound = sum_dur / base.scale + N * max_delay;   // no end time, nor one plus a delay, exceeds this
+  while ((1ll << plan.T) <= bound) ++plan.T;
+  if (plan.T > 30) return plan;
+  const dagsched_host::SharedCells cells = dagsched_host::share_cells(N, reduced.ptr, reduced.idx, read_ptr, read_idx, (int)((1u << (31 - plan.T)) - 1u));
+  PipelineParams &p = plan.p;
+  p.n_cells = (uint32_t)cells.n_cells + 2u;
+  if (p.n_cells * 4u > 65535u) return plan;              // (an op holds 16-bit offsets)
+  const uint32_t unread = (p.n_cells - 1u) * 4u;
+  plan.ops.resize((size_t)N + 1);
+  for (int v = 0; v < N; ++v) {
+    uint32_t at = 0, key = 0;
+    if (read_ptr[v + 1] > read_ptr[v]) {
+      const int32_t u = read_idx[read_ptr[v]];
+      const uint32_t delay = pi[u] != pi[v] ? (uint32_t)(d->comm[pi[u] * P + pi[v]] / base.scale) : 0u;
+      at = (uint32_t)cells.cell[u] * 4u;
+      key = delay - ((uint32_t)cells.user[u] << plan.T);
+    }
+    const uint32_t own = cells.cell[v] ? (uint32_t)cells.cell[v] * 4u : unread;
+    plan.ops[v] = make_uint4(at | (own << 16), key, (uint32_t)(d->dur[v] / base.scale) + ((uint32_t)cells.user[v] << plan.T),
+                             (uint32_t)local[v] | ((before[v] < 0 ? 0xFFFFu : (uint32_t)local[before[v]]) << 16));
+  }
+  plan.ops[N] = make_uint4(unread << 16, 0x80000000u, 0u, 0xFFFF0000u);
+  const int longest = *std::max_element(count.begin(), count.end());
+  if (longest >= 0xFFFF || N + P + 3 > 0xFFFF) return plan;
+  p.seen_words = (uint32_t)(longest + 31) / 32u;
+  p.limit = 1u << plan.T;
+  p.G = kWave / Pseg;
+  p.o_mem = (uint32_t)(N + 1) * 16u;
+  p.o_mach = p.o_mem + (uint32_t)N * 8u;
+  p.o_cand = align_up(p.o_mach + (uint32_t)(N + 3) / 4u * 4u, 16u);
+  p.o_list = p.n_cells * 4u;
+  p.cand_stride = align_up(p.o_list + (uint32_t)(N + P + 4) / 2u * 4u, 16u);
+  const int lds_cu = 160 * 1024;
+  const int forced_w = d->shape ? d->shape->static_waves : 0;
+  int64_t best_score = -1;
+  for (int w = 1; w <= 4; ++w) {                         // (512 threads)
+    if (p.G * w > kWave || (forced_w && w != forced_w)) continue;
+    const uint32_t o_seen = p.o_cand + (uint32_t)(p.G * w) * p.cand_stride, o_book = align_up(o_seen + (uint32_t)w * p.seen_words * 256u, 16u);
+    const uint32_t total = o_book + 1024u + 512u * (uint32_t)w;
+    if ((int)total > lds_max) break;
+    const int wgs = std::max(1, std::min(lds_cu / (int)align_up(total, 1280), 32 / (pipeline_threads(w) / kWave)));
+    const int64_t batches = ((int64_t)d->max_candidates + p.G * w - 1) / (p.G * w);
+    if (!forced_w && batches < n_cu) continue;           // (not enough for every CU: the ring kernel's single launch)
+    const int64_t relaxers = std::min<int64_t>({8, (int64_t)wgs * w, (batches + n_cu - 1) / n_cu * w});   // at work on a CU
+    const int64_t score = relaxers * 16 + (wgs >= 2 ? 8 : 0) + w;
+    if (score > best_score) { best_score = score; p.W = w; plan.wgs = wgs; p.o_seen = o_seen; p.o_book = o_book; p.total = total; }
+  }
+  plan.ok = best_score >= 0;
   return plan;
 }
 
@@ -882,10 +972,15 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
     launch_general(h, n_cand, pl, rk, out, nullptr, nullptr, stream);
   } else if (h->variant == kVariantStatic) {
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, stream, h->d_fb_count);
+    const int per_wg = h->pl.total ? h->pl.G * h->pl.W : h->st.G * h->st.W;
+    const unsigned blocks = (unsigned)std::min((n_cand + per_wg - 1) / per_wg, h->st_grid);
     StaticParams p = h->st;
     p.C = n_cand; p.placement = pl; p.rank = rk; p.out = out;
-    const int per_wg = p.G * p.W;
-    const unsigned blocks = (unsigned)std::min((n_cand + per_wg - 1) / per_wg, h->st_grid);
+    if (h->pl.total) {
+      PipelineParams q = h->pl;
+      q.C = n_cand; q.placement = pl; q.rank = rk; q.out = out;
+      hipLaunchKernelGGL(relax_pipeline_kernel, dim3(blocks), dim3((unsigned)pipeline_threads(q.W)), (size_t)q.total, stream, q);
+    } else
     hipLaunchKernelGGL(h->st_preds == 2 ? relax_static_kernel<2> : relax_static_kernel<4>, dim3(blocks),
                        dim3((unsigned)static_threads(p.W)), (size_t)p.total, stream, p);
     launch_general(h, n_cand, pl, rk, out, h->d_fb_list, h->d_fb_count, stream);   // candidates with another placement
@@ -1015,10 +1110,13 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
 
   RingPlan plan;
   StaticPlan splan;
+  PipelinePlan pplan;
   const PredLists reduced = reduce_preds(desc, pred_ptr, pred_idx);
   const bool force_general = desc->shape && desc->shape->kernel == 1;
   if (!force_general && desc->shared_placement && !(desc->shape && desc->shape->ignore_shared_placement))
     splan = plan_static(desc, pred_ptr, pred_idx, sum_dur, lds_max, n_cu);
+  if (splan.fits_format) pplan = plan_pipeline(desc, splan, reduced, sum_dur, lds_max, n_cu);
+  splan.ok = splan.ok || pplan.ok;
   if (!force_general && !splan.ok) plan = plan_ring(desc, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
   const bool need_general = splan.ok || !plan.ok || !plan.exact;
 
@@ -1065,9 +1163,10 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   if (ok && splan.ok) {
     h->variant = kVariantStatic;
     h->time_scale = splan.scale;
-    h->st_preds = splan.preds;
-    h->st_grid = n_cu * splan.wgs;
-    ok = upload(&h->d_st_ops, splan.ops.data(), splan.ops.size()) &&
+    h->st_preds = pplan.ok ? 1 : splan.preds;
+    h->st_grid = n_cu * (pplan.ok ? pplan.wgs : splan.wgs);
+    const std::vector<uint4> &st_ops = pplan.ok ? pplan.ops : splan.ops;
+    ok = upload(&h->d_st_ops, st_ops.data(), st_ops.size()) &&
          upload(&h->d_st_machine, splan.machine.data(), splan.machine.size()) &&
          upload(&h->d_st_off, splan.off.data(), splan.off.size()) &&
          (splan.base.empty() || upload(&h->d_st_base, splan.base.data(), splan.base.size())) &&
@@ -1080,7 +1179,14 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     s.fb_count = h->d_fb_count; s.fb_list = h->d_fb_list;
     s.o_mem = splan.o_mem; s.o_mach = splan.o_mach; s.o_cand = splan.o_cand; s.cand_stride = splan.cand_stride; s.o_list = splan.o_list; s.o_book = splan.o_book;
     s.total = splan.total;
-    if (ok && s.total > 48 * 1024)
+    if (pplan.ok) {
+      PipelineParams &q = h->pl;
+      q = pplan.p;
+      q.N = h->N; q.P = h->P; q.Pseg = h->Pseg; q.log_pseg = s.log_pseg;
+      q.ops = s.ops; q.machine = s.machine; q.off = s.off; q.mem_delta = s.mem_delta; q.base = s.base; q.mem_limit = s.mem_limit;
+      q.sum_dur = s.sum_dur; q.time_scale = s.time_scale; q.fb_count = s.fb_count; q.fb_list = s.fb_list;
+      if (ok && q.total > 48 * 1024) ok = allow_large_lds((const void *)relax_pipeline_kernel, h->device, (int)q.total);
+    } else if (ok && s.total > 48 * 1024)
       ok = allow_large_lds(splan.preds == 2 ? (const void *)relax_static_kernel<2> : (const void *)relax_static_kernel<4>, h->device, (int)s.total);
   }
   if (ok && plan.ok) {
@@ -1513,7 +1619,11 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
   StaticPlan splan;
   if (!force_general && cleaned.shared_placement && !(cleaned.shape && cleaned.shape->ignore_shared_placement))
     splan = plan_static(&cleaned, pred_ptr, pred_idx, sum_dur, lds_bytes, n_cu);
-  if (!force_general && !splan.ok) plan = plan_ring(&cleaned, pred_ptr, pred_idx, reduce_preds(&cleaned, pred_ptr, pred_idx), sum_dur, lds_bytes, n_cu);
+  const PredLists reduced = reduce_preds(&cleaned, pred_ptr, pred_idx);
+  PipelinePlan pplan;
+  if (splan.fits_format) pplan = plan_pipeline(&cleaned, splan, reduced, sum_dur, lds_bytes, n_cu);
+  splan.ok = splan.ok || pplan.ok;
+  if (!force_general && !splan.ok) plan = plan_ring(&cleaned, pred_ptr, pred_idx, reduced, sum_dur, lds_bytes, n_cu);
   if (splan.ok || !plan.ok || !plan.exact) {
     h.gen_G = kWave / h.Pseg;
     const int64_t lds_need = (int64_t)h.gen_G * h.N * 4;
@@ -1525,6 +1635,7 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
     h.variant = kVariantStatic;
     h.time_scale = splan.scale; h.st_preds = splan.preds;
     h.st.G = splan.G; h.st.W = splan.W; h.st.total = splan.total;
+    if (pplan.ok) { h.pl = pplan.p; h.st_preds = 1; }
   }
   if (plan.ok) {
     h.variant = !plan.exact ? kVariantRingOptimistic : plan.cell32 ? kVariantRing32 : kVariantRingExact;
@@ -1544,9 +1655,11 @@ int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info) {
   info->lds_bytes = ring ? (int32_t)h->lds.total : h->gen_lds;
   info->state_bits = ring && h->lds.cell_bytes != 4 ? 16 : 32;
   if (h->variant == kVariantStatic) {
-    info->cand_per_block = h->st.G * h->st.W;
-    info->block_threads = static_threads(h->st.W);
-    info->lds_bytes = (int32_t)h->st.total;
+    const bool pipeline = h->pl.total != 0;
+    info->cand_per_block = pipeline ? h->pl.G * h->pl.W : h->st.G * h->st.W;
+    info->block_threads = pipeline ? pipeline_threads(h->pl.W) : static_threads(h->st.W);
+    info->lds_bytes = (int32_t)(pipeline ? h->pl.total : h->st.total);
+    info->kernel_kind = pipeline ? 3 : 0;
     info->state_bits = 16;
     info->time_scale = h->time_scale;
     info->preds_per_op = (int8_t)h->st_preds;

@@ -12,6 +12,7 @@ constexpr int kWave = 64;
 
 // bits collected per candidate while it is being evaluated; turned into one DAGSCHED_FLAG_* at the end
 constexpr int kBitCyclic = 1, kBitBadPlacement = 2, kBitBadRank = 4, kBitInternal = 8, kBitOverMemory = 16;
+constexpr int kBitOtherPlacement = 64;   // the candidate does not use the shared placement: another kernel evaluates it
 
 __device__ __forceinline__ int flag_from_bits(int bits) {
   return (bits & kBitBadPlacement) ? DAGSCHED_FLAG_BAD_PLACEMENT

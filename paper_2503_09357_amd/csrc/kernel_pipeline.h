@@ -1,0 +1,310 @@
+// Pipeline kernel: candidates that share one placement (as for kernel_static.h) on a graph where every operation waits
+// for at most one operation whose end time has to be looked up.
+//
+// With the allocation known, an edge between two operations of one machine needs no end time: the machine runs them
+// one after the other, so eqs. (11)-(13) hold exactly when the order has them the right way round, and a candidate
+// that has not is cyclic.  Of a pipeline's edges the ones that other paths imply are dropped, and what is left is one
+// edge per operation that crosses machines, so
+//
+//   relaxers     (waves 0 .. W-1) read one cell a step: x = max(e_chainpred, cell + K), one addition and one maximum
+//                (K: delay and the number of the cell's user that is waited for, see share_cells.h)
+//   accountants  (waves W .. 2W-1) walk the orders for the memory levels (eqs. (17)-(19)) and check, with a bit per
+//                operation, that the operations of one machine keep the order of B.
+//
+// A candidate's cells are few (zero-bubble pipeline: 34 words instead of 768 half words), so two workgroups fit a CU and one
+// relaxes while the other reads its next candidates: everybody takes part in the ingest.
+//
+// What bounds it: the steps, a chain of LDS round trips with 11 vector instructions of one wavefront between them.
+// Written out in assembly because what a lane does only when its operation has run (most lanes wait in most steps)
+// is done under the lanes' mask, without a branch and without a wait: the cell is written, the next operation moves up
+// and the one after it is requested by those lanes only, which is what keeps eight relaxers from queueing for the LDS.
+// Zero-bubble pipeline, 768 operations, 65536 candidates: 291 us with kernel_static.h (218 cycles a step, four relaxers a
+// CU), 161 us here (156 cycles, eight); 4096 candidates: 48 (ring kernel) and 31 us.
+#pragma once
+
+#include "device_common.h"
+
+namespace dagsched_dev {
+
+struct PipelineParams {
+  int32_t N, P, Pseg, log_pseg, G, W, C;   // G candidates per relaxer, W relaxers per workgroup
+  const uint4 *ops;          // [N + 1] x = offset of the cell read | of the own cell << 16, y = K, z = duration + (own user << T),
+                             //         w = number of the operation on its machine | number of the one that must come before it << 16
+                             //         (0xFFFF: none); entry N: never ready, ends every machine's list
+  const uint8_t *machine;    // [N rounded up to 4] the shared placement
+  const int32_t *off;        // [Pseg + 1] operations on the machines before machine j
+  const int64_t *mem_delta;  // [N]
+  const int64_t *base;       // [P] static memory on each machine under the shared placement (eq. (16)), or NULL
+  const int64_t *mem_limit;  // [P] or NULL
+  int64_t sum_dur;           // original units
+  int32_t time_scale;
+  uint32_t limit;            // 1 << T
+  const int32_t *placement, *rank;   // [C][N]
+  int32_t *fb_count, *fb_list;       // candidates with another placement
+  uint32_t n_cells;                  // cell 0 (always 0), the shared ones, one that nobody reads
+  uint32_t o_mem, o_mach, o_cand, cand_stride, o_list, o_seen, seen_words, o_book, total;   // LDS: ops at 0; per candidate cells, then list
+  OutPtrs out;
+};
+
+// One step of the relaxer, for all lanes whose machine can go on.  e: the cell that cur waits for; v[40:43]: the next
+// operation; idn: number of the one after it; lp: where the list goes on.  Order of the LDS accesses: own cell, cell
+// waited for, next operation, list.  The first wait is for the cell (two accesses after it may be on their way), the
+// second for next operation and list, which the access before them has had a whole step to let through.
+#define DAGSCHED_PIPELINE_STEP                                                                                                  \
+  "s_waitcnt lgkmcnt(2)\n\t"                                                                                                    \
+  "v_add_u32 %[x], %[e], %[k]\n\t"                                                                                              \
+  "v_max_u32 %[x], %[xa], %[x]\n\t"                                                                                             \
+  "v_cmp_gt_u32 vcc, %[lim], %[x]\n\t"                                                                                          \
+  "v_add_u32 %[y], %[x], %[d]\n\t"                                                                                              \
+  "s_or_b64 %[moved], %[moved], vcc\n\t"                                                                                        \
+  "s_mov_b64 exec, vcc\n\t"                                                                                                     \
+  "ds_write_b32 %[own], %[y]\n\t"                                                                                               \
+  "s_waitcnt lgkmcnt(1)\n\t"                                                                                                    \
+  "v_add_u32_sdwa %[at], %[cb], v40 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"                     \
+  "s_mov_b64 exec, %[all]\n\t"                                                                                                  \
+  "ds_read_b32 %[e], %[at]\n\t"                                                                                                 \
+  "s_mov_b64 exec, vcc\n\t"                                                                                                     \
+  "v_and_b32 %[xa], %[tm], %[y]\n\t"                                                                                            \
+  "v_add_u32_sdwa %[own], %[cb], v40 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"                    \
+  "v_mov_b32 %[k], v41\n\t"                                                                                                     \
+  "v_mov_b32 %[d], v42\n\t"                                                                                                     \
+  "v_lshl_add_u32 %[x], %[idn], 4, %[ob]\n\t"                                                                                   \
+  "ds_read_b128 v[40:43], %[x]\n\t"                                                                                             \
+  "ds_read_u16 %[idn], %[lp]\n\t"                                                                                               \
+  "v_add_u32 %[lp], 2, %[lp]\n\t"                                                                                               \
+  "s_mov_b64 exec, %[all]\n\t"
+
+__global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int T = (int)blockDim.x;                            // at least 128 * W
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = p.N, P = p.P, Pseg = p.Pseg, G = p.G, W = p.W;
+  const int GW = G * W;                                     // candidates per batch, at most 64
+  const int n_batches = (int)(((int64_t)p.C + GW - 1) / GW);
+  lds_byte_t *const ldsb = (lds_byte_t *)lds;
+  uint4 *const opsw = (uint4 *)lds;
+  int64_t *const memw = (int64_t *)(lds + p.o_mem);         // [N] A_i
+  uint32_t *const machw = (uint32_t *)(lds + p.o_mach);     // [N / 4 rounded up] the shared placement, four machines per word
+  uint32_t *const seenw = (uint32_t *)(lds + p.o_seen);     // [W][seen_words][64] operations of the lane's machine that have been passed
+  int32_t *const flagw = (int32_t *)(lds + p.o_book);       // [64]
+  uint32_t *const pairw = (uint32_t *)(lds + p.o_book + 256);   // [64] start of machine j in every list | operations << 16
+  uint8_t *const overb = lds + p.o_book + 512;              // [64] 1 = some machine of the candidate is over its memory limit
+  int32_t *const cycw = (int32_t *)(lds + p.o_book + 576);  // [64] 1 = an order contradicts B inside a machine
+  uint16_t *const idle_list = (uint16_t *)(lds + p.o_book + 832);   // four entries that name operation N
+  int64_t *const peakw = (int64_t *)(lds + p.o_book + 1024);    // [W][64]
+
+  const int tpc = T / GW, team = tid / tpc, tt = tid - team * tpc;   // ingest: a team of consecutive threads per candidate
+  constexpr int kChunk = 6;
+  const bool vec_ok = ((N & 3) == 0) && ((((uintptr_t)p.placement) | ((uintptr_t)p.rank)) & 15) == 0;
+  const int nq = N >> 2;
+  const int n_list = N + P + 3;                             // entries: a terminal per machine, three more at the end
+  const int cwords = (int)p.n_cells, lwords = (n_list + 1) / 2;
+
+  for (int i = tid; i <= N; i += T) opsw[i] = p.ops[i];
+  for (int i = tid; i < N; i += T) memw[i] = p.mem_delta[i];
+  for (int i = tid; i < (N + 3) / 4; i += T) machw[i] = ((const uint32_t *)p.machine)[i];
+  if (tid < 64) pairw[tid] = tid < P ? (uint32_t)(p.off[tid] + tid) | ((uint32_t)(p.off[tid + 1] - p.off[tid]) << 16) : 0u;
+  if (tid < 4) idle_list[tid] = (uint16_t)N;
+
+  const bool lane_on = lane < G * Pseg;
+  const int ql = lane_on ? lane : 0;
+  const int g = ql >> p.log_pseg, j = ql & (Pseg - 1);
+  const int role_wave = wave < W ? wave : wave < 2 * W ? wave - W : 0;
+  const int gi = role_wave * G + g;                         // candidate slot of this lane (roles only)
+
+  for (int b = (int)blockIdx.x; b < n_batches; b += (int)gridDim.x) {
+    const int64_t c0 = (int64_t)b * GW;
+    const int ng = (int)min((int64_t)GW, (int64_t)p.C - c0);
+    // ---------------------------------------------------------------- ingest
+    int4 a4[kChunk], r4[kChunk];
+    const bool mine = team < ng;
+    // (one base per batch and row in scalar registers, and offsets worked out at the loads from a number the compiler cannot
+    // see through: carried along from batch to batch they would not fit the registers)
+    const char *const base_pl = (const char *)(p.placement + c0 * N), *const base_rk = (const char *)(p.rank + c0 * N);
+    auto request = [&](int q0) {
+      asm volatile("" : "+v"(q0));
+      const uint32_t row = (uint32_t)(mine ? team : 0) * (uint32_t)N * 4u;
+#pragma unroll
+      for (int u = 0; u < kChunk; ++u) {
+        const uint32_t at = row + (uint32_t)min(q0 + u * tpc, nq - 1) * 16u;
+        a4[u] = *(const int4 *)(base_pl + at);
+        r4[u] = *(const int4 *)(base_rk + at);
+      }
+    };
+    if (vec_ok && mine) request(tt);
+    if (tid < 64) { flagw[tid] = 0; overb[tid] = 0; cycw[tid] = 0; }
+    for (int i = tid; i < (int)(W * kWave * p.seen_words); i += T) seenw[i] = 0;
+    if (team < GW) {
+      uint32_t *const w = (uint32_t *)(lds + p.o_cand + team * p.cand_stride);
+      for (int i = tt; i < cwords + lwords; i += tpc) w[i] = i < cwords ? 0u : 0xFFFFFFFFu;   // (the list follows the cells)
+    }
+    __syncthreads();
+    // x as promised (else: another kernel's candidate), ranks inside the machine's range (eqs. (6)-(8))
+    if (mine) {
+      const int32_t *const pl = p.placement + (c0 + team) * N, *const rk = p.rank + (c0 + team) * N;
+      uint16_t *const list = (uint16_t *)(lds + p.o_cand + team * p.cand_stride + p.o_list);
+      for (int m = tt; m < P; m += tpc) list[(pairw[m] & 0xFFFFu) + (pairw[m] >> 16)] = (uint16_t)N;
+      if (tt < 3) list[N + P + tt] = (uint16_t)N;
+      int bits = 0;
+      // (without a branch, so that the LDS reads of a round are all in flight together: an operation that cannot be put into
+      // its list goes to the last entry, which nobody reads)
+      const uint32_t dump = (uint32_t)n_list - 1u;
+      auto place = [&](int v, bool live, int32_t a, int32_t r, uint32_t m, uint32_t pair) {
+        const bool bad_pl = (uint32_t)a >= (uint32_t)P, other = (uint32_t)a != m, bad_rk = (uint32_t)r >= (pair >> 16);
+        bits |= (live && bad_pl) ? kBitBadPlacement : 0;
+        bits |= (live && !bad_pl && other) ? kBitOtherPlacement : 0;
+        bits |= (live && !other && bad_rk) ? kBitBadRank : 0;
+        list[live && !other && !bad_rk ? (pair & 0xFFFFu) + (uint32_t)r : dump] = (uint16_t)v;
+      };
+      if (vec_ok) {
+        for (int q0 = tt; q0 < nq; q0 += kChunk * tpc) {
+          if (q0 != tt) request(q0);
+          int qs = q0;
+          asm volatile("" : "+v"(qs));
+          uint32_t mw[kChunk];
+#pragma unroll
+          for (int u = 0; u < kChunk; ++u) mw[u] = machw[min(qs + u * tpc, nq - 1)];
+#pragma unroll
+          for (int half = 0; half < kChunk; half += 2) {
+            uint32_t pr[2][4];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+              for (int e = 0; e < 4; ++e) pr[u][e] = pairw[(mw[half + u] >> (8 * e)) & 0xFF];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+              const int q = qs + (half + u) * tpc;
+              const int32_t av[4] = {a4[half + u].x, a4[half + u].y, a4[half + u].z, a4[half + u].w};
+              const int32_t rv[4] = {r4[half + u].x, r4[half + u].y, r4[half + u].z, r4[half + u].w};
+#pragma unroll
+              for (int e = 0; e < 4; ++e) place(4 * q + e, q < nq, av[e], rv[e], (mw[half + u] >> (8 * e)) & 0xFF, pr[u][e]);
+            }
+          }
+        }
+      } else {
+        for (int v = tt; v < N; v += tpc) {
+          const uint32_t m = (machw[v >> 2] >> ((v & 3) << 3)) & 0xFF;
+          place(v, true, pl[v], rk[v], m, pairw[m]);
+        }
+      }
+      if (bits) atomicOr(&flagw[team], bits);
+    }
+    __syncthreads();
+    // N operations into N slots: no slot left unwritten <=> every (machine, rank) slot hit exactly once
+    if (mine && !(flagw[team] & (kBitBadPlacement | kBitOtherPlacement))) {
+      const uint32_t *const lw = (const uint32_t *)(lds + p.o_cand + team * p.cand_stride + p.o_list);
+      bool hole = false;
+      const int nw = (N + P + 1) / 2;                       // (entry N + P is a terminal)
+      for (int i0 = tt; i0 < nw; i0 += 8 * tpc) {
+        uint32_t w[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) w[u] = lw[min(i0 + u * tpc, nw - 1)];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) hole |= (w[u] & 0xFFFFu) == 0xFFFFu || (w[u] >> 16) == 0xFFFFu;
+      }
+      if (hole) atomicOr(&flagw[team], kBitBadRank);
+    }
+    __syncthreads();
+
+    const bool ok = wave < 2 * W && lane_on && gi < ng && flagw[gi] == 0 && j < P;
+    const uint32_t pair = ok ? pairw[j] : 0u, n_ops = pair >> 16;
+    int32_t z = 0;
+    if (wave < W) {
+      // -------------------------------------------------------------- relaxer
+      const uint32_t cb = (uint32_t)(uintptr_t)(ldsb + p.o_cand + (uint32_t)(gi < GW ? gi : 0) * p.cand_stride);
+      auto ld16 = [](uint32_t a) -> uint32_t { return (uint32_t)*(lds_vu16_t *)(uintptr_t)a; };
+      const uint32_t ob = (uint32_t)(uintptr_t)ldsb;
+      const uint32_t l0 = ok ? cb + p.o_list + 2u * (pair & 0xFFFFu) : ob + p.o_book + 832u;
+      const u32x4_t first = *(lds_vu32x4_t *)(uintptr_t)(ob + ld16(l0) * 16u);
+      u32x4_t next = *(lds_vu32x4_t *)(uintptr_t)(ob + ld16(l0 + 2) * 16u);
+      uint32_t idn = ld16(l0 + 4), lp = l0 + 6;
+      uint32_t lp_end = l0 + 6 + 2 * n_ops;                  // where lp is when the machine is through (or given up)
+      uint32_t xa = 0, k = first.y, d = first.z, own = cb + (first.x >> 16), at = cb + (first.x & 0xFFFFu);
+      uint32_t e = *(lds_vu32_t *)(uintptr_t)at;
+      const uint64_t seg0 = (Pseg == kWave) ? ~0ull : ((1ull << Pseg) - 1ull);
+      const uint32_t seg_shift = (uint32_t)(g * Pseg);
+      const uint32_t tm = p.limit - 1u;
+      const uint64_t all = ~0ull;
+      __builtin_amdgcn_s_setprio(3);
+      // (every window completes an operation or gives up a candidate)
+      const uint32_t max_windows = (uint32_t)N * (uint32_t)G + (uint32_t)G + 2u;
+      for (uint32_t win = 0; win < max_windows; ++win) {
+        uint64_t moved = 0;
+        uint32_t x, y;
+        asm volatile("s_waitcnt lgkmcnt(0)\n\t" DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP
+                     DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP "s_waitcnt lgkmcnt(0)"
+                     : [x] "=&v"(x), [y] "=&v"(y), [e] "+v"(e), [k] "+v"(k), [d] "+v"(d), [xa] "+v"(xa), [own] "+v"(own), [at] "+v"(at),
+                       [idn] "+v"(idn), [lp] "+v"(lp), "+{v[40:43]}"(next), [moved] "+s"(moved)
+                     : [cb] "v"(cb), [lim] "s"(p.limit), [tm] "s"(tm), [ob] "s"(ob), [all] "s"(all)
+                     : "vcc", "scc", "memory");
+        const bool open = lp != lp_end;
+        if (__ballot(open) == 0) break;
+        if (open && ((moved >> seg_shift) & seg0) == 0) {    // nothing moved in this candidate: a cycle
+          atomicOr(&flagw[gi], kBitCyclic);
+          lp_end = lp;
+        }
+      }
+      if (lp != lp_end) atomicOr(&flagw[gi], kBitInternal);  // the bound on the windows ran out: never expected
+      __builtin_amdgcn_s_setprio(0);
+      z = (int32_t)xa;
+    } else if (wave < 2 * W) {
+      // -------------------------------------------------------------- accountant
+      const uint16_t *const list = (const uint16_t *)(lds + p.o_cand + (uint32_t)(gi < GW ? gi : 0) * p.cand_stride + p.o_list) + (pair & 0xFFFFu);
+      lds_vu32_t *const seen = (lds_vu32_t *)(ldsb + p.o_seen) + (uint32_t)(role_wave * p.seen_words) * kWave + lane;
+      int64_t level = 0, peak = 0;
+      bool wrong = false;
+      for (uint32_t k = 0; __ballot(k < n_ops) != 0; k += 4) {
+        uint32_t id[4], chk[4], before[4];
+        int64_t m[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) id[u] = k + u < n_ops ? list[k + u] : (uint32_t)N;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { chk[u] = opsw[id[u]].w; m[u] = id[u] < (uint32_t)N ? memw[id[u]] : 0; }
+        // (an operation passed, then the next one's look for its predecessor: the LDS keeps their order)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const uint32_t mine_at = chk[u] & 0xFFFFu, pre = chk[u] >> 16;
+          before[u] = pre == 0xFFFFu ? ~0u : seen[(pre >> 5) * kWave] >> (pre & 31u);
+          if (id[u] < (uint32_t)N)
+            (void)__hip_atomic_fetch_or((DAGSCHED_LDS uint32_t *)&seen[(mine_at >> 5) * kWave], 1u << (mine_at & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          wrong |= !(before[u] & 1u);
+          level += m[u];
+          peak = max(peak, level);                           // eq. (19) along the chain
+        }
+      }
+      if (wrong) cycw[gi] = 1;
+      if (ok && p.base) peak += p.base[j];
+      if (ok && p.mem_limit && peak > p.mem_limit[j]) overb[gi] = 1;
+      if (lane_on) peakw[role_wave * kWave + ql] = peak;
+    }
+    __syncthreads();
+    // ---------------------------------------------------------------- reductions and outputs
+    if (wave < W) {
+      for (int s = 1; s < Pseg; s <<= 1) z = max(z, __shfl_xor(z, s, Pseg));
+      if (lane_on && gi < ng && j < P) {
+        const int64_t c = c0 + gi;
+        const int bits = flagw[gi] | (overb[gi] ? kBitOverMemory : 0) | (cycw[gi] ? kBitCyclic : 0);
+        if ((bits & kBitOtherPlacement) && !(bits & kBitBadPlacement)) {
+          if (j == 0) { const int slot = atomicAdd(p.fb_count, 1); p.fb_list[slot] = (int32_t)c; }   // the general kernel writes this candidate
+        } else {
+          const int flag = flag_from_bits(bits);
+          const int64_t zz = (int64_t)z * p.time_scale;
+          p.out.peak_mem[c * p.out.peak_stride_c + j * p.out.peak_stride_j] = flag ? -1 : peakw[wave * kWave + ql];
+          if (j == 0) {
+            p.out.makespan[c] = flag ? -1 : (int32_t)zz;
+            p.out.bubble[c] = flag ? -1 : (int64_t)P * zz - p.sum_dur;
+            p.out.flags[c] = flag;
+          }
+        }
+      }
+    }
+    __syncthreads();                                         // flags and peaks are reset by the next batch
+  }
+}
+#undef DAGSCHED_PIPELINE_STEP
+
+}  // namespace dagsched_dev

@@ -33,7 +33,7 @@
 
 namespace dagsched_dev {
 
-constexpr int kBitOtherPlacement = 64;   // internal: the candidate does not use the shared placement
+
 
 struct StaticParams {
   int32_t N, P, Pseg, log_pseg, G, W, C;   // G candidates per relaxer wavefront, W relaxers per workgroup
