@@ -125,6 +125,7 @@ struct dagsched {
   uint4 *d_st_ops = nullptr;
   uint8_t *d_st_machine = nullptr;
   int32_t *d_st_off = nullptr;
+  uint32_t *d_st_pairs = nullptr;
   int64_t *d_st_base = nullptr;
   // ... its form for pipelines (pl.total == 0: not in use); the tables above serve both
   PipelineParams pl{};
@@ -267,7 +268,7 @@ void free_handle(dagsched *h) {
   void *bufs[] = {h->problem_tables, h->channel_tables, h->ws_list, h->ws_end, h->d_rec,
                   h->d_comm_scaled, h->d_nparts, h->ws_list16, h->ws_pib, h->ws_cnt, h->ws_sched_list, h->ws_sched_end,
                   h->d_fb_count, h->d_fb_list, h->ws_meta, h->ws_tp, h->ws_tr,
-                  h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_base, h->ws_te,
+                  h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_pairs, h->d_st_base, h->ws_te,
                   h->wc_list, h->wc_end, h->wc_tlist, h->wc_tend, h->wc_ccnt, h->wc_coff, h->wc_echan,
                   h->wc_stream, h->d_tr_list};
   for (void *b : bufs)
@@ -819,6 +820,7 @@ struct PipelinePlan {
   PipelineParams p{};
   int wgs = 1;
   std::vector<uint4> ops;
+  std::vector<uint32_t> pairs;
 };
 
 int pipeline_threads(int relaxers) { return std::max(256, 2 * relaxers * kWave); }
@@ -829,19 +831,18 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, const StaticPlan &base, con
   const int32_t *pi = d->shared_placement;
   if (!base.fits_format) return plan;
   // one predecessor on the operation's own machine is a matter of the order; what is left is read
-  std::vector<int32_t> local((size_t)N), before((size_t)N, -1), read_ptr((size_t)N + 1, 0), read_idx, count((size_t)P, 0);
-  for (int v = 0; v < N; ++v) local[v] = count[pi[v]]++;
+  std::vector<int32_t> read_ptr((size_t)N + 1, 0), read_idx;
   int64_t max_delay = 0;
   for (int v = 0; v < N; ++v) {
     int32_t other = -1;
     for (int32_t u : reduced[v]) {
-      if (pi[u] == pi[v] && (before[v] < 0 || before[v] == u)) before[v] = u;
+      if (pi[u] == pi[v]) plan.pairs.push_back((uint32_t)u | ((uint32_t)v << 16));
       else if (other < 0 || other == u) other = u;
       else return plan;
     }
     if (other >= 0) {
       read_idx.push_back(other);
-      if (pi[other] != pi[v]) max_delay = std::max<int64_t>(max_delay, d->comm[pi[other] * P + pi[v]] / base.scale);
+      max_delay = std::max<int64_t>(max_delay, d->comm[pi[other] * P + pi[v]] / base.scale);
     }
     read_ptr[v + 1] = (int32_t)read_idx.size();
   }
@@ -850,6 +851,14 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, const StaticPlan &base, con
   if (plan.T > 30) return plan;
   const dagsched_host::SharedCells cells = dagsched_host::share_cells(N, reduced.ptr, reduced.idx, read_ptr, read_idx, (int)((1u << (31 - plan.T)) - 1u));
   PipelineParams &p = plan.p;
+  // memory levels in 32 bits, in units of the common factor of the A_i
+  uint64_t factor = 0;
+  for (int v = 0; v < N; ++v) factor = std::gcd<uint64_t, uint64_t>(factor, d->mem_delta[v] < 0 ? 0ull - (uint64_t)d->mem_delta[v] : (uint64_t)d->mem_delta[v]);
+  if (factor > (uint64_t)INT64_MAX) return plan;
+  p.mem_scale = factor ? (int64_t)factor : 1;
+  int64_t swing = 0;                                     // no level is further from 0 than this
+  for (int v = 0; v < N && swing <= INT32_MAX; ++v) swing += std::min<int64_t>(std::abs(d->mem_delta[v] / p.mem_scale), (int64_t)INT32_MAX + 1);
+  if (swing > INT32_MAX) return plan;
   p.n_cells = (uint32_t)cells.n_cells + 2u;
   if (p.n_cells * 4u > 65535u) return plan;              // (an op holds 16-bit offsets)
   const uint32_t unread = (p.n_cells - 1u) * 4u;
@@ -858,22 +867,20 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, const StaticPlan &base, con
     uint32_t at = 0, key = 0;
     if (read_ptr[v + 1] > read_ptr[v]) {
       const int32_t u = read_idx[read_ptr[v]];
-      const uint32_t delay = pi[u] != pi[v] ? (uint32_t)(d->comm[pi[u] * P + pi[v]] / base.scale) : 0u;
+      const uint32_t delay = (uint32_t)(d->comm[pi[u] * P + pi[v]] / base.scale);
       at = (uint32_t)cells.cell[u] * 4u;
       key = delay - ((uint32_t)cells.user[u] << plan.T);
     }
     const uint32_t own = cells.cell[v] ? (uint32_t)cells.cell[v] * 4u : unread;
-    plan.ops[v] = make_uint4(at | (own << 16), key, (uint32_t)(d->dur[v] / base.scale) + ((uint32_t)cells.user[v] << plan.T),
-                             (uint32_t)local[v] | ((before[v] < 0 ? 0xFFFFu : (uint32_t)local[before[v]]) << 16));
+    plan.ops[v] = make_uint4(key, (uint32_t)(d->dur[v] / base.scale) + ((uint32_t)cells.user[v] << plan.T), at | (own << 16),
+                             (uint32_t)(int32_t)(d->mem_delta[v] / p.mem_scale));
   }
-  plan.ops[N] = make_uint4(unread << 16, 0x80000000u, 0u, 0xFFFF0000u);
-  const int longest = *std::max_element(count.begin(), count.end());
-  if (longest >= 0xFFFF || N + P + 3 > 0xFFFF) return plan;
-  p.seen_words = (uint32_t)(longest + 31) / 32u;
+  plan.ops[N] = make_uint4(0x80000000u, 0u, unread << 16, 0u);
+  if (N + P + 3 > 0xFFFF) return plan;
+  p.n_pairs = (int32_t)plan.pairs.size();
   p.limit = 1u << plan.T;
   p.G = kWave / Pseg;
-  p.o_mem = (uint32_t)(N + 1) * 16u;
-  p.o_mach = p.o_mem + (uint32_t)N * 8u;
+  p.o_mach = (uint32_t)(N + 1) * 16u;
   p.o_cand = align_up(p.o_mach + (uint32_t)(N + 3) / 4u * 4u, 16u);
   p.o_list = p.n_cells * 4u;
   p.cand_stride = align_up(p.o_list + (uint32_t)(N + P + 4) / 2u * 4u, 16u);
@@ -882,15 +889,15 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, const StaticPlan &base, con
   int64_t best_score = -1;
   for (int w = 1; w <= 4; ++w) {                         // (512 threads)
     if (p.G * w > kWave || (forced_w && w != forced_w)) continue;
-    const uint32_t o_seen = p.o_cand + (uint32_t)(p.G * w) * p.cand_stride, o_book = align_up(o_seen + (uint32_t)w * p.seen_words * 256u, 16u);
-    const uint32_t total = o_book + 1024u + 512u * (uint32_t)w;
+    const uint32_t o_book = p.o_cand + (uint32_t)(p.G * w) * p.cand_stride, total = o_book + 784u;
     if ((int)total > lds_max) break;
     const int wgs = std::max(1, std::min(lds_cu / (int)align_up(total, 1280), 32 / (pipeline_threads(w) / kWave)));
     const int64_t batches = ((int64_t)d->max_candidates + p.G * w - 1) / (p.G * w);
     if (!forced_w && batches < n_cu) continue;           // (not enough for every CU: the ring kernel's single launch)
+    if (!forced_w && wgs * w < 2) continue;              // (a lone relaxer on a CU: the ring kernel holds as many candidates and more)
     const int64_t relaxers = std::min<int64_t>({8, (int64_t)wgs * w, (batches + n_cu - 1) / n_cu * w});   // at work on a CU
     const int64_t score = relaxers * 16 + (wgs >= 2 ? 8 : 0) + w;
-    if (score > best_score) { best_score = score; p.W = w; plan.wgs = wgs; p.o_seen = o_seen; p.o_book = o_book; p.total = total; }
+    if (score > best_score) { best_score = score; p.W = w; plan.wgs = wgs; p.o_book = o_book; p.total = total; }
   }
   plan.ok = best_score >= 0;
   return plan;
@@ -1183,7 +1190,8 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       PipelineParams &q = h->pl;
       q = pplan.p;
       q.N = h->N; q.P = h->P; q.Pseg = h->Pseg; q.log_pseg = s.log_pseg;
-      q.ops = s.ops; q.machine = s.machine; q.off = s.off; q.mem_delta = s.mem_delta; q.base = s.base; q.mem_limit = s.mem_limit;
+      ok = ok && upload(&h->d_st_pairs, pplan.pairs.data(), pplan.pairs.size());
+      q.ops = s.ops; q.machine = s.machine; q.off = s.off; q.pairs = h->d_st_pairs; q.base = s.base; q.mem_limit = s.mem_limit;
       q.sum_dur = s.sum_dur; q.time_scale = s.time_scale; q.fb_count = s.fb_count; q.fb_list = s.fb_list;
       if (ok && q.total > 48 * 1024) ok = allow_large_lds((const void *)relax_pipeline_kernel, h->device, (int)q.total);
     } else if (ok && s.total > 48 * 1024)

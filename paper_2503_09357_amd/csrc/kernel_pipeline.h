@@ -6,20 +6,21 @@
 // that has not is cyclic.  Of a pipeline's edges the ones that other paths imply are dropped, and what is left is one
 // edge per operation that crosses machines, so
 //
-//   relaxers     (waves 0 .. W-1) read one cell a step: x = max(e_chainpred, cell + K), one addition and one maximum
-//                (K: delay and the number of the cell's user that is waited for, see share_cells.h)
-//   accountants  (waves W .. 2W-1) walk the orders for the memory levels (eqs. (17)-(19)) and check, with a bit per
-//                operation, that the operations of one machine keep the order of B.
+//   relaxers   (waves 0 .. W-1) read one cell a step: x = max(e_chainpred, cell + K), one addition and one maximum
+//              (K: delay and the number of the cell's user that is waited for, see share_cells.h), and keep the machine's memory
+//              level and its peak (eqs. (17)-(19)) as its operations pass
+//   checkers   (the other waves) look the ranks of operations that share a machine up again and compare them with B
 //
 // A candidate's cells are few (zero-bubble pipeline: 34 words instead of 768 half words), so two workgroups fit a CU and one
-// relaxes while the other reads its next candidates: everybody takes part in the ingest.
+// relaxes while the other reads its next candidates; the rows of a workgroup's next batch are on their way while it relaxes.
 //
-// What bounds it: the steps, a chain of LDS round trips with 11 vector instructions of one wavefront between them.
-// Written out in assembly because what a lane does only when its operation has run (most lanes wait in most steps)
+// What bounds it: the steps, each 22 instructions of a lone wavefront (five cycles an instruction, whether the one before is
+// waited for or not; an LDS round trip is 49, and what the lanes' mask costs on its way from the comparison 13), and the LDS
+// that eight of them share.  Written out in assembly because what a lane does only when its operation has run (most lanes wait in most steps)
 // is done under the lanes' mask, without a branch and without a wait: the cell is written, the next operation moves up
-// and the one after it is requested by those lanes only, which is what keeps eight relaxers from queueing for the LDS.
-// Zero-bubble pipeline, 768 operations, 65536 candidates: 291 us with kernel_static.h (218 cycles a step, four relaxers a
-// CU), 161 us here (156 cycles, eight); 4096 candidates: 48 (ring kernel) and 31 us.
+// and the one after it is requested by those lanes only; and because the compiler made 400 cycles of what decides between two blocks of steps.
+// Zero-bubble pipeline, 768 operations, 65536 candidates: 291 us with kernel_static.h (218 cycles a step, one workgroup of four
+// relaxers a CU), 161 with this kernel while accountants took the levels through the LDS and the decisions were the compiler's, 130 now.
 #pragma once
 
 #include "device_common.h"
@@ -28,12 +29,13 @@ namespace dagsched_dev {
 
 struct PipelineParams {
   int32_t N, P, Pseg, log_pseg, G, W, C;   // G candidates per relaxer, W relaxers per workgroup
-  const uint4 *ops;          // [N + 1] x = offset of the cell read | of the own cell << 16, y = K, z = duration + (own user << T),
-                             //         w = number of the operation on its machine | number of the one that must come before it << 16
-                             //         (0xFFFF: none); entry N: never ready, ends every machine's list
+  const uint4 *ops;          // [N + 1] x = K, y = duration + (own user << T), z = offset of the cell read | of the own cell << 16,
+                             //         w = A_i / mem_scale; entry N: never ready, ends every machine's list
   const uint8_t *machine;    // [N rounded up to 4] the shared placement
   const int32_t *off;        // [Pseg + 1] operations on the machines before machine j
-  const int64_t *mem_delta;  // [N]
+  const uint32_t *pairs;     // [n_pairs] u | v << 16: edges of B inside a machine that no cell stands for
+  int32_t n_pairs;
+  int64_t mem_scale;         // common factor of the A_i
   const int64_t *base;       // [P] static memory on each machine under the shared placement (eq. (16)), or NULL
   const int64_t *mem_limit;  // [P] or NULL
   int64_t sum_dur;           // original units
@@ -42,37 +44,53 @@ struct PipelineParams {
   const int32_t *placement, *rank;   // [C][N]
   int32_t *fb_count, *fb_list;       // candidates with another placement
   uint32_t n_cells;                  // cell 0 (always 0), the shared ones, one that nobody reads
-  uint32_t o_mem, o_mach, o_cand, cand_stride, o_list, o_seen, seen_words, o_book, total;   // LDS: ops at 0; per candidate cells, then list
+  uint32_t o_mach, o_cand, cand_stride, o_list, o_book, total;   // LDS: ops at 0; per candidate cells, then list
   OutPtrs out;
 };
 
-// One step of the relaxer, for all lanes whose machine can go on.  e: the cell that cur waits for; v[40:43]: the next
-// operation; idn: number of the one after it; lp: where the list goes on.  Order of the LDS accesses: own cell, cell
+// One step of the relaxer, for all lanes whose machine can go on.  e: the cell that the operation at work waits for; v[44:45]: its K and D;
+// v[40:43]: the next operation; idn: number of the one after it; lp: where the list goes on.  Order of the LDS accesses: own cell, cell
 // waited for, next operation, list.  The first wait is for the cell (two accesses after it may be on their way), the
 // second for next operation and list, which the access before them has had a whole step to let through.
 #define DAGSCHED_PIPELINE_STEP                                                                                                  \
   "s_waitcnt lgkmcnt(2)\n\t"                                                                                                    \
-  "v_add_u32 %[x], %[e], %[k]\n\t"                                                                                              \
+  "v_add_u32 %[x], %[e], v44\n\t"                                                                                              \
   "v_max_u32 %[x], %[xa], %[x]\n\t"                                                                                             \
   "v_cmp_gt_u32 vcc, %[lim], %[x]\n\t"                                                                                          \
-  "v_add_u32 %[y], %[x], %[d]\n\t"                                                                                              \
-  "s_or_b64 %[moved], %[moved], vcc\n\t"                                                                                        \
-  "s_mov_b64 exec, vcc\n\t"                                                                                                     \
+  "v_add_u32 %[y], %[x], v45\n\t"                                                                                              \
+  "s_mov_b64 exec, vcc\n\t"                                                                                                    \
   "ds_write_b32 %[own], %[y]\n\t"                                                                                               \
   "s_waitcnt lgkmcnt(1)\n\t"                                                                                                    \
-  "v_add_u32_sdwa %[at], %[cb], v40 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"                     \
+  "v_add_u32_sdwa %[at], %[cb], v42 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"                     \
   "s_mov_b64 exec, %[all]\n\t"                                                                                                  \
   "ds_read_b32 %[e], %[at]\n\t"                                                                                                 \
   "s_mov_b64 exec, vcc\n\t"                                                                                                     \
   "v_and_b32 %[xa], %[tm], %[y]\n\t"                                                                                            \
-  "v_add_u32_sdwa %[own], %[cb], v40 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"                    \
-  "v_mov_b32 %[k], v41\n\t"                                                                                                     \
-  "v_mov_b32 %[d], v42\n\t"                                                                                                     \
+  "v_add_u32_sdwa %[own], %[cb], v42 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"                    \
+  "v_mov_b64 v[44:45], v[40:41]\n\t"                                                                                           \
+  "v_add_u32 %[lvl], %[lvl], v43\n\t"                                                                                          \
+  "v_max_i32 %[pk], %[pk], %[lvl]\n\t"                                                                                         \
   "v_lshl_add_u32 %[x], %[idn], 4, %[ob]\n\t"                                                                                   \
   "ds_read_b128 v[40:43], %[x]\n\t"                                                                                             \
   "ds_read_u16 %[idn], %[lp]\n\t"                                                                                               \
   "v_add_u32 %[lp], 2, %[lp]\n\t"                                                                                               \
   "s_mov_b64 exec, %[all]\n\t"
+// Blocks of eight steps as long as some lane is not through and something ran in a block's last step, at most `turns` of them.
+#define DAGSCHED_PIPELINE_LOOP                                                                                                  \
+  "s_waitcnt lgkmcnt(0)\n"                                                                                                      \
+  ".Lpipeline%=:\n\t"                                                                                                           \
+  DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP                                   \
+  DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP                                   \
+  "s_mov_b64 %[moved], vcc\n\t"                                                                                                \
+  "v_cmp_ne_u32 vcc, %[lp], %[end]\n\t"                                                                                        \
+  "s_sub_u32 %[turns], %[turns], 1\n\t"                                                                                        \
+  "s_cbranch_vccz .Lpipeline_end%=\n\t"                                                                                        \
+  "s_cmp_eq_u64 %[moved], 0\n\t"                                                                                               \
+  "s_cbranch_scc1 .Lpipeline_end%=\n\t"                                                                                        \
+  "s_cmp_lg_u32 %[turns], 0\n\t"                                                                                               \
+  "s_cbranch_scc1 .Lpipeline%=\n"                                                                                              \
+  ".Lpipeline_end%=:\n\t"                                                                                                       \
+  "s_waitcnt lgkmcnt(0)"
 
 __global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p) {
   extern __shared__ __align__(16) unsigned char lds[];
@@ -84,15 +102,11 @@ __global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p
   const int n_batches = (int)(((int64_t)p.C + GW - 1) / GW);
   lds_byte_t *const ldsb = (lds_byte_t *)lds;
   uint4 *const opsw = (uint4 *)lds;
-  int64_t *const memw = (int64_t *)(lds + p.o_mem);         // [N] A_i
   uint32_t *const machw = (uint32_t *)(lds + p.o_mach);     // [N / 4 rounded up] the shared placement, four machines per word
-  uint32_t *const seenw = (uint32_t *)(lds + p.o_seen);     // [W][seen_words][64] operations of the lane's machine that have been passed
   int32_t *const flagw = (int32_t *)(lds + p.o_book);       // [64]
   uint32_t *const pairw = (uint32_t *)(lds + p.o_book + 256);   // [64] start of machine j in every list | operations << 16
-  uint8_t *const overb = lds + p.o_book + 512;              // [64] 1 = some machine of the candidate is over its memory limit
-  int32_t *const cycw = (int32_t *)(lds + p.o_book + 576);  // [64] 1 = an order contradicts B inside a machine
-  uint16_t *const idle_list = (uint16_t *)(lds + p.o_book + 832);   // four entries that name operation N
-  int64_t *const peakw = (int64_t *)(lds + p.o_book + 1024);    // [W][64]
+  int32_t *const cycw = (int32_t *)(lds + p.o_book + 512);  // [64] 1 = an order contradicts B inside a machine
+  uint16_t *const idle_list = (uint16_t *)(lds + p.o_book + 768);   // four entries that name operation N
 
   const int tpc = T / GW, team = tid / tpc, tt = tid - team * tpc;   // ingest: a team of consecutive threads per candidate
   constexpr int kChunk = 6;
@@ -102,7 +116,6 @@ __global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p
   const int cwords = (int)p.n_cells, lwords = (n_list + 1) / 2;
 
   for (int i = tid; i <= N; i += T) opsw[i] = p.ops[i];
-  for (int i = tid; i < N; i += T) memw[i] = p.mem_delta[i];
   for (int i = tid; i < (N + 3) / 4; i += T) machw[i] = ((const uint32_t *)p.machine)[i];
   if (tid < 64) pairw[tid] = tid < P ? (uint32_t)(p.off[tid] + tid) | ((uint32_t)(p.off[tid + 1] - p.off[tid]) << 16) : 0u;
   if (tid < 4) idle_list[tid] = (uint16_t)N;
@@ -110,31 +123,32 @@ __global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p
   const bool lane_on = lane < G * Pseg;
   const int ql = lane_on ? lane : 0;
   const int g = ql >> p.log_pseg, j = ql & (Pseg - 1);
-  const int role_wave = wave < W ? wave : wave < 2 * W ? wave - W : 0;
-  const int gi = role_wave * G + g;                         // candidate slot of this lane (roles only)
+  const int gi = wave < W ? wave * G + g : 0;               // candidate slot of this lane (relaxers)
+
+  int4 a4[kChunk], r4[kChunk];                              // rows on their way
+  // (one base per batch and row in scalar registers, and offsets worked out at the loads from a number the compiler cannot
+  // see through: carried along from batch to batch they would not fit the registers)
+  auto request = [&](int b, int q0) {
+    const int64_t bs = __builtin_amdgcn_readfirstlane(b);
+    if (!vec_ok || team >= GW || bs >= n_batches || bs * GW + team >= p.C) return;
+    const char *const base_pl = (const char *)(p.placement + bs * GW * N), *const base_rk = (const char *)(p.rank + bs * GW * N);
+    asm volatile("" : "+v"(q0));
+    const uint32_t row = (uint32_t)team * (uint32_t)N * 4u;
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) {
+      const uint32_t at = row + (uint32_t)min(q0 + u * tpc, nq - 1) * 16u;
+      a4[u] = *(const int4 *)(base_pl + at);
+      r4[u] = *(const int4 *)(base_rk + at);
+    }
+  };
+  request((int)blockIdx.x, tt);
 
   for (int b = (int)blockIdx.x; b < n_batches; b += (int)gridDim.x) {
     const int64_t c0 = (int64_t)b * GW;
     const int ng = (int)min((int64_t)GW, (int64_t)p.C - c0);
     // ---------------------------------------------------------------- ingest
-    int4 a4[kChunk], r4[kChunk];
     const bool mine = team < ng;
-    // (one base per batch and row in scalar registers, and offsets worked out at the loads from a number the compiler cannot
-    // see through: carried along from batch to batch they would not fit the registers)
-    const char *const base_pl = (const char *)(p.placement + c0 * N), *const base_rk = (const char *)(p.rank + c0 * N);
-    auto request = [&](int q0) {
-      asm volatile("" : "+v"(q0));
-      const uint32_t row = (uint32_t)(mine ? team : 0) * (uint32_t)N * 4u;
-#pragma unroll
-      for (int u = 0; u < kChunk; ++u) {
-        const uint32_t at = row + (uint32_t)min(q0 + u * tpc, nq - 1) * 16u;
-        a4[u] = *(const int4 *)(base_pl + at);
-        r4[u] = *(const int4 *)(base_rk + at);
-      }
-    };
-    if (vec_ok && mine) request(tt);
-    if (tid < 64) { flagw[tid] = 0; overb[tid] = 0; cycw[tid] = 0; }
-    for (int i = tid; i < (int)(W * kWave * p.seen_words); i += T) seenw[i] = 0;
+    if (tid < 64) { flagw[tid] = 0; cycw[tid] = 0; }
     if (team < GW) {
       uint32_t *const w = (uint32_t *)(lds + p.o_cand + team * p.cand_stride);
       for (int i = tt; i < cwords + lwords; i += tpc) w[i] = i < cwords ? 0u : 0xFFFFFFFFu;   // (the list follows the cells)
@@ -159,9 +173,9 @@ __global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p
       };
       if (vec_ok) {
         for (int q0 = tt; q0 < nq; q0 += kChunk * tpc) {
-          if (q0 != tt) request(q0);
+          if (q0 != tt) request(b, q0);                     // (the first of them were requested a batch ago)
           int qs = q0;
-          asm volatile("" : "+v"(qs));
+          asm volatile("" : "+&v"(qs));
           uint32_t mw[kChunk];
 #pragma unroll
           for (int u = 0; u < kChunk; ++u) mw[u] = machw[min(qs + u * tpc, nq - 1)];
@@ -207,93 +221,85 @@ __global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p
     }
     __syncthreads();
 
-    const bool ok = wave < 2 * W && lane_on && gi < ng && flagw[gi] == 0 && j < P;
-    const uint32_t pair = ok ? pairw[j] : 0u, n_ops = pair >> 16;
-    int32_t z = 0;
+    request(b + (int)gridDim.x, tt);                         // the next batch's rows: on their way while this one is relaxed
+    const bool ok = wave < W && lane_on && gi < ng && flagw[gi] == 0 && j < P;
+    int32_t z = 0, peak = 0;
     if (wave < W) {
       // -------------------------------------------------------------- relaxer
+      const uint32_t pair = ok ? pairw[j] : 0u, n_ops = pair >> 16;
       const uint32_t cb = (uint32_t)(uintptr_t)(ldsb + p.o_cand + (uint32_t)(gi < GW ? gi : 0) * p.cand_stride);
       auto ld16 = [](uint32_t a) -> uint32_t { return (uint32_t)*(lds_vu16_t *)(uintptr_t)a; };
       const uint32_t ob = (uint32_t)(uintptr_t)ldsb;
-      const uint32_t l0 = ok ? cb + p.o_list + 2u * (pair & 0xFFFFu) : ob + p.o_book + 832u;
+      const uint32_t l0 = ok ? cb + p.o_list + 2u * (pair & 0xFFFFu) : ob + p.o_book + 768u;
       const u32x4_t first = *(lds_vu32x4_t *)(uintptr_t)(ob + ld16(l0) * 16u);
       u32x4_t next = *(lds_vu32x4_t *)(uintptr_t)(ob + ld16(l0 + 2) * 16u);
+      typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+      u32x2_t kd = {first.x, first.y};
       uint32_t idn = ld16(l0 + 4), lp = l0 + 6;
-      uint32_t lp_end = l0 + 6 + 2 * n_ops;                  // where lp is when the machine is through (or given up)
-      uint32_t xa = 0, k = first.y, d = first.z, own = cb + (first.x >> 16), at = cb + (first.x & 0xFFFFu);
+      uint32_t end = l0 + 6 + 2 * n_ops;                     // where lp is when the machine is through (or given up)
+      uint32_t x = 0, y = 0, xa = 0, own = cb + (first.z >> 16), at = cb + (first.z & 0xFFFFu);
+      int32_t lvl = (int32_t)first.w, pk = max(0, lvl);      // (an operation counts as it moves up: the order is all that matters)
       uint32_t e = *(lds_vu32_t *)(uintptr_t)at;
       const uint64_t seg0 = (Pseg == kWave) ? ~0ull : ((1ull << Pseg) - 1ull);
       const uint32_t seg_shift = (uint32_t)(g * Pseg);
       const uint32_t tm = p.limit - 1u;
       const uint64_t all = ~0ull;
       __builtin_amdgcn_s_setprio(3);
-      // (every window completes an operation or gives up a candidate)
-      const uint32_t max_windows = (uint32_t)N * (uint32_t)G + (uint32_t)G + 2u;
-      for (uint32_t win = 0; win < max_windows; ++win) {
+      // (every round completes an operation or gives up a candidate)
+      const uint32_t max_rounds = (uint32_t)N * (uint32_t)G + (uint32_t)G + 2u;
+      for (uint32_t round = 0; round < max_rounds; ++round) {
         uint64_t moved = 0;
-        uint32_t x, y;
-        asm volatile("s_waitcnt lgkmcnt(0)\n\t" DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP
-                     DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP "s_waitcnt lgkmcnt(0)"
-                     : [x] "=&v"(x), [y] "=&v"(y), [e] "+v"(e), [k] "+v"(k), [d] "+v"(d), [xa] "+v"(xa), [own] "+v"(own), [at] "+v"(at),
-                       [idn] "+v"(idn), [lp] "+v"(lp), "+{v[40:43]}"(next), [moved] "+s"(moved)
-                     : [cb] "v"(cb), [lim] "s"(p.limit), [tm] "s"(tm), [ob] "s"(ob), [all] "s"(all)
+        uint32_t turns = 16;
+        asm volatile(DAGSCHED_PIPELINE_LOOP
+                     : [x] "+&v"(x), [y] "+&v"(y), [e] "+&v"(e), [xa] "+&v"(xa), [own] "+&v"(own), [at] "+&v"(at), [idn] "+&v"(idn), [lp] "+&v"(lp),
+                       [lvl] "+&v"(lvl), [pk] "+&v"(pk), "+&{v[40:43]}"(next), "+&{v[44:45]}"(kd), [moved] "+&s"(moved), [turns] "+&s"(turns)
+                     : [cb] "v"(cb), [end] "v"(end), [lim] "s"(p.limit), [tm] "s"(tm), [ob] "s"(ob), [all] "s"(all)
                      : "vcc", "scc", "memory");
-        const bool open = lp != lp_end;
+        const bool open = lp != end;
         if (__ballot(open) == 0) break;
-        if (open && ((moved >> seg_shift) & seg0) == 0) {    // nothing moved in this candidate: a cycle
+        if (open && ((moved >> seg_shift) & seg0) == 0) {    // nothing of this candidate ran in the last step: a cycle
           atomicOr(&flagw[gi], kBitCyclic);
-          lp_end = lp;
+          end = lp;
         }
       }
-      if (lp != lp_end) atomicOr(&flagw[gi], kBitInternal);  // the bound on the windows ran out: never expected
+      if (lp != end) atomicOr(&flagw[gi], kBitInternal);     // the bound on the rounds ran out: never expected
       __builtin_amdgcn_s_setprio(0);
       z = (int32_t)xa;
-    } else if (wave < 2 * W) {
-      // -------------------------------------------------------------- accountant
-      const uint16_t *const list = (const uint16_t *)(lds + p.o_cand + (uint32_t)(gi < GW ? gi : 0) * p.cand_stride + p.o_list) + (pair & 0xFFFFu);
-      lds_vu32_t *const seen = (lds_vu32_t *)(ldsb + p.o_seen) + (uint32_t)(role_wave * p.seen_words) * kWave + lane;
-      int64_t level = 0, peak = 0;
-      bool wrong = false;
-      for (uint32_t k = 0; __ballot(k < n_ops) != 0; k += 4) {
-        uint32_t id[4], chk[4], before[4];
-        int64_t m[4];
+      peak = pk;
+    } else {
+      // -------------------------------------------------------------- checkers: a wavefront goes along the pairs for four candidates at a time
+      const int n_check = (T >> 6) - W;
+      for (int s0 = (wave - W) * 4; s0 < ng; s0 += n_check * 4) {
+        for (int k0 = lane; k0 < p.n_pairs; k0 += kWave) {
+          const uint32_t uv = p.pairs[k0];
+          int32_t ru[4], rv[4];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) id[u] = k + u < n_ops ? list[k + u] : (uint32_t)N;
+          for (int u = 0; u < 4; ++u) {
+            const int32_t *const rk = p.rank + (c0 + min(s0 + u, ng - 1)) * N;
+            ru[u] = rk[uv & 0xFFFFu];
+            rv[u] = rk[uv >> 16];
+          }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) { chk[u] = opsw[id[u]].w; m[u] = id[u] < (uint32_t)N ? memw[id[u]] : 0; }
-        // (an operation passed, then the next one's look for its predecessor: the LDS keeps their order)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          const uint32_t mine_at = chk[u] & 0xFFFFu, pre = chk[u] >> 16;
-          before[u] = pre == 0xFFFFu ? ~0u : seen[(pre >> 5) * kWave] >> (pre & 31u);
-          if (id[u] < (uint32_t)N)
-            (void)__hip_atomic_fetch_or((DAGSCHED_LDS uint32_t *)&seen[(mine_at >> 5) * kWave], 1u << (mine_at & 31u), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-          wrong |= !(before[u] & 1u);
-          level += m[u];
-          peak = max(peak, level);                           // eq. (19) along the chain
+          for (int u = 0; u < 4; ++u)
+            if (ru[u] > rv[u]) cycw[min(s0 + u, ng - 1)] = 1;
         }
       }
-      if (wrong) cycw[gi] = 1;
-      if (ok && p.base) peak += p.base[j];
-      if (ok && p.mem_limit && peak > p.mem_limit[j]) overb[gi] = 1;
-      if (lane_on) peakw[role_wave * kWave + ql] = peak;
     }
     __syncthreads();
     // ---------------------------------------------------------------- reductions and outputs
     if (wave < W) {
-      for (int s = 1; s < Pseg; s <<= 1) z = max(z, __shfl_xor(z, s, Pseg));
+      const int64_t peak64 = peak * p.mem_scale + (p.base && j < P ? p.base[j] : 0);
+      uint32_t over = ok && p.mem_limit && peak64 > p.mem_limit[j] ? 1u : 0u;
+      for (int s = 1; s < Pseg; s <<= 1) { z = max(z, __shfl_xor(z, s, Pseg)); over |= __shfl_xor(over, s, Pseg); }
       if (lane_on && gi < ng && j < P) {
         const int64_t c = c0 + gi;
-        const int bits = flagw[gi] | (overb[gi] ? kBitOverMemory : 0) | (cycw[gi] ? kBitCyclic : 0);
+        const int bits = flagw[gi] | (over ? kBitOverMemory : 0) | (cycw[gi] ? kBitCyclic : 0);
         if ((bits & kBitOtherPlacement) && !(bits & kBitBadPlacement)) {
           if (j == 0) { const int slot = atomicAdd(p.fb_count, 1); p.fb_list[slot] = (int32_t)c; }   // the general kernel writes this candidate
         } else {
           const int flag = flag_from_bits(bits);
           const int64_t zz = (int64_t)z * p.time_scale;
-          p.out.peak_mem[c * p.out.peak_stride_c + j * p.out.peak_stride_j] = flag ? -1 : peakw[wave * kWave + ql];
+          p.out.peak_mem[c * p.out.peak_stride_c + j * p.out.peak_stride_j] = flag ? -1 : peak64;
           if (j == 0) {
             p.out.makespan[c] = flag ? -1 : (int32_t)zz;
             p.out.bubble[c] = flag ? -1 : (int64_t)P * zz - p.sum_dur;
@@ -302,9 +308,10 @@ __global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p
         }
       }
     }
-    __syncthreads();                                         // flags and peaks are reset by the next batch
+    __syncthreads();                                         // the flags are reset by the next batch
   }
 }
 #undef DAGSCHED_PIPELINE_STEP
+#undef DAGSCHED_PIPELINE_LOOP
 
 }  // namespace dagsched_dev

@@ -80,3 +80,17 @@ def test_pipeline_kernel(gpu_lib, stages, micros, machines, n_cand, split, waves
         seen |= set(want[3].tolist())
     if n_cand > 100:
         assert {0, 1, 2, 4} <= seen, seen
+
+
+def test_memory_levels_beyond_32_bits_stay_with_the_general_form(gpu_lib):
+    """Levels are kept in 32 bits, in units of the common factor: numbers without one go to the kernel that keeps 64 bits."""
+    import torch
+    rng = np.random.default_rng(9)
+    w, fixed = _pipeline(rng, 4, 6, 4, 80, True)
+    for mem, kind in ((w.mem_delta * (1 << 40), 3), (w.mem_delta * (1 << 40) + 1, 0), (w.mem_delta * 0, 3)):
+        w.mem_delta = mem
+        with gpu_lib.Evaluator.for_workload(w, shared_placement=fixed, shape=dict(static_waves=1)) as ev:
+            assert ev.info()["variant"] == 6 and ev.info()["kernel_kind"] == kind
+            got = ev.evaluate(torch.from_numpy(w.placement).cuda(), torch.from_numpy(w.rank).cuda())
+            for a, o in zip(got, oracle.evaluate_workload(w, threads=8)):
+                assert np.array_equal(a.cpu().numpy(), o), mem[:4]
