@@ -320,6 +320,9 @@ typedef struct {
   int8_t placement_mode;   /* ring kernel: where the placement bytes sit (0 L2, 1 LDS, 2 LDS as four bits per node) */
   int8_t preds_per_op;     /* predecessors read per op: 1, 2 or 4 (ring and shared-placement kernels) */
   int8_t window_log2;      /* ring kernel in window mode: log2 of the end-time cells per candidate, else 0 */
+  int32_t two_launches;    /* 1: the pipeline kernel in two launches evaluates (a shared placement, at most one end time to wait for, orders
+                              that do not fit the LDS); everything above then describes the kernel behind it, which
+                              takes the candidates that place differently */
 } dagsched_info_t;
 int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info);
 

@@ -125,10 +125,20 @@ struct dagsched {
   uint4 *d_st_ops = nullptr;
   uint8_t *d_st_machine = nullptr;
   int32_t *d_st_off = nullptr;
-  uint32_t *d_st_pairs = nullptr;
   int64_t *d_st_base = nullptr;
-  // ... its form for pipelines (pl.total == 0: not in use); the tables above serve both
+  // pipeline kernels: fused (pl.total != 0, stands for the shared-placement kernel) or in two launches (pl_stream.total != 0, stands
+  // in front of the kernel that `variant` names)
   PipelineParams pl{};
+  PipelineIngest pl_in{};
+  PipelineStream pl_stream{};
+  int32_t pl_grid = 1;
+  unsigned char *pipeline_tables = nullptr;
+  uint4 *d_pl_ops = nullptr;
+  uint8_t *d_pl_machine = nullptr;
+  int32_t *d_pl_off = nullptr, *d_pl_seg = nullptr, *d_pl_count = nullptr, *ws_bad = nullptr;
+  uint32_t *d_pl_pairs = nullptr;
+  int64_t *d_pl_base = nullptr;
+  uint16_t *ws_orders = nullptr;
   // search helpers: machine counts of a base schedule
   int32_t *ws_cnt = nullptr;
   // start and end times of one schedule: rows of scratch, where the end times live, ring slots, LDS of the workgroup
@@ -265,10 +275,10 @@ bool dev_alloc(T **dst, size_t n) {
 
 void free_handle(dagsched *h) {
   if (!h) return;
-  void *bufs[] = {h->problem_tables, h->channel_tables, h->ws_list, h->ws_end, h->d_rec,
+  void *bufs[] = {h->problem_tables, h->channel_tables, h->pipeline_tables, h->ws_orders, h->ws_bad, h->ws_list, h->ws_end, h->d_rec,
                   h->d_comm_scaled, h->d_nparts, h->ws_list16, h->ws_pib, h->ws_cnt, h->ws_sched_list, h->ws_sched_end,
                   h->d_fb_count, h->d_fb_list, h->ws_meta, h->ws_tp, h->ws_tr,
-                  h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_pairs, h->d_st_base, h->ws_te,
+                  h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_base, h->ws_te,
                   h->wc_list, h->wc_end, h->wc_tlist, h->wc_tend, h->wc_ccnt, h->wc_coff, h->wc_echan,
                   h->wc_stream, h->d_tr_list};
   for (void *b : bufs)
@@ -812,27 +822,41 @@ StaticPlan plan_static(const dagsched_desc_t *d, const std::vector<int32_t> &pre
   return plan;
 }
 
-// Plan of the pipeline kernel, the leaner form of the shared-placement kernel for graphs whose operations wait for at most
-// one end time each.  base: what plan_static says about times and predecessors (its limits hold here as well).
+// Plan of the pipeline kernels, the leaner forms of the shared-placement kernel for graphs whose operations wait for at most
+// one end time of another machine each: fused where the orders fit the LDS beside the operations, else two launches.
 struct PipelinePlan {
-  bool ok = false;
+  bool ok = false, stream = false;
   int T = 0;                                             // bits of an end time in a cell
-  PipelineParams p{};
   int wgs = 1;
+  PipelineParams p{};
+  PipelineStream s{};
+  PipelineIngest in{};
   std::vector<uint4> ops;
   std::vector<uint32_t> pairs;
+  std::vector<uint8_t> machine;
+  std::vector<int32_t> off, seg, count;
+  std::vector<int64_t> base;
 };
 
 int pipeline_threads(int relaxers) { return std::max(256, 2 * relaxers * kWave); }
+int stream_threads(const PipelineStream &s) { return (s.W + s.feeders) * kWave; }
 
-PipelinePlan plan_pipeline(const dagsched_desc_t *d, const StaticPlan &base, const PredLists &reduced, int64_t sum_dur, int lds_max, int n_cu) {
+// a shared placement is named, and nothing is asked for that only other kernels have
+bool may_pipeline(const dagsched_desc_t *d) {
+  const dagsched_shape_t *s = d->shape;
+  return d->shared_placement && (!s || (!s->ignore_shared_placement && !s->cand_per_block && !s->ring_slots && !s->feeders && s->placement_mode < 0 &&
+                                        !s->block_threads && !s->state_bits && !s->preds_per_op && !s->kernel && !s->window_cells));
+}
+
+// fused_ok: the fused form may be taken (the rules of plan_static about predecessors and times hold, or it is asked for)
+PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, const PredLists &reduced, int64_t sum_dur, int lds_max, int n_cu) {
   PipelinePlan plan;
   const int N = d->n_nodes, P = d->n_devices, Pseg = next_pow2(P);
   const int32_t *pi = d->shared_placement;
-  if (!base.fits_format) return plan;
-  // one predecessor on the operation's own machine is a matter of the order; what is left is read
+  // an edge inside a machine is a matter of the order; of the others each operation may have one, which is read
   std::vector<int32_t> read_ptr((size_t)N + 1, 0), read_idx;
-  int64_t max_delay = 0;
+  int64_t scale = 0, max_delay = 0;
+  for (int v = 0; v < N; ++v) scale = std::gcd<int64_t, int64_t>(scale, d->dur[v]);
   for (int v = 0; v < N; ++v) {
     int32_t other = -1;
     for (int32_t u : reduced[v]) {
@@ -842,52 +866,65 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, const StaticPlan &base, con
     }
     if (other >= 0) {
       read_idx.push_back(other);
-      max_delay = std::max<int64_t>(max_delay, d->comm[pi[other] * P + pi[v]] / base.scale);
+      scale = std::gcd<int64_t, int64_t>(scale, d->comm[pi[other] * P + pi[v]]);
+      max_delay = std::max<int64_t>(max_delay, d->comm[pi[other] * P + pi[v]]);
     }
     read_ptr[v + 1] = (int32_t)read_idx.size();
   }
-  const int64_t bound = sum_dur / base.scale + N * max_delay;   // no end time, nor one plus a delay, exceeds this
+  if (scale == 0) scale = 1;
+  const int64_t bound = sum_dur / scale + N * (max_delay / scale);   // no end time, nor one plus a delay, exceeds this
   while ((1ll << plan.T) <= bound) ++plan.T;
   if (plan.T > 30) return plan;
+  // memory levels in 32 bits, in units of the common factor of the A_i
+  auto size_of = [&](int v) { return d->mem_delta[v] < 0 ? 0ull - (uint64_t)d->mem_delta[v] : (uint64_t)d->mem_delta[v]; };
+  uint64_t factor = 0, swing = 0;                        // swing: no level is further from 0
+  for (int v = 0; v < N; ++v) factor = std::gcd<uint64_t, uint64_t>(factor, size_of(v));
+  if (factor > (uint64_t)INT64_MAX) return plan;
+  if (factor == 0) factor = 1;
+  for (int v = 0; v < N; ++v) {
+    swing += size_of(v) / factor;
+    if (swing > (uint64_t)INT32_MAX) return plan;
+  }
   const dagsched_host::SharedCells cells = dagsched_host::share_cells(N, reduced.ptr, reduced.idx, read_ptr, read_idx, (int)((1u << (31 - plan.T)) - 1u));
   PipelineParams &p = plan.p;
-  // memory levels in 32 bits, in units of the common factor of the A_i
-  uint64_t factor = 0;
-  for (int v = 0; v < N; ++v) factor = std::gcd<uint64_t, uint64_t>(factor, d->mem_delta[v] < 0 ? 0ull - (uint64_t)d->mem_delta[v] : (uint64_t)d->mem_delta[v]);
-  if (factor > (uint64_t)INT64_MAX) return plan;
-  p.mem_scale = factor ? (int64_t)factor : 1;
-  int64_t swing = 0;                                     // no level is further from 0 than this
-  for (int v = 0; v < N && swing <= INT32_MAX; ++v) swing += std::min<int64_t>(std::abs(d->mem_delta[v] / p.mem_scale), (int64_t)INT32_MAX + 1);
-  if (swing > INT32_MAX) return plan;
   p.n_cells = (uint32_t)cells.n_cells + 2u;
-  if (p.n_cells * 4u > 65535u) return plan;              // (an op holds 16-bit offsets)
+  if (p.n_cells * 4u > 65535u || N + P + 3 > 0xFFFF) return plan;   // (an op holds 16-bit offsets, an order 16-bit numbers)
   const uint32_t unread = (p.n_cells - 1u) * 4u;
   plan.ops.resize((size_t)N + 1);
   for (int v = 0; v < N; ++v) {
     uint32_t at = 0, key = 0;
     if (read_ptr[v + 1] > read_ptr[v]) {
       const int32_t u = read_idx[read_ptr[v]];
-      const uint32_t delay = (uint32_t)(d->comm[pi[u] * P + pi[v]] / base.scale);
       at = (uint32_t)cells.cell[u] * 4u;
-      key = delay - ((uint32_t)cells.user[u] << plan.T);
+      key = (uint32_t)(d->comm[pi[u] * P + pi[v]] / scale) - ((uint32_t)cells.user[u] << plan.T);
     }
     const uint32_t own = cells.cell[v] ? (uint32_t)cells.cell[v] * 4u : unread;
-    plan.ops[v] = make_uint4(key, (uint32_t)(d->dur[v] / base.scale) + ((uint32_t)cells.user[v] << plan.T), at | (own << 16),
-                             (uint32_t)(int32_t)(d->mem_delta[v] / p.mem_scale));
+    plan.ops[v] = make_uint4(key, (uint32_t)(d->dur[v] / scale) + ((uint32_t)cells.user[v] << plan.T), at | (own << 16),
+                             (uint32_t)(int32_t)(d->mem_delta[v] / (int64_t)factor));
   }
   plan.ops[N] = make_uint4(0x80000000u, 0u, unread << 16, 0u);
-  if (N + P + 3 > 0xFFFF) return plan;
+  plan.machine.assign((size_t)(N + 3) / 4 * 4, 0);
+  plan.count.assign(P, 0);
+  for (int v = 0; v < N; ++v) { plan.machine[v] = (uint8_t)pi[v]; ++plan.count[pi[v]]; }
+  plan.off.assign(Pseg + 1, N);
+  plan.seg.assign(P + 1, 0);
+  for (int j = 0, at = 0; j <= Pseg; ++j) { plan.off[j] = at; at += j < P ? plan.count[j] : 0; }
+  for (int j = 0; j < P; ++j) plan.seg[j + 1] = plan.seg[j] + (plan.count[j] + 3 + 7) / 8 * 8;   // (three more entries are read ahead)
+  if (d->weight) {
+    plan.base.assign(P, 0);
+    for (int v = 0; v < N; ++v) plan.base[pi[v]] += d->weight[v];
+  }
+  p.N = N; p.P = P; p.Pseg = Pseg; p.log_pseg = ilog2(Pseg); p.G = kWave / Pseg;
   p.n_pairs = (int32_t)plan.pairs.size();
-  p.limit = 1u << plan.T;
-  p.G = kWave / Pseg;
+  p.limit = 1u << plan.T; p.time_scale = (int32_t)scale; p.mem_scale = (int64_t)factor; p.sum_dur = sum_dur;
   p.o_mach = (uint32_t)(N + 1) * 16u;
   p.o_cand = align_up(p.o_mach + (uint32_t)(N + 3) / 4u * 4u, 16u);
   p.o_list = p.n_cells * 4u;
   p.cand_stride = align_up(p.o_list + (uint32_t)(N + P + 4) / 2u * 4u, 16u);
   const int lds_cu = 160 * 1024;
   const int forced_w = d->shape ? d->shape->static_waves : 0;
-  int64_t best_score = -1;
-  for (int w = 1; w <= 4; ++w) {                         // (512 threads)
+  int64_t best_score = -1, best_relaxers = 0;
+  for (int w = 1; w <= 4 && fused_ok; ++w) {             // (512 threads)
     if (p.G * w > kWave || (forced_w && w != forced_w)) continue;
     const uint32_t o_book = p.o_cand + (uint32_t)(p.G * w) * p.cand_stride, total = o_book + 784u;
     if ((int)total > lds_max) break;
@@ -897,9 +934,36 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, const StaticPlan &base, con
     if (!forced_w && wgs * w < 2) continue;              // (a lone relaxer on a CU: the ring kernel holds as many candidates and more)
     const int64_t relaxers = std::min<int64_t>({8, (int64_t)wgs * w, (batches + n_cu - 1) / n_cu * w});   // at work on a CU
     const int64_t score = relaxers * 16 + (wgs >= 2 ? 8 : 0) + w;
-    if (score > best_score) { best_score = score; p.W = w; plan.wgs = wgs; p.o_book = o_book; p.total = total; }
+    if (score > best_score) { best_score = score; best_relaxers = relaxers; p.W = w; plan.wgs = wgs; p.o_book = o_book; p.total = total; }
   }
   plan.ok = best_score >= 0;
+  if (forced_w || (int64_t)d->max_candidates < (int64_t)n_cu * p.G) return plan;
+  // two launches: where they put more relaxers to work on a CU than the fused form, for batches that need them
+  const int64_t wanted = std::min<int64_t>(8, ((int64_t)d->max_candidates + (int64_t)n_cu * p.G - 1) / ((int64_t)n_cu * p.G));
+  for (int w = (int)wanted; w >= 1 && w > best_relaxers; --w) {
+    PipelineStream s{};
+    uint32_t at = (uint32_t)(N + 1) * 16u;
+    s.W = w; s.feeders = (w + 1) / 2;
+    s.cell_stride = align_up(p.n_cells * 4u, 16u);
+    s.o_cells = at; at += (uint32_t)(p.G * w) * s.cell_stride;
+    s.o_ring = at = align_up(at, kPipelineRing); at += (uint32_t)w * kWave * kPipelineRing;
+    s.o_fed = at; at += (uint32_t)w * 256u;
+    s.o_loaded = at; at += (uint32_t)w * 256u;
+    s.o_book = at; at += 16u;
+    s.total = at;
+    PipelineIngest in{};
+    in.row = plan.seg[P];
+    in.o_rank = (uint32_t)in.row * 2u;
+    in.o_book = in.o_rank + align_up((uint32_t)N * 2u, 16u);
+    in.total = in.o_book + 64u * 4u * 2u + 16u;
+    if ((int)s.total > lds_max || (int)in.total > lds_max) continue;
+    s.N = in.N = N; s.P = in.P = P; s.Pseg = Pseg; s.log_pseg = p.log_pseg; s.G = p.G;
+    s.row = in.row; s.mem_scale = p.mem_scale; s.sum_dur = sum_dur; s.time_scale = p.time_scale; s.limit = p.limit; s.n_cells = p.n_cells;
+    in.n_pairs = p.n_pairs;
+    plan.s = s; plan.in = in;
+    plan.ok = plan.stream = true;
+    break;
+  }
   return plan;
 }
 
@@ -963,6 +1027,26 @@ void launch_general(dagsched *h, int32_t n_cand, const int32_t *pl, const int32_
     hipLaunchKernelGGL(relax_general_kernel<false>, dim3(blocks), dim3(kWave), 0, stream, p);
 }
 
+RingParams ring_params(const dagsched *h, int32_t n_cand, const int32_t *pl, const int32_t *rk, const OutPtrs &out, bool optimistic) {
+  RingParams p;
+  const int32_t N = h->N;
+  p.N = N; p.P = h->P; p.Pseg = h->Pseg; p.log_pseg = ilog2(h->Pseg); p.G = h->ring_G; p.C = n_cand;
+  p.optimistic = optimistic ? 1 : 0;
+  p.list_stride = h->list_stride;
+  p.rec = h->d_rec; p.rec_plane = h->rec_plane; p.id_bits = h->id_bits; p.nparts = h->d_nparts; p.comm = h->d_comm_scaled; p.mem_delta = h->d_mem;
+  p.weight = h->d_weight; p.mem_limit = h->d_limit;
+  p.sum_dur = h->sum_dur; p.time_scale = h->time_scale;
+  p.placement = pl; p.rank = rk;
+  p.ws_list = h->ws_list16; p.ws_pib = h->ws_pib; p.pib_stride = h->pib_stride;
+  p.fb_count = h->d_fb_count; p.fb_list = h->d_fb_list;
+  p.cand_list = nullptr; p.cand_count = nullptr;
+  p.spin_cap = h->spin_cap;
+  p.win_magic = h->win_magic; p.ws_meta = h->ws_meta;
+  p.out = out;
+  p.lds = h->lds;
+  return p;
+}
+
 int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const int32_t *rank, int32_t *makespan,
                     int64_t *bubble, int64_t *peak_mem, int32_t *flags, hipStream_t stream) {
   const int32_t N = h->N;
@@ -975,39 +1059,45 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
     rk = h->ws_tr;
   }
   const OutPtrs out = make_out(h, n_cand, makespan, bubble, peak_mem, flags);
-  if (h->variant == kVariantGeneralLds || h->variant == kVariantGeneralGlobal) {
+  if (h->pl_stream.total) {
+    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, stream, h->d_fb_count);
+    PipelineIngest in = h->pl_in;
+    in.C = n_cand; in.placement = pl; in.rank = rk;
+    hipLaunchKernelGGL(pipeline_ingest_kernel, dim3((unsigned)n_cand), dim3(256), (size_t)in.total, stream, in);
+    PipelineStream s = h->pl_stream;
+    s.C = n_cand; s.out = out;
+    const int per_wg = s.G * s.W;
+    hipLaunchKernelGGL(relax_stream_kernel, dim3((unsigned)((n_cand + per_wg - 1) / per_wg)), dim3((unsigned)stream_threads(s)), (size_t)s.total, stream, s);
+    // candidates with another placement
+    if (h->variant == kVariantRingExact || h->variant == kVariantRing32) {
+      RingParams p = ring_params(h, n_cand, pl, rk, out, false);
+      p.cand_list = h->d_fb_list; p.cand_count = h->d_fb_count;
+      hipLaunchKernelGGL(ring_kernel_for(h), dim3((unsigned)((n_cand + h->ring_G - 1) / h->ring_G)), dim3((unsigned)h->ring_block), (size_t)h->lds.total, stream, p);
+    } else {
+      launch_general(h, n_cand, pl, rk, out, h->d_fb_list, h->d_fb_count, stream);
+    }
+  } else if (h->variant == kVariantGeneralLds || h->variant == kVariantGeneralGlobal) {
     launch_general(h, n_cand, pl, rk, out, nullptr, nullptr, stream);
   } else if (h->variant == kVariantStatic) {
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, stream, h->d_fb_count);
-    const int per_wg = h->pl.total ? h->pl.G * h->pl.W : h->st.G * h->st.W;
-    const unsigned blocks = (unsigned)std::min((n_cand + per_wg - 1) / per_wg, h->st_grid);
-    StaticParams p = h->st;
-    p.C = n_cand; p.placement = pl; p.rank = rk; p.out = out;
     if (h->pl.total) {
-      PipelineParams q = h->pl;
-      q.C = n_cand; q.placement = pl; q.rank = rk; q.out = out;
-      hipLaunchKernelGGL(relax_pipeline_kernel, dim3(blocks), dim3((unsigned)pipeline_threads(q.W)), (size_t)q.total, stream, q);
-    } else
-    hipLaunchKernelGGL(h->st_preds == 2 ? relax_static_kernel<2> : relax_static_kernel<4>, dim3(blocks),
-                       dim3((unsigned)static_threads(p.W)), (size_t)p.total, stream, p);
+      PipelineParams p = h->pl;
+      p.C = n_cand; p.placement = pl; p.rank = rk; p.out = out;
+      const int per_wg = p.G * p.W;
+      hipLaunchKernelGGL(relax_pipeline_kernel, dim3((unsigned)std::min((n_cand + per_wg - 1) / per_wg, h->pl_grid)),
+                         dim3((unsigned)pipeline_threads(p.W)), (size_t)p.total, stream, p);
+    } else {
+      StaticParams p = h->st;
+      p.C = n_cand; p.placement = pl; p.rank = rk; p.out = out;
+      const int per_wg = p.G * p.W;
+      hipLaunchKernelGGL(h->st_preds == 2 ? relax_static_kernel<2> : relax_static_kernel<4>, dim3((unsigned)std::min((n_cand + per_wg - 1) / per_wg, h->st_grid)),
+                         dim3((unsigned)static_threads(p.W)), (size_t)p.total, stream, p);
+    }
     launch_general(h, n_cand, pl, rk, out, h->d_fb_list, h->d_fb_count, stream);   // candidates with another placement
   } else {
     const bool optimistic = h->variant == kVariantRingOptimistic;
     if (optimistic) hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, stream, h->d_fb_count);
-    RingParams p;
-    p.N = N; p.P = h->P; p.Pseg = h->Pseg; p.log_pseg = ilog2(h->Pseg); p.G = h->ring_G; p.C = n_cand;
-    p.optimistic = optimistic ? 1 : 0;
-    p.list_stride = h->list_stride;
-    p.rec = h->d_rec; p.rec_plane = h->rec_plane; p.id_bits = h->id_bits; p.nparts = h->d_nparts; p.comm = h->d_comm_scaled; p.mem_delta = h->d_mem;
-    p.weight = h->d_weight; p.mem_limit = h->d_limit;
-    p.sum_dur = h->sum_dur; p.time_scale = h->time_scale;
-    p.placement = pl; p.rank = rk;
-    p.ws_list = h->ws_list16; p.ws_pib = h->ws_pib; p.pib_stride = h->pib_stride;
-    p.fb_count = h->d_fb_count; p.fb_list = h->d_fb_list;
-    p.cand_list = nullptr; p.cand_count = nullptr;
-    p.spin_cap = h->spin_cap;
-    p.win_magic = h->win_magic; p.ws_meta = h->ws_meta;
-    p.out = out;
+    RingParams p = ring_params(h, n_cand, pl, rk, out, optimistic);
     const unsigned blocks = (unsigned)((n_cand + h->ring_G - 1) / h->ring_G);
     if (h->lds.win_log2) {                                // window mode: the lists are built by a launch of their own
       p.lds = h->lds_ingest;
@@ -1122,8 +1212,9 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   const bool force_general = desc->shape && desc->shape->kernel == 1;
   if (!force_general && desc->shared_placement && !(desc->shape && desc->shape->ignore_shared_placement))
     splan = plan_static(desc, pred_ptr, pred_idx, sum_dur, lds_max, n_cu);
-  if (splan.fits_format) pplan = plan_pipeline(desc, splan, reduced, sum_dur, lds_max, n_cu);
-  splan.ok = splan.ok || pplan.ok;
+  // (the fused form stands for the shared-placement kernel; the two launches stand in front of whatever kernel is planned besides)
+  if (may_pipeline(desc)) pplan = plan_pipeline(desc, splan.fits_format, reduced, sum_dur, lds_max, n_cu);
+  splan.ok = splan.ok || (pplan.ok && !pplan.stream);
   if (!force_general && !splan.ok) plan = plan_ring(desc, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
   const bool need_general = splan.ok || !plan.ok || !plan.exact;
 
@@ -1167,13 +1258,12 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       ok = allow_large_lds((const void *)relax_general_kernel<true>, h->device, h->gen_lds);
     h->variant = h->gen_lds_state ? kVariantGeneralLds : kVariantGeneralGlobal;
   }
-  if (ok && splan.ok) {
+  if (ok && splan.ok && !pplan.ok) {
     h->variant = kVariantStatic;
     h->time_scale = splan.scale;
-    h->st_preds = pplan.ok ? 1 : splan.preds;
-    h->st_grid = n_cu * (pplan.ok ? pplan.wgs : splan.wgs);
-    const std::vector<uint4> &st_ops = pplan.ok ? pplan.ops : splan.ops;
-    ok = upload(&h->d_st_ops, st_ops.data(), st_ops.size()) &&
+    h->st_preds = splan.preds;
+    h->st_grid = n_cu * splan.wgs;
+    ok = upload(&h->d_st_ops, splan.ops.data(), splan.ops.size()) &&
          upload(&h->d_st_machine, splan.machine.data(), splan.machine.size()) &&
          upload(&h->d_st_off, splan.off.data(), splan.off.size()) &&
          (splan.base.empty() || upload(&h->d_st_base, splan.base.data(), splan.base.size())) &&
@@ -1186,15 +1276,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     s.fb_count = h->d_fb_count; s.fb_list = h->d_fb_list;
     s.o_mem = splan.o_mem; s.o_mach = splan.o_mach; s.o_cand = splan.o_cand; s.cand_stride = splan.cand_stride; s.o_list = splan.o_list; s.o_book = splan.o_book;
     s.total = splan.total;
-    if (pplan.ok) {
-      PipelineParams &q = h->pl;
-      q = pplan.p;
-      q.N = h->N; q.P = h->P; q.Pseg = h->Pseg; q.log_pseg = s.log_pseg;
-      ok = ok && upload(&h->d_st_pairs, pplan.pairs.data(), pplan.pairs.size());
-      q.ops = s.ops; q.machine = s.machine; q.off = s.off; q.pairs = h->d_st_pairs; q.base = s.base; q.mem_limit = s.mem_limit;
-      q.sum_dur = s.sum_dur; q.time_scale = s.time_scale; q.fb_count = s.fb_count; q.fb_list = s.fb_list;
-      if (ok && q.total > 48 * 1024) ok = allow_large_lds((const void *)relax_pipeline_kernel, h->device, (int)q.total);
-    } else if (ok && s.total > 48 * 1024)
+    if (ok && s.total > 48 * 1024)
       ok = allow_large_lds(splan.preds == 2 ? (const void *)relax_static_kernel<2> : (const void *)relax_static_kernel<4>, h->device, (int)s.total);
   }
   if (ok && plan.ok) {
@@ -1250,6 +1332,38 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     }
     if (ok && h->lds.total > 48 * 1024)
       ok = allow_large_lds((const void *)ring_kernel_for(h), h->device, (int)h->lds.total);
+  }
+  if (ok && pplan.ok) {
+    if (!pplan.stream) { h->variant = kVariantStatic; h->time_scale = pplan.p.time_scale; h->st_preds = 1; }
+    Tables t;
+    PipelineParams &q = h->pl;
+    q = pplan.p;
+    t.add(&h->d_pl_ops, pplan.ops.data(), pplan.ops.size());
+    t.add(&h->d_pl_machine, pplan.machine.data(), pplan.machine.size());
+    t.add(&h->d_pl_off, pplan.off.data(), pplan.off.size());
+    t.add(&h->d_pl_seg, pplan.seg.data(), pplan.seg.size());
+    t.add(&h->d_pl_count, pplan.count.data(), pplan.count.size());
+    t.add(&h->d_pl_pairs, pplan.pairs.data(), pplan.pairs.size());
+    if (!pplan.base.empty()) t.add(&h->d_pl_base, pplan.base.data(), pplan.base.size());
+    ok = t.send(&h->pipeline_tables) && (h->d_fb_count || dev_alloc(&h->d_fb_count, 2)) && (h->d_fb_list || dev_alloc(&h->d_fb_list, maxc));
+    q.ops = h->d_pl_ops; q.machine = h->d_pl_machine; q.off = h->d_pl_off; q.pairs = h->d_pl_pairs; q.base = h->d_pl_base; q.mem_limit = h->d_limit;
+    q.fb_count = h->d_fb_count; q.fb_list = h->d_fb_list;
+    h->pl_grid = n_cu * pplan.wgs;
+    if (pplan.stream) {
+      q.total = 0;
+      PipelineIngest &in = h->pl_in;
+      PipelineStream &s = h->pl_stream;
+      in = pplan.in; s = pplan.s;
+      ok = ok && dev_alloc(&h->ws_orders, maxc * (size_t)in.row) && dev_alloc(&h->ws_bad, maxc) &&
+           (in.total <= 48 * 1024 || allow_large_lds((const void *)pipeline_ingest_kernel, h->device, (int)in.total)) &&
+           (s.total <= 48 * 1024 || allow_large_lds((const void *)relax_stream_kernel, h->device, (int)s.total));
+      in.machine = q.machine; in.seg = s.seg = h->d_pl_seg; in.count = s.count = h->d_pl_count; in.pairs = q.pairs;
+      in.lists = h->ws_orders; s.lists = h->ws_orders; in.bad = h->ws_bad; s.bad = h->ws_bad;
+      s.ops = q.ops; s.base = q.base; s.mem_limit = q.mem_limit; s.fb_count = q.fb_count; s.fb_list = q.fb_list;
+      s.spin_cap = (uint32_t)std::min<int64_t>(((int64_t)h->N + h->E + 1024) * 64, 0x7FFFFFFF);
+    } else if (ok && q.total > 48 * 1024) {
+      ok = allow_large_lds((const void *)relax_pipeline_kernel, h->device, (int)q.total);
+    }
   }
   if (ok && h->layout == DAGSCHED_CAND_MINOR)
     ok = dev_alloc(&h->ws_tp, maxc * (size_t)h->N) && dev_alloc(&h->ws_tr, maxc * (size_t)h->N);
@@ -1629,8 +1743,8 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
     splan = plan_static(&cleaned, pred_ptr, pred_idx, sum_dur, lds_bytes, n_cu);
   const PredLists reduced = reduce_preds(&cleaned, pred_ptr, pred_idx);
   PipelinePlan pplan;
-  if (splan.fits_format) pplan = plan_pipeline(&cleaned, splan, reduced, sum_dur, lds_bytes, n_cu);
-  splan.ok = splan.ok || pplan.ok;
+  if (may_pipeline(&cleaned)) pplan = plan_pipeline(&cleaned, splan.fits_format, reduced, sum_dur, lds_bytes, n_cu);
+  splan.ok = splan.ok || (pplan.ok && !pplan.stream);
   if (!force_general && !splan.ok) plan = plan_ring(&cleaned, pred_ptr, pred_idx, reduced, sum_dur, lds_bytes, n_cu);
   if (splan.ok || !plan.ok || !plan.exact) {
     h.gen_G = kWave / h.Pseg;
@@ -1643,8 +1757,9 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
     h.variant = kVariantStatic;
     h.time_scale = splan.scale; h.st_preds = splan.preds;
     h.st.G = splan.G; h.st.W = splan.W; h.st.total = splan.total;
-    if (pplan.ok) { h.pl = pplan.p; h.st_preds = 1; }
+    if (pplan.ok) { h.pl = pplan.p; h.st_preds = 1; h.time_scale = pplan.p.time_scale; }
   }
+  if (pplan.stream) h.pl_stream = pplan.s;
   if (plan.ok) {
     h.variant = !plan.exact ? kVariantRingOptimistic : plan.cell32 ? kVariantRing32 : kVariantRingExact;
     h.ring_G = plan.G; h.ring_slots = plan.ring; h.ring_feeders = plan.feeders; h.ring_kind = plan.kind; h.ring_block = plan.block;
@@ -1657,6 +1772,7 @@ int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info) {
   if (!h || !info) return DAGSCHED_EINVAL;
   memset(info, 0, sizeof(*info));
   info->variant = h->variant;
+  info->two_launches = h->pl_stream.total != 0;
   const bool ring = h->variant == kVariantRingExact || h->variant == kVariantRingOptimistic || h->variant == kVariantRing32;
   info->cand_per_block = ring ? h->ring_G : h->gen_G;
   info->block_threads = ring ? h->ring_block : kWave;
@@ -1689,7 +1805,7 @@ int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info) {
 int dagsched_last_fallbacks(dagsched_t *h, void *hip_stream, int32_t *count) {
   if (!h || !count) return DAGSCHED_EINVAL;
   *count = 0;
-  const bool has_list = h->d_fb_count && (h->variant == kVariantRingOptimistic || h->variant == kVariantStatic);
+  const bool has_list = h->d_fb_count && (h->variant == kVariantRingOptimistic || h->variant == kVariantStatic || h->pl_stream.total);
   if (!has_list) return DAGSCHED_OK;
   if (!hip_ok(hipMemcpyAsync(count, h->d_fb_count, sizeof(int32_t), hipMemcpyDeviceToHost, (hipStream_t)hip_stream),
               "hipMemcpyAsync") ||

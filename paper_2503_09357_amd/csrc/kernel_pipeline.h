@@ -314,4 +314,311 @@ __global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p
 #undef DAGSCHED_PIPELINE_STEP
 #undef DAGSCHED_PIPELINE_LOOP
 
+// ---------------------------------------------------------------------------------------------------------------------
+// The same for problems whose order lists do not fit the LDS beside the operations (bidirectional pipeline: 6144 operations, 98 KB
+// of them): two launches.  The first reads the candidates' rows and writes the orders to a workspace, a segment of a multiple of
+// eight entries per machine; the second keeps the operations and the cells of up to eight relaxers' candidates in the LDS (one
+// workgroup per CU, 32 candidates of the bidirectional pipeline where the ring kernel holds eight) and streams the orders past
+// them: a thread per machine copies eight entries at a time into a ring of 32.
+// Bidirectional pipeline, 6144 operations, 16384 candidates: 1182 us with the ring kernel (two relaxers a CU, 275 cycles a step, fed
+// by wavefronts that look up placements and delays), 420 here: ingest 187 us (1.01 GB at 5.4 TB/s), relaxation 242 in two rounds.
+
+struct PipelineIngest {
+  int32_t N, P, C;
+  const uint8_t *machine;              // [N rounded up to 4] the shared placement
+  const int32_t *seg;                  // [P + 1] first entry of machine j's segment, a multiple of 8
+  const int32_t *count;                // [P] its operations
+  const uint32_t *pairs;               // as in PipelineParams
+  int32_t n_pairs;
+  const int32_t *placement, *rank;     // [C][N]
+  uint16_t *lists;                     // [C][row]
+  int64_t row;
+  int32_t *bad;                        // [C] flag bits
+  uint32_t o_rank, o_book, total;      // LDS: the candidate's lists at 0, then these
+};
+
+__global__ __launch_bounds__(256) void pipeline_ingest_kernel(PipelineIngest p) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  constexpr int T = 256, kChunk = 4;
+  const int tid = threadIdx.x;
+  const int N = p.N, P = p.P, row = (int)p.row;
+  uint16_t *const list = (uint16_t *)lds, *const rank16 = (uint16_t *)(lds + p.o_rank);
+  int32_t *const seg = (int32_t *)(lds + p.o_book), *const count = seg + 64, *const flag = count + 64;
+  const int64_t c = blockIdx.x;
+  const int32_t *const pl = p.placement + c * N, *const rk = p.rank + c * N;
+  const bool vec = ((N & 3) == 0) && ((((uintptr_t)p.placement) | ((uintptr_t)p.rank)) & 15) == 0;
+  const int nq = N >> 2;
+  const uint32_t *const machw = (const uint32_t *)p.machine;
+  int4 a4[kChunk], r4[kChunk];
+  auto request = [&](int q0) {
+#pragma unroll
+    for (int u = 0; u < kChunk; ++u) { a4[u] = ((const int4 *)pl)[min(q0 + u * T, nq - 1)]; r4[u] = ((const int4 *)rk)[min(q0 + u * T, nq - 1)]; }
+  };
+  if (vec) request(tid);
+  if (tid < 64) { seg[tid] = tid < P ? p.seg[tid] : 0; count[tid] = tid < P ? p.count[tid] : 0; }
+  if (tid == 0) *flag = 0;
+  for (int i = tid; i < row / 2; i += T) ((uint32_t *)list)[i] = 0xFFFFFFFFu;
+  __syncthreads();
+  int bits = 0;
+  auto place = [&](int v, int32_t a, int32_t r, uint32_t m) {
+    const bool bad_pl = (uint32_t)a >= (uint32_t)P, other = (uint32_t)a != m, bad_rk = (uint32_t)r >= (uint32_t)count[m];
+    bits |= bad_pl ? kBitBadPlacement : other ? kBitOtherPlacement : bad_rk ? kBitBadRank : 0;
+    rank16[v] = (uint16_t)r;
+    if (!other && !bad_rk) list[seg[m] + r] = (uint16_t)v;
+  };
+  if (vec) {
+    for (int q0 = tid; q0 < nq; q0 += kChunk * T) {
+      int4 a[kChunk], r[kChunk];
+#pragma unroll
+      for (int u = 0; u < kChunk; ++u) { a[u] = a4[u]; r[u] = r4[u]; }
+      if (q0 + kChunk * T < nq) request(q0 + kChunk * T);
+#pragma unroll
+      for (int u = 0; u < kChunk; ++u) {
+        const int q = q0 + u * T;
+        if (q >= nq) break;
+        const uint32_t m = machw[q];
+        place(4 * q, a[u].x, r[u].x, m & 0xFF); place(4 * q + 1, a[u].y, r[u].y, (m >> 8) & 0xFF);
+        place(4 * q + 2, a[u].z, r[u].z, (m >> 16) & 0xFF); place(4 * q + 3, a[u].w, r[u].w, m >> 24);
+      }
+    }
+  } else {
+    for (int v = tid; v < N; v += T) place(v, pl[v], rk[v], (machw[v >> 2] >> ((v & 3) << 3)) & 0xFF);
+  }
+  for (int j = tid; j < P; j += T)                          // behind a machine's operations: the one that is never ready
+    for (int i = seg[j] + count[j]; i < (j + 1 < P ? seg[j + 1] : row); ++i) list[i] = (uint16_t)N;
+  if (bits) atomicOr(flag, bits);
+  __syncthreads();
+  if (!(*flag & (kBitBadPlacement | kBitOtherPlacement | kBitBadRank))) {
+    // N operations into N slots: no slot left unwritten <=> every (machine, rank) slot hit exactly once
+    bits = 0;
+    uint4 *const out = (uint4 *)(p.lists + c * p.row);
+    for (int i = tid; i < row / 8; i += T) {
+      const uint4 w = ((const uint4 *)list)[i];
+      auto hole = [](uint32_t x) { return (x & 0xFFFFu) == 0xFFFFu || (x >> 16) == 0xFFFFu; };
+      if (hole(w.x) || hole(w.y) || hole(w.z) || hole(w.w)) bits |= kBitBadRank;
+      out[i] = w;
+    }
+    // operations of one machine in the order of B
+#pragma unroll 4
+    for (int k = tid; k < p.n_pairs; k += T) {
+      const uint32_t uv = p.pairs[k];
+      if (rank16[uv & 0xFFFFu] > rank16[uv >> 16]) bits |= kBitCyclic;
+    }
+    if (bits) atomicOr(flag, bits);
+  }
+  __syncthreads();
+  if (tid == 0) p.bad[c] = *flag;
+}
+
+struct PipelineStream {
+  int32_t N, P, Pseg, log_pseg, G, W, feeders, C;
+  const uint4 *ops;                    // [N + 1] as in PipelineParams
+  const int32_t *seg, *count;          // as in PipelineIngest
+  const uint16_t *lists;
+  int64_t row;
+  const int32_t *bad;
+  int64_t mem_scale;
+  const int64_t *base, *mem_limit;
+  int64_t sum_dur;
+  int32_t time_scale;
+  uint32_t limit, spin_cap;
+  int32_t *fb_count, *fb_list;
+  uint32_t n_cells, cell_stride, o_cells, o_ring, o_fed, o_loaded, o_book, total;   // LDS: operations at 0, then these
+  OutPtrs out;
+};
+
+constexpr uint32_t kPipelineRing = 64;                      // bytes of a lane's ring: 32 entries
+
+// lp: bytes of the order loaded so far; everything else as in DAGSCHED_PIPELINE_STEP
+#define DAGSCHED_STREAM_STEP                                                                                                    \
+  "s_waitcnt lgkmcnt(2)\n\t"                                                                                                    \
+  "v_add_u32 %[x], %[e], v44\n\t"                                                                                              \
+  "v_max_u32 %[x], %[xa], %[x]\n\t"                                                                                             \
+  "v_cmp_gt_u32 vcc, %[lim], %[x]\n\t"                                                                                          \
+  "v_add_u32 %[y], %[x], v45\n\t"                                                                                              \
+  "s_mov_b64 exec, vcc\n\t"                                                                                                    \
+  "ds_write_b32 %[own], %[y]\n\t"                                                                                               \
+  "s_waitcnt lgkmcnt(1)\n\t"                                                                                                    \
+  "v_add_u32_sdwa %[at], %[cb], v42 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"                     \
+  "s_mov_b64 exec, %[all]\n\t"                                                                                                  \
+  "ds_read_b32 %[e], %[at]\n\t"                                                                                                 \
+  "s_mov_b64 exec, vcc\n\t"                                                                                                     \
+  "v_and_b32 %[xa], %[tm], %[y]\n\t"                                                                                            \
+  "v_add_u32_sdwa %[own], %[cb], v42 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"                    \
+  "v_mov_b64 v[44:45], v[40:41]\n\t"                                                                                           \
+  "v_add_u32 %[lvl], %[lvl], v43\n\t"                                                                                          \
+  "v_max_i32 %[pk], %[pk], %[lvl]\n\t"                                                                                         \
+  "v_lshl_add_u32 %[x], %[idn], 4, %[ob]\n\t"                                                                                   \
+  "v_and_or_b32 %[y], %[lp], 63, %[ring]\n\t"                                                                                   \
+  "ds_read_b128 v[40:43], %[x]\n\t"                                                                                             \
+  "ds_read_u16 %[idn], %[y]\n\t"                                                                                                \
+  "v_add_u32 %[lp], 2, %[lp]\n\t"                                                                                               \
+  "s_mov_b64 exec, %[all]\n\t"
+// Eight steps where the entries for them are there, else two, one block after the other (at most `turns`) as long as there are entries and
+// something ran in a block's last step.
+#define DAGSCHED_STREAM_LOOP                                                                                                    \
+  "s_waitcnt lgkmcnt(0)\n"                                                                                                      \
+  ".Lstream%=:\n\t"                                                                                                             \
+  "v_sub_u32 %[x], %[fed], %[lp]\n\t"                                                                                          \
+  "v_cmp_gt_i32 vcc, 16, %[x]\n\t"                                                                                             \
+  "s_cbranch_vccz .Lstream_eight%=\n\t"                                                                                        \
+  "v_cmp_gt_i32 vcc, 4, %[x]\n\t"                                                                                              \
+  "s_cbranch_vccnz .Lstream_end%=\n\t"                                                                                         \
+  "ds_read_b32 %[fed], %[fedat]\n\t" DAGSCHED_STREAM_STEP DAGSCHED_STREAM_STEP                                                 \
+  "s_branch .Lstream_done%=\n"                                                                                                 \
+  ".Lstream_eight%=:\n\t"                                                                                                       \
+  "ds_read_b32 %[fed], %[fedat]\n\t"                                                                                           \
+  DAGSCHED_STREAM_STEP DAGSCHED_STREAM_STEP DAGSCHED_STREAM_STEP DAGSCHED_STREAM_STEP                                           \
+  DAGSCHED_STREAM_STEP DAGSCHED_STREAM_STEP DAGSCHED_STREAM_STEP DAGSCHED_STREAM_STEP                                           \
+  ".Lstream_done%=:\n\t"                                                                                                        \
+  "s_mov_b64 %[moved], vcc\n\t"                                                                                                \
+  "ds_write_b32 %[loadedat], %[lp]\n\t"                                                                                        \
+  "s_sub_u32 %[turns], %[turns], 1\n\t"                                                                                        \
+  "s_cmp_eq_u64 %[moved], 0\n\t"                                                                                               \
+  "s_cbranch_scc1 .Lstream_end%=\n\t"                                                                                          \
+  "s_cmp_lg_u32 %[turns], 0\n\t"                                                                                               \
+  "s_cbranch_scc1 .Lstream%=\n"                                                                                                \
+  ".Lstream_end%=:\n\t"                                                                                                         \
+  "s_waitcnt lgkmcnt(0)"
+
+__global__ __launch_bounds__(1024) void relax_stream_kernel(PipelineStream p) {
+  extern __shared__ __align__(16) unsigned char lds[];
+  const int T = (int)blockDim.x;                            // 64 * (W + feeders)
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int N = p.N, P = p.P, Pseg = p.Pseg, G = p.G, W = p.W;
+  lds_byte_t *const ldsb = (lds_byte_t *)lds;
+  const uint32_t ob = (uint32_t)(uintptr_t)ldsb;
+  constexpr uint32_t kAll = 0x40000000u;
+  const int64_t c0 = (int64_t)blockIdx.x * G * W;
+  const int g = lane >> p.log_pseg, j = lane & (Pseg - 1);
+  // machine of relaxer w's lane: its candidate is there and well-formed, and it has operations
+  auto count_of = [&](int w) -> int32_t {
+    const int64_t c = c0 + (int64_t)w * G + g;
+    return lane < G * Pseg && j < P && c < p.C && p.bad[c] == 0 ? p.count[j] : 0;
+  };
+  for (int i = tid; i <= N; i += T) ((uint4 *)lds)[i] = p.ops[i];
+  for (int i = tid; i < (int)(G * W * p.cell_stride / 4); i += T) ((uint32_t *)(lds + p.o_cells))[i] = 0;
+  for (int w = wave; w < W; w += T >> 6) {
+    ((uint32_t *)(lds + p.o_fed))[w * kWave + lane] = count_of(w) ? 0u : kAll;
+    ((uint32_t *)(lds + p.o_loaded))[w * kWave + lane] = 0u;
+  }
+  if (tid < 4) ((uint16_t *)(lds + p.o_book))[tid] = (uint16_t)N;   // an order for lanes without one
+  if (tid == 0) *(uint32_t *)(lds + p.o_book + 8) = kAll;           // ... of which all is there
+  __syncthreads();
+
+  if (wave < W) {
+    // ---------------------------------------------------------------- relaxer
+    const int32_t n_ops = count_of(wave);
+    const bool ok = n_ops > 0;
+    const bool lane_on = lane < G * Pseg;
+    const uint32_t cb = ob + p.o_cells + (uint32_t)(wave * G + (lane_on ? g : 0)) * p.cell_stride;
+    const uint32_t ring = ob + p.o_ring + (uint32_t)(wave * kWave + lane) * kPipelineRing;   // (a multiple of its size)
+    uint32_t fedat = ob + p.o_fed + (uint32_t)(wave * kWave + lane) * 4u, loadedat = ob + p.o_loaded + (uint32_t)(wave * kWave + lane) * 4u;
+    auto ld16 = [](uint32_t a) -> uint32_t { return (uint32_t)*(lds_vu16_t *)(uintptr_t)a; };
+    uint32_t fed = 0, round = 0;
+    for (;; ++round) {                                       // the first entries of every lane
+      fed = *(lds_vu32_t *)(uintptr_t)fedat;
+      if (__ballot(fed < 16u) == 0 || round >= p.spin_cap) break;
+      __builtin_amdgcn_s_sleep(1);
+    }
+    const uint32_t l0 = ok ? ring : ob + p.o_book;
+    const u32x4_t first = *(lds_vu32x4_t *)(uintptr_t)(ob + ld16(l0) * 16u);
+    u32x4_t next = *(lds_vu32x4_t *)(uintptr_t)(ob + ld16(l0 + 2) * 16u);
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    u32x2_t kd = {first.x, first.y};
+    uint32_t idn = ld16(l0 + 4), lp = 6u, end = 6u + 2u * (uint32_t)n_ops;
+    uint32_t x = 0, y = 0, xa = 0, own = cb + (first.z >> 16), at = cb + (first.z & 0xFFFFu);
+    int32_t lvl = (int32_t)first.w, pk = max(0, lvl);        // (an operation counts as it moves up: the order is all that matters)
+    uint32_t e = *(lds_vu32_t *)(uintptr_t)at;
+    const uint64_t segmask = ((Pseg == kWave) ? ~0ull : ((1ull << Pseg) - 1ull)) << ((lane_on ? g : 0) * Pseg);
+    const uint32_t tm = p.limit - 1u;
+    const uint64_t all = ~0ull;
+    int halted = 0;
+    bool expired = true;
+    __builtin_amdgcn_s_setprio(3);
+    for (; round < p.spin_cap; ++round) {
+      uint64_t moved = ~0ull;
+      uint32_t turns = 32;
+      asm volatile(DAGSCHED_STREAM_LOOP
+                   : [x] "+&v"(x), [y] "+&v"(y), [e] "+&v"(e), [xa] "+&v"(xa), [own] "+&v"(own), [at] "+&v"(at), [idn] "+&v"(idn), [lp] "+&v"(lp),
+                     [lvl] "+&v"(lvl), [pk] "+&v"(pk), [fed] "+&v"(fed), "+&{v[40:43]}"(next), "+&{v[44:45]}"(kd), [moved] "+&s"(moved), [turns] "+&s"(turns)
+                   : [cb] "v"(cb), [ring] "v"(ring), [fedat] "v"(fedat), [loadedat] "v"(loadedat), [lim] "s"(p.limit), [tm] "s"(tm), [ob] "s"(ob), [all] "s"(all)
+                   : "vcc", "scc", "memory");
+      const bool open = lp != end;
+      if (__ballot(open) == 0) { expired = false; break; }
+      // in the last step nothing of the candidate ran although some machine is not through: a cycle.  (moved stays all ones where
+      // there was no step.)  Its feeders are told that everything has been taken.
+      if (open && (moved & segmask) == 0) {
+        halted = kBitCyclic;
+        end = lp;
+        *(lds_vu32_t *)(uintptr_t)loadedat = kAll;
+        fedat = ob + p.o_book + 8u;
+        loadedat = ob + p.o_book + 12u;
+      }
+      if (__ballot((int32_t)(fed - lp) < 4) != 0) fed = *(lds_vu32_t *)(uintptr_t)fedat;   // (it came out for want of entries, perhaps)
+    }
+    if (expired && lp != end) { halted = kBitInternal; *(lds_vu32_t *)(uintptr_t)loadedat = kAll; }   // never expected
+    __builtin_amdgcn_s_setprio(0);
+    // ---------------------------------------------------------------- reductions and outputs
+    int32_t z = (int32_t)xa;
+    const int64_t peak64 = pk * p.mem_scale + (p.base && j < P ? p.base[j] : 0);
+    uint32_t bits = (uint32_t)halted | (lane_on && j < P && p.mem_limit && peak64 > p.mem_limit[j] ? (uint32_t)kBitOverMemory : 0u);
+    for (int s = 1; s < Pseg; s <<= 1) { z = max(z, __shfl_xor(z, s, Pseg)); bits |= __shfl_xor(bits, s, Pseg); }
+    const int64_t c = c0 + (int64_t)wave * G + g;
+    if (lane_on && c < p.C && j < P) {
+      bits |= (uint32_t)p.bad[c];
+      if ((bits & kBitOtherPlacement) && !(bits & kBitBadPlacement)) {
+        if (j == 0) { const int slot = atomicAdd(p.fb_count, 1); p.fb_list[slot] = (int32_t)c; }   // the general kernel writes this candidate
+      } else {
+        const int flag = flag_from_bits((int)bits);
+        const int64_t zz = (int64_t)z * p.time_scale;
+        p.out.peak_mem[c * p.out.peak_stride_c + j * p.out.peak_stride_j] = flag ? -1 : peak64;
+        if (j == 0) {
+          p.out.makespan[c] = flag ? -1 : (int32_t)zz;
+          p.out.bubble[c] = flag ? -1 : (int64_t)P * zz - p.sum_dur;
+          p.out.flags[c] = flag;
+        }
+      }
+    }
+  } else {
+    // ---------------------------------------------------------------- feeders: relaxers f, f + feeders, a thread per lane
+    constexpr int kPer = 2;
+    const int f = wave - W;
+    uint32_t k[kPer], n[kPer];                               // next chunk of eight entries, and how many there are
+    const uint4 *from[kPer];
+    uint4 held[kPer];
+    bool asked[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+      const int w = f + u * p.feeders;
+      const bool on = w < W && count_of(w < W ? w : 0) > 0;
+      k[u] = 0;
+      n[u] = on ? (uint32_t)((j + 1 < P ? p.seg[j + 1] : (int32_t)p.row) - p.seg[j]) / 8u : 0u;
+      from[u] = (const uint4 *)(p.lists + (on ? (c0 + (int64_t)w * G + g) * p.row + p.seg[j] : 0));
+      held[u] = make_uint4(0, 0, 0, 0);
+      asked[u] = false;
+    }
+    for (uint32_t it = 0; it < p.spin_cap; ++it) {
+      bool any = false;
+#pragma unroll
+      for (int u = 0; u < kPer; ++u) {
+        const uint32_t at = (uint32_t)((f + u * p.feeders) * kWave + lane);
+        if (asked[u]) {
+          *(lds_vu32x4_t *)(ldsb + p.o_ring + at * kPipelineRing + ((k[u] * 16u) & (kPipelineRing - 1u))) = u32x4_t{held[u].x, held[u].y, held[u].z, held[u].w};
+          ++k[u];
+          *(lds_vu32_t *)(ldsb + p.o_fed + at * 4u) = k[u] == n[u] ? kAll : k[u] * 16u;   // after the entries
+        }
+        asked[u] = k[u] < n[u] && (int32_t)((k[u] + 1u) * 16u - *(lds_vu32_t *)(ldsb + p.o_loaded + at * 4u)) <= (int32_t)kPipelineRing;
+        if (asked[u]) held[u] = from[u][k[u]];
+        any = any || k[u] < n[u];
+      }
+      if (__ballot(any) == 0) break;
+      if (__ballot(asked[0] || asked[kPer - 1]) == 0) __builtin_amdgcn_s_sleep(2);
+    }
+  }
+}
+#undef DAGSCHED_STREAM_STEP
+#undef DAGSCHED_STREAM_LOOP
+
 }  // namespace dagsched_dev
