@@ -55,7 +55,9 @@ def measured_traffic(cfg: int, kernel: str = "relax_ring_kernel"):
 
 
 def dominant_kernel(info: dict) -> str:
-    """Name of the kernel that does the evaluation, from dagsched_get_info's variant."""
+    """Name of the kernel that does the evaluation, from dagsched_get_info's fields."""
+    if info["two_launches"]:
+        return "relax_stream_kernel"
     shared = "relax_pipeline_kernel" if info["kernel_kind"] == 3 else "relax_static_kernel"
     return {1: "relax_general_kernel", 2: "relax_general_kernel", 6: shared}.get(info["variant"], "relax_ring_kernel")
 

@@ -312,7 +312,10 @@ typedef struct {
   int16_t ring_slots;      /* ring kernel: slots per lane of the op ring, else 0 */
   int8_t kernel_kind;      /* ring kernel: 0 operations split into parts of four predecessors, 1 every operation a
                               single part, 2 at most two predecessors per operation, 3 at most one; shared-placement
-                              kernel: 3 in the form for pipelines (at most one end time to wait for), else 0 */
+                              kernel: 3 in the form for pipelines (at most one end time to wait for), else 0.  Plus 4
+                              when the pipeline kernel in two launches evaluates (a shared placement, orders that do not
+                              fit the LDS): the fields then describe the kernel behind it, which takes the candidates
+                              that place differently */
   int8_t wide_ops;         /* ring kernel: 1 when ops name machines instead of delays (delays above 255 or durations
                               above 65534 after the common factor is divided out) */
   int32_t time_scale;      /* common factor of every duration and delay, divided out inside the kernels */
@@ -320,9 +323,6 @@ typedef struct {
   int8_t placement_mode;   /* ring kernel: where the placement bytes sit (0 L2, 1 LDS, 2 LDS as four bits per node) */
   int8_t preds_per_op;     /* predecessors read per op: 1, 2 or 4 (ring and shared-placement kernels) */
   int8_t window_log2;      /* ring kernel in window mode: log2 of the end-time cells per candidate, else 0 */
-  int32_t two_launches;    /* 1: the pipeline kernel in two launches evaluates (a shared placement, at most one end time to wait for, orders
-                              that do not fit the LDS); everything above then describes the kernel behind it, which
-                              takes the candidates that place differently */
 } dagsched_info_t;
 int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info);
 

@@ -1354,11 +1354,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       PipelineIngest &in = h->pl_in;
       PipelineStream &s = h->pl_stream;
       in = pplan.in; s = pplan.s;
-      ok = ok && dev_alloc(&h->ws_orders, maxc * (size_t)in.row) && dev_alloc(&h->ws_bad, maxc) &&
-           (in.total <= 48 * 1024 || allow_large_lds((const void *)pipeline_ingest_kernel, h->device, (int)in.total)) &&
-           (s.total <= 48 * 1024 || allow_large_lds((const void *)relax_stream_kernel, h->device, (int)s.total));
       in.machine = q.machine; in.seg = s.seg = h->d_pl_seg; in.count = s.count = h->d_pl_count; in.pairs = q.pairs;
-      in.lists = h->ws_orders; s.lists = h->ws_orders; in.bad = h->ws_bad; s.bad = h->ws_bad;
       s.ops = q.ops; s.base = q.base; s.mem_limit = q.mem_limit; s.fb_count = q.fb_count; s.fb_list = q.fb_list;
       s.spin_cap = (uint32_t)std::min<int64_t>(((int64_t)h->N + h->E + 1024) * 64, 0x7FFFFFFF);
     } else if (ok && q.total > 48 * 1024) {
@@ -1436,6 +1432,23 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     } else {
       tp.total = 0;
       ok = ok && channels.send(&h->channel_tables);
+    }
+  }
+  if (ok && h->pl_stream.total) {
+    // The workspace of the two launches comes last, and a handle that fits the memory only without it is made without it: the
+    // kernel that `variant` names takes every call then (hipMalloc's error is read, so that no launch reports it).
+    PipelineIngest &in = h->pl_in;
+    PipelineStream &s = h->pl_stream;
+    if (dev_alloc(&h->ws_orders, maxc * (size_t)in.row) && dev_alloc(&h->ws_bad, maxc)) {
+      in.lists = h->ws_orders; s.lists = h->ws_orders; in.bad = h->ws_bad; s.bad = h->ws_bad;
+      ok = (in.total <= 48 * 1024 || allow_large_lds((const void *)pipeline_ingest_kernel, h->device, (int)in.total)) &&
+           (s.total <= 48 * 1024 || allow_large_lds((const void *)relax_stream_kernel, h->device, (int)s.total));
+    } else {
+      (void)hipGetLastError();
+      g_hip_error[0] = 0;
+      if (h->ws_orders) (void)hipFree(h->ws_orders);
+      h->ws_orders = nullptr;
+      s.total = 0;
     }
   }
   if (!ok) {
@@ -1772,7 +1785,7 @@ int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info) {
   if (!h || !info) return DAGSCHED_EINVAL;
   memset(info, 0, sizeof(*info));
   info->variant = h->variant;
-  info->two_launches = h->pl_stream.total != 0;
+  const int in_front = h->pl_stream.total ? 4 : 0;          // two launches in front of the kernel described
   const bool ring = h->variant == kVariantRingExact || h->variant == kVariantRingOptimistic || h->variant == kVariantRing32;
   info->cand_per_block = ring ? h->ring_G : h->gen_G;
   info->block_threads = ring ? h->ring_block : kWave;
@@ -1783,19 +1796,19 @@ int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info) {
     info->cand_per_block = pipeline ? h->pl.G * h->pl.W : h->st.G * h->st.W;
     info->block_threads = pipeline ? pipeline_threads(h->pl.W) : static_threads(h->st.W);
     info->lds_bytes = (int32_t)(pipeline ? h->pl.total : h->st.total);
-    info->kernel_kind = pipeline ? 3 : 0;
+    info->kernel_kind = (int8_t)((pipeline ? 3 : 0) + in_front);
     info->state_bits = 16;
     info->time_scale = h->time_scale;
     info->preds_per_op = (int8_t)h->st_preds;
     return DAGSCHED_OK;
   }
   info->time_scale = h->time_scale;
+  info->kernel_kind = (int8_t)((ring ? h->ring_kind : 0) + in_front);
   if (ring) {
     info->ring_slots = (int16_t)h->ring_slots;
     info->feeders = (int8_t)h->ring_feeders;
     info->placement_mode = (int8_t)h->lds.pib_mode;
     info->preds_per_op = (int8_t)(h->ring_kind == 3 ? 1 : h->ring_kind == 2 ? 2 : 4);
-    info->kernel_kind = (int8_t)h->ring_kind;
     info->wide_ops = (int8_t)h->lds.wide;
     info->window_log2 = (int8_t)h->lds.win_log2;
   }

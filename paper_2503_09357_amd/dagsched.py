@@ -75,7 +75,7 @@ class Info(ctypes.Structure):
                 ("ring_slots", ctypes.c_int16), ("kernel_kind", ctypes.c_int8), ("wide_ops", ctypes.c_int8),
                 ("time_scale", ctypes.c_int32),
                 ("feeders", ctypes.c_int8), ("placement_mode", ctypes.c_int8), ("preds_per_op", ctypes.c_int8),
-                ("window_log2", ctypes.c_int8), ("two_launches", ctypes.c_int32)]
+                ("window_log2", ctypes.c_int8)]
 
 
 class ContendedInfo(ctypes.Structure):
@@ -248,7 +248,8 @@ def validate(n_devices, row_ptr, col_idx, dur, comm, mem_delta, max_candidates=1
 def _info_dict(i: "Info") -> dict:
     d = {k: getattr(i, k) for k in ("variant", "cand_per_block", "block_threads", "lds_bytes", "state_bits",
                                     "ring_slots", "time_scale", "feeders", "preds_per_op", "kernel_kind", "wide_ops",
-                                    "window_log2", "two_launches")}
+                                    "window_log2")}
+    d.update(kernel_kind=i.kernel_kind & 3, two_launches=i.kernel_kind >> 2)
     d["placement_bytes_in_lds"] = i.placement_mode
     return d
 

@@ -239,3 +239,14 @@ def test_plan_takes_the_window_of_end_time_cells_only_where_it_is_sound():
     lev4 = (w4.n_devices, rp, ci, w4.dur[by_level].copy(), w4.comm, w4.mem_delta[by_level].copy())
     assert dagsched.plan(*lev4, max_candidates=4096)["window_log2"] == 0
     assert dagsched.plan(*lev4, max_candidates=4096, shape={"window_cells": 4096})["window_log2"] == 12
+
+
+def test_info_fills_the_struct_of_its_callers_and_no_more():
+    """A caller brings the memory: 32 bytes; what else is to be said of a launch shape goes into the fields that are there."""
+    assert ctypes.sizeof(dagsched.Info) == 32
+    row_ptr, col = W.csr_from_edges(2, np.array([0]), np.array([1]))
+    hp = dagsched._HostProblem(1, row_ptr, col, [1, 1], np.zeros((1, 1), np.int32), [0, 0], 1, 0, 0)
+    room = (ctypes.c_ubyte * 64)(*([0xA5] * 64))
+    lib = dagsched.load(import_torch_first=False)
+    assert lib.dagsched_plan(ctypes.byref(hp.desc), 160 * 1024, 256, ctypes.cast(room, ctypes.POINTER(dagsched.Info))) == 0
+    assert bytes(room[32:]) == b"\xa5" * 32
