@@ -1060,7 +1060,6 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
   }
   const OutPtrs out = make_out(h, n_cand, makespan, bubble, peak_mem, flags);
   if (h->pl_stream.total) {
-    hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, stream, h->d_fb_count);
     PipelineIngest in = h->pl_in;
     in.C = n_cand; in.placement = pl; in.rank = rk;
     hipLaunchKernelGGL(pipeline_ingest_kernel, dim3((unsigned)n_cand), dim3(256), (size_t)in.total, stream, in);
@@ -1258,7 +1257,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       ok = allow_large_lds((const void *)relax_general_kernel<true>, h->device, h->gen_lds);
     h->variant = h->gen_lds_state ? kVariantGeneralLds : kVariantGeneralGlobal;
   }
-  if (ok && splan.ok && !pplan.ok) {
+  if (ok && splan.ok && (!pplan.ok || pplan.stream)) {
     h->variant = kVariantStatic;
     h->time_scale = splan.scale;
     h->st_preds = splan.preds;
@@ -1355,7 +1354,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       PipelineStream &s = h->pl_stream;
       in = pplan.in; s = pplan.s;
       in.machine = q.machine; in.seg = s.seg = h->d_pl_seg; in.count = s.count = h->d_pl_count; in.pairs = q.pairs;
-      s.ops = q.ops; s.base = q.base; s.mem_limit = q.mem_limit; s.fb_count = q.fb_count; s.fb_list = q.fb_list;
+      s.ops = q.ops; s.base = q.base; s.mem_limit = q.mem_limit; s.fb_count = in.fb_count = q.fb_count; s.fb_list = q.fb_list;
       s.spin_cap = (uint32_t)std::min<int64_t>(((int64_t)h->N + h->E + 1024) * 64, 0x7FFFFFFF);
     } else if (ok && q.total > 48 * 1024) {
       ok = allow_large_lds((const void *)relax_pipeline_kernel, h->device, (int)q.total);
@@ -1770,7 +1769,7 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
     h.variant = kVariantStatic;
     h.time_scale = splan.scale; h.st_preds = splan.preds;
     h.st.G = splan.G; h.st.W = splan.W; h.st.total = splan.total;
-    if (pplan.ok) { h.pl = pplan.p; h.st_preds = 1; h.time_scale = pplan.p.time_scale; }
+    if (pplan.ok && !pplan.stream) { h.pl = pplan.p; h.st_preds = 1; h.time_scale = pplan.p.time_scale; }
   }
   if (pplan.stream) h.pl_stream = pplan.s;
   if (plan.ok) {

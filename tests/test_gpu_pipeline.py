@@ -123,3 +123,18 @@ def test_pipeline_in_two_launches(gpu_lib, stages, micros, machines, n_cand, spl
                 assert np.array_equal(a.cpu().numpy(), o), (name, w.name, info)
     seen = set(oracle.evaluate_workload(w, threads=8)[3].tolist())
     assert n_cand <= 100 or ({1, 2, 4} <= seen and seen & {0, 16}), seen      # (a limit that nothing keeps is among them)
+
+
+def test_two_launches_in_front_of_the_shared_placement_kernel(gpu_lib):
+    """16-bit times whose orders fit the LDS for few candidates only: the shared-placement kernel's general form stands behind the
+    two launches, and the host's plan says what the handle does."""
+    import torch
+    w, fixed = _pipeline(np.random.default_rng(4), 8, 80, 8, 70, True)
+    kw = dict(shared_placement=fixed, max_candidates=256 * 8 * 8)
+    with gpu_lib.Evaluator.for_workload(w, **kw) as ev:
+        info = ev.info()
+        assert info["two_launches"] == 1 and info["variant"] == 6 and info["kernel_kind"] == 0, info
+        assert info == gpu_lib.plan(w.n_devices, w.row_ptr, w.col_idx, w.dur, w.comm, w.mem_delta, **kw)
+        got = ev.evaluate(torch.from_numpy(w.placement).cuda(), torch.from_numpy(w.rank).cuda())
+        for a, o in zip(got, oracle.evaluate_workload(w, threads=8)):
+            assert np.array_equal(a.cpu().numpy(), o), info
