@@ -848,11 +848,17 @@ bool may_pipeline(const dagsched_desc_t *d) {
                                         !s->block_threads && !s->state_bits && !s->preds_per_op && !s->kernel && !s->window_cells));
 }
 
-// fused_ok: the fused form may be taken (the rules of plan_static about predecessors and times hold, or it is asked for)
-PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, const PredLists &reduced, int64_t sum_dur, int lds_max, int n_cu) {
+// fused_ok: the fused form may be taken (the rules of plan_static about predecessors and times hold); static_planned: plan_static took
+// the problem
+PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, bool static_planned, const PredLists &reduced, int64_t sum_dur, int lds_max, int n_cu) {
   PipelinePlan plan;
   const int N = d->n_nodes, P = d->n_devices, Pseg = next_pow2(P);
   const int32_t *pi = d->shared_placement;
+  // Two launches more than the ring kernel's one are 5 us of host time each call, and a small batch is over before the host is: ten steps
+  // of the search on 90 operations, 1562 candidates, 705 us with the ring kernel and 763 with the fused form, on 468 operations, 1032
+  // candidates, 720 and 760; on 864 operations, 3312 candidates, 905 and 743.  (plan_static's kernel has the launches anyway.)
+  const bool forced = d->shape && d->shape->static_waves;
+  if (!forced && !static_planned && (int64_t)N * d->max_candidates < (1 << 20)) return plan;
   // an edge inside a machine is a matter of the order; of the others each operation may have one, which is read
   std::vector<int32_t> read_ptr((size_t)N + 1, 0), read_idx;
   int64_t scale = 0, max_delay = 0;
@@ -1212,7 +1218,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   if (!force_general && desc->shared_placement && !(desc->shape && desc->shape->ignore_shared_placement))
     splan = plan_static(desc, pred_ptr, pred_idx, sum_dur, lds_max, n_cu);
   // (the fused form stands for the shared-placement kernel; the two launches stand in front of whatever kernel is planned besides)
-  if (may_pipeline(desc)) pplan = plan_pipeline(desc, splan.fits_format, reduced, sum_dur, lds_max, n_cu);
+  if (may_pipeline(desc)) pplan = plan_pipeline(desc, splan.fits_format, splan.ok, reduced, sum_dur, lds_max, n_cu);
   splan.ok = splan.ok || (pplan.ok && !pplan.stream);
   if (!force_general && !splan.ok) plan = plan_ring(desc, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
   const bool need_general = splan.ok || !plan.ok || !plan.exact;
@@ -1755,7 +1761,7 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
     splan = plan_static(&cleaned, pred_ptr, pred_idx, sum_dur, lds_bytes, n_cu);
   const PredLists reduced = reduce_preds(&cleaned, pred_ptr, pred_idx);
   PipelinePlan pplan;
-  if (may_pipeline(&cleaned)) pplan = plan_pipeline(&cleaned, splan.fits_format, reduced, sum_dur, lds_bytes, n_cu);
+  if (may_pipeline(&cleaned)) pplan = plan_pipeline(&cleaned, splan.fits_format, splan.ok, reduced, sum_dur, lds_bytes, n_cu);
   splan.ok = splan.ok || (pplan.ok && !pplan.stream);
   if (!force_general && !splan.ok) plan = plan_ring(&cleaned, pred_ptr, pred_idx, reduced, sum_dur, lds_bytes, n_cu);
   if (splan.ok || !plan.ok || !plan.exact) {

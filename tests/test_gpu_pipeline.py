@@ -103,7 +103,8 @@ def test_memory_levels_beyond_32_bits_stay_with_the_general_form(gpu_lib):
     (64, 40, 64, 17, True, 8)])
 @pytest.mark.parametrize("layout", [0, 1])
 def test_pipeline_in_two_launches(gpu_lib, stages, micros, machines, n_cand, split, per_cu, layout):
-    """Times beyond 16 bits take the form that streams the orders; per_cu: relaxers per workgroup (from the size of the batch)."""
+    """Times beyond 16 bits take the form that streams the orders; per_cu: relaxers per workgroup (from the size of the
+    batch, which is of 2^20 operations at least)."""
     import torch
     rng = np.random.default_rng(stages * 1000 + micros)
     g = 64 // (1 << (machines - 1).bit_length())
@@ -112,7 +113,7 @@ def test_pipeline_in_two_launches(gpu_lib, stages, micros, machines, n_cand, spl
     w.weight = rng.integers(0, 30, w.n_nodes).astype(np.int64)
     w.mem_limit = rng.integers(10, 40 + 15 * w.n_nodes // machines, machines).astype(np.int64)
     _say("%s layout=%d" % (w.name, layout))
-    with gpu_lib.Evaluator.for_workload(w, shared_placement=fixed, layout=layout, max_candidates=256 * g * per_cu) as ev:
+    with gpu_lib.Evaluator.for_workload(w, shared_placement=fixed, layout=layout, max_candidates=max(256 * g * per_cu, -(-2 ** 20 // w.n_nodes))) as ev:
         info = ev.info()
         assert info["two_launches"] == 1 and info["variant"] in (3, 4, 5), info
         for count in (n_cand, max(1, n_cand // 3)):
