@@ -1068,7 +1068,8 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
   if (h->pl_stream.total) {
     PipelineIngest in = h->pl_in;
     in.C = n_cand; in.placement = pl; in.rank = rk;
-    hipLaunchKernelGGL(pipeline_ingest_kernel, dim3((unsigned)n_cand), dim3(256), (size_t)in.total, stream, in);
+    const unsigned across = (unsigned)std::min(n_cand, 1 << 20);
+    hipLaunchKernelGGL(pipeline_ingest_kernel, dim3(across, ((unsigned)n_cand + across - 1) / across), dim3(256), (size_t)in.total, stream, in);
     PipelineStream s = h->pl_stream;
     s.C = n_cand; s.out = out;
     const int per_wg = s.G * s.W;

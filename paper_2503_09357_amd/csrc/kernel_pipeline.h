@@ -345,7 +345,8 @@ __global__ __launch_bounds__(256) void pipeline_ingest_kernel(PipelineIngest p) 
   const int N = p.N, P = p.P, row = (int)p.row;
   uint16_t *const list = (uint16_t *)lds, *const rank16 = (uint16_t *)(lds + p.o_rank);
   int32_t *const seg = (int32_t *)(lds + p.o_book), *const count = seg + 64, *const flag = count + 64;
-  const int64_t c = blockIdx.x;
+  const int64_t c = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;   // (a grid of one dimension holds fewer than 2^32 threads)
+  if (c >= p.C) return;
   const int32_t *const pl = p.placement + c * N, *const rk = p.rank + c * N;
   const bool vec = ((N & 3) == 0) && ((((uintptr_t)p.placement) | ((uintptr_t)p.rank)) & 15) == 0;
   const int nq = N >> 2;

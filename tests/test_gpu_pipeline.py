@@ -139,3 +139,25 @@ def test_two_launches_in_front_of_the_shared_placement_kernel(gpu_lib):
         got = ev.evaluate(torch.from_numpy(w.placement).cuda(), torch.from_numpy(w.rank).cuda())
         for a, o in zip(got, oracle.evaluate_workload(w, threads=8)):
             assert np.array_equal(a.cpu().numpy(), o), info
+
+
+def test_more_candidates_than_a_grid_of_one_dimension_holds(gpu_lib):
+    """2^24 workgroups of 256 threads are 2^32 threads, one more than a dimension of a grid can count."""
+    import torch
+    rng = np.random.default_rng(2)
+    n_cand = 2 ** 24 + 2 ** 20 + 37
+    pl = np.tile(np.array([[0, 1]], np.int32), (41, 1))
+    rk = np.zeros((41, 2), np.int32)
+    pl[5], rk[9], pl[13], rk[13] = (0, 2), (0, 1), (1, 1), (0, 1)     # no such machine, no such rank, another placement
+    rp, ci = W.csr_from_edges(2, np.array([0]), np.array([1]))
+    w = W.Workload("two operations", 2, rp, ci, np.array([70001, 3], np.int32), np.array([[0, 5], [7, 0]], np.int32),
+                   rng.integers(-3, 4, 2).astype(np.int64), pl, rk)
+    want = oracle.evaluate_workload(w)
+    with gpu_lib.Evaluator.for_workload(w, max_candidates=n_cand, shared_placement=pl[0]) as ev:
+        assert ev.info()["two_launches"] == 1, ev.info()
+        _say("%d candidates of two operations" % n_cand)
+        tile = lambda a: torch.from_numpy(a).cuda().repeat(-(-n_cand // 41), *[1] * (a.ndim - 1))[:n_cand].contiguous()
+        got = ev.evaluate(tile(pl), tile(rk))
+        for name, a, o in zip(("makespan", "bubble", "peak_mem", "flags"), got, want):
+            assert torch.equal(a, tile(o)), name
+    assert {0, 2, 4} == set(want[3].tolist())
