@@ -103,7 +103,8 @@ struct dagsched {
   uint8_t *ws_pib = nullptr;
   LdsLayout lds{};
   // Fallback of the optimistic 16-bit run and of the window mode: the same problem in the 32-bit form of the ring
-  // kernel (exact), launched over the list of candidates the first run left; fb_G == 0: the general kernel instead
+  // kernel (exact), launched over the list of candidates the first run left, or the pipeline kernel that stands in front of
+  // it; fb_G == 0: the general kernel instead
   int32_t fb_G = 0, fb_slots = 0, fb_feeders = 1, fb_block = 256, fb_kind = 0;
   bool fb_optimistic = false;             // the fallback is itself a 16-bit run with the general kernel behind it (window mode on
                                           // a problem too large for 32-bit cells)
@@ -1053,6 +1054,28 @@ RingParams ring_params(const dagsched *h, int32_t n_cand, const int32_t *pl, con
   return p;
 }
 
+// The candidates that the launches before have put on the first list, again, by the kernel that the handle holds for them: ring
+// kernel where its end times are proven to fit, else its 32-bit form, else the int32 kernel.  (The 32-bit form and not the optimistic 16-bit run
+// for candidates that leave a shared placement: that run needs another launch behind it, 4 us for every batch, also of those without such a candidate.)
+void launch_listed(dagsched *h, int32_t n_cand, const int32_t *pl, const int32_t *rk, const OutPtrs &out, hipStream_t stream) {
+  const int32_t *second_list = h->d_fb_list, *second_count = h->d_fb_count;
+  const bool exact = h->variant == kVariantRingExact || h->variant == kVariantRing32;
+  if (exact || h->fb_G) {
+    RingParams p = ring_params(h, n_cand, pl, rk, out, !exact && h->fb_optimistic);
+    p.cand_list = h->d_fb_list; p.cand_count = h->d_fb_count;
+    if (!exact) {
+      p.G = h->fb_G; p.lds = h->fb_lds;
+      p.fb_list = h->d_fb_list + h->max_cand; p.fb_count = h->d_fb_count + 1;   // (what this run leaves in its turn)
+      second_list = p.fb_list; second_count = p.fb_count;
+    }
+    const unsigned blocks = (unsigned)((n_cand + p.G - 1) / p.G);   // as if every candidate were on the list
+    hipLaunchKernelGGL(exact ? ring_kernel_for(h) : fallback_kernel(h), dim3(blocks), dim3((unsigned)(exact ? h->ring_block : h->fb_block)),
+                       (size_t)p.lds.total, stream, p);
+    if (!p.optimistic) return;
+  }
+  launch_general(h, n_cand, pl, rk, out, second_list, second_count, stream);
+}
+
 int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const int32_t *rank, int32_t *makespan,
                     int64_t *bubble, int64_t *peak_mem, int32_t *flags, hipStream_t stream) {
   const int32_t N = h->N;
@@ -1074,14 +1097,7 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
     s.C = n_cand; s.out = out;
     const int per_wg = s.G * s.W;
     hipLaunchKernelGGL(relax_stream_kernel, dim3((unsigned)((n_cand + per_wg - 1) / per_wg)), dim3((unsigned)stream_threads(s)), (size_t)s.total, stream, s);
-    // candidates with another placement
-    if (h->variant == kVariantRingExact || h->variant == kVariantRing32) {
-      RingParams p = ring_params(h, n_cand, pl, rk, out, false);
-      p.cand_list = h->d_fb_list; p.cand_count = h->d_fb_count;
-      hipLaunchKernelGGL(ring_kernel_for(h), dim3((unsigned)((n_cand + h->ring_G - 1) / h->ring_G)), dim3((unsigned)h->ring_block), (size_t)h->lds.total, stream, p);
-    } else {
-      launch_general(h, n_cand, pl, rk, out, h->d_fb_list, h->d_fb_count, stream);
-    }
+    launch_listed(h, n_cand, pl, rk, out, stream);           // candidates with another placement
   } else if (h->variant == kVariantGeneralLds || h->variant == kVariantGeneralGlobal) {
     launch_general(h, n_cand, pl, rk, out, nullptr, nullptr, stream);
   } else if (h->variant == kVariantStatic) {
@@ -1099,7 +1115,7 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
       hipLaunchKernelGGL(h->st_preds == 2 ? relax_static_kernel<2> : relax_static_kernel<4>, dim3((unsigned)std::min((n_cand + per_wg - 1) / per_wg, h->st_grid)),
                          dim3((unsigned)static_threads(p.W)), (size_t)p.total, stream, p);
     }
-    launch_general(h, n_cand, pl, rk, out, h->d_fb_list, h->d_fb_count, stream);   // candidates with another placement
+    launch_listed(h, n_cand, pl, rk, out, stream);           // candidates with another placement
   } else {
     const bool optimistic = h->variant == kVariantRingOptimistic;
     if (optimistic) hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, stream, h->d_fb_count);
@@ -1114,18 +1130,7 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
     p.lds = h->lds;
     hipLaunchKernelGGL(ring_kernel_for(h), dim3(blocks), dim3((unsigned)h->ring_block), (size_t)h->lds.total,
                        stream, p);
-    if (optimistic && h->fb_G) {
-      // what the run above left: the same candidates again with 32-bit end times (exact), straight off the list
-      RingParams q = p;
-      q.G = h->fb_G; q.optimistic = h->fb_optimistic ? 1 : 0; q.lds = h->fb_lds;
-      q.cand_list = h->d_fb_list; q.cand_count = h->d_fb_count;
-      q.fb_list = h->d_fb_list + h->max_cand; q.fb_count = h->d_fb_count + 1;   // (what this run leaves in its turn)
-      const unsigned blocks2 = (unsigned)((n_cand + h->fb_G - 1) / h->fb_G);   // as if every candidate were on the list
-      hipLaunchKernelGGL(fallback_kernel(h), dim3(blocks2), dim3((unsigned)h->fb_block), (size_t)h->fb_lds.total, stream, q);
-      if (h->fb_optimistic) launch_general(h, n_cand, pl, rk, out, h->d_fb_list + h->max_cand, h->d_fb_count + 1, stream);
-    } else if (optimistic) {
-      launch_general(h, n_cand, pl, rk, out, h->d_fb_list, h->d_fb_count, stream);
-    }
+    if (optimistic) launch_listed(h, n_cand, pl, rk, out, stream);
   }
   // the evaluation ran with delay 0 on pairs without a channel; candidates that use one are flagged now
   if (h->d_no_channel)

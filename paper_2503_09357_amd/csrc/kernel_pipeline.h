@@ -334,7 +334,7 @@ struct PipelineIngest {
   uint16_t *lists;                     // [C][row]
   int64_t row;
   int32_t *bad;                        // [C] flag bits
-  int32_t *fb_count;                   // set to 0 for the launch behind (as a launch of its own that took 4 us)
+  int32_t *fb_count;                   // two words, set to 0 for the launches behind (as a launch of its own that took 4 us)
   uint32_t o_rank, o_book, total;      // LDS: the candidate's lists at 0, then these
 };
 
@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256) void pipeline_ingest_kernel(PipelineIngest p) 
   if (vec) request(tid);
   if (tid < 64) { seg[tid] = tid < P ? p.seg[tid] : 0; count[tid] = tid < P ? p.count[tid] : 0; }
   if (tid == 0) *flag = 0;
-  if (tid == 0 && c == 0) *p.fb_count = 0;
+  if (tid < 2 && c == 0) p.fb_count[tid] = 0;
   for (int i = tid; i < row / 2; i += T) ((uint32_t *)list)[i] = 0xFFFFFFFFu;
   __syncthreads();
   int bits = 0;

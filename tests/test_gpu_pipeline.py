@@ -161,3 +161,57 @@ def test_more_candidates_than_a_grid_of_one_dimension_holds(gpu_lib):
         for name, a, o in zip(("makespan", "bubble", "peak_mem", "flags"), got, want):
             assert torch.equal(a, tile(o)), name
     assert {0, 2, 4} == set(want[3].tolist())
+
+
+def _with_strangers(rng, stages, micros, machines, n_cand, long_times):
+    """-> (workload whose candidates use one placement, the same with one operation of every candidate on another machine, placement)"""
+    ids, src, dst = W.pipeline_dag(stages, micros, split_w=True)
+    n = len(ids)
+    rp, ci = W.csr_from_edges(n, src, dst)
+    fixed = np.zeros(n, np.int32)
+    for (_, s, _), v in ids.items():
+        fixed[v] = s
+    dur, comm = rng.integers(1, 9, n), rng.integers(0, 4, (machines, machines))
+    if long_times:                                            # no common factor
+        dur, comm = dur * 37 + rng.integers(0, 37, n), comm * 30
+    if long_times > 1:
+        dur[0] += 70001
+    mem = rng.integers(-3, 4, n).astype(np.int64)
+    moved = fixed.copy()
+    moved[n // 2] = (moved[n // 2] + 1) % machines
+    both = []
+    for place in (fixed, moved):
+        pl, rk = W.list_schedules(rp, ci, machines, n_cand, int(rng.integers(0, 2 ** 62)), fixed_placement=place)
+        both.append(W.Workload("pipeline %d x %d" % (stages, micros), machines, rp, ci, dur.astype(np.int32), comm.astype(np.int32), mem, pl, rk))
+    return both[0], both[1], fixed
+
+
+@pytest.mark.parametrize("stages,micros,long_times,n_cand,two_launches,variant,most", [
+    (16, 128, 0, 2048, 1, 3, 3), (8, 32, 1, 16384, 1, 4, 4), (8, 32, 2, 16384, 1, 5, 3), (8, 80, 0, 16384, 1, 6, None), (8, 16, 0, 32768, 0, 6, None)])
+def test_candidates_that_place_differently(gpu_lib, stages, micros, long_times, n_cand, two_launches, variant, most):
+    """Every kernel that takes them.  most: where that is a form of the ring kernel, a batch of nothing else takes at most that many times as
+    long as on a handle without the hint (measured: 1.2 exact, 1.6 with the 32-bit form; the int32 kernel takes 7 times as long)."""
+    import torch
+    rng = np.random.default_rng(stages * micros + long_times)
+    alike, moved, fixed = _with_strangers(rng, stages, micros, stages, 61, long_times)
+    want = [oracle.evaluate_workload(w, threads=8) for w in (alike, moved)]
+    tile = lambda a: torch.from_numpy(a).cuda().repeat(-(-n_cand // 61), *[1] * (a.ndim - 1))[:n_cand].contiguous()
+    (pl0, rk0), (pl1, rk1) = ((tile(w.placement), tile(w.rank)) for w in (alike, moved))
+    with gpu_lib.Evaluator.for_workload(alike, max_candidates=n_cand, shared_placement=fixed) as ev:
+        info = ev.info()
+        assert (info["two_launches"], info["variant"]) == (two_launches, variant), info
+        out = ev.alloc_outputs(n_cand)
+        for every in (0, 97, 3, 1):                           # none, a few, many, all of them
+            _say("%s: every %d. candidate places differently" % (alike.name, every))
+            pick = (torch.arange(n_cand, device="cuda") % every == every - 1) if every else torch.zeros(n_cand, dtype=torch.bool, device="cuda")
+            ev.evaluate(torch.where(pick[:, None], pl1, pl0), torch.where(pick[:, None], rk1, rk0), out)
+            assert ev.last_fallbacks() == int(pick.sum())
+            for name, a, o0, o1 in zip(("makespan", "bubble", "peak_mem", "flags"), out, *want):
+                assert torch.equal(a, torch.where(pick.view(-1, *[1] * (a.dim() - 1)), tile(o1), tile(o0))), (name, every, info)
+        if most:
+            with gpu_lib.Evaluator.for_workload(alike, max_candidates=n_cand, shared_placement=None) as plain:
+                times = []
+                for e in (ev, plain):
+                    e.evaluate(pl1, rk1, out)
+                    times.append(min(e.time_evaluate(pl1, rk1, out, reps=3) for _ in range(3)))
+            assert times[0] < most * times[1], times
