@@ -106,6 +106,7 @@ struct dagsched {
   // kernel (exact), launched over the list of candidates the first run left, or the pipeline kernel that stands in front of
   // it; fb_G == 0: the general kernel instead
   int32_t fb_G = 0, fb_slots = 0, fb_feeders = 1, fb_block = 256, fb_kind = 0;
+  bool ring_exact = false;                // a ring kernel is planned that takes any candidate
   bool fb_optimistic = false;             // the fallback is itself a 16-bit run with the general kernel behind it (window mode on
                                           // a problem too large for 32-bit cells)
   LdsLayout fb_lds{};
@@ -1059,7 +1060,7 @@ RingParams ring_params(const dagsched *h, int32_t n_cand, const int32_t *pl, con
 // for candidates that leave a shared placement: that run needs another launch behind it, 4 us for every batch, also of those without such a candidate.)
 void launch_listed(dagsched *h, int32_t n_cand, const int32_t *pl, const int32_t *rk, const OutPtrs &out, hipStream_t stream) {
   const int32_t *second_list = h->d_fb_list, *second_count = h->d_fb_count;
-  const bool exact = h->variant == kVariantRingExact || h->variant == kVariantRing32;
+  const bool exact = h->ring_exact;
   if (exact || h->fb_G) {
     RingParams p = ring_params(h, n_cand, pl, rk, out, !exact && h->fb_optimistic);
     p.cand_list = h->d_fb_list; p.cand_count = h->d_fb_count;
@@ -1225,7 +1226,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     splan = plan_static(desc, pred_ptr, pred_idx, sum_dur, lds_max, n_cu);
   // (the fused form stands for the shared-placement kernel; the two launches stand in front of whatever kernel is planned besides)
   if (may_pipeline(desc)) pplan = plan_pipeline(desc, splan.fits_format, splan.ok, reduced, sum_dur, lds_max, n_cu);
-  splan.ok = splan.ok || (pplan.ok && !pplan.stream);
+  // (the ring kernel is planned behind either, unless the shared-placement kernel would evaluate without them)
   if (!force_general && !splan.ok) plan = plan_ring(desc, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
   const bool need_general = splan.ok || !plan.ok || !plan.exact;
 
@@ -1292,6 +1293,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   }
   if (ok && plan.ok) {
     h->variant = !plan.exact ? kVariantRingOptimistic : plan.cell32 ? kVariantRing32 : kVariantRingExact;   // (window mode is never exact)
+    h->ring_exact = plan.exact;
     h->ring_G = plan.G; h->ring_slots = plan.ring; h->ring_feeders = plan.feeders; h->ring_kind = plan.kind; h->ring_block = plan.block; h->lds = plan.lds; h->time_scale = plan.scale;
     h->rec_plane = plan.rec_plane; h->id_bits = plan.id_bits;
     const int64_t cap = ((int64_t)h->N + h->E + 1024) * 64;
@@ -1345,7 +1347,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       ok = allow_large_lds((const void *)ring_kernel_for(h), h->device, (int)h->lds.total);
   }
   if (ok && pplan.ok) {
-    if (!pplan.stream) { h->variant = kVariantStatic; h->time_scale = pplan.p.time_scale; h->st_preds = 1; }
+    if (!pplan.stream) { h->variant = kVariantStatic; h->st_preds = 1; }
     Tables t;
     PipelineParams &q = h->pl;
     q = pplan.p;
@@ -1768,7 +1770,6 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
   const PredLists reduced = reduce_preds(&cleaned, pred_ptr, pred_idx);
   PipelinePlan pplan;
   if (may_pipeline(&cleaned)) pplan = plan_pipeline(&cleaned, splan.fits_format, splan.ok, reduced, sum_dur, lds_bytes, n_cu);
-  splan.ok = splan.ok || (pplan.ok && !pplan.stream);
   if (!force_general && !splan.ok) plan = plan_ring(&cleaned, pred_ptr, pred_idx, reduced, sum_dur, lds_bytes, n_cu);
   if (splan.ok || !plan.ok || !plan.exact) {
     h.gen_G = kWave / h.Pseg;
@@ -1781,7 +1782,6 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
     h.variant = kVariantStatic;
     h.time_scale = splan.scale; h.st_preds = splan.preds;
     h.st.G = splan.G; h.st.W = splan.W; h.st.total = splan.total;
-    if (pplan.ok && !pplan.stream) { h.pl = pplan.p; h.st_preds = 1; h.time_scale = pplan.p.time_scale; }
   }
   if (pplan.stream) h.pl_stream = pplan.s;
   if (plan.ok) {
@@ -1789,6 +1789,7 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
     h.ring_G = plan.G; h.ring_slots = plan.ring; h.ring_feeders = plan.feeders; h.ring_kind = plan.kind; h.ring_block = plan.block;
     h.lds = plan.lds; h.time_scale = plan.scale;
   }
+  if (pplan.ok && !pplan.stream) { h.variant = kVariantStatic; h.pl = pplan.p; h.st_preds = 1; }
   return dagsched_get_info(&h, info);
 }
 
@@ -1809,7 +1810,7 @@ int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info) {
     info->lds_bytes = (int32_t)(pipeline ? h->pl.total : h->st.total);
     info->kernel_kind = (int8_t)((pipeline ? 3 : 0) + in_front);
     info->state_bits = 16;
-    info->time_scale = h->time_scale;
+    info->time_scale = pipeline ? h->pl.time_scale : h->time_scale;
     info->preds_per_op = (int8_t)h->st_preds;
     return DAGSCHED_OK;
   }
