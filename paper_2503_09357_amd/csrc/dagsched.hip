@@ -962,8 +962,9 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, bool static_
     PipelineIngest in{};
     in.row = plan.seg[P];
     in.o_rank = (uint32_t)in.row * 2u;
-    in.o_book = in.o_rank + align_up((uint32_t)N * 2u, 16u);
-    in.total = in.o_book + 64u * 4u * 2u + 16u;
+    in.team_stride = in.o_rank + align_up((uint32_t)N * 2u, 16u);
+    in.o_book = (uint32_t)pipeline_ingest_shape(N, d->max_candidates).teams * in.team_stride;   // (one for any C where one for this)
+    in.total = in.o_book + 64u * 4u * 3u;
     if ((int)s.total > lds_max || (int)in.total > lds_max) continue;
     s.N = in.N = N; s.P = in.P = P; s.Pseg = Pseg; s.log_pseg = p.log_pseg; s.G = p.G;
     s.row = in.row; s.mem_scale = p.mem_scale; s.sum_dur = sum_dur; s.time_scale = p.time_scale; s.limit = p.limit; s.n_cells = p.n_cells;
@@ -987,6 +988,20 @@ bool allow_large_lds(const void *kernel, int device, int bytes) {
   if (!hip_ok(hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes), "hipFuncSetAttribute")) return false;
   have = bytes;
   return true;
+}
+
+using IngestKernel = void (*)(PipelineIngest);
+IngestKernel pipeline_ingest_for(int N, int C) {
+  const PipelineIngestShape s = pipeline_ingest_shape(N, C);
+  switch (s.threads * 100 + s.teams) {
+    case 25601: return pipeline_ingest_kernel<256, 1>;
+    case 12801: return pipeline_ingest_kernel<128, 1>;
+    case 6401: return pipeline_ingest_kernel<64, 1>;
+    case 6402: return pipeline_ingest_kernel<64, 2>;
+    case 6404: return pipeline_ingest_kernel<64, 4>;
+    case 6408: return pipeline_ingest_kernel<64, 8>;
+    default: return pipeline_ingest_kernel<64, 16>;
+  }
 }
 
 using TransferKernel = void (*)(TransferParams);
@@ -1092,8 +1107,9 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
   if (h->pl_stream.total) {
     PipelineIngest in = h->pl_in;
     in.C = n_cand; in.placement = pl; in.rank = rk;
-    const unsigned across = (unsigned)std::min(n_cand, 1 << 20);
-    hipLaunchKernelGGL(pipeline_ingest_kernel, dim3(across, ((unsigned)n_cand + across - 1) / across), dim3(256), (size_t)in.total, stream, in);
+    const PipelineIngestShape shape = pipeline_ingest_shape(N, n_cand);
+    const unsigned groups = ((unsigned)n_cand + shape.teams - 1) / shape.teams, across = std::min(groups, 1u << 20);
+    hipLaunchKernelGGL(pipeline_ingest_for(N, n_cand), dim3(across, (groups + across - 1) / across), dim3((unsigned)shape.threads), (size_t)in.total, stream, in);
     PipelineStream s = h->pl_stream;
     s.C = n_cand; s.out = out;
     const int per_wg = s.G * s.W;
@@ -1454,7 +1470,9 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     PipelineStream &s = h->pl_stream;
     if (dev_alloc(&h->ws_orders, maxc * (size_t)in.row) && dev_alloc(&h->ws_bad, maxc)) {
       in.lists = h->ws_orders; s.lists = h->ws_orders; in.bad = h->ws_bad; s.bad = h->ws_bad;
-      ok = (in.total <= 48 * 1024 || allow_large_lds((const void *)pipeline_ingest_kernel, h->device, (int)in.total)) &&
+      for (int c : {1, h->max_cand})
+        ok = ok && (in.total <= 48 * 1024 || allow_large_lds((const void *)pipeline_ingest_for(h->N, c), h->device, (int)in.total));
+      ok = ok &&
            (s.total <= 48 * 1024 || allow_large_lds((const void *)relax_stream_kernel, h->device, (int)s.total));
     } else {
       (void)hipGetLastError();

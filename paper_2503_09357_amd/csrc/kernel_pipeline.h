@@ -335,67 +335,87 @@ struct PipelineIngest {
   int64_t row;
   int32_t *bad;                        // [C] flag bits
   int32_t *fb_count;                   // two words, set to 0 for the launches behind (as a launch of its own that took 4 us)
-  uint32_t o_rank, o_book, total;      // LDS: the candidate's lists at 0, then these
+  uint32_t o_rank, team_stride, o_book, total;      // LDS: per candidate its lists and at o_rank its ranks, then the rest
 };
 
-__global__ __launch_bounds__(256) void pipeline_ingest_kernel(PipelineIngest p) {
+// Workgroups of T threads, K candidates each, a team of T / K threads to a candidate.  What bounds it is HBM for large candidates and the workgroups
+// themselves for small ones: with 256 threads to every candidate, 240 operations take 2.6 ns a candidate (at 5 TB/s 0.4).  So T and K follow
+// the number of operations.
+// Both launches, us, 256 threads to a candidate and this shape: 4 operations on 2 machines, 262144 candidates 564 and 34 (ring kernel 71); 64 on 4, 65536: 164 and 35
+// (65); 240 on 2, 65536: 180 and 80 (146).  T = 64, 128, 256: 768 on 8, 65536: 193, 225, 284; 1200 on 8, 20000: 120, 121, 138; 1536 on 8, 20000: 151, 149, 168;
+// 3072 on 16, 20000: 347, 314, 314; 3840 on 16, 20000: 443, 400, 390; 6144 on 16, 4096: 197, 172, 158.
+struct PipelineIngestShape { int threads, teams; };
+inline PipelineIngestShape pipeline_ingest_shape(int N, int C) {   // (few candidates: 1024 operations on 32 machines, 1024 candidates 30.3 us with 64, 29.0 with 256)
+  return N > 3072 || (N > 768 && C <= 1280) ? PipelineIngestShape{256, 1}
+       : N > 1280 ? PipelineIngestShape{128, 1} : PipelineIngestShape{64, N > 128 ? 1 : N > 64 ? 2 : N > 32 ? 4 : N > 16 ? 8 : 16};
+}
+
+template <int T, int K>
+__global__ __launch_bounds__(T) void pipeline_ingest_kernel(PipelineIngest p) {
   extern __shared__ __align__(16) unsigned char lds[];
-  constexpr int T = 256, kChunk = 4;
-  const int tid = threadIdx.x;
+  constexpr int kTeam = T / K, kChunk = 4;
+  const int tid = threadIdx.x, team = K == 1 ? 0 : tid / kTeam, tt = K == 1 ? tid : tid % kTeam;
   const int N = p.N, P = p.P, row = (int)p.row;
-  uint16_t *const list = (uint16_t *)lds, *const rank16 = (uint16_t *)(lds + p.o_rank);
-  int32_t *const seg = (int32_t *)(lds + p.o_book), *const count = seg + 64, *const flag = count + 64;
-  const int64_t c = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;   // (a grid of one dimension holds fewer than 2^32 threads)
-  if (c >= p.C) return;
-  const int32_t *const pl = p.placement + c * N, *const rk = p.rank + c * N;
+  uint16_t *const list = (uint16_t *)(lds + team * p.team_stride), *const rank16 = (uint16_t *)(lds + team * p.team_stride + p.o_rank);
+  int32_t *const seg = (int32_t *)(lds + p.o_book), *const count = seg + 64, *const flag = count + 64 + team;
+  const int64_t block = (int64_t)blockIdx.y * gridDim.x + blockIdx.x;   // (a grid of one dimension holds fewer than 2^32 threads)
+  const int64_t c = block * K + team;
+  if (K == 1 && c >= p.C) return;
+  const bool on = K == 1 || c < p.C;                        // (a team without a candidate goes along for the barriers)
+  const int32_t *const pl = p.placement + (on ? c : 0) * N, *const rk = p.rank + (on ? c : 0) * N;
   const bool vec = ((N & 3) == 0) && ((((uintptr_t)p.placement) | ((uintptr_t)p.rank)) & 15) == 0;
   const int nq = N >> 2;
   const uint32_t *const machw = (const uint32_t *)p.machine;
   int4 a4[kChunk], r4[kChunk];
   auto request = [&](int q0) {
 #pragma unroll
-    for (int u = 0; u < kChunk; ++u) { a4[u] = ((const int4 *)pl)[min(q0 + u * T, nq - 1)]; r4[u] = ((const int4 *)rk)[min(q0 + u * T, nq - 1)]; }
+    for (int u = 0; u < kChunk; ++u) {
+      a4[u] = ((const int4 *)pl)[min(q0 + u * kTeam, nq - 1)];
+      r4[u] = ((const int4 *)rk)[min(q0 + u * kTeam, nq - 1)];
+    }
   };
-  if (vec) request(tid);
+  if (vec) request(tt);
   if (tid < 64) { seg[tid] = tid < P ? p.seg[tid] : 0; count[tid] = tid < P ? p.count[tid] : 0; }
-  if (tid == 0) *flag = 0;
-  if (tid < 2 && c == 0) p.fb_count[tid] = 0;
-  for (int i = tid; i < row / 2; i += T) ((uint32_t *)list)[i] = 0xFFFFFFFFu;
+  if (tt == 0) *flag = 0;
+  if (tid < 2 && block == 0) p.fb_count[tid] = 0;
+  for (int i = tt; i < row / 2; i += kTeam) ((uint32_t *)list)[i] = 0xFFFFFFFFu;
   __syncthreads();
   int bits = 0;
-  auto place = [&](int v, int32_t a, int32_t r, uint32_t m) {
-    const bool bad_pl = (uint32_t)a >= (uint32_t)P, other = (uint32_t)a != m, bad_rk = (uint32_t)r >= (uint32_t)count[m];
-    bits |= bad_pl ? kBitBadPlacement : other ? kBitOtherPlacement : bad_rk ? kBitBadRank : 0;
-    rank16[v] = (uint16_t)r;
-    if (!other && !bad_rk) list[seg[m] + r] = (uint16_t)v;
-  };
-  if (vec) {
-    for (int q0 = tid; q0 < nq; q0 += kChunk * T) {
-      int4 a[kChunk], r[kChunk];
+  if (on) {
+    auto place = [&](int v, int32_t a, int32_t r, uint32_t m) {
+      const bool bad_pl = (uint32_t)a >= (uint32_t)P, other = (uint32_t)a != m, bad_rk = (uint32_t)r >= (uint32_t)count[m];
+      bits |= bad_pl ? kBitBadPlacement : other ? kBitOtherPlacement : bad_rk ? kBitBadRank : 0;
+      rank16[v] = (uint16_t)r;
+      if (!other && !bad_rk) list[seg[m] + r] = (uint16_t)v;
+    };
+    if (vec) {
+      for (int q0 = tt; q0 < nq; q0 += kChunk * kTeam) {
+        int4 a[kChunk], r[kChunk];
 #pragma unroll
-      for (int u = 0; u < kChunk; ++u) { a[u] = a4[u]; r[u] = r4[u]; }
-      if (q0 + kChunk * T < nq) request(q0 + kChunk * T);
+        for (int u = 0; u < kChunk; ++u) { a[u] = a4[u]; r[u] = r4[u]; }
+        if (q0 + kChunk * kTeam < nq) request(q0 + kChunk * kTeam);
 #pragma unroll
-      for (int u = 0; u < kChunk; ++u) {
-        const int q = q0 + u * T;
-        if (q >= nq) break;
-        const uint32_t m = machw[q];
-        place(4 * q, a[u].x, r[u].x, m & 0xFF); place(4 * q + 1, a[u].y, r[u].y, (m >> 8) & 0xFF);
-        place(4 * q + 2, a[u].z, r[u].z, (m >> 16) & 0xFF); place(4 * q + 3, a[u].w, r[u].w, m >> 24);
+        for (int u = 0; u < kChunk; ++u) {
+          const int q = q0 + u * kTeam;
+          if (q >= nq) break;
+          const uint32_t m = machw[q];
+          place(4 * q, a[u].x, r[u].x, m & 0xFF); place(4 * q + 1, a[u].y, r[u].y, (m >> 8) & 0xFF);
+          place(4 * q + 2, a[u].z, r[u].z, (m >> 16) & 0xFF); place(4 * q + 3, a[u].w, r[u].w, m >> 24);
+        }
       }
+    } else {
+      for (int v = tt; v < N; v += kTeam) place(v, pl[v], rk[v], (machw[v >> 2] >> ((v & 3) << 3)) & 0xFF);
     }
-  } else {
-    for (int v = tid; v < N; v += T) place(v, pl[v], rk[v], (machw[v >> 2] >> ((v & 3) << 3)) & 0xFF);
+    for (int j = tt; j < P; j += kTeam)                     // behind a machine's operations: the one that is never ready
+      for (int i = seg[j] + count[j]; i < (j + 1 < P ? seg[j + 1] : row); ++i) list[i] = (uint16_t)N;
+    if (bits) atomicOr(flag, bits);
   }
-  for (int j = tid; j < P; j += T)                          // behind a machine's operations: the one that is never ready
-    for (int i = seg[j] + count[j]; i < (j + 1 < P ? seg[j + 1] : row); ++i) list[i] = (uint16_t)N;
-  if (bits) atomicOr(flag, bits);
   __syncthreads();
-  if (!(*flag & (kBitBadPlacement | kBitOtherPlacement | kBitBadRank))) {
+  if (on && !(*flag & (kBitBadPlacement | kBitOtherPlacement | kBitBadRank))) {
     // N operations into N slots: no slot left unwritten <=> every (machine, rank) slot hit exactly once
     bits = 0;
     uint4 *const out = (uint4 *)(p.lists + c * p.row);
-    for (int i = tid; i < row / 8; i += T) {
+    for (int i = tt; i < row / 8; i += kTeam) {
       const uint4 w = ((const uint4 *)list)[i];
       auto hole = [](uint32_t x) { return (x & 0xFFFFu) == 0xFFFFu || (x >> 16) == 0xFFFFu; };
       if (hole(w.x) || hole(w.y) || hole(w.z) || hole(w.w)) bits |= kBitBadRank;
@@ -403,14 +423,14 @@ __global__ __launch_bounds__(256) void pipeline_ingest_kernel(PipelineIngest p) 
     }
     // operations of one machine in the order of B
 #pragma unroll 4
-    for (int k = tid; k < p.n_pairs; k += T) {
+    for (int k = tt; k < p.n_pairs; k += kTeam) {
       const uint32_t uv = p.pairs[k];
       if (rank16[uv & 0xFFFFu] > rank16[uv >> 16]) bits |= kBitCyclic;
     }
     if (bits) atomicOr(flag, bits);
   }
   __syncthreads();
-  if (tid == 0) p.bad[c] = *flag;
+  if (on && tt == 0) p.bad[c] = *flag;
 }
 
 struct PipelineStream {
