@@ -946,7 +946,11 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, bool static_
   }
   plan.ok = best_score >= 0;
   if (forced_w || (int64_t)d->max_candidates < (int64_t)n_cu * p.G) return plan;
-  // two launches: where they put more relaxers to work on a CU than the fused form, for batches that need them
+  // Two launches, for batches that put more relaxers to work on a CU that way.  Against the fused form, whose orders stay in the LDS: its relaxers on a
+  // CU and the operations decide.  Zero-bubble pipelines, us, 65536 and 20000 candidates, fused and two launches: 2 relaxers 480 operations 116 and 145,
+  // 57 and 79; 600 operations 165 and 160, 80 and 71; 3 relaxers 960 operations 225 and 243, 82 and 87; 1024 operations 306 and 259, 105 and 91; 4 relaxers 1344
+  // operations 334 and 330, 122 and 131; 1920 operations (20000) 191 and 173; 6 relaxers 960 operations 191 and 239; 8 relaxers 1920 operations (20000) 178 and 192.
+  if (plan.ok && (best_relaxers > 4 || N < 400 * best_relaxers - 200)) return plan;
   const int64_t wanted = std::min<int64_t>(8, ((int64_t)d->max_candidates + (int64_t)n_cu * p.G - 1) / ((int64_t)n_cu * p.G));
   for (int w = (int)wanted; w >= 1 && w > best_relaxers; --w) {
     PipelineStream s{};

@@ -250,3 +250,22 @@ def test_info_fills_the_struct_of_its_callers_and_no_more():
     lib = dagsched.load(import_torch_first=False)
     assert lib.dagsched_plan(ctypes.byref(hp.desc), 160 * 1024, 256, ctypes.cast(room, ctypes.POINTER(dagsched.Info))) == 0
     assert bytes(room[32:]) == b"\xa5" * 32
+
+
+@pytest.mark.parametrize("stages,micros,machines,n_cand,long_times,form", [
+    (2, 40, 2, 65536, 0, "fused"), (2, 40, 2, 262144, 0, "fused"), (2, 32, 1, 262144, 0, "fused"), (4, 40, 4, 65536, 0, "fused"), (8, 40, 8, 65536, 0, "fused"),
+    (8, 32, 1, 65536, 0, "two launches"), (4, 100, 4, 20000, 0, "two launches"), (16, 40, 16, 20000, 0, "two launches"), (8, 32, 8, 65536, 0, "fused"),
+    (2, 40, 2, 65536, 1, "two launches"), (8, 4, 8, 65536, 1, "two launches"), (2, 1, 2, 65536, 0, "other")])
+def test_plan_of_a_pipeline(stages, micros, machines, n_cand, long_times, form):
+    """Fused where its relaxers are many or the operations few, two launches where the operations are many or the times long; another kernel for small batches."""
+    ids, src, dst = W.pipeline_dag(stages, micros, split_w=True)
+    fixed = np.zeros(len(ids), np.int32)
+    for (_, s, _), v in ids.items():
+        fixed[v] = s * machines // stages
+    rp, ci = W.csr_from_edges(len(ids), src, dst)
+    rng = np.random.default_rng(3)
+    dur, comm = rng.integers(1, 9, len(ids)), rng.integers(1, 5, (machines, machines))
+    if long_times:
+        dur[0] += 70001
+    i = dagsched.plan(machines, rp, ci, dur, comm, rng.integers(-3, 4, len(ids)), max_candidates=n_cand, shared_placement=fixed)
+    assert form == ("two launches" if i["two_launches"] else "fused" if i["variant"] == 6 and i["kernel_kind"] == 3 else "other"), i
