@@ -829,6 +829,9 @@ StaticPlan plan_static(const dagsched_desc_t *d, const std::vector<int32_t> &pre
 struct PipelinePlan {
   bool ok = false, stream = false;
   int T = 0;                                             // bits of an end time in a cell
+  // workgroups of the fused form launched per CU: what is resident, so that each has many batches to overlap (1536 operations on 32 machines, 65536 candidates
+  // 436 us, twice as many 533; 240 on 3, 262144: 189 and 226); twice as many where a relaxer has one candidate, whose lengths differ more than those of
+  // several together (1152 on 64, 20000: 234 us, 246 with what is resident)
   int wgs = 1;
   PipelineParams p{};
   PipelineStream s{};
@@ -936,13 +939,14 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, bool static_
     if (p.G * w > kWave || (forced_w && w != forced_w)) continue;
     const uint32_t o_book = p.o_cand + (uint32_t)(p.G * w) * p.cand_stride, total = o_book + 784u;
     if ((int)total > lds_max) break;
-    const int wgs = std::max(1, std::min(lds_cu / (int)align_up(total, 1280), 32 / (pipeline_threads(w) / kWave)));
+    const int fit = lds_cu / (int)align_up(total, 1280), held = 4 * kPipelineWavesPerSimd / (pipeline_threads(w) / kWave);
+    const int wgs = std::max(1, std::min(fit, held));
     const int64_t batches = ((int64_t)d->max_candidates + p.G * w - 1) / (p.G * w);
     if (!forced_w && batches < n_cu) continue;           // (not enough for every CU: the ring kernel's single launch)
     if (!forced_w && wgs * w < 2) continue;              // (a lone relaxer on a CU: the ring kernel holds as many candidates and more)
     const int64_t relaxers = std::min<int64_t>({8, (int64_t)wgs * w, (batches + n_cu - 1) / n_cu * w});   // at work on a CU
     const int64_t score = relaxers * 16 + (wgs >= 2 ? 8 : 0) + w;
-    if (score > best_score) { best_score = score; best_relaxers = relaxers; p.W = w; plan.wgs = wgs; p.o_book = o_book; p.total = total; }
+    if (score > best_score) { best_score = score; best_relaxers = relaxers; p.W = w; plan.wgs = std::max(1, std::min(fit, p.G == 1 ? 2 * held : held)); p.o_book = o_book; p.total = total; }
   }
   plan.ok = best_score >= 0;
   if (forced_w || (int64_t)d->max_candidates < (int64_t)n_cu * p.G) return plan;

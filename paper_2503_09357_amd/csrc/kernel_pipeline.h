@@ -92,7 +92,9 @@ struct PipelineParams {
   ".Lpipeline_end%=:\n\t"                                                                                                       \
   "s_waitcnt lgkmcnt(0)"
 
-__global__ __launch_bounds__(512, 4) void relax_pipeline_kernel(PipelineParams p) {
+constexpr int kPipelineWavesPerSimd = 4;                     // (128 registers: the rows on their way take 48 of them)
+
+__global__ __launch_bounds__(512, kPipelineWavesPerSimd) void relax_pipeline_kernel(PipelineParams p) {
   extern __shared__ __align__(16) unsigned char lds[];
   const int T = (int)blockDim.x;                            // at least 128 * W
   const int tid = threadIdx.x, lane = tid & 63;
