@@ -938,7 +938,10 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, bool static_
   const int lds_cu = 160 * 1024;
   const int forced_w = d->shape ? d->shape->static_waves : 0;
   int64_t best_score = -1, best_relaxers = 0;
-  for (int w = 1; w <= 4 && fused_ok; ++w) {             // (512 threads)
+  // (one machine with few operations: a batch of the fused form is mostly its barriers.  Us, the kernels before it, fused, two launches: 2 operations,
+  // 524288 candidates 43, 55, 37; 6, 262144: 31, 32, 28; 12, 87382: 21, 21, 17; 16, 65536: 15, 17, 15; 24, 65536: 19, 17, 20)
+  const bool worth = forced_w || P > 1 || N >= 24;
+  for (int w = 1; w <= 4 && fused_ok && worth; ++w) {    // (512 threads)
     if (p.G * w > kWave || (forced_w && w != forced_w)) continue;
     const uint32_t o_book = p.o_cand + (uint32_t)(p.G * w) * p.cand_stride, total = o_book + 784u;
     if ((int)total > lds_max) break;

@@ -255,7 +255,7 @@ def test_info_fills_the_struct_of_its_callers_and_no_more():
 @pytest.mark.parametrize("stages,micros,machines,n_cand,long_times,form", [
     (2, 40, 2, 65536, 0, "fused"), (2, 40, 2, 262144, 0, "fused"), (2, 32, 1, 262144, 0, "fused"), (4, 40, 4, 65536, 0, "fused"), (8, 40, 8, 65536, 0, "fused"),
     (8, 32, 1, 65536, 0, "two launches"), (4, 100, 4, 20000, 0, "two launches"), (16, 40, 16, 20000, 0, "two launches"), (8, 32, 8, 65536, 0, "fused"),
-    (2, 40, 2, 65536, 1, "two launches"), (8, 4, 8, 65536, 1, "two launches"), (2, 1, 2, 65536, 0, "other")])
+    (2, 40, 2, 65536, 1, "two launches"), (8, 4, 8, 65536, 1, "two launches"), (2, 1, 2, 65536, 0, "other"), (1, 4, 1, 262144, 0, "two launches"), (1, 8, 1, 65536, 0, "fused")])
 def test_plan_of_a_pipeline(stages, micros, machines, n_cand, long_times, form):
     """Fused where its relaxers are many or the operations few, two launches where the operations are many or the times long; another kernel for small batches."""
     ids, src, dst = W.pipeline_dag(stages, micros, split_w=True)
