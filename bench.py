@@ -158,7 +158,7 @@ def main() -> int:
         "edge_relax_per_s": cand_per_s * (w.n_edges + w.n_nodes - w.n_devices),
         "ms_kernel_hip_events": ms_kernel,
         "ms_kernel_median_single_launch": ms_kernel_median,
-        "candidates_sent_to_int32_kernel": n_fallback,
+        "candidates_evaluated_again": n_fallback,
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": measured_traffic(args.config, dominant_kernel(ev.info())),
                      "kernel": dominant_kernel(ev.info()),
@@ -240,7 +240,7 @@ def main() -> int:
                            "node_relax_per_s": w2.n_cand * w2.n_nodes / (ms2 * 1e-3),
                            "roofline_frac": ab2 / (ms2 * 1e-3) / 1e9 / HBM_PEAK_GBS,
                            "traffic": measured_traffic(cfg, dominant_kernel(info2)) if layout == 0 and not long_times else None,
-                           "candidates_sent_to_int32_kernel": ev2.last_fallbacks(),
+                           "candidates_evaluated_again": ev2.last_fallbacks(),
                            "parity_vs_oracle": parity2, "kernel": info2})
             ev2.close()
             del p2, r2, o2, w2

@@ -133,8 +133,8 @@ typedef struct {
                                      machine map, as in Sec. V) and only the orders differ.  The library may then
                                      resolve the delay of every edge once (eqs. (11)-(13)) and evaluate such
                                      candidates with a kernel of their own; candidates that place differently
-                                     are still evaluated, one by one and slowly.  Results never depend on it.
-                                     Entries outside [0, P): DAGSCHED_EINVAL                                   */
+                                     are still evaluated, but more slowly (see dagsched_last_fallbacks).  Results
+                                     never depend on it.  Entries outside [0, P): DAGSCHED_EINVAL              */
   int32_t contention;       /* 1: dagsched_evaluate_contended will be called on this handle; create then also
                                checks sum(dur) + E * max comm <= INT32_MAX (a path may pay one transfer per edge)
                                and allocates that call's workspace.  0 otherwise                               */
@@ -313,9 +313,8 @@ typedef struct {
   int8_t kernel_kind;      /* ring kernel: 0 operations split into parts of four predecessors, 1 every operation a
                               single part, 2 at most two predecessors per operation, 3 at most one; shared-placement
                               kernel: 3 in the form for pipelines (at most one end time to wait for), else 0.  Plus 4
-                              when the pipeline kernel in two launches evaluates (a shared placement, orders that do not
-                              fit the LDS): the fields then describe the kernel behind it, which takes the candidates
-                              that place differently */
+                              when the pipeline kernel in two launches evaluates (a shared placement, many operations
+                              or long times): the fields then describe the kernel planned behind it */
   int8_t wide_ops;         /* ring kernel: 1 when ops name machines instead of delays (delays above 255 or durations
                               above 65534 after the common factor is divided out) */
   int32_t time_scale;      /* common factor of every duration and delay, divided out inside the kernels */
@@ -339,8 +338,11 @@ int dagsched_plan(const dagsched_desc_t *desc, int32_t lds_bytes, int32_t n_cu, 
  * the 16-bit range of an optimistic run or whose schedule did not fit the window (variant 4: they are evaluated
  * again by the 32-bit form of the ring kernel, where a 32-bit end time per operation fits the GPU's LDS, else by
  * the general int32 kernel one by one, which is an order of magnitude slower per candidate), or that do not use
- * the shared placement (variant 6: the general kernel).  A caller who sees a large count should ask for 32-bit
- * state (dagsched_shape_t.state_bits), forbid the window (window_cells = -1) or drop the hint.  Synchronises hip_stream, the stream the
+ * the shared placement (variant 6, and every variant with two launches in front, where end times do not count).  These
+ * go to the ring kernel where one is planned behind a pipeline kernel (variants 3 and 5; variant 4: its 32-bit form; variant
+ * 6: where the batch is too small for the general shared-placement kernel), else to the general int32 kernel.  A caller who sees a
+ * large count should ask for 32-bit state (dagsched_shape_t.state_bits), forbid the window (window_cells = -1) or, where
+ * candidates place differently, drop the hint.  Synchronises hip_stream, the stream the
  * evaluate was enqueued on, and copies one word to the host: not for the asynchronous path.  *count = 0 for
  * variants without such a list.
  */

@@ -939,7 +939,7 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, bool static_
   const int forced_w = d->shape ? d->shape->static_waves : 0;
   int64_t best_score = -1, best_relaxers = 0;
   // (one machine with few operations: a batch of the fused form is mostly its barriers.  Us, the kernels before it, fused, two launches: 2 operations,
-  // 524288 candidates 43, 55, 37; 6, 262144: 31, 32, 28; 12, 87382: 21, 21, 17; 16, 65536: 15, 17, 15; 24, 65536: 19, 17, 20)
+  // 524288 candidates 43, 55, 37; 6, 262144: 31, 32, 28; 12, 87382: 21, 21, 17; 16, 65536: 15, 17, 15; without two launches 24, 65536: 19, 17)
   const bool worth = forced_w || P > 1 || N >= 24;
   for (int w = 1; w <= 4 && fused_ok && worth; ++w) {    // (512 threads)
     if (p.G * w > kWave || (forced_w && w != forced_w)) continue;
@@ -1841,7 +1841,7 @@ int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info) {
     info->block_threads = pipeline ? pipeline_threads(h->pl.W) : static_threads(h->st.W);
     info->lds_bytes = (int32_t)(pipeline ? h->pl.total : h->st.total);
     info->kernel_kind = (int8_t)((pipeline ? 3 : 0) + in_front);
-    info->state_bits = 16;
+    info->state_bits = pipeline ? 32 : 16;
     info->time_scale = pipeline ? h->pl.time_scale : h->time_scale;
     info->preds_per_op = (int8_t)h->st_preds;
     return DAGSCHED_OK;

@@ -341,7 +341,7 @@ class Evaluator:
         return _info_dict(i)
 
     def last_fallbacks(self, stream=None) -> int:
-        """Candidates of the last evaluate that went to the int32 kernel one by one (synchronises the stream)."""
+        """Candidates of the last evaluate that another kernel evaluated again, or instead (synchronises the stream)."""
         import torch
         s = torch.cuda.current_stream(self.hip_device) if stream is None else stream
         n = ctypes.c_int32()
