@@ -64,6 +64,7 @@ thread_local char g_hip_error[256] = "";
 bool hip_ok(hipError_t e, const char *what) {
   if (e == hipSuccess) return true;
   snprintf(g_hip_error, sizeof(g_hip_error), "%s: %s", what, hipGetErrorString(e));
+  (void)hipGetLastError();                                 // (reported here, so no later launch of this thread may report it)
   return false;
 }
 

@@ -1,0 +1,85 @@
+"""What the library's host side asks of the HIP runtime, without a GPU (tests/fake_hip.c): handles that fit the memory only
+without the pipeline kernels, memory given back, grids that every launch can have."""
+from __future__ import annotations
+
+import ctypes
+import json
+import os
+import subprocess
+import sys
+
+import numpy as np
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ATTRIBUTES = ("-DLDS_ATTRIBUTE=74", "-DCU_ATTRIBUTE=63")     # hipDeviceAttributeMaxSharedMemoryPerBlock, ...MultiprocessorCount
+
+
+def _in_child(shim):
+    """Runs in a process of its own, where the library's calls resolve to the shim."""
+    sys.path.insert(0, os.path.dirname(HERE))
+    fake = ctypes.CDLL(shim, ctypes.RTLD_GLOBAL)
+    fake.fake_used.restype = ctypes.c_size_t
+    fake.fake_budget.argtypes = [ctypes.c_size_t]
+    from paper_2503_09357_amd import dagsched, workloads as W
+    lib = dagsched.load(import_torch_first=False)
+    some = ctypes.c_void_p(1 << 20)                           # (nothing is read or written through it)
+
+    def problem(stages, micros, scale, n_cand, split=True):
+        ids, src, dst = W.pipeline_dag(stages, micros, split_w=split)
+        fixed = np.zeros(len(ids), np.int32)
+        for (_, s, _), v in ids.items():
+            fixed[v] = s
+        rp, ci = W.csr_from_edges(len(ids), src, dst)
+        rng = np.random.default_rng(1)
+        dur = rng.integers(1, 9, len(ids)) * scale + rng.integers(0, scale, len(ids))
+        return dagsched._HostProblem(stages, rp, ci, dur, rng.integers(1, 5, (stages, stages)) * scale, rng.integers(-3, 4, len(ids)), n_cand, 0, 0,
+                                     shared_placement=fixed)
+
+    def make(hp, calls, budget=1 << 62):
+        fake.fake_budget(budget)
+        h, i = ctypes.c_void_p(), dagsched.Info()
+        out = dict(rc=lib.dagsched_create(ctypes.byref(hp.desc), ctypes.byref(h)))
+        if out["rc"] == 0:
+            lib.dagsched_get_info(h, ctypes.byref(i))
+            out.update(dagsched._info_dict(i), used=fake.fake_used(), calls=[])
+            for n in calls:
+                fake.fake_launches()
+                rc = lib.dagsched_evaluate(h, n, some, some, some, some, some, some, None)
+                out["calls"].append((rc, fake.fake_launches()))
+            lib.dagsched_destroy(h)
+        return dict(out, left=fake.fake_used())
+
+    got = {}
+    for name, args in (("optimistic", (8, 32, 37, 65536)), ("exact", (16, 128, 1, 2048)), ("fused for ring", (3, 20, 1, 20000)),
+                       ("fused for general", (8, 16, 1, 32768))):
+        hp = problem(*args)
+        full = make(hp, (7,))
+        got[name] = (full, make(hp, (7,), full["used"] - 1))
+    got["after a refusal"] = make(problem(3, 20, 1, 20000), (7,))
+    got["many"] = make(problem(5, 1, 20011, 2 ** 26), (1, 2 ** 20 + 1, 2 ** 24 + 1, 2 ** 26))
+    print(json.dumps(got))
+
+
+@pytest.fixture(scope="module")
+def seen(tmp_path_factory):
+    shim = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-w", *ATTRIBUTES, os.path.join(HERE, "fake_hip.c"), "-o", shim], check=True)
+    from paper_2503_09357_amd import _build
+    _build.ensure_hip()
+    run = subprocess.run([sys.executable, os.path.abspath(__file__), shim], stdout=subprocess.PIPE, check=True, timeout=600)
+    return json.loads(run.stdout)
+
+
+def test_a_refused_handle_leaves_no_error_behind(seen):
+    """The launches of the next handle do not report that there was no memory for the one before."""
+    assert seen["fused for general"][1]["rc"] == -4 and seen["after a refusal"]["calls"][0][0] == 0
+
+
+def test_grids_of_large_batches(seen):
+    """No dimension of a grid counts 2^32 threads or more."""
+    assert seen["many"]["two_launches"] == 1 and seen["many"]["calls"] == [[0, 3]] * 4
+
+
+if __name__ == "__main__":
+    _in_child(sys.argv[1])
