@@ -887,6 +887,7 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, bool static_
   const int64_t bound = sum_dur / scale + N * (max_delay / scale);   // no end time, nor one plus a delay, exceeds this
   while ((1ll << plan.T) <= bound) ++plan.T;
   if (plan.T > 30) return plan;
+  if (((int64_t)N + 1) * 16 > lds_max) return plan;      // (the operations are in the LDS in either form)
   // memory levels in 32 bits, in units of the common factor of the A_i
   auto size_of = [&](int v) { return d->mem_delta[v] < 0 ? 0ull - (uint64_t)d->mem_delta[v] : (uint64_t)d->mem_delta[v]; };
   uint64_t factor = 0, swing = 0;                        // swing: no level is further from 0
@@ -1377,34 +1378,6 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     if (ok && h->lds.total > 48 * 1024)
       ok = allow_large_lds((const void *)ring_kernel_for(h), h->device, (int)h->lds.total);
   }
-  if (ok && pplan.ok) {
-    if (!pplan.stream) { h->variant = kVariantStatic; h->st_preds = 1; }
-    Tables t;
-    PipelineParams &q = h->pl;
-    q = pplan.p;
-    t.add(&h->d_pl_ops, pplan.ops.data(), pplan.ops.size());
-    t.add(&h->d_pl_machine, pplan.machine.data(), pplan.machine.size());
-    t.add(&h->d_pl_off, pplan.off.data(), pplan.off.size());
-    t.add(&h->d_pl_seg, pplan.seg.data(), pplan.seg.size());
-    t.add(&h->d_pl_count, pplan.count.data(), pplan.count.size());
-    t.add(&h->d_pl_pairs, pplan.pairs.data(), pplan.pairs.size());
-    if (!pplan.base.empty()) t.add(&h->d_pl_base, pplan.base.data(), pplan.base.size());
-    ok = t.send(&h->pipeline_tables) && (h->d_fb_count || dev_alloc(&h->d_fb_count, 2)) && (h->d_fb_list || dev_alloc(&h->d_fb_list, maxc));
-    q.ops = h->d_pl_ops; q.machine = h->d_pl_machine; q.off = h->d_pl_off; q.pairs = h->d_pl_pairs; q.base = h->d_pl_base; q.mem_limit = h->d_limit;
-    q.fb_count = h->d_fb_count; q.fb_list = h->d_fb_list;
-    h->pl_grid = n_cu * pplan.wgs;
-    if (pplan.stream) {
-      q.total = 0;
-      PipelineIngest &in = h->pl_in;
-      PipelineStream &s = h->pl_stream;
-      in = pplan.in; s = pplan.s;
-      in.machine = q.machine; in.seg = s.seg = h->d_pl_seg; in.count = s.count = h->d_pl_count; in.pairs = q.pairs;
-      s.ops = q.ops; s.base = q.base; s.mem_limit = q.mem_limit; s.fb_count = in.fb_count = q.fb_count; s.fb_list = q.fb_list;
-      s.spin_cap = (uint32_t)std::min<int64_t>(((int64_t)h->N + h->E + 1024) * 64, 0x7FFFFFFF);
-    } else if (ok && q.total > 48 * 1024) {
-      ok = allow_large_lds((const void *)relax_pipeline_kernel, h->device, (int)q.total);
-    }
-  }
   if (ok && h->layout == DAGSCHED_CAND_MINOR)
     ok = dev_alloc(&h->ws_tp, maxc * (size_t)h->N) && dev_alloc(&h->ws_tr, maxc * (size_t)h->N);
   if (ok && desc->contention) {
@@ -1478,23 +1451,47 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       ok = ok && channels.send(&h->channel_tables);
     }
   }
-  if (ok && h->pl_stream.total) {
-    // The workspace of the two launches comes last, and a handle that fits the memory only without it is made without it: the
-    // kernel that `variant` names takes every call then (hipMalloc's error is read, so that no launch reports it).
-    PipelineIngest &in = h->pl_in;
-    PipelineStream &s = h->pl_stream;
-    if (dev_alloc(&h->ws_orders, maxc * (size_t)in.row) && dev_alloc(&h->ws_bad, maxc)) {
-      in.lists = h->ws_orders; s.lists = h->ws_orders; in.bad = h->ws_bad; s.bad = h->ws_bad;
-      for (int c : {1, h->max_cand})
-        ok = ok && (in.total <= 48 * 1024 || allow_large_lds((const void *)pipeline_ingest_for(h->N, c), h->device, (int)in.total));
-      ok = ok &&
-           (s.total <= 48 * 1024 || allow_large_lds((const void *)relax_stream_kernel, h->device, (int)s.total));
-    } else {
-      (void)hipGetLastError();
+  if (ok && pplan.ok) {
+    // The pipeline kernels come last: a handle that fits the memory only without what they need is made without them, and the kernel planned
+    // besides takes every call (none is where the fused form stands for the general shared-placement kernel, which needs the same lists).
+    Tables t;
+    t.add(&h->d_pl_ops, pplan.ops.data(), pplan.ops.size());
+    t.add(&h->d_pl_machine, pplan.machine.data(), pplan.machine.size());
+    t.add(&h->d_pl_off, pplan.off.data(), pplan.off.size());
+    t.add(&h->d_pl_seg, pplan.seg.data(), pplan.seg.size());
+    t.add(&h->d_pl_count, pplan.count.data(), pplan.count.size());
+    t.add(&h->d_pl_pairs, pplan.pairs.data(), pplan.pairs.size());
+    if (!pplan.base.empty()) t.add(&h->d_pl_base, pplan.base.data(), pplan.base.size());
+    if (t.send(&h->pipeline_tables) && (h->d_fb_count || dev_alloc(&h->d_fb_count, 2)) && (h->d_fb_list || dev_alloc(&h->d_fb_list, maxc)) &&
+        (!pplan.stream || (dev_alloc(&h->ws_orders, maxc * (size_t)pplan.in.row) && dev_alloc(&h->ws_bad, maxc)))) {
+      PipelineParams &q = h->pl;
+      q = pplan.p;
+      q.ops = h->d_pl_ops; q.machine = h->d_pl_machine; q.off = h->d_pl_off; q.pairs = h->d_pl_pairs; q.base = h->d_pl_base; q.mem_limit = h->d_limit;
+      q.fb_count = h->d_fb_count; q.fb_list = h->d_fb_list;
+      h->pl_grid = n_cu * pplan.wgs;
+      if (pplan.stream) {
+        q.total = 0;
+        PipelineIngest &in = h->pl_in;
+        PipelineStream &st = h->pl_stream;
+        in = pplan.in; st = pplan.s;
+        in.machine = q.machine; in.seg = st.seg = h->d_pl_seg; in.count = st.count = h->d_pl_count; in.pairs = q.pairs;
+        in.lists = h->ws_orders; st.lists = h->ws_orders; in.bad = h->ws_bad; st.bad = h->ws_bad;
+        st.ops = q.ops; st.base = q.base; st.mem_limit = q.mem_limit; st.fb_count = in.fb_count = q.fb_count; st.fb_list = q.fb_list;
+        st.spin_cap = (uint32_t)std::min<int64_t>(((int64_t)h->N + h->E + 1024) * 64, 0x7FFFFFFF);
+        for (int c : {1, h->max_cand})
+          ok = ok && (in.total <= 48 * 1024 || allow_large_lds((const void *)pipeline_ingest_for(h->N, c), h->device, (int)in.total));
+        ok = ok && (st.total <= 48 * 1024 || allow_large_lds((const void *)relax_stream_kernel, h->device, (int)st.total));
+      } else {
+        h->variant = kVariantStatic; h->st_preds = 1;
+        ok = q.total <= 48 * 1024 || allow_large_lds((const void *)relax_pipeline_kernel, h->device, (int)q.total);
+      }
+    } else if (pplan.stream || plan.ok) {
       g_hip_error[0] = 0;
-      if (h->ws_orders) (void)hipFree(h->ws_orders);
-      h->ws_orders = nullptr;
-      s.total = 0;
+      for (void *x : {(void *)h->pipeline_tables, (void *)h->ws_orders})
+        if (x) (void)hipFree(x);
+      h->pipeline_tables = nullptr; h->ws_orders = nullptr;
+    } else {
+      ok = false;
     }
   }
   if (!ok) {

@@ -71,6 +71,23 @@ def seen(tmp_path_factory):
     return json.loads(run.stdout)
 
 
+@pytest.mark.parametrize("name,form,without,launches", [
+    ("optimistic", (4, 1), (4, 0), (3, 3)), ("exact", (3, 1), (3, 0), (3, 1)), ("fused for ring", (6, 0), (3, 0), (3, 1))])
+def test_a_handle_that_fits_only_without_the_pipeline_kernels(seen, name, form, without, launches):
+    """One byte less than it takes: the kernel planned besides takes every call."""
+    full, short = seen[name]
+    assert (full["rc"], full["variant"], full["two_launches"]) == (0, *form)
+    assert (short["rc"], short["variant"], short["two_launches"]) == (0, *without) and short["used"] < full["used"]
+    assert full["calls"] == [[0, launches[0]]] and short["calls"] == [[0, launches[1]]]
+    assert full["left"] == short["left"] == 0
+
+
+def test_no_handle_where_nothing_is_planned_besides(seen):
+    full, short = seen["fused for general"]
+    assert (full["rc"], full["variant"], full["kernel_kind"]) == (0, 6, 3) and full["calls"] == [[0, 3]]
+    assert short["rc"] == -4 and full["left"] == short["left"] == 0
+
+
 def test_a_refused_handle_leaves_no_error_behind(seen):
     """The launches of the next handle do not report that there was no memory for the one before."""
     assert seen["fused for general"][1]["rc"] == -4 and seen["after a refusal"]["calls"][0][0] == 0
