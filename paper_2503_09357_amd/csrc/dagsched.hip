@@ -983,7 +983,7 @@ PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, bool static_
     in.total = in.o_book + 64u * 4u * 3u;
     if ((int)s.total > lds_max || (int)in.total > lds_max) continue;
     s.N = in.N = N; s.P = in.P = P; s.Pseg = Pseg; s.log_pseg = p.log_pseg; s.G = p.G;
-    s.row = in.row; s.mem_scale = p.mem_scale; s.sum_dur = sum_dur; s.time_scale = p.time_scale; s.limit = p.limit; s.n_cells = p.n_cells;
+    s.row = in.row; s.mem_scale = p.mem_scale; s.sum_dur = sum_dur; s.time_scale = p.time_scale; s.limit = p.limit;
     in.n_pairs = p.n_pairs;
     plan.s = s; plan.in = in;
     plan.ok = plan.stream = true;

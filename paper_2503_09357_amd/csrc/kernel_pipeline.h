@@ -51,8 +51,9 @@ struct PipelineParams {
 // One step of the relaxer, for all lanes whose machine can go on.  e: the cell that the operation at work waits for; v[44:45]: its K and D;
 // v[40:43]: the next operation; idn: number of the one after it; lp: where the list goes on.  Order of the LDS accesses: own cell, cell
 // waited for, next operation, list.  The first wait is for the cell (two accesses after it may be on their way), the
-// second for next operation and list, which the access before them has had a whole step to let through.
-#define DAGSCHED_PIPELINE_STEP                                                                                                  \
+// second for next operation and list, which the access before them has had a whole step to let through.  list_address: instructions that
+// work out where the list goes on, list: the register that holds it.
+#define DAGSCHED_PIPELINE_STEP(list_address, list)                                                                              \
   "s_waitcnt lgkmcnt(2)\n\t"                                                                                                    \
   "v_add_u32 %[x], %[e], v44\n\t"                                                                                              \
   "v_max_u32 %[x], %[xa], %[x]\n\t"                                                                                             \
@@ -71,16 +72,19 @@ struct PipelineParams {
   "v_add_u32 %[lvl], %[lvl], v43\n\t"                                                                                          \
   "v_max_i32 %[pk], %[pk], %[lvl]\n\t"                                                                                         \
   "v_lshl_add_u32 %[x], %[idn], 4, %[ob]\n\t"                                                                                   \
+  list_address                                                                                                                  \
   "ds_read_b128 v[40:43], %[x]\n\t"                                                                                             \
-  "ds_read_u16 %[idn], %[lp]\n\t"                                                                                               \
+  "ds_read_u16 %[idn], " list "\n\t"                                                                                           \
   "v_add_u32 %[lp], 2, %[lp]\n\t"                                                                                               \
   "s_mov_b64 exec, %[all]\n\t"
+#define DAGSCHED_FUSED_STEP DAGSCHED_PIPELINE_STEP("", "%[lp]")
+#define DAGSCHED_STREAM_STEP DAGSCHED_PIPELINE_STEP("v_and_or_b32 %[y], %[lp], 63, %[ring]\n\t", "%[y]")   // lp: bytes of the order loaded so far
 // Blocks of eight steps as long as some lane is not through and something ran in a block's last step, at most `turns` of them.
 #define DAGSCHED_PIPELINE_LOOP                                                                                                  \
   "s_waitcnt lgkmcnt(0)\n"                                                                                                      \
   ".Lpipeline%=:\n\t"                                                                                                           \
-  DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP                                   \
-  DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP DAGSCHED_PIPELINE_STEP                                   \
+  DAGSCHED_FUSED_STEP DAGSCHED_FUSED_STEP DAGSCHED_FUSED_STEP DAGSCHED_FUSED_STEP                                               \
+  DAGSCHED_FUSED_STEP DAGSCHED_FUSED_STEP DAGSCHED_FUSED_STEP DAGSCHED_FUSED_STEP                                               \
   "s_mov_b64 %[moved], vcc\n\t"                                                                                                \
   "v_cmp_ne_u32 vcc, %[lp], %[end]\n\t"                                                                                        \
   "s_sub_u32 %[turns], %[turns], 1\n\t"                                                                                        \
@@ -313,7 +317,7 @@ __global__ __launch_bounds__(512, kPipelineWavesPerSimd) void relax_pipeline_ker
     __syncthreads();                                         // the flags are reset by the next batch
   }
 }
-#undef DAGSCHED_PIPELINE_STEP
+#undef DAGSCHED_FUSED_STEP
 #undef DAGSCHED_PIPELINE_LOOP
 
 // ---------------------------------------------------------------------------------------------------------------------
@@ -448,37 +452,12 @@ struct PipelineStream {
   int32_t time_scale;
   uint32_t limit, spin_cap;
   int32_t *fb_count, *fb_list;
-  uint32_t n_cells, cell_stride, o_cells, o_ring, o_fed, o_loaded, o_book, total;   // LDS: operations at 0, then these
+  uint32_t cell_stride, o_cells, o_ring, o_fed, o_loaded, o_book, total;   // LDS: operations at 0, then these
   OutPtrs out;
 };
 
 constexpr uint32_t kPipelineRing = 64;                      // bytes of a lane's ring: 32 entries
 
-// lp: bytes of the order loaded so far; everything else as in DAGSCHED_PIPELINE_STEP
-#define DAGSCHED_STREAM_STEP                                                                                                    \
-  "s_waitcnt lgkmcnt(2)\n\t"                                                                                                    \
-  "v_add_u32 %[x], %[e], v44\n\t"                                                                                              \
-  "v_max_u32 %[x], %[xa], %[x]\n\t"                                                                                             \
-  "v_cmp_gt_u32 vcc, %[lim], %[x]\n\t"                                                                                          \
-  "v_add_u32 %[y], %[x], v45\n\t"                                                                                              \
-  "s_mov_b64 exec, vcc\n\t"                                                                                                    \
-  "ds_write_b32 %[own], %[y]\n\t"                                                                                               \
-  "s_waitcnt lgkmcnt(1)\n\t"                                                                                                    \
-  "v_add_u32_sdwa %[at], %[cb], v42 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_0\n\t"                     \
-  "s_mov_b64 exec, %[all]\n\t"                                                                                                  \
-  "ds_read_b32 %[e], %[at]\n\t"                                                                                                 \
-  "s_mov_b64 exec, vcc\n\t"                                                                                                     \
-  "v_and_b32 %[xa], %[tm], %[y]\n\t"                                                                                            \
-  "v_add_u32_sdwa %[own], %[cb], v42 dst_sel:DWORD dst_unused:UNUSED_PAD src0_sel:DWORD src1_sel:WORD_1\n\t"                    \
-  "v_mov_b64 v[44:45], v[40:41]\n\t"                                                                                           \
-  "v_add_u32 %[lvl], %[lvl], v43\n\t"                                                                                          \
-  "v_max_i32 %[pk], %[pk], %[lvl]\n\t"                                                                                         \
-  "v_lshl_add_u32 %[x], %[idn], 4, %[ob]\n\t"                                                                                   \
-  "v_and_or_b32 %[y], %[lp], 63, %[ring]\n\t"                                                                                   \
-  "ds_read_b128 v[40:43], %[x]\n\t"                                                                                             \
-  "ds_read_u16 %[idn], %[y]\n\t"                                                                                                \
-  "v_add_u32 %[lp], 2, %[lp]\n\t"                                                                                               \
-  "s_mov_b64 exec, %[all]\n\t"
 // Eight steps where the entries for them are there, else two, one block after the other (at most `turns`) as long as there are entries and
 // something ran in a block's last step.
 #define DAGSCHED_STREAM_LOOP                                                                                                    \
@@ -644,6 +623,7 @@ __global__ __launch_bounds__(1024) void relax_stream_kernel(PipelineStream p) {
   }
 }
 #undef DAGSCHED_STREAM_STEP
+#undef DAGSCHED_PIPELINE_STEP
 #undef DAGSCHED_STREAM_LOOP
 
 }  // namespace dagsched_dev

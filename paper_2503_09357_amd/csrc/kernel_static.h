@@ -33,8 +33,6 @@
 
 namespace dagsched_dev {
 
-
-
 struct StaticParams {
   int32_t N, P, Pseg, log_pseg, G, W, C;   // G candidates per relaxer wavefront, W relaxers per workgroup
   const uint4 *ops;          // [N] x = o(pred0) | o(pred1) << 16, y = o(pred2) | o(pred3) << 16, z = four 8-bit delays,
