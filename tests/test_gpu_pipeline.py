@@ -293,3 +293,46 @@ def test_lists_do_not_meet_in_one_bank(gpu_lib):
     (measured: 212 us so, 98 with the lists 272 bytes apart; 105 operations 89)."""
     aligned, other = (_time(gpu_lib, 1, micros, 1, 262144, True, False) for micros in (40, 35))
     assert aligned < 1.6 * other, (aligned, other)
+
+
+@pytest.mark.parametrize("scale", [1, 400])
+@pytest.mark.parametrize("pair", [(0, 4), (1, 2)])
+def test_missing_channels(gpu_lib, scale, pair):
+    """A pair that only candidates with another placement use, and one that every candidate uses; fused (16-bit times) and in two launches."""
+    import torch
+    rng = np.random.default_rng(scale + pair[0])
+    w, fixed = _pipeline(rng, 5, 12, 5, 131, True, scale)
+    w.comm[pair], w.comm[pair[::-1]] = -1, -1
+    kw = dict(shape=dict(static_waves=3)) if scale == 1 else dict(max_candidates=2 ** 16)
+    if scale > 1:
+        w.dur[0] += 70001
+    _say("%s scale=%d pair=%s" % (w.name, scale, pair))
+    want = oracle.evaluate_workload(w, threads=8)
+    with gpu_lib.Evaluator.for_workload(w, shared_placement=fixed, **kw) as ev:
+        info = ev.info()
+        assert info["two_launches"] == (scale > 1) and (scale > 1 or info["kernel_kind"] == 3), info
+        got = ev.evaluate(torch.from_numpy(w.placement).cuda(), torch.from_numpy(w.rank).cuda())
+        for name, a, o in zip(("makespan", "bubble", "peak_mem", "flags"), got, want):
+            assert np.array_equal(a.cpu().numpy(), o), (name, info)
+    flags = set(want[3].tolist())
+    assert {4, 32} <= flags and (0 in flags) == (pair == (0, 4)), flags
+
+
+def test_fused_rows_that_are_not_aligned(gpu_lib):
+    """Rows of a multiple of four operations whose base is not a multiple of 16 bytes; the next batch's rows are on their way as in the aligned case."""
+    import torch
+    rng = np.random.default_rng(8)
+    w, fixed = _pipeline(rng, 8, 16, 8, 700, False)
+    assert w.n_nodes % 4 == 0
+    want = oracle.evaluate_workload(w, threads=8)
+    with gpu_lib.Evaluator.for_workload(w, shared_placement=fixed, shape=dict(static_waves=2)) as ev:
+        assert ev.info()["kernel_kind"] == 3
+        for shift in (0, 1, 3):
+            rows = []
+            for a in (w.placement, w.rank):
+                room = torch.empty(a.size + shift, dtype=torch.int32, device="cuda")
+                rows.append(room[shift:].view(a.shape))
+                rows[-1].copy_(torch.from_numpy(a))
+            _say("%s shift=%d" % (w.name, shift))
+            for name, a, o in zip(("makespan", "bubble", "peak_mem", "flags"), ev.evaluate(*rows), want):
+                assert np.array_equal(a.cpu().numpy(), o), (name, shift)
