@@ -308,7 +308,8 @@ typedef struct {
   int32_t cand_per_block;  /* candidates evaluated by one workgroup */
   int32_t block_threads;   /* workgroup size */
   int32_t lds_bytes;       /* dynamic LDS per workgroup */
-  int32_t state_bits;      /* width of the per-node end-time state (16 or 32) */
+  int32_t state_bits;      /* width of the end times kept on chip (16 or 32; the pipeline form of the shared-placement kernel,
+                              16, keeps them in words of 32 beside the number of the operation that holds the word) */
   int16_t ring_slots;      /* ring kernel: slots per lane of the op ring, else 0 */
   int8_t kernel_kind;      /* ring kernel: 0 operations split into parts of four predecessors, 1 every operation a
                               single part, 2 at most two predecessors per operation, 3 at most one; shared-placement

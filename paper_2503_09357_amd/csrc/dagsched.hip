@@ -1839,7 +1839,7 @@ int dagsched_get_info(const dagsched_t *h, dagsched_info_t *info) {
     info->block_threads = pipeline ? pipeline_threads(h->pl.W) : static_threads(h->st.W);
     info->lds_bytes = (int32_t)(pipeline ? h->pl.total : h->st.total);
     info->kernel_kind = (int8_t)((pipeline ? 3 : 0) + in_front);
-    info->state_bits = pipeline ? 32 : 16;
+    info->state_bits = 16;                                 // (also the fused form: its 32-bit cells hold a 16-bit end time beside a number)
     info->time_scale = pipeline ? h->pl.time_scale : h->time_scale;
     info->preds_per_op = (int8_t)h->st_preds;
     return DAGSCHED_OK;

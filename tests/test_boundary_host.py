@@ -268,5 +268,4 @@ def test_plan_of_a_pipeline(stages, micros, machines, n_cand, long_times, form):
     if long_times:
         dur[0] += 70001
     i = dagsched.plan(machines, rp, ci, dur, comm, rng.integers(-3, 4, len(ids)), max_candidates=n_cand, shared_placement=fixed)
-    assert form != "fused" or i["state_bits"] == 32          # (cells of user number and end time)
     assert form == ("two launches" if i["two_launches"] else "fused" if i["variant"] == 6 and i["kernel_kind"] == 3 else "other"), i
