@@ -89,7 +89,7 @@ struct dagsched {
   int32_t N = 0, E = 0, P = 0, Pseg = 0, max_cand = 0, layout = 0, device = 0;
   int64_t sum_dur = 0;
   int32_t variant = 0;
-  unsigned char *problem_tables = nullptr, *channel_tables = nullptr;   // blocks that hold the description (Tables)
+  unsigned char *problem_tables = nullptr, *channel_tables = nullptr;   // blocks that hold the description and the ring kernel's tables (Tables)
   // general kernel
   int32_t gen_G = 0, gen_lds = 0;
   bool gen_lds_state = false;
@@ -278,8 +278,7 @@ bool dev_alloc(T **dst, size_t n) {
 
 void free_handle(dagsched *h) {
   if (!h) return;
-  void *bufs[] = {h->problem_tables, h->channel_tables, h->pipeline_tables, h->ws_orders, h->ws_bad, h->ws_list, h->ws_end, h->d_rec,
-                  h->d_comm_scaled, h->d_nparts, h->ws_list16, h->ws_pib, h->ws_cnt, h->ws_sched_list, h->ws_sched_end,
+  void *bufs[] = {h->problem_tables, h->channel_tables, h->pipeline_tables, h->ws_orders, h->ws_bad, h->ws_list, h->ws_end, h->ws_list16, h->ws_pib, h->ws_cnt, h->ws_sched_list, h->ws_sched_end,
                   h->d_fb_count, h->d_fb_list, h->ws_meta, h->ws_tp, h->ws_tr,
                   h->d_st_ops, h->d_st_machine, h->d_st_off, h->d_st_base, h->ws_te,
                   h->wc_list, h->wc_end, h->wc_tlist, h->wc_tend, h->wc_ccnt, h->wc_coff, h->wc_echan,
@@ -1277,6 +1276,11 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     tables.add(&h->d_no_channel, no_channel.data(), no_channel.size());
     tables.add(&h->d_edges, edges.data(), edges.size());
   }
+  if (plan.ok) {
+    tables.add(&h->d_rec, plan.rec.data(), plan.rec.size());
+    tables.add(&h->d_comm_scaled, plan.comm_scaled.data(), plan.comm_scaled.size());
+    if (!plan.nparts.empty()) tables.add(&h->d_nparts, plan.nparts.data(), plan.nparts.size());
+  }
   h->n_red = (int32_t)reduced.idx.size();
   bool ok = tables.send(&h->problem_tables) &&
        (!any_missing || channel_flag_lds(h->N) <= 48 * 1024 ||
@@ -1330,10 +1334,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
     h->rec_plane = plan.rec_plane; h->id_bits = plan.id_bits;
     const int64_t cap = ((int64_t)h->N + h->E + 1024) * 64;
     h->spin_cap = (uint32_t)std::min<int64_t>(cap, 0x7FFFFFFF);
-    ok = upload(&h->d_rec, plan.rec.data(), plan.rec.size()) &&
-         upload(&h->d_comm_scaled, plan.comm_scaled.data(), plan.comm_scaled.size()) &&
-         (plan.nparts.empty() || upload(&h->d_nparts, plan.nparts.data(), plan.nparts.size())) &&
-         dev_alloc(&h->ws_list16, maxc * (size_t)h->list_stride) &&
+    ok = dev_alloc(&h->ws_list16, maxc * (size_t)h->list_stride) &&
          (plan.lds.pib_mode != 0 || dev_alloc(&h->ws_pib, maxc * (size_t)h->pib_stride));   // only read when the placement is not in LDS
     if (ok && !plan.exact) ok = dev_alloc(&h->d_fb_count, 2) && dev_alloc(&h->d_fb_list, 2 * maxc);   // (two lists)
     if (ok && !plan.exact && !plan.lds.wide) {
