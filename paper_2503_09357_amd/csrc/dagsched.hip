@@ -13,9 +13,9 @@
 // lanes of a candidate sit in one 64-wide wavefront (P <= 64), so "no lane of the candidate advanced"
 // (a ballot) is an exact deadlock test, i.e. a cycle of the combined graph.
 //
-// Two kernels: the ring kernel (kernel_ring.h; 16-bit end times in LDS, relaxer + feeder wavefronts)
-// is the fast path; the general kernel (kernel_general.h; int32 end times) takes what the ring kernel
-// cannot prove or finish.  No MFMA anywhere: integer max/plus with data-dependent gathers is not a
+// The ring kernel (kernel_ring.h; end times in LDS, relaxer + feeder wavefronts) is the path for candidates that place
+// differently, kernel_static.h and kernel_pipeline.h that for candidates that place alike; the general kernel
+// (kernel_general.h; int32 end times) takes what none of them can prove or finish.  No MFMA anywhere: integer max/plus with data-dependent gathers is not a
 // contraction.
 
 #include <hip/hip_runtime.h>
@@ -853,8 +853,8 @@ bool may_pipeline(const dagsched_desc_t *d) {
                                         !s->block_threads && !s->state_bits && !s->preds_per_op && !s->kernel && !s->window_cells));
 }
 
-// fused_ok: the fused form may be taken (the rules of plan_static about predecessors and times hold); static_planned: plan_static took
-// the problem
+// fused_ok: the fused form may be taken (the rules of plan_static about predecessors and times hold; its cells have room for longer
+// times, which was never measured); static_planned: plan_static took the problem
 PipelinePlan plan_pipeline(const dagsched_desc_t *d, bool fused_ok, bool static_planned, const PredLists &reduced, int64_t sum_dur, int lds_max, int n_cu) {
   PipelinePlan plan;
   const int N = d->n_nodes, P = d->n_devices, Pseg = next_pow2(P);

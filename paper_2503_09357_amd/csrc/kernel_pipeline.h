@@ -14,13 +14,14 @@
 // A candidate's cells are few (zero-bubble pipeline: 34 words instead of 768 half words), so two workgroups fit a CU and one
 // relaxes while the other reads its next candidates; the rows of a workgroup's next batch are on their way while it relaxes.
 //
-// What bounds it: the steps, each 22 instructions of a lone wavefront (five cycles an instruction, whether the one before is
-// waited for or not; an LDS round trip is 49, and what the lanes' mask costs on its way from the comparison 13), and the LDS
-// that eight of them share.  Written out in assembly because what a lane does only when its operation has run (most lanes wait in most steps)
+// What bounds it: HBM traffic, part of it of its own making.  Zero-bubble pipeline, 768 operations, 65536 candidates: 124 us in the kernel, 594 MB by the counters,
+// 4.8 TB/s, what a copy reaches; 408 MB would do.  The rest is a second read of nearly every rank row: the checkers come to it after the next
+// batch's rows have pushed it out of the L2.  The LDS is busy 59 % of the time (47 % of that bank conflicts of the 16-byte gathers), the VALU 57 %.
+// The step is written out in assembly because what a lane does only when its operation has run (most lanes wait in most steps)
 // is done under the lanes' mask, without a branch and without a wait: the cell is written, the next operation moves up
-// and the one after it is requested by those lanes only; and because the compiler made 400 cycles of what decides between two blocks of steps.
-// Zero-bubble pipeline, 768 operations, 65536 candidates: 291 us with kernel_static.h (218 cycles a step, one workgroup of four
-// relaxers a CU), 161 with this kernel while accountants took the levels through the LDS and the decisions were the compiler's, 130 now.
+// and the one after it is requested by those lanes only; the decisions between two blocks of steps are part of it.
+// The same batch, whole evaluation: 291 us with kernel_static.h (one workgroup of four relaxers a CU), 161 with this kernel while accountants took the
+// levels through the LDS and the decisions were the compiler's, 130 now.
 #pragma once
 
 #include "device_common.h"
@@ -326,8 +327,9 @@ __global__ __launch_bounds__(512, kPipelineWavesPerSimd) void relax_pipeline_ker
 // eight entries per machine; the second keeps the operations and the cells of up to eight relaxers' candidates in the LDS (one
 // workgroup per CU, 32 candidates of the bidirectional pipeline where the ring kernel holds eight) and streams the orders past
 // them: a thread per machine copies eight entries at a time into a ring of 32.
-// Bidirectional pipeline, 6144 operations, 16384 candidates: 1182 us with the ring kernel (two relaxers a CU, 275 cycles a step, fed
-// by wavefronts that look up placements and delays), 420 here: ingest 187 us (1.01 GB at 5.4 TB/s), relaxation 242 in two rounds.
+// Bidirectional pipeline, 6144 operations, 16384 candidates: 1180 us with the ring kernel (two relaxers a CU, fed
+// by wavefronts that look up placements and delays), 418 here: ingest 183 us (806 MB read and 206 written, 5.5 TB/s), relaxation 234 in two rounds, in
+// which the LDS that eight relaxers and four feeders share is busy 58 % of the time (40 % of that bank conflicts) and the VALU 51 %.
 
 struct PipelineIngest {
   int32_t N, P, C;

@@ -4,8 +4,9 @@
 // still waited for at any moment.  Which ones depends on the candidate, but B alone already says a lot: once an
 // operation x runs, everything that precedes x in B has run.  So x may take over the cell of u as soon as every
 // operation that reads u's end time is x itself or a predecessor of x in B (by any path), whatever the candidate:
-// along a chain one cell goes from hand to hand.  (MoE graph of 61 layers and 8 micro-batches, 11712 operations: 88
-// cells; zero-bubble pipeline, 768: 32; bidirectional pipeline, 6144: 64; layered graph, 50000: about 1600.)
+// along a chain one cell goes from hand to hand.  (1F1B pipeline, 64 operations: 8 cells; zero-bubble pipeline, 768: 32;
+// bidirectional pipeline, 6144: 64.  Where many operations run side by side the bounded search below finds little:
+// the layered graph, 50000 operations, keeps some 45000.)
 //
 // A reader may look at a cell long before the end time it waits for is there, when the cell still holds an earlier
 // user's.  So the users of a cell are numbered 1, 2, 3, ... (0: nobody yet), and a cell holds number << T | end time.
