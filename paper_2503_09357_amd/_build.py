@@ -13,6 +13,8 @@ from __future__ import annotations
 import os
 import shutil
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG_DIR = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(PKG_DIR, "csrc")
@@ -21,7 +23,10 @@ INCLUDE = os.path.join(os.path.dirname(PKG_DIR), "include")
 HIP_LIB = os.path.join(PKG_DIR, "libdagsched.so")
 GEN_LIB = os.path.join(PKG_DIR, "libdagsched_workload.so")
 
-HIP_SOURCES = ["dagsched.hip"]
+# The host code with most kernels, and the instantiations of the ring kernel: (cell format, lanes per machine) a unit.
+RING_UNITS = [(0, 1), (1, 1), (2, 1), (3, 1), (4, 1), (5, 1), (0, 2), (2, 2), (0, 4), (2, 4)]
+HIP_UNITS = [("dagsched.hip", [])] + [("ring_kernels.hip", ["-DDAGSCHED_RING_HALF=%d" % h, "-DDAGSCHED_RING_SUB=%d" % s]) for h, s in RING_UNITS]
+HIP_FLAGS = ["--offload-arch=gfx950", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-function", "-I", INCLUDE]
 
 
 def _run(cmd):
@@ -39,17 +44,14 @@ def _hipcc() -> str:
 
 
 def build_hip(verbose: bool = False) -> str:
-    """hipcc -> libdagsched.so (gfx950 only)."""
+    """hipcc -> libdagsched.so (gfx950 only); the units are compiled side by side."""
     tmp = HIP_LIB + ".tmp"
-    cmd = [
-        _hipcc(), "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
-        "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-        "-Wall", "-Wno-unused-function",
-        "-I", INCLUDE,
-        *[os.path.join(CSRC, s) for s in HIP_SOURCES],
-        "-o", tmp,
-    ]
-    out = _run(cmd)
+    with tempfile.TemporaryDirectory(prefix="dagsched_build_") as where, ThreadPoolExecutor(min(8, os.cpu_count() or 1)) as pool:
+        objects = [os.path.join(where, "%d.o" % i) for i in range(len(HIP_UNITS))]
+        jobs = [pool.submit(_run, [_hipcc(), *HIP_FLAGS, "-O3", "-fPIC", "-Wall", *defines, "-c", os.path.join(CSRC, source), "-o", obj])
+                for obj, (source, defines) in zip(objects, HIP_UNITS)]
+        out = "".join(j.result() for j in jobs)
+        out += _run([_hipcc(), "--offload-arch=gfx950", "-fPIC", "-shared", *objects, "-o", tmp])
     os.replace(tmp, HIP_LIB)
     if verbose and out.strip():
         print(out)

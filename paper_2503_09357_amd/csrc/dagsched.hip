@@ -42,6 +42,7 @@
 #include "kernel_static.h"
 #include "kernel_transfers.h"
 #include "kernel_util.h"
+#include "ring_kernels.h"
 #include "share_cells.h"
 
 using namespace dagsched_dev;
@@ -98,7 +99,7 @@ struct dagsched {
   int64_t *d_mem = nullptr, *d_weight = nullptr, *d_limit = nullptr;
   int32_t *ws_list = nullptr, *ws_end = nullptr;
   // ring kernel
-  int32_t ring_G = 0, ring_slots = 0, ring_feeders = 1, ring_kind = 0, ring_block = 256, rec_plane = 0, id_bits = 16, time_scale = 1;
+  int32_t ring_G = 0, ring_sub = 1, ring_slots = 0, ring_feeders = 1, ring_kind = 0, ring_block = 256, rec_plane = 0, id_bits = 16, time_scale = 1;
   uint8_t *d_nparts = nullptr;
   int64_t list_stride = 0, pib_stride = 0;
   uint8_t *ws_pib = nullptr;
@@ -106,7 +107,7 @@ struct dagsched {
   // Fallback of the optimistic 16-bit run and of the window mode: the same problem in the 32-bit form of the ring
   // kernel (exact), launched over the list of candidates the first run left, or the pipeline kernel that stands in front of
   // it; fb_G == 0: the general kernel instead
-  int32_t fb_G = 0, fb_slots = 0, fb_feeders = 1, fb_block = 256, fb_kind = 0;
+  int32_t fb_G = 0, fb_sub = 1, fb_slots = 0, fb_feeders = 1, fb_block = 256, fb_kind = 0;
   bool ring_exact = false;                // a ring kernel is planned that takes any candidate
   bool fb_optimistic = false;             // the fallback is itself a 16-bit run with the general kernel behind it (window mode on
                                           // a problem too large for 32-bit cells)
@@ -305,14 +306,14 @@ LdsLayout ring_layout(int N, int P, int G, int ring, int pib_lds, int cell_bytes
   at = align_up(at, 16);
   o.o_ring = at;  at += (uint32_t)ring * kWave * 16u;
   o.o_scr = at;   at += kWave * ((win_log2 && cell_bytes == 4) ? 8u : 4u);
-  o.o_total = at; at += kWave * 4u;
-  at = align_up(at, 8);
-  o.o_peak = at;  at += kWave * 8u;
-  o.o_cnt = at;   at += kWave * 4u;
-  o.o_off = at;   at += kWave * 4u;
-  o.o_flag = at;  at += kWave * 4u;
-  o.o_abort = at; at += kWave * 4u;
-  o.o_over = at;  at += kWave;
+  // (a word per machine, a word per candidate: four workgroups of one candidate of the MoE graph fill the LDS to the last byte)
+  const uint32_t machines = (uint32_t)G * (uint32_t)next_pow2(P);
+  o.o_total = at; at += machines * 4u;
+  o.o_cnt = at;   at += machines * 4u;
+  o.o_off = at;   at += machines * 4u;
+  o.o_flag = at;  at += (uint32_t)G * 4u;
+  o.o_abort = at; at += (uint32_t)G * 4u;
+  o.o_over = at;  at += align_up((uint32_t)G, 4);
   o.wide = wide ? 1u : 0u;
   // channel delays: a byte each, rows [source machine + the dummy's][destination]; wide ops: a dword each, 64 rows
   o.o_comm = at;  at += wide ? (uint32_t)kWave * (uint32_t)next_pow2(P) * 4u
@@ -325,17 +326,16 @@ LdsLayout ring_layout(int N, int P, int G, int ring, int pib_lds, int cell_bytes
 // Needs: every scaled delay <= 255, at most 65536 overflow records, the scaled lower bound on any
 // makespan (critical path of B, heaviest possible average load) below the 16-bit range, and an LDS
 // footprint that fits a workgroup.
-using RingKernel = void (*)(RingParams);
-template <int HALF>
-RingKernel ring_kernel_pick(int ring, int feeders, int pib_lds, int kind);
+RingKernel ring_kernel_with(const LdsLayout &lds, int G, int sub, int ring, int feeders, int kind);
 
 struct RingPlan {
   bool ok = false, exact = false, cell32 = false;
-  int G = 0, ring = 0, feeders = 1, kind = 0, block = 256;
+  int G = 0, sub = 1, ring = 0, feeders = 1, kind = 0, block = 256;
   int32_t scale = 1;
   LdsLayout lds{};
   std::vector<uint4> rec;
   int rec_plane = 0, id_bits = 16;
+  int64_t total_parts = 0;
   std::vector<uint8_t> nparts;
   std::vector<int32_t> comm_scaled;
   // window mode: cells per candidate (0: off), the layout and workgroup size of the ingest launch
@@ -416,7 +416,9 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
     if (d->dur[v] / g >= 256 * 65535) return plan;       // ... whose durations are low + 65535 * high, high < 256
   // longest path of B alone in scaled units (no delays): a lower bound on every makespan
   std::vector<int64_t> fin(N, -1);
+  int32_t levels = 1;                                  // operations on the longest path of B
   {
+    std::vector<int32_t> level(N, 1);
     std::vector<int32_t> order;                        // topological order by repeated peeling on pred lists
     std::vector<int32_t> indeg(N);
     for (int v = 0; v < N; ++v) indeg[v] = pred_ptr[v + 1] - pred_ptr[v];
@@ -425,7 +427,8 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
     for (size_t i = 0; i < order.size(); ++i) {
       const int u = order[i];
       int64_t best = 0;
-      for (int k = pred_ptr[u]; k < pred_ptr[u + 1]; ++k) best = std::max(best, fin[pred_idx[k]]);
+      for (int k = pred_ptr[u]; k < pred_ptr[u + 1]; ++k) { best = std::max(best, fin[pred_idx[k]]); level[u] = std::max(level[u], level[pred_idx[k]] + 1); }
+      levels = std::max(levels, level[u]);
       fin[u] = best + d->dur[u] / g;
       for (int k = d->row_ptr[u]; k < d->row_ptr[u + 1]; ++k)
         if (--indeg[d->col_idx[k]] == 0) order.push_back(d->col_idx[k]);
@@ -444,7 +447,7 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   for (int v = 0; v < N; ++v) max_parts = std::max(max_parts, (op_preds.size(v) + PR - 1) / PR);
   if (max_parts > 16) return plan;                     // very wide fan-in: leave it to the general kernel
   {                                                    // the kernel counts a lane's op parts in 16 bits
-    int64_t total_parts = 0;
+    int64_t &total_parts = plan.total_parts;
     for (int v = 0; v < N; ++v) total_parts += std::max(1, (op_preds.size(v) + PR - 1) / PR);
     if (total_parts >= 65536) return plan;
   }
@@ -497,13 +500,16 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   plan.comm_scaled.resize((size_t)P * P);
   for (int i = 0; i < P * P; ++i) plan.comm_scaled[i] = (i / P != i % P) ? (int32_t)(d->comm[i] / g) : 0;
 
-  // shape: most candidates resident per CU first.  Placement bytes in LDS give the fastest feeders but cost
+  // shape: fewest rounds of the batch first, a round's time by what its workgroups are.  Placement bytes in LDS give the fastest feeders but cost
   // N bytes per candidate; in L2 they leave room for more candidates or a deeper ring.  Measured weights: a
-  // four-slot ring counts 0.7 (hot lanes outrun it), placement bytes in L2 count 0.7 (0.85 with two predecessors
+  // four-slot ring counts 0.7 (hot lanes outrun it; 0.8 with several lanes per machine, which have a ring each), placement bytes in L2 count 0.7 (0.85 with two predecessors
   // per op: half the gathers; a 36-layer MoE graph, N = 6912: four workgroups per CU with them in L2 0.179 us per
   // candidate, three with them in LDS 0.135), and workgroups beyond
-  // five per CU count nothing, half-empty wavefronts count 0.65 (the feeders do the same work for half the
-  // candidates); at equal counts, more workgroups of fewer candidates.
+  // five per CU count nothing (six with several lanes per machine), half-empty wavefronts count 0.65 (the feeders do the same work for half the
+  // candidates), every further workgroup on the CU costs 5 % of the round.  Measured (us, shape taken first, in brackets the candidates of a wavefront): MoE graph, 4096 candidates
+  // 975 (1) and 1050 (2), 256 candidates 186 (1), 243 (2); its 16-layer form on 8 machines, 4096: 56 (4), 62 (8); random graph of 3001 operations on 11 machines, 2051: 91 (1),
+  // 123 (2), 153 (4); of 2000 on 16, 8192: 125 (2), 140 (1), 157 (4); of 500 on 7, 30000: 125 (4), 121 (8); layered, 5000 on 30, 1000: 72 (1), 80 (2); 1F1B of 64 on 4,
+  // 65536: 47 (16), 58 (8).
   // a shape given with the description wins, field by field
   const dagsched_shape_t *sh = d->shape;
   // Width of the end times.  16 bits when every end time provably fits, or when most candidates can be expected to
@@ -561,8 +567,13 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   const int force_ring = sh ? sh->ring_slots : 0;
   const int force_feeders = sh ? sh->feeders : 0;
   const int force_pib = sh ? sh->placement_mode : -1;
-  int64_t best_score = -1;
-  int best_wgs = 0;
+  // Levels of B for every operation that a machine has on the average: where chains across the machines are long, several
+  // lanes per machine save fewer trips.  Trips of one lane over those of two and of four, by simulation: MoE graph (1.7 levels) 1.48, 1.75, layered
+  // graph (0.5) 1.52, 1.81, four-stage 1F1B (0.5) 1.54, 1.96; zero-bubble and bidirectional pipelines (0.2), random graph (0.1) 1.85 to 1.9, 3.0 to 3.1.
+  // A trip takes 240 cycles with one lane, 265 with two, 370 with four.
+  const bool deep = 3 * (int64_t)levels * P > (int64_t)N;
+  double best_score = -1;
+  int best_wgs = 0, best_at_once = 0;
   for (int G = kWave / Pseg; G >= 1; G >>= 1) {
     if (force_g && G != force_g) continue;
     for (int pib_lds : {1, 2, 0}) {
@@ -577,7 +588,17 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
         if (!win_log2 && (uint64_t)G * (o.s_stride >> (plan.cell32 ? 2 : 1)) > 65536u) continue;   // half (quarter) addresses must fit 16 bits
         // window mode: the ingest launch builds the lists of the workgroup's G candidates in LDS, 2 N bytes each
         if (win_log2 && (int)ring_layout(N, P, G, 0, 0, 2, false).total > lds_max) continue;
-        int wgs = std::min(5, lds_max / (int)align_up(o.total, 512));   // beyond ~20 wavefronts the CU is issue-bound
+        // several lanes per machine where the candidates leave a wavefront some
+        auto is_built = [&](int sub) {
+          for (int f = force_feeders ? force_feeders : 1; f <= (force_feeders ? force_feeders : 4); ++f)
+            if (ring_kernel_with(o, G, sub, ring, f, plan.kind) || (plan.kind == 3 && (sub == 1 || plan.cell32) && ring_kernel_with(o, G, sub, ring, f, 2)))
+              return true;
+          return false;
+        };
+        int sub = wide || win_log2 ? 1 : std::min(4, kWave / (G * Pseg));
+        while (sub > 1 && !is_built(sub)) sub >>= 1;
+        if (!is_built(sub)) continue;
+        int wgs = std::min(sub > 1 ? 6 : 5, lds_max / (int)align_up(o.total, 512));   // beyond ~20 wavefronts the CU is issue-bound
         if (wgs < 1) continue;
         // window mode relaxes every candidate of a full batch at once when it can: workgroups per CU beyond what the
         // batch fills count nothing, nor do those that leave the number of rounds as it is (four per CU needed: three
@@ -588,26 +609,28 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
           const int64_t rounds = (need + wgs - 1) / wgs;
           wgs = (int)std::min<int64_t>(wgs, (need + rounds - 1) / rounds);
         }
-        const int64_t score = (int64_t)wgs * G * (ring >= 8 ? 100 : 70) * (pib_lds == 1 ? 100 : pib_lds == 2 ? 99 : plan.kind == 2 ? 85 : 70) *
-                                  (G * Pseg < kWave ? 65 : 100) + (ring == 16 ? 2 : 0) - G;
-        if (score > best_score) { best_score = score; best_wgs = wgs; plan.G = G; plan.ring = ring; plan.lds = o; }
+        // rounds of the batch times what a round takes, the smaller the better
+        const int64_t at_once = std::max<int64_t>(1, ((d->max_candidates + G - 1) / G + n_cu - 1) / n_cu);   // workgroups per CU that the batch has
+        const int64_t rounds = (at_once + wgs - 1) / wgs;
+        const double lanes = sub == 4 ? (deep ? 1.4 : 2.3) : sub == 2 ? (deep ? 1.4 : 1.7) : 1.0;
+        const double rate = lanes * (ring >= 8 ? 1.0 : sub > 1 ? 0.8 : 0.7) * (pib_lds == 1 ? 1.0 : pib_lds == 2 ? 0.99 : plan.kind == 2 ? 0.85 : 0.7) *
+                            (G * Pseg * sub < kWave ? 0.65 : 1.0) * (ring == 16 ? 1.001 : 1.0);
+        const double score = rate / ((double)rounds * (1.0 + 0.05 * (double)(std::min<int64_t>(wgs, at_once) - 1)));
+        if (score > best_score) { best_score = score; best_wgs = wgs; best_at_once = (int)std::min<int64_t>(wgs, at_once); plan.G = G; plan.sub = sub; plan.ring = ring; plan.lds = o; }
       }
     }
   }
   // feeders (measured): four when a single workgroup has the CU to itself and every placement byte comes from L2
   // (config 5: 3.6 % over two), three with one or two workgroups per CU (config 3: 13 % over two, config 4: 2.4 %),
   // two with more (config 2: three cost 16 %), one when the CU is full of wavefronts anyway
+  // (a large problem: by the workgroups per CU that the batch has; 256 candidates of the MoE graph, one per CU: three 186 us, two 194)
+  const bool large = plan.kind <= 1 && N >= 2048;
   plan.feeders = force_feeders ? force_feeders
                : (best_wgs == 1 && plan.lds.pib_mode == 0 && plan.ring == 16) ? 4
-               : best_wgs <= 2 ? 3
+               : (large ? best_at_once : best_wgs) <= 2 ? 3
                : (best_wgs * 4 <= 24 ? 2 : 1);
-  auto built = [&](int feeders) {
-    return win_log2    ? (plan.cell32 ? ring_kernel_pick<5>(plan.ring, feeders, (int)plan.lds.pib_mode, plan.kind) != nullptr
-                                      : ring_kernel_pick<4>(plan.ring, feeders, (int)plan.lds.pib_mode, plan.kind) != nullptr)
-         : wide        ? ring_kernel_pick<3>(plan.ring, feeders, (int)plan.lds.pib_mode, plan.kind) != nullptr
-         : plan.cell32 ? ring_kernel_pick<2>(plan.ring, feeders, (int)plan.lds.pib_mode, plan.kind) != nullptr
-                       : ring_kernel_pick<0>(plan.ring, feeders, (int)plan.lds.pib_mode, plan.kind) != nullptr;
-  };
+  auto built = [&](int feeders) { return ring_kernel_with(plan.lds, plan.G, plan.sub, plan.ring, feeders, plan.kind) != nullptr; };
+  if (!force_feeders && plan.sub > 1 && plan.kind == 3 && !plan.cell32 && !built(plan.feeders)) plan.feeders = 2;
   // the one-predecessor kind exists for the 16-bit cells and the common shapes: else the two-predecessor kind does
   if (plan.kind == 3 && (win_log2 || wide || plan.cell32 || !built(plan.feeders))) plan.kind = 2;
   if (!force_feeders && !built(plan.feeders)) plan.feeders = 2;
@@ -624,106 +647,39 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
     plan.ingest_block = ingest_wgs == 1 ? 1024 : ingest_wgs == 2 ? 512 : 256;
   }
   // workgroup size: the wavefronts with a role, plus helpers for the ingest phase when the LDS leaves the CU
-  // nearly empty of wavefronts (one workgroup per CU: 1024 threads, two: 512)
+  // or the batch leaves the CU nearly empty of wavefronts (one workgroup per CU: 1024 threads, two: 512; 256 candidates of the MoE graph, one per
+  // CU: 1024 threads 180 us, 320 190; but four workgroups per CU of 384 threads instead of 256: 1311 us, 975)
   plan.block = ring_threads(plan.feeders);
   const int force_block = sh ? sh->block_threads : 0;
   if (force_block >= plan.block && force_block <= 1024 && force_block % kWave == 0) plan.block = force_block;
-  else if (best_wgs == 1) plan.block = 1024;
+  else if (best_wgs == 1 || (large && best_at_once == 1)) plan.block = 1024;
   else if (best_wgs == 2) plan.block = std::max(plan.block, 512);
   plan.ok = best_score >= 0;
   return plan;
 }
 
-using RingKernel = void (*)(RingParams);
-// The instantiated shapes: placement bytes in LDS with 4 or 8 ring slots, as nibbles in LDS likewise, in L2 with 8, 16
-// or 32; one to four feeders where that was ever measured useful; each in the three kinds of the kernel.
-#define DAGSCHED_RING_CASES(PIB, RING, F)                                                         \
-  case 0 * 10000 + PIB * 1000 + RING * 10 + F: return relax_ring_kernel<RING, F, HALF, PIB, 0>;    \
-  case 1 * 10000 + PIB * 1000 + RING * 10 + F: return relax_ring_kernel<RING, F, HALF, PIB, 1>;    \
-  case 2 * 10000 + PIB * 1000 + RING * 10 + F: return relax_ring_kernel<RING, F, HALF, PIB, 2>;
-// the one-predecessor kind: 16-bit cells only
-#define DAGSCHED_RING_CASES_ONE(PIB, RING, F)                                                     \
-  case 3 * 10000 + PIB * 1000 + RING * 10 + F: return relax_ring_kernel<RING, F, HALF, PIB, 3>;
-// window mode: the relaxation launch (PHASE = 2) in the shapes that large layered problems get, and the ingest launch
-#define DAGSCHED_WIN_CASES(RING, F)                                                               \
-  case 0 * 10000 + RING * 10 + F: return relax_ring_kernel<RING, F, 4, 0, 0, 2>;                  \
-  case 1 * 10000 + RING * 10 + F: return relax_ring_kernel<RING, F, 4, 0, 1, 2>;                  \
-  case 2 * 10000 + RING * 10 + F: return relax_ring_kernel<RING, F, 4, 0, 2, 2>;
-#define DAGSCHED_WIN32_CASES(RING, F)                                                             \
-  case 0 * 10000 + RING * 10 + F: return relax_ring_kernel<RING, F, 5, 0, 0, 2>;                  \
-  case 1 * 10000 + RING * 10 + F: return relax_ring_kernel<RING, F, 5, 0, 1, 2>;                  \
-  case 2 * 10000 + RING * 10 + F: return relax_ring_kernel<RING, F, 5, 0, 2, 2>;
-RingKernel ring_ingest_kernel(int kind) {
-  return kind == 0 ? relax_ring_kernel<8, 2, 4, 0, 0, 1> : kind == 1 ? relax_ring_kernel<8, 2, 4, 0, 1, 1> : relax_ring_kernel<8, 2, 4, 0, 2, 1>;
-}
-template <int HALF>
-RingKernel ring_kernel_pick(int ring, int feeders, int pib_lds, int kind) {
-  if constexpr (HALF == 5) {                                    // window mode with 32-bit end times: fewer shapes
-    if (pib_lds != 0) return nullptr;
-    switch (kind * 10000 + ring * 10 + feeders) {
-      DAGSCHED_WIN32_CASES(8, 2) DAGSCHED_WIN32_CASES(16, 2) DAGSCHED_WIN32_CASES(16, 3)
-      default: return nullptr;
-    }
-  } else if constexpr (HALF == 4) {
-    if (pib_lds != 0) return nullptr;
-    switch (kind * 10000 + ring * 10 + feeders) {
-      DAGSCHED_WIN_CASES(8, 1) DAGSCHED_WIN_CASES(8, 2) DAGSCHED_WIN_CASES(8, 3)
-      DAGSCHED_WIN_CASES(16, 2) DAGSCHED_WIN_CASES(16, 3) DAGSCHED_WIN_CASES(16, 4)
-      default: return nullptr;
-    }
-  } else if constexpr (HALF == 2) {                             // 32-bit end times: the shapes that large problems get
-    switch (kind * 10000 + pib_lds * 1000 + ring * 10 + feeders) {
-      DAGSCHED_RING_CASES(1, 8, 1) DAGSCHED_RING_CASES(1, 8, 2) DAGSCHED_RING_CASES(1, 8, 3)
-      DAGSCHED_RING_CASES(2, 8, 2) DAGSCHED_RING_CASES(2, 8, 3)
-      DAGSCHED_RING_CASES(0, 8, 2) DAGSCHED_RING_CASES(0, 16, 2) DAGSCHED_RING_CASES(0, 16, 3) DAGSCHED_RING_CASES(0, 16, 4)
-      default: return nullptr;
-    }
-  } else if constexpr (HALF == 3) {                      // ... and wide ops (no nibbles)
-    switch (kind * 10000 + pib_lds * 1000 + ring * 10 + feeders) {
-      DAGSCHED_RING_CASES(1, 8, 1) DAGSCHED_RING_CASES(1, 8, 2) DAGSCHED_RING_CASES(1, 8, 3)
-      DAGSCHED_RING_CASES(0, 8, 2) DAGSCHED_RING_CASES(0, 16, 2) DAGSCHED_RING_CASES(0, 16, 3) DAGSCHED_RING_CASES(0, 16, 4)
-      default: return nullptr;
-    }
-  } else {
-  switch (kind * 10000 + pib_lds * 1000 + ring * 10 + feeders) {
-    DAGSCHED_RING_CASES(1, 4, 1) DAGSCHED_RING_CASES(1, 4, 2)
-    DAGSCHED_RING_CASES(1, 8, 1) DAGSCHED_RING_CASES(1, 8, 2) DAGSCHED_RING_CASES(1, 8, 3) DAGSCHED_RING_CASES(1, 8, 4)
-    DAGSCHED_RING_CASES(2, 4, 1) DAGSCHED_RING_CASES(2, 4, 2)
-    DAGSCHED_RING_CASES(2, 8, 1) DAGSCHED_RING_CASES(2, 8, 2) DAGSCHED_RING_CASES(2, 8, 3)
-    DAGSCHED_RING_CASES(0, 8, 1) DAGSCHED_RING_CASES(0, 8, 2) DAGSCHED_RING_CASES(0, 8, 3)
-    DAGSCHED_RING_CASES(0, 16, 1) DAGSCHED_RING_CASES(0, 16, 2) DAGSCHED_RING_CASES(0, 16, 3) DAGSCHED_RING_CASES(0, 16, 4)
-    DAGSCHED_RING_CASES(0, 32, 1) DAGSCHED_RING_CASES(0, 32, 2) DAGSCHED_RING_CASES(0, 32, 3)
-    DAGSCHED_RING_CASES_ONE(1, 4, 1) DAGSCHED_RING_CASES_ONE(1, 4, 2)
-    DAGSCHED_RING_CASES_ONE(1, 8, 1) DAGSCHED_RING_CASES_ONE(1, 8, 2) DAGSCHED_RING_CASES_ONE(1, 8, 3)
-    DAGSCHED_RING_CASES_ONE(2, 8, 1) DAGSCHED_RING_CASES_ONE(2, 8, 2) DAGSCHED_RING_CASES_ONE(2, 8, 3)
-    DAGSCHED_RING_CASES_ONE(0, 8, 2) DAGSCHED_RING_CASES_ONE(0, 8, 3) DAGSCHED_RING_CASES_ONE(0, 16, 2) DAGSCHED_RING_CASES_ONE(0, 16, 3)
-    default: return nullptr;
-  }
-  }
-}
-#undef DAGSCHED_RING_CASES
-#undef DAGSCHED_RING_CASES_ONE
-RingKernel ring_kernel_for(const dagsched *h) {
+RingKernel ring_kernel_with(const LdsLayout &lds, int G, int sub, int ring, int feeders, int kind) {
   // byte addresses when the workgroup's end-time arrays fit 64 KB, half addresses otherwise
-  const bool half = (uint64_t)h->ring_G * h->lds.s_stride > 65536u;
-  const int pib_lds = (int)h->lds.pib_mode;
-  if (h->lds.win_log2)
-    return h->lds.cell_bytes == 4 ? ring_kernel_pick<5>(h->ring_slots, h->ring_feeders, pib_lds, h->ring_kind)
-                                  : ring_kernel_pick<4>(h->ring_slots, h->ring_feeders, pib_lds, h->ring_kind);
-  if (h->lds.wide) return ring_kernel_pick<3>(h->ring_slots, h->ring_feeders, pib_lds, h->ring_kind);
-  if (h->lds.cell_bytes == 4) return ring_kernel_pick<2>(h->ring_slots, h->ring_feeders, pib_lds, h->ring_kind);
-  return half ? ring_kernel_pick<1>(h->ring_slots, h->ring_feeders, pib_lds, h->ring_kind)
-              : ring_kernel_pick<0>(h->ring_slots, h->ring_feeders, pib_lds, h->ring_kind);
+  const bool half = (uint64_t)G * lds.s_stride > 65536u;
+  const int pib_lds = (int)lds.pib_mode;
+  if (sub > 1) {
+    if (lds.win_log2 || lds.wide || (half && lds.cell_bytes != 4)) return nullptr;
+    return lds.cell_bytes == 4 ? (sub == 2 ? ring_kernel_pick<2, 2>(ring, feeders, pib_lds, kind) : ring_kernel_pick<2, 4>(ring, feeders, pib_lds, kind))
+                               : (sub == 2 ? ring_kernel_pick<0, 2>(ring, feeders, pib_lds, kind) : ring_kernel_pick<0, 4>(ring, feeders, pib_lds, kind));
+  }
+  if (lds.win_log2) return lds.cell_bytes == 4 ? ring_kernel_pick<5, 1>(ring, feeders, pib_lds, kind) : ring_kernel_pick<4, 1>(ring, feeders, pib_lds, kind);
+  if (lds.wide) return ring_kernel_pick<3, 1>(ring, feeders, pib_lds, kind);
+  if (lds.cell_bytes == 4) return ring_kernel_pick<2, 1>(ring, feeders, pib_lds, kind);
+  return half ? ring_kernel_pick<1, 1>(ring, feeders, pib_lds, kind) : ring_kernel_pick<0, 1>(ring, feeders, pib_lds, kind);
 }
-
+RingKernel ring_kernel_for(const dagsched *h) {
+  return ring_kernel_with(h->lds, h->ring_G, h->ring_sub, h->ring_slots, h->ring_feeders, h->ring_kind);
+}
 // the kernel of the second run over the candidates the first one left (32-bit cells, or 16-bit ones behind a window)
 RingKernel fallback_kernel(const dagsched *h) {
-  const int pib_lds = (int)h->fb_lds.pib_mode;
-  if (h->fb_lds.cell_bytes == 4) return ring_kernel_pick<2>(h->fb_slots, h->fb_feeders, pib_lds, h->fb_kind);
-  const bool half = (uint64_t)h->fb_G * h->fb_lds.s_stride > 65536u;
-  return half ? ring_kernel_pick<1>(h->fb_slots, h->fb_feeders, pib_lds, h->fb_kind)
-              : ring_kernel_pick<0>(h->fb_slots, h->fb_feeders, pib_lds, h->fb_kind);
+  return ring_kernel_with(h->fb_lds, h->fb_G, h->fb_sub, h->fb_slots, h->fb_feeders, h->fb_kind);
 }
+
 
 int static_threads(int relaxers) {                       // relaxers, accountants and as many wavefronts again for ingest
   return std::min(1024, 4 * relaxers * kWave);
@@ -1244,7 +1200,6 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   h->max_cand = desc->max_candidates; h->layout = desc->layout; h->device = desc->hip_device;
   h->sum_dur = sum_dur;
   h->row_stride = ((int64_t)h->N + 31) / 32 * 32;     // 128-byte rows: no cache line shared by two candidates
-  h->list_stride = ((int64_t)h->N + 63) / 64 * 64;
   h->pib_stride = ((int64_t)h->N + 1 + 127) / 128 * 128;
   const size_t maxc = (size_t)h->max_cand;
 
@@ -1330,10 +1285,11 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   if (ok && plan.ok) {
     h->variant = !plan.exact ? kVariantRingOptimistic : plan.cell32 ? kVariantRing32 : kVariantRingExact;   // (window mode is never exact)
     h->ring_exact = plan.exact;
-    h->ring_G = plan.G; h->ring_slots = plan.ring; h->ring_feeders = plan.feeders; h->ring_kind = plan.kind; h->ring_block = plan.block; h->lds = plan.lds; h->time_scale = plan.scale;
+    h->ring_G = plan.G; h->ring_sub = plan.sub; h->ring_slots = plan.ring; h->ring_feeders = plan.feeders; h->ring_kind = plan.kind; h->ring_block = plan.block; h->lds = plan.lds; h->time_scale = plan.scale;
     h->rec_plane = plan.rec_plane; h->id_bits = plan.id_bits;
     const int64_t cap = ((int64_t)h->N + h->E + 1024) * 64;
     h->spin_cap = (uint32_t)std::min<int64_t>(cap, 0x7FFFFFFF);
+    h->list_stride = (plan.total_parts + 63) / 64 * 64;   // an entry per op part
     ok = dev_alloc(&h->ws_list16, maxc * (size_t)h->list_stride) &&
          (plan.lds.pib_mode != 0 || dev_alloc(&h->ws_pib, maxc * (size_t)h->pib_stride));   // only read when the placement is not in LDS
     if (ok && !plan.exact) ok = dev_alloc(&h->d_fb_count, 2) && dev_alloc(&h->d_fb_list, 2 * maxc);   // (two lists)
@@ -1349,9 +1305,9 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       // (same records, part counts and delays: both plans divide by the same common factor and drop the same edges)
       if (fp.ok && fp.exact && fp.cell32 && !fp.lds.wide && fp.scale == plan.scale && fp.rec_plane == plan.rec_plane &&
           fp.id_bits == plan.id_bits && fp.rec.size() == plan.rec.size()) {
-        h->fb_G = fp.G; h->fb_slots = fp.ring; h->fb_feeders = fp.feeders; h->fb_block = fp.block; h->fb_lds = fp.lds; h->fb_kind = fp.kind;
+        h->fb_G = fp.G; h->fb_sub = fp.sub; h->fb_slots = fp.ring; h->fb_feeders = fp.feeders; h->fb_block = fp.block; h->fb_lds = fp.lds; h->fb_kind = fp.kind;
         if (fp.lds.pib_mode == 0 && !h->ws_pib) ok = dev_alloc(&h->ws_pib, maxc * (size_t)h->pib_stride);
-        const void *fk = (const void *)ring_kernel_pick<2>(fp.ring, fp.feeders, (int)fp.lds.pib_mode, fp.kind);
+        const void *fk = (const void *)fallback_kernel(h);
         if (!fk) h->fb_G = 0;
         if (ok && fp.lds.total > 48 * 1024) ok = allow_large_lds(fk, h->device, (int)fp.lds.total);
       }
@@ -1362,7 +1318,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
         const RingPlan gp = plan_ring(&fd, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
         if (gp.ok && !gp.cell32 && !gp.win_log2 && !gp.lds.wide && gp.scale == plan.scale && gp.rec_plane == plan.rec_plane &&
             gp.id_bits == plan.id_bits && gp.rec.size() == plan.rec.size()) {
-          h->fb_G = gp.G; h->fb_slots = gp.ring; h->fb_feeders = gp.feeders; h->fb_block = gp.block; h->fb_lds = gp.lds; h->fb_kind = gp.kind;
+          h->fb_G = gp.G; h->fb_sub = gp.sub; h->fb_slots = gp.ring; h->fb_feeders = gp.feeders; h->fb_block = gp.block; h->fb_lds = gp.lds; h->fb_kind = gp.kind;
           h->fb_optimistic = !gp.exact;
           if (gp.lds.pib_mode == 0 && !h->ws_pib) ok = dev_alloc(&h->ws_pib, maxc * (size_t)h->pib_stride);
           const void *gk = (const void *)fallback_kernel(h);
@@ -1817,7 +1773,7 @@ int dagsched_plan(const dagsched_desc_t *caller_desc, int32_t lds_bytes, int32_t
   if (pplan.stream) h.pl_stream = pplan.s;
   if (plan.ok) {
     h.variant = !plan.exact ? kVariantRingOptimistic : plan.cell32 ? kVariantRing32 : kVariantRingExact;
-    h.ring_G = plan.G; h.ring_slots = plan.ring; h.ring_feeders = plan.feeders; h.ring_kind = plan.kind; h.ring_block = plan.block;
+    h.ring_G = plan.G; h.ring_sub = plan.sub; h.ring_slots = plan.ring; h.ring_feeders = plan.feeders; h.ring_kind = plan.kind; h.ring_block = plan.block;
     h.lds = plan.lds; h.time_scale = plan.scale;
   }
   if (pplan.ok && !pplan.stream) { h.variant = kVariantStatic; h.pl = pplan.p; h.st_preds = 1; }

@@ -65,7 +65,7 @@ constexpr int ring_threads(int feeders) { return (2 + feeders) * kWave; }   // r
 //   x = u0 | u1 << 16, y = u2 | u3 << 16, z = dur (30 bits) | first_part << 30 | has_more << 31, w = v << 16
 struct LdsLayout {
   uint32_t s_stride, pi_stride;                       // bytes per candidate; the state array starts at 0
-  uint32_t o_pi, o_ring, o_scr, o_total, o_peak, o_cnt, o_off, o_flag, o_abort, o_over, o_comm, total;
+  uint32_t o_pi, o_ring, o_scr, o_total, o_cnt, o_off, o_flag, o_abort, o_over, o_comm, total;
   uint32_t pib_mode;                                  // where the placement bytes are: 0 L2 workspace, 1 LDS, 2 LDS as nibbles
   uint32_t cell_bytes;                                // 2: 16-bit end times, 4: 32-bit
   uint32_t wide;                                      // 1: wide ops (machines instead of delays, durations below 256 * 65535)
@@ -76,9 +76,9 @@ struct RingParams {
   int32_t N, P, Pseg, log_pseg, G, C;
   int32_t optimistic;                  // 1: candidates stopped by the 16-bit range go to fb_list, 0: a deadlock is always a cycle
   int64_t list_stride;                 // uint16 elements per candidate in ws_list
-  const uint4 *rec;                    // [parts][rec_plane] shared operator records (times divided by time_scale)
+  const uint4 *rec;                    // shared operator records (times divided by time_scale)
   int32_t rec_plane;                   // records per part plane (>= N)
-  int32_t id_bits;                     // order-list entry = node | (parts - 1) << id_bits
+  int32_t id_bits;                     // order-list entry = node | part << id_bits
   const uint8_t *nparts;               // [N] parts per node, or NULL when every node has one part
   const int32_t *comm;                 // [P*P] channel delays divided by time_scale (all <= 255)
   const int64_t *mem_delta;            // [N]
@@ -87,7 +87,7 @@ struct RingParams {
   int64_t sum_dur;                     // in original units
   int32_t time_scale;                  // gcd of every duration and delay
   const int32_t *placement, *rank;     // [C][N]
-  uint16_t *ws_list;                   // [C][list_stride]
+  uint16_t *ws_list;                   // [C][list_stride] the machines' op parts in the order they run
   uint8_t *ws_pib;                     // [C][pib_stride] placement as one byte per node; entry N = P (the dummy node's machine)
   int64_t pib_stride;
   int32_t *fb_count, *fb_list;         // candidates left to the fallback (the 32-bit form of this kernel, or the general kernel)
@@ -128,7 +128,18 @@ struct RingParams {
 // and the relaxation (PHASE = 2) runs with several workgroups per CU.  PHASE = 0 is the fused kernel.
 // HALF = 5 is the window mode for end times that need 32 bits: a cell is 64 bits, name above and end time below,
 // written with a 64-bit LDS maximum; names, ops and the ingest launch are the same.
-template <int RING, int FEEDERS, int HALF, int PIBL, int KIND = 0, int PHASE = 0>
+//
+// SUB: lanes per machine, 1, 2 or 4.  A lane runs at most one op a trip, and with one lane per machine that is one op of
+// the machine a trip however many of them are ready.  With SUB lanes the machine's stream is dealt out to them in
+// turn (op i to lane i mod SUB, each with its own ring), they hold SUB consecutive ops, and the end of one goes on to
+// the next through a DPP move within the trip: x = max(predecessors, machine free) + duration, where "machine free"
+// is what the lane before has just worked out.  The lane whose op is the next in the order (the head) has a finite
+// x_acc, the others one of kNotDone or more; whatever waits for an op that has not run is above kNotDone as well, so
+// the test whether an op runs is the same in every lane.  MoE graph: 2040 trips of 240 cycles with one lane (of two candidates in a
+// wavefront), 1340 of 262 with two; random graph of 3001 operations on 11 machines: 510 of 290, 150 of 375 with four.  Whole evaluations, us, before and now:
+// MoE graph, 256 candidates 243, 180; 4096 1038, 977; random graph, 2051 candidates in the candidate-minor layout 238, 131; 1F1B pipeline of 64 operations, 1024 candidates
+// 13.6, 10.1.
+template <int RING, int FEEDERS, int HALF, int PIBL, int KIND = 0, int PHASE = 0, int SUB = 1>
 __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
   // ring_threads(FEEDERS) threads have a role while the schedule is relaxed; the host may launch more (a
   // multiple of 64): the extra wavefronts only help with ingest and then wait at the final barrier.
@@ -141,6 +152,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
   static_assert(KIND != 3 || HALF <= 1, "the one-predecessor kind is built for the 16-bit cells only");
   static_assert(HALF >= 0 && HALF <= 5, "byte, half or quarter addresses; 3: quarter addresses and delays looked up by the relaxer; 4, 5: window");
   static_assert(PHASE >= 0 && PHASE <= 2, "fused, ingest only, relaxation only");
+  static_assert(SUB == 1 || ((SUB == 2 || SUB == 4) && HALF != 3 && HALF < 4), "several lanes per machine: cells of their own, plain ops");
   constexpr bool kWin = HALF == 4 || HALF == 5;             // a window of named cells per candidate
   constexpr bool kWin32 = HALF == 5;                        // ... of 64 bits: name above, 32-bit end time below
   static_assert(!kWin || PIBL == 0, "window mode keeps the placement bytes in the workspace row");
@@ -153,11 +165,13 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
   constexpr int kNodeShift = (kCell32 || kWin) ? 0 : 1 - HALF;   // node -> offset of its cell in the units of the 16-bit addresses
   constexpr int PR = KIND == 3 ? 1 : KIND == 2 ? 2 : 4;     // DAG predecessors per op
   constexpr uint32_t kOrigin = PIBL == 2 ? 255u : 0u;
+  constexpr bool kStations = RING == 4 && SUB > 1 && KIND == 0 && PIBL == 1;   // (see the feeders)
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lane = tid & 63;
   const int N = p.N, P = p.P, Pseg = p.Pseg, G = p.G;
-  const int L = G * Pseg;                                   // lanes in use per wavefront
+  const int M = G * Pseg;                                   // machines of the workgroup's candidates
+  const int L = M * SUB;                                    // lanes in use per wavefront
   const int64_t c0 = (int64_t)blockIdx.x * G;
   // (a launch over a list of candidates is sized for the longest list possible: the workgroups beyond its end leave)
   const int64_t n_todo = p.cand_list ? (int64_t)*p.cand_count : (int64_t)p.C;
@@ -168,13 +182,14 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
   lds_byte_t *const ldsb = (lds_byte_t *)lds;
 
   uint32_t *ringw = (uint32_t *)(lds + o.o_ring);
-  uint32_t *totalw = (uint32_t *)(lds + o.o_total);        // [64] ops (operation parts) in the lane's stream
-  int64_t *peakw = (int64_t *)(lds + o.o_peak);            // [64]
-  int32_t *cntw = (int32_t *)(lds + o.o_cnt);              // [64] operations per (candidate, machine)
-  int32_t *offw = (int32_t *)(lds + o.o_off);              // [64] start of the machine inside the list
-  int32_t *flagw = (int32_t *)(lds + o.o_flag);            // [64] (G used)
-  int32_t *abortw = (int32_t *)(lds + o.o_abort);          // [64] (G used) 0, 1 = stopped by the 16-bit range (or internal), 2 = cycle
-  // [64] (G used) 1 = some machine of the candidate is over its memory limit.  Kept apart from flagw, which every
+  uint32_t *totalw = (uint32_t *)(lds + o.o_total);        // [M] ops (operation parts) in the machine's stream
+  int64_t *peakw = (int64_t *)(lds + o.o_ring);            // [M] over the ring, when that is done with
+  int32_t *cntw = (int32_t *)(lds + o.o_cnt);              // [M] operations per (candidate, machine)
+  uint32_t *offw = (uint32_t *)(lds + o.o_off);            // [M] start of the machine inside the list | its operations << 16 while
+                                                           // the list is built
+  int32_t *flagw = (int32_t *)(lds + o.o_flag);            // [G]
+  int32_t *abortw = (int32_t *)(lds + o.o_abort);          // [G] 0, 1 = stopped by the 16-bit range (or internal), 2 = cycle
+  // [G] 1 = some machine of the candidate is over its memory limit.  Kept apart from flagw, which every
   // wavefront reads when it takes up its role: the accountant finds this out while the others are already relaxing.
   uint8_t *overb = lds + o.o_over;
   uint8_t *commb = (uint8_t *)(lds + o.o_comm);            // [(P+1)][Pseg], diagonal and dummy row zero
@@ -188,11 +203,35 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
     return v == (uint32_t)p.N ? win_dummy : v + 3u * __umulhi(v, p.win_magic) + 1u;
   };
   // ---------------------------------------------------------------- ingest (all wavefronts)
-  if (tid < kWave) {
-    if (PHASE != 2) { cntw[tid] = 0; totalw[tid] = 0; flagw[tid] = 0; }
-    else { cntw[tid] = meta[tid]; offw[tid] = meta[kWave + tid]; totalw[tid] = (uint32_t)meta[2 * kWave + tid]; flagw[tid] = meta[3 * kWave + tid]; }
-    abortw[tid] = 0; peakw[tid] = 0; overb[tid] = 0;
+  // The candidates of the workgroup are ingested side by side, a team of kThreads / G consecutive threads
+  // each, so that small problems do not pay one round of load latency per candidate.
+  const int tpc = kThreads / G;
+  const int team = tid / tpc, tt = tid - team * tpc;        // this thread's team and its place in it
+  const bool mine = team < ng;
+  // Rows are read in 16-byte loads, kIn of them per thread on their way while the kIn before are looked at: the first of the
+  // placement row while the LDS is prepared, the first of the rank row while the machines' operations are counted.
+  constexpr int kIn = 4;
+  const int32_t *const pl = PHASE == 2 ? nullptr : p.placement + cid(mine ? team : 0) * N;
+  const int32_t *const rk = PHASE == 2 ? nullptr : p.rank + cid(mine ? team : 0) * N;
+  const bool vec_ok = PHASE != 2 && mine && ((N & 3) == 0) && ((((uintptr_t)p.placement) | ((uintptr_t)p.rank)) & 15) == 0;
+  const int nq = N >> 2;
+  const uint32_t *const np4 = KIND == 0 ? (const uint32_t *)p.nparts : nullptr;   // four part counts per load (N % 4 == 0 where it is read)
+  int4 row[kIn];
+  uint32_t row_np[kIn];
+  auto request = [&](const int32_t *from, int q0, bool ranks) {
+#pragma unroll
+    for (int u = 0; u < kIn; ++u) {
+      const int q = min(q0 + u * tpc, nq - 1);
+      row[u] = ((const int4 *)from)[q];
+      row_np[u] = ranks && np4 ? np4[q] - 0x01010101u : 0u;   // every count is at least 1: no borrow between bytes
+    }
+  };
+  if (vec_ok) request(pl, tt, false);
+  if (tid < M) {
+    if (PHASE != 2) { cntw[tid] = 0; totalw[tid] = 0; }
+    else { cntw[tid] = meta[tid]; offw[tid] = (uint32_t)meta[kWave + tid]; totalw[tid] = (uint32_t)meta[2 * kWave + tid]; }
   }
+  if (tid < G) { flagw[tid] = PHASE == 2 ? meta[3 * kWave + tid] : 0; abortw[tid] = 0; overb[tid] = 0; }
   if (PHASE != 1)
   for (int i = tid; i < RING * kWave; i += kThreads) {     // every slot free, as if ops -RING .. -1 had been taken
     // (a free slot is copied and looked at like an op: some cell of the workgroup, no delay)
@@ -213,55 +252,38 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
       commb[i] = (a < P && b < P && a != b) ? (uint8_t)p.comm[a * P + b] : (uint8_t)0;
     }
   }
-  // The candidates of the workgroup are ingested side by side, a team of kThreads / G consecutive threads
-  // each, so that small problems do not pay one round of load latency per candidate.
-  const int n_teams = G;
-  const int tpc = kThreads / n_teams;
-  const int team = tid / tpc, tt = tid - team * tpc;        // this thread's team and its place in it
   if (PHASE != 2) {
   // The order lists are first built in LDS, over the (not yet used) end-time arrays: every entry starts as
   // "unwritten" (0xFFFF, which no list entry equals: the host checks that)
-  for (int gg = team; gg < ng; gg += n_teams) {
-    uint32_t *lw = (uint32_t *)(lds + gg * o.s_stride);
-    for (int i = tt; i < (N + 1) / 2; i += tpc) lw[i] = 0xFFFFFFFFu;
-  }
+  uint16_t *const lds_list = (uint16_t *)(lds + team * o.s_stride);
+  uint8_t *const pib = PIBL ? lds + o.o_pi + team * o.pi_stride : p.ws_pib + cid(mine ? team : 0) * p.pib_stride;
+  if (mine)
+    for (int i = tt; i < (N + 1) / 2; i += tpc) ((uint32_t *)lds_list)[i] = 0xFFFFFFFFu;
   __syncthreads();
 
-  // 16-byte loads a thread keeps in flight per row pass (measured: eight instead of four 5 % on config 2, 2 % on
-  // config 5; with the general kind's register needs 2 % slower on config 4)
-  constexpr int kIn = KIND == 0 ? 4 : 8;
-  const bool vec_ok = ((N & 3) == 0) && ((((uintptr_t)p.placement) | ((uintptr_t)p.rank)) & 15) == 0;
-  const int nq = N >> 2;
-
   // placement in range (eq. (6)), operations per machine
-  for (int gg = team; gg < ng; gg += n_teams) {
-    const int32_t *pl = p.placement + cid(gg) * N;
-    uint8_t *pib = PIBL ? lds + o.o_pi + gg * o.pi_stride : p.ws_pib + cid(gg) * p.pib_stride;
-    int32_t *cnt_g = cntw + gg * Pseg;
+  if (mine) {
+    int32_t *const cnt_g = cntw + team * Pseg;
+    bool bad = false;
     if (PIBL == 2) { if (tt == 0 && !(N & 1)) pib[N >> 1] = 0; }   // the dummy's nibble: any machine will do
     else if (tt == 0) pib[N] = (uint8_t)P;                  // the dummy node sits on a dummy machine whose delays are all zero
     if (vec_ok) {
-      const int4 *pl4 = (const int4 *)pl;
-      uint32_t *piw = (uint32_t *)pib;
-      uint16_t *pih = (uint16_t *)pib;
       for (int q0 = tt; q0 < nq; q0 += kIn * tpc) {
         int4 a[kIn];
 #pragma unroll
-        for (int u = 0; u < kIn; ++u) {
-          const int q = q0 + u * tpc;
-          a[u] = (q < nq) ? pl4[q] : make_int4(0, 0, 0, 0);
-        }
+        for (int u = 0; u < kIn; ++u) a[u] = row[u];
+        const bool more = q0 + kIn * tpc < nq;
+        request(more ? pl : rk, more ? q0 + kIn * tpc : tt, !more);
 #pragma unroll
         for (int u = 0; u < kIn; ++u) {
           const int q = q0 + u * tpc;
           if (q < nq) {
             const uint32_t hi = (uint32_t)a[u].x | (uint32_t)a[u].y | (uint32_t)a[u].z | (uint32_t)a[u].w;
-            const bool bad = hi >= 64u || a[u].x >= P || a[u].y >= P || a[u].z >= P || a[u].w >= P;
-            if (bad) {
-              atomicOr(&flagw[gg], kBitBadPlacement);
+            if (hi >= 64u || a[u].x >= P || a[u].y >= P || a[u].z >= P || a[u].w >= P) {
+              bad = true;
             } else {
-              if (PIBL == 2) pih[q] = (uint16_t)((uint32_t)a[u].x | ((uint32_t)a[u].y << 4) | ((uint32_t)a[u].z << 8) | ((uint32_t)a[u].w << 12));
-              else piw[q] = (uint32_t)a[u].x | ((uint32_t)a[u].y << 8) | ((uint32_t)a[u].z << 16) | ((uint32_t)a[u].w << 24);
+              if (PIBL == 2) ((uint16_t *)pib)[q] = (uint16_t)((uint32_t)a[u].x | ((uint32_t)a[u].y << 4) | ((uint32_t)a[u].z << 8) | ((uint32_t)a[u].w << 12));
+              else ((uint32_t *)pib)[q] = (uint32_t)a[u].x | ((uint32_t)a[u].y << 8) | ((uint32_t)a[u].z << 16) | ((uint32_t)a[u].w << 24);
               atomicAdd(&cnt_g[a[u].x], 1); atomicAdd(&cnt_g[a[u].y], 1);
               atomicAdd(&cnt_g[a[u].z], 1); atomicAdd(&cnt_g[a[u].w], 1);
             }
@@ -272,7 +294,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
       for (int h = tt; 2 * h < N; h += tpc) {               // two nodes per thread: one byte of nibbles (node N is the dummy)
         const int32_t pa = pl[2 * h], pb = (2 * h + 1 < N) ? pl[2 * h + 1] : 0;
         if ((uint32_t)pa >= (uint32_t)P || (uint32_t)pb >= (uint32_t)P) {
-          atomicOr(&flagw[gg], kBitBadPlacement);
+          bad = true;
         } else {
           pib[h] = (uint8_t)(pa | (pb << 4));
           atomicAdd(&cnt_g[pa], 1);
@@ -283,108 +305,161 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
       for (int v = tt; v < N; v += tpc) {
         const int32_t pi = pl[v];
         if ((uint32_t)pi >= (uint32_t)P) {
-          atomicOr(&flagw[gg], kBitBadPlacement);
+          bad = true;
         } else {
           pib[v] = (uint8_t)pi;
           atomicAdd(&cnt_g[pi], 1);
         }
       }
     }
+    if (bad) atomicOr(&flagw[team], kBitBadPlacement);
   }
   __syncthreads();
-  if (wave == 0) {                                          // exclusive prefix over the machines of each candidate
-    const int my = lane < L ? cntw[lane] : 0;
+  // exclusive prefix over the machines of each candidate
+  auto prefix = [&](int my) -> uint32_t {
     int incl = my;
     const int jj = lane & (Pseg - 1);
     for (int d = 1; d < Pseg; d <<= 1) {
       const int t = __shfl_up(incl, d, Pseg);
       if (jj >= d) incl += t;
     }
-    if (lane < L) offw[lane] = incl - my;
+    return (uint32_t)(incl - my);
+  };
+  if (wave == 0) {
+    const int my = lane < M ? cntw[lane] : 0;
+    const uint32_t start = prefix(my);
+    if (lane < M) offw[lane] = (start & 0xFFFFu) | ((uint32_t)my << 16);   // (fewer than 65536 operations)
   }
   __syncthreads();
   // dense ranks (eqs. (7)-(8)): every rank inside its machine's range and, after N writes into N slots,
   // no slot left unwritten <=> every (machine, rank) slot hit exactly once
-  for (int gg = team; gg < ng; gg += n_teams) {
-    if (flagw[gg] & kBitBadPlacement) continue;
-    const int32_t *rk = p.rank + cid(gg) * N;
-    const uint8_t *pib = PIBL ? lds + o.o_pi + gg * o.pi_stride
-                              : p.ws_pib + cid(gg) * p.pib_stride;   // written by this workgroup before the barrier above
-    uint16_t *lds_list = (uint16_t *)(lds + gg * o.s_stride);
-    const int32_t *cnt_g = cntw + gg * Pseg, *off_g = offw + gg * Pseg;
-    int32_t *flag_g = flagw + gg;
+  if (mine && !(flagw[team] & kBitBadPlacement)) {
+    const uint32_t *const off_g = offw + team * Pseg;
+    bool bad = false;
     // list entry: node | (parts - 1) << id_bits
-    uint32_t *extra_g = totalw + gg * Pseg;                 // parts beyond the first, per machine
-    auto place = [&](int v, int pi, int32_t r, uint32_t np1) {
-      if ((uint32_t)r >= (uint32_t)cnt_g[pi]) {
-        atomicOr(flag_g, kBitBadRank);
+    uint32_t *const extra_g = totalw + team * Pseg;         // parts beyond the first, per machine
+    auto place = [&](int v, int pi, uint32_t pair, int32_t r, uint32_t np1) {
+      if ((uint32_t)r >= (pair >> 16)) {
+        bad = true;
       } else {
-        lds_list[off_g[pi] + r] = (uint16_t)((uint32_t)v | (np1 << p.id_bits));
+        lds_list[(pair & 0xFFFFu) + (uint32_t)r] = (uint16_t)((uint32_t)v | (np1 << p.id_bits));
         if (KIND == 0 && np1) atomicAdd(&extra_g[pi], np1);
       }
     };
     if (vec_ok) {
-      const int4 *rk4 = (const int4 *)rk;
-      const uint32_t *piw = (const uint32_t *)pib;
-      const uint16_t *pih = (const uint16_t *)pib;
-      const uint32_t *np4 = (const uint32_t *)p.nparts;     // four part counts per load (N % 4 == 0 here)
       for (int q0 = tt; q0 < nq; q0 += kIn * tpc) {
         int4 a[kIn];
-        uint32_t npw[kIn];
+        uint32_t npw[kIn], pw[kIn];
 #pragma unroll
         for (int u = 0; u < kIn; ++u) {
-          const int q = q0 + u * tpc;
-          a[u] = (q < nq) ? rk4[q] : make_int4(0, 0, 0, 0);
-          npw[u] = (np4 && q < nq) ? np4[q] - 0x01010101u : 0u;   // every count is at least 1: no borrow between bytes
+          a[u] = row[u]; npw[u] = row_np[u];
+          const int q = min(q0 + u * tpc, nq - 1);
+          if (PIBL == 2) {                                  // four nibbles, spread to four bytes
+            const uint32_t h = ((const uint16_t *)pib)[q];
+            pw[u] = (h & 0xFu) | ((h & 0xF0u) << 4) | ((h & 0xF00u) << 8) | ((h & 0xF000u) << 12);
+          } else {
+            pw[u] = ((const uint32_t *)pib)[q];             // (in L2: written by this workgroup before the barrier above)
+          }
         }
+        if (q0 + kIn * tpc < nq) request(rk, q0 + kIn * tpc, true);
 #pragma unroll
         for (int u = 0; u < kIn; ++u) {
           const int q = q0 + u * tpc;
           if (q < nq) {
-            uint32_t pw;
-            if (PIBL == 2) {                                  // four nibbles, spread to four bytes
-              const uint32_t h = pih[q];
-              pw = (h & 0xFu) | ((h & 0xF0u) << 4) | ((h & 0xF00u) << 8) | ((h & 0xF000u) << 12);
-            } else {
-              pw = piw[q];
-            }
-            place(4 * q + 0, pw & 0xFF, a[u].x, npw[u] & 0xFF);
-            place(4 * q + 1, (pw >> 8) & 0xFF, a[u].y, (npw[u] >> 8) & 0xFF);
-            place(4 * q + 2, (pw >> 16) & 0xFF, a[u].z, (npw[u] >> 16) & 0xFF);
-            place(4 * q + 3, pw >> 24, a[u].w, npw[u] >> 24);
+            const uint32_t m[4] = {pw[u] & 0xFF, (pw[u] >> 8) & 0xFF, (pw[u] >> 16) & 0xFF, pw[u] >> 24};
+            const uint32_t pair[4] = {off_g[m[0]], off_g[m[1]], off_g[m[2]], off_g[m[3]]};
+            place(4 * q + 0, m[0], pair[0], a[u].x, npw[u] & 0xFF);
+            place(4 * q + 1, m[1], pair[1], a[u].y, (npw[u] >> 8) & 0xFF);
+            place(4 * q + 2, m[2], pair[2], a[u].z, (npw[u] >> 16) & 0xFF);
+            place(4 * q + 3, m[3], pair[3], a[u].w, npw[u] >> 24);
           }
         }
       }
     } else {
-      for (int v = tt; v < N; v += tpc)
-        place(v, PIBL == 2 ? (pib[v >> 1] >> ((v & 1) << 2)) & 0xF : pib[v], rk[v], p.nparts ? (uint32_t)p.nparts[v] - 1u : 0u);
+      for (int v = tt; v < N; v += tpc) {
+        const int m = PIBL == 2 ? (pib[v >> 1] >> ((v & 1) << 2)) & 0xF : pib[v];
+        place(v, m, off_g[m], rk[v], KIND == 0 && p.nparts ? (uint32_t)p.nparts[v] - 1u : 0u);
+      }
     }
+    if (bad) atomicOr(&flagw[team], kBitBadRank);
   }
   __syncthreads();
-  // order lists to HBM (coalesced), looking for unwritten slots on the way
-  for (int gg = team; gg < ng; gg += n_teams) {
-    if (flagw[gg] & kBitBadPlacement) continue;
-    const uint32_t *lw = (const uint32_t *)(lds + gg * o.s_stride);
-    uint32_t *gw = (uint32_t *)(p.ws_list + cid(gg) * p.list_stride);       // rows are 128-byte aligned
+  // Order lists to HBM, looking for unwritten slots on the way.  Feeders and accountant walk op parts, so an operation of
+  // several is several entries there: a feeder that stepped through the parts of an operation itself spent half of its
+  // instructions on that.
+  uint32_t *const row_off = (uint32_t *)(lds + o.o_scr);    // [M] start of the machine in that list (KIND 0)
+  if (KIND == 0) {
+    if (wave == 0) {
+      const uint32_t start = prefix(lane < M ? cntw[lane] + (int)totalw[lane] : 0);
+      if (lane < M) row_off[lane] = start;
+    }
+    __syncthreads();
+    // some consecutive machines to a wavefront, an operation to a lane; the parts in front of a lane's are counted with ballots
+    const int n_waves = kThreads >> 6, per_cand = max(1, min(Pseg, n_waves / G)), part_bits = 16 - p.id_bits;
+    const uint32_t part1 = 1u << p.id_bits;
+    for (int job = wave; job < ng * per_cand; job += n_waves) {
+      const int gg = job / per_cand, m0 = (job % per_cand) * Pseg / per_cand, m1 = (job % per_cand + 1) * Pseg / per_cand;
+      if (flagw[gg] & kBitBadPlacement) continue;
+      const int at = __builtin_amdgcn_readfirstlane((int)(offw[gg * Pseg + m0] & 0xFFFFu));
+      const int n = __builtin_amdgcn_readfirstlane(m1 < Pseg ? (int)(offw[gg * Pseg + m1] & 0xFFFFu) : N) - at;
+      const uint16_t *const src = (const uint16_t *)(lds + gg * o.s_stride) + at;
+      uint16_t *const dst = p.ws_list + cid(gg) * p.list_stride;
+      uint32_t to = (uint32_t)__builtin_amdgcn_readfirstlane((int)row_off[gg * Pseg + m0]);
+      uint64_t holes = 0;
+      constexpr int kAhead = 4;
+      for (int b0 = 0; b0 < n; b0 += kAhead * kWave) {
+        uint32_t w[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) w[u] = src[min(b0 + u * kWave + lane, n - 1)];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          const bool on = b0 + u * kWave + lane < n, hole = w[u] == 0xFFFFu;
+          holes |= __ballot(on && hole);
+          // (an unwritten slot, whose candidate is flagged, counts as one part: nothing goes beyond the row)
+          const uint32_t np1 = on && !hole ? w[u] >> p.id_bits : 0u;
+          uint32_t i = to + (uint32_t)lane;
+          to += kWave;
+          for (int k = 0; k < part_bits; ++k) {
+            const uint64_t m = __ballot((np1 >> k) & 1u);
+            i += __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u)) << k;
+            to += (uint32_t)__popcll(m) << k;
+          }
+          uint32_t v = w[u] & (part1 - 1u);
+          if (on) dst[i] = (uint16_t)v;
+          for (uint32_t part = 1; __ballot(np1 >= part) != 0; ++part) {
+            v += part1;
+            if (np1 >= part) dst[i + part] = (uint16_t)v;
+          }
+        }
+      }
+      if (holes && lane == 0) atomicOr(&flagw[gg], kBitBadRank);
+    }
+  } else if (mine && !(flagw[team] & kBitBadPlacement)) {
+    const uint32_t *const lw = (const uint32_t *)lds_list;
+    uint32_t *const gw = (uint32_t *)(p.ws_list + cid(team) * p.list_stride);   // rows are 128-byte aligned
     bool hole = false;
     for (int i = tt; i < (N + 1) / 2; i += tpc) {
       const uint32_t w = lw[i];
       hole |= (w & 0xFFFFu) == 0xFFFFu || (2 * i + 1 < N && (w >> 16) == 0xFFFFu);
       gw[i] = w;
     }
-    if (hole) atomicOr(&flagw[gg], kBitBadRank);
+    if (hole) atomicOr(&flagw[team], kBitBadRank);
   }
   __syncthreads();                                          // workgroup scope: the lists are read by this workgroup only
-  if (tid < kWave) totalw[tid] += (uint32_t)cntw[tid];      // ops per lane: its operations plus their further parts
+  if (tid < M) {
+    totalw[tid] += (uint32_t)cntw[tid];                     // ops per machine: its operations plus their further parts
+    offw[tid] = KIND == 0 ? row_off[tid] : offw[tid] & 0xFFFFu;
+  }
   if (PHASE == 1) {                                         // the relaxation is a launch of its own
-    if (tid < kWave) { meta[tid] = cntw[tid]; meta[kWave + tid] = offw[tid]; meta[2 * kWave + tid] = (int32_t)totalw[tid]; meta[3 * kWave + tid] = flagw[tid]; }
+    if (tid < M) { meta[tid] = cntw[tid]; meta[kWave + tid] = (int32_t)offw[tid]; meta[2 * kWave + tid] = (int32_t)totalw[tid]; }
+    if (tid < G) meta[3 * kWave + tid] = flagw[tid];
     return;
   }
   }
   // end-time state: every operation "not ended"; the dummy node N has ended at time 0 on a dummy
   // machine P whose delays are all zero; cell N+1 is a trash cell for parts that do not end an operation
-  for (int gg = team; gg < ng; gg += n_teams) {
-    uint32_t *sw = (uint32_t *)(lds + gg * o.s_stride);
+  if (mine) {
+    uint32_t *sw = (uint32_t *)(lds + team * o.s_stride);
     if (kWin) {                                             // no name anywhere, but the dummy's in its slot, ended at 0
       if (kWin32) {
         for (uint32_t i = (uint32_t)tt; i <= win_mask; i += (uint32_t)tpc) { sw[2 * i] = 0u; sw[2 * i + 1] = i == win_dummy ? win_dummy : 0u; }
@@ -404,7 +479,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
 
   // ---------------------------------------------------------------- roles
   const bool lane_on = lane < L;
-  const int ql = lane_on ? lane : 0;
+  const int ql = lane_on ? lane / SUB : 0, sub_lane = lane_on ? lane % SUB : 0;
   const int g = ql >> p.log_pseg, j = ql & (Pseg - 1);
   const bool cand_ok = lane_on && g < ng && flagw[g] == 0;
   const bool has_ops = cand_ok && j < P && cntw[ql] > 0;
@@ -414,15 +489,17 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
   auto win_addr = [&](uint32_t name) -> uint32_t { return sbase + ((name & win_mask) << (kWin32 ? 3 : 2)); };
 
   int32_t acc = 0;
+  int64_t peak = 0;                                         // (accountant)
   bool stalled = false;
 
   if (wave == 0) {
     // ------------------------------------------------------------ relaxer
     lds_byte_t *const ring_lane = ldsb + o.o_ring + (uint32_t)lane * 16u;   // ring layout: [slot][lane] of 16 bytes
     // the lane is through when it has taken this many ops (counted at ingest) and holds none: tm then equals this
-    const uint32_t tm_end = (totalw[lane] << 16) | kNotDone16;
+    const uint32_t tm_end = (((lane_on ? totalw[ql] : 0u) + (uint32_t)(SUB - 1 - sub_lane)) / SUB << 16) | kNotDone16;
     lds_vi32_t *const abort_p = (lds_vi32_t *)(ldsb + o.o_abort) + g;
-    const uint64_t segmask = ((Pseg == kWave) ? ~0ull : ((1ull << Pseg) - 1ull)) << (g * Pseg);
+    const int seg = Pseg * SUB;                             // lanes of a candidate
+    const uint64_t segmask = ((seg == kWave) ? ~0ull : ((1ull << seg) - 1ull)) << (g * seg);
     auto cell = [&](uint32_t a16) -> uint32_t {
       if (kWin) return *(lds_vu32_t *)(uintptr_t)win_addr(a16);     // name << 16 | end time
       return kCell32 ? *(lds_vu32_t *)(uintptr_t)(a16 << 2) : (uint32_t)*(lds_vu16_t *)(uintptr_t)(a16 << kAsh);
@@ -446,7 +523,11 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
     __builtin_amdgcn_s_setprio(3);                          // the relaxer's trip is the critical path of the workgroup:
                                                             // it goes first wherever it shares a SIMD (measured: 4-5 % on the MoE workload)
     bool idle = true, dead = !has_ops;                      // idle: the registers hold a free slot's content, not an op
-    uint32_t x_acc = kOrigin;                               // the machine is free from the time origin on
+    uint32_t x_acc = sub_lane == 0 ? kOrigin : kNotDone;    // the machine is free from the time origin on
+    // what the lane before works out: lane ^ 1 of two, the lane before in a ring of four
+    auto before = [](uint32_t v) -> uint32_t {
+      return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, SUB == 4 ? 0x93 : 0xB1, 0xF, 0xF, true);
+    };
     // ops taken from the ring, as t << 16 | 0xFFFF: the free mark that the slot of op t gets when op t is taken
     // (the host sends a problem with 65536 op parts or more to the general kernel)
     uint32_t tm = kNotDone16;
@@ -512,6 +593,20 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
           if (PR == 4) x = max(max(x, (e2 & 0xFFFFu) + ((w2 >> 16) & 0xFFu)), (e3 & 0xFFFFu) + (w2 >> 24));
           x += w3 & 0xFFFFu;
           ran = named && x < kNotDone;                        // (a free slot's "duration" 0xFFFF lifts x over the range)
+        } else if (SUB > 1) {
+          uint32_t t = PR == 1 ? e0 + w2 : max(e0 + (w2 & 0xFFu), e1 + (PR == 4 ? (w2 >> 8) & 0xFFu : w2 >> 8));
+          if (PR == 4) t = max(max(t, e2 + ((w2 >> 16) & 0xFFu)), e3 + (w2 >> 24));
+          const uint32_t d = w3 & 0xFFFFu;
+          if (kCell32) t = idle ? kNotDone : t;               // (a free slot's "duration" lifts x over the 16-bit sentinel only)
+          uint32_t b = x_acc;
+          x = max(t, b) + d;
+#pragma unroll
+          for (int k = 1; k < SUB; ++k) { b = min(b, before(x)); x = max(t, b) + d; }
+          ran = x < kNotDone;
+          // an op has run: the lane is the head again if it was and all the others' ops have run too; else it is when the op before
+          // has run (every value of kNotDone or more stays below 2^32: the smaller of two goes on, and the head's is finite)
+          const uint32_t last = before(x);
+          x_acc = ran ? max(x_acc, last) : b;
         } else {
           if (PR == 1) x = max(x_acc, e0 + w2);
           else x = max(max(x_acc, e0 + (w2 & 0xFFu)), e1 + (PR == 4 ? (w2 >> 8) & 0xFFu : w2 >> 8));
@@ -521,7 +616,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
           // 16-bit sentinel, not over the 32-bit one: there the lane's state is asked)
           ran = kCell32 ? (x < kNotDone && !idle) : x < kNotDone;
         }
-        x_acc = ran ? x : x_acc;                            // the machine is busy until x (chain edge, eq. (7))
+        if (SUB == 1) x_acc = ran ? x : x_acc;              // the machine is busy until x (chain edge, eq. (7))
         set_cell(ran ? (w3 >> 16) : trash, x);
         const bool next = ran || idle;                      // the registers take the content of slot t
         const bool idle_next = next && empty;               // ... which is still free: nothing held (not next: an op is held)
@@ -583,7 +678,8 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
           }
           win_stop = named || later;
         }
-        const bool range_stop = deadlock && !idle && (kWin ? win_stop : max(max(e0, PR >= 2 ? e1 : 0u), PR == 4 ? max(e2, e3) : 0u) < kNotDone);
+        // (an op behind the head's waits for that one, whatever has ended)
+        const bool range_stop = deadlock && !idle && (SUB == 1 || x_acc < kNotDone) && (kWin ? win_stop : max(max(e0, PR >= 2 ? e1 : 0u), PR == 4 ? max(e2, e3) : 0u) < kNotDone);
         const bool overflow = (__ballot(range_stop) & segmask) != 0;
         if (deadlock) *abort_p = overflow ? 1 : 2;
         stalled = stalled || deadlock;
@@ -596,18 +692,11 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
       const bool fin = dead || (idle && tm == tm_end);
       if (!fin) { flagw[g] = kBitInternal; *abort_p = 1; }
     }
-    acc = (int32_t)(x_acc - kOrigin);
+    acc = SUB == 1 || x_acc < kNotDone ? (int32_t)(x_acc - kOrigin) : 0;
   } else if (wave <= kFeeders) {
     // ------------------------------------------------------------ feeders
-    // Per lane the op parts of machine j form a stream (the parts of one operation are consecutive;
-    // the order-list entry of a node carries its part count, so the stream is known from the ids
-    // alone).  Feeder f owns every kFeeders-th part.  A part is ADMITTED when the relaxer has copied the
-    // previous part out of its ring slot, then moves through a fixed pipeline without ever stalling:
-    //   trip t    record requested from L2
-    //   trip t+1  placement bytes of its predecessors requested (L2), or read from LDS
-    //   trip t+2  (trip t+1 when the placement bytes are in LDS) channel delays read from LDS, op packed
-    //             and written to the ring
-    // The loop is unrolled by the pipeline depth so that the registers rotate by renaming, not by moves.
+    // The op parts of machine j form a stream, its list in ws_list.  Every SUB-th part is the lane's, and feeder f owns every
+    // kFeeders-th of those.
     const int f = wave - 1;
     const uint8_t *const pib_g = p.ws_pib + cid(cand_ok ? g : 0) * p.pib_stride;   // L2-resident: this workgroup wrote it
     lds_cu8_t *const pib_l = (lds_cu8_t *)(ldsb + o.o_pi + g * o.pi_stride);
@@ -621,171 +710,225 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
     const uint16_t *list = p.ws_list + cid(cand_ok ? g : 0) * p.list_stride;
     const uint32_t base2 = sbase | (sbase << 16);
     const uint32_t trash = kWin ? win_trash : sbase + (((uint32_t)N + 1u) << kNodeShift);
-    const uint32_t vbits = (uint32_t)p.id_bits, vmask = (1u << vbits) - 1u;
-    const uint32_t n_plane = (uint32_t)p.rec_plane;
+    const uint32_t vbits = (uint32_t)p.id_bits, vmask = (1u << vbits) - 1u, n_plane = (uint32_t)p.rec_plane;
+    auto record = [&](uint32_t entry) -> uint32_t { return KIND == 0 ? (entry & vmask) + (entry >> vbits) * n_plane : entry; };
     const uint32_t lps = (uint32_t)p.log_pseg;
-    const uint32_t k0 = has_ops ? (uint32_t)offw[ql] : 1u;
-    const uint32_t klast = has_ops ? k0 + (uint32_t)cntw[ql] - 1u : 0u;   // list position of the lane's last node
-    bool pending = false;
-    uint32_t admitted = 0, written = 0;
-    uint32_t aseq = (uint32_t)f;                            // index in the lane's stream of the next part to admit
-    uint32_t wseq = (uint32_t)f;                            // ... of the next part to write
-    // cursor: the next part to admit is the record at `addr`; `rem` more parts of the same node follow;
-    // the node sits at list position k, and k > klast means the stream is exhausted
-    // When every operation is a single part, feeder f simply owns the nodes at list positions k0 + f,
-    // k0 + f + kFeeders, ... and looks one of them ahead.
-    constexpr bool kSingle = KIND != 0;
-    uint32_t k = kSingle ? k0 + (uint32_t)f : k0;
-    const uint32_t w0 = has_ops ? (uint32_t)list[min(k, klast)] : 0u;
-    uint32_t addr = w0 & vmask, rem = kSingle ? 0u : w0 >> vbits;
-    // list entries of the next kFeeders nodes: one trip moves the cursor by kFeeders parts, so it can
-    // enter at most that many nodes
-    uint32_t ids[kFeeders];
-#pragma unroll
-    for (int i = 0; i < kFeeders; ++i) ids[i] = has_ops ? (uint32_t)list[min(k0 + 1u + (uint32_t)i, klast)] : 0u;
-    // move the cursor one part ahead
-    auto advance = [&]() {
-      const bool in_node = rem != 0;
-      addr = in_node ? addr + n_plane : (ids[0] & vmask);
-      rem = in_node ? rem - 1u : (ids[0] >> vbits);
-      k += in_node ? 0u : 1u;
-#pragma unroll
-      for (int i = 0; i + 1 < kFeeders; ++i) ids[i] = in_node ? ids[i] : ids[i + 1];
-    };
-    if (kSingle) {
-      ids[0] = has_ops ? (uint32_t)list[min(k + (uint32_t)kFeeders, klast)] : 0u;
-    } else {
-      for (int i = 0; i < f; ++i) advance();                // feeder f starts at its first own part
-#pragma unroll
-      for (int i = 0; i < kFeeders; ++i) ids[i] = has_ops ? (uint32_t)list[min(k + 1u + (uint32_t)i, klast)] : 0u;
-    }
-    struct Entry { uint4 rec; uint32_t q0, q1, q2, q3, fl; };   // fl: 1 valid
-    constexpr int kStages = PIBL ? 2 : 3;
-    Entry E[kStages];
-#pragma unroll
-    for (int i = 0; i < kStages; ++i) { E[i].rec = make_uint4(0, 0, 0, 0); E[i].q0 = E[i].q1 = E[i].q2 = E[i].q3 = 0; E[i].fl = 0; }
+    if (kStations) {
+      // The four-slot ring of the general kind with several lanes per machine, which the host takes when that is what lets another
+      // candidate onto the CU: the CU is then full of wavefronts, the vector units busy 88 % of the time with the loop below, most of that
+      // for lanes that had nothing to admit.  Here a part has two stations in its feeder's lane, "asked" (its record is on its way from L2)
+      // and "packed" (the finished op waits in registers for its ring slot), and moves on when the next one is free, under the mask
+      // of the lanes where it does.  A trip takes longer, for what it does is one wait behind the other, but costs the CU
+      // little.  MoE graph, four candidates per CU: 1063 us with the loop below, 975 with this one; with one candidate per CU
+      // 186 and 192.
+      const uint32_t klast = has_ops ? offw[ql] + totalw[ql] - 1u : 0u;   // list position of the machine's last part
+      constexpr uint32_t kStep = kFeeders * SUB;
+      uint32_t k = has_ops ? offw[ql] + (uint32_t)(f * SUB + sub_lane) : 1u;   // ... of the next part to ask for (beyond klast: none is left)
+      uint32_t entry = has_ops ? (uint32_t)list[min(k, klast)] : 0u;          // its list entry
+      uint32_t ahead = has_ops ? (uint32_t)list[min(k + kStep, klast)] : 0u;  // ... and the one after it
+      uint32_t wseq = (uint32_t)f;                            // index in the lane's stream of the next part to write
+      bool asked = false, packed = false;
+      uint4 rec = make_uint4(0, 0, 0, 0);                     // the record asked for
+      uint32_t op0 = 0, op1 = 0, op2 = 0, op3 = 0;            // the finished op
+      auto look_up_and_pack = [&]() {
+        const uint32_t q0 = pib(rec.x & 0xFFFFu), q1 = pib(rec.x >> 16), q2 = pib(rec.y & 0xFFFFu), q3 = pib(rec.y >> 16);
+        const uint32_t d0 = commr[q0 << lps], d1 = commr[q1 << lps], d2 = commr[q2 << lps], d3 = commr[q3 << lps];
+        const uint32_t dst = (rec.z >> 31) ? trash : sbase + ((rec.w >> 16) << kNodeShift);
+        // (node ids below 32768 whenever they are shifted, so shifting both halves at once cannot carry over)
+        op0 = (rec.x << kNodeShift) + base2;
+        op1 = (rec.y << kNodeShift) + base2;
+        op2 = d0 | (d1 << 8) | (d2 << 16) | (d3 << 24);
+        op3 = (rec.z & 0xFFFFu) | (dst << 16);
+      };
 
-    // The look at the relaxer's "given up" flag and the end test wait for LDS and cost a dozen instructions: once
-    // per kRounds turns of the pipeline.  Four turns where the relaxer limits (the general kind: 2 % on the MoE
-    // workload); one where the feeders do and a workgroup's last ops are waited for (3 % on the pipelines).
-    constexpr int kRounds = KIND == 0 ? 4 : 1;
-    for (uint32_t it = 0; it < p.spin_cap; it += kStages * kRounds) {
-      if (*abort_p) { k = klast + 1u; written = admitted; }   // the relaxer gave this candidate up
-      if (__ballot(!(k > klast && written == admitted)) == 0) break;
-#pragma unroll
-      for (int s_ = 0; s_ < kStages * kRounds; ++s_) {
-        const int s = s_ % kStages;
-        Entry &e0 = E[s];                             // admitted in this trip
-        Entry &e1 = E[(s + kStages - 1) % kStages];   // admitted one trip ago: its record has arrived
-        Entry &e2 = E[(s + 1) % kStages];             // the oldest: written in this trip (e1 itself when the depth is two)
-        if (kStages == 2) {
-          e1.q0 = pib(e1.rec.x & 0xFFFFu);
-          if (PR >= 2) e1.q1 = pib(e1.rec.x >> 16);
-          if (PR == 4) { e1.q2 = pib(e1.rec.y & 0xFFFFu); e1.q3 = pib(e1.rec.y >> 16); }
-        }
-        // (A) channel delays of e2
-        // (wide ops carry the machines themselves; the dummy node's machine P becomes this lane's own: no delay)
-        const uint32_t d0 = kWide ? (e2.q0 == (uint32_t)P ? (uint32_t)j : e2.q0) : commr[e2.q0 << lps];
-        const uint32_t d1 = PR < 2 ? 0u : kWide ? (e2.q1 == (uint32_t)P ? (uint32_t)j : e2.q1) : commr[e2.q1 << lps];
-        const uint32_t d2 = PR != 4 ? 0u : kWide ? (e2.q2 == (uint32_t)P ? (uint32_t)j : e2.q2) : commr[e2.q2 << lps];
-        const uint32_t d3 = PR != 4 ? 0u : kWide ? (e2.q3 == (uint32_t)P ? (uint32_t)j : e2.q3) : commr[e2.q3 << lps];
-        // (1) move the cursor past the part admitted in the previous trip and the other feeders' parts
-        // (2) entries of the next nodes (consumed one trip later at the earliest).  Lanes whose cursor stayed
-        // keep theirs and all read the same entry instead, which costs the vector cache one line, not one per lane.
-        const bool moved = pending;
-        if (kSingle) {
-          addr = moved ? ids[0] & vmask : addr;
-          k += moved ? (uint32_t)kFeeders : 0u;
-          aseq += moved ? (uint32_t)kFeeders : 0u;
-          const uint32_t t = list[moved ? min(k + (uint32_t)kFeeders, klast) : 0u];
-          ids[0] = moved ? t : ids[0];
-        } else {
-          if (pending) {
-#pragma unroll
-            for (int a = 0; a < kFeeders; ++a) advance();
-            aseq += kFeeders;
-          }
-#pragma unroll
-          for (int i = 0; i < kFeeders; ++i) {
-            const uint32_t t = list[moved ? min(k + 1u + (uint32_t)i, klast) : 0u];
-            ids[i] = moved ? t : ids[i];
-          }
-        }
-        // (3) admission
-        // (measured: with two predecessors per op a branch around the read for exhausted lanes pays, 3 %; else not, 1 %)
-        lds_vu32_t *const mark_p = (lds_vu32_t *)(ring_lane + ((aseq & (uint32_t)(RING - 1)) << 10) + 12);
-        const uint32_t mark_free = ((aseq - (uint32_t)RING) << 16) | kNotDone16;
-        if (KIND >= 2) {
-          pending = (k <= klast) && *mark_p == mark_free;
-        } else {
-          const uint32_t mark = *mark_p;
-          pending = (k <= klast) & (mark == mark_free);
-        }
-        e0.fl = pending ? 1u : 0u;
-        e0.rec = p.rec[pending ? addr : 0u];                 // lanes that admit nothing share one record
-        admitted += pending ? 1u : 0u;
-        // (B) placement bytes of e1's predecessors (its record was requested one trip ago)
-        if (kStages == 3) {
-          if (!(e1.fl & 1u)) e1.rec.x = e1.rec.y = (uint32_t)N | ((uint32_t)N << 16);   // nothing admitted: the dummy node's byte
-          e1.q0 = pib(e1.rec.x & 0xFFFFu);
-          if (PR >= 2) e1.q1 = pib(e1.rec.x >> 16);
-          if (PR == 4) { e1.q2 = pib(e1.rec.y & 0xFFFFu); e1.q3 = pib(e1.rec.y >> 16); }
-        }
-        // (D) pack e2 and publish it
-        if (e2.fl & 1u) {
-          const bool more = !kSingle && (e2.rec.z >> 31) != 0;
-          const uint32_t dst = more ? trash : kWin ? name_of(e2.rec.w >> 16) : sbase + ((e2.rec.w >> 16) << kNodeShift);
-          const uint32_t dur = e2.rec.z & 0xFFFFu;
+      // (the look at the relaxer's "given up" flag and the end test: once every eight trips)
+      constexpr int kRounds = 8;
+      for (uint32_t it = 0; it < p.spin_cap; it += kRounds) {
+        if (*abort_p) { k = klast + 1u; asked = packed = false; }   // the relaxer gave this candidate up
+        if (__ballot(k <= klast || asked || packed) == 0) break;
+#pragma unroll 1
+        for (int round = 0; round < kRounds; ++round) {
+          // the slot of the op in `packed` is free: the whole slot with its free mark unchanged, then the last dword
           lds_byte_t *const sp = ring_lane + ((wseq & (uint32_t)(RING - 1)) << 10);
-          // node ids below 32768 whenever they are shifted, so shifting both halves at once cannot carry over;
-          // the whole slot first with its free mark unchanged, then the last dword
-          const u32x4_t val = {kWin ? name_of(e2.rec.x & 0xFFFFu) | (name_of(e2.rec.x >> 16) << 16) : (e2.rec.x << kNodeShift) + base2,
-                               kWin ? (PR == 4 ? name_of(e2.rec.y & 0xFFFFu) | (name_of(e2.rec.y >> 16) << 16) : win_dummy * 0x10001u)
-                                    : (e2.rec.y << kNodeShift) + base2,
-                               kWide ? d0 | (d1 << 6) | (d2 << 12) | (d3 << 18) | (((e2.rec.z >> 16) & 0xFFu) << 24)
-                                     : d0 | (d1 << 8) | (d2 << 16) | (d3 << 24),
-                               ((wseq - (uint32_t)RING) << 16) | kNotDone16};
-          *(lds_vu32x4_t *)sp = val;
-          *(lds_vu32_t *)(sp + 12) = dur | (dst << 16);
-          wseq += kFeeders;
-          ++written;
+          const uint32_t mark_free = ((wseq - (uint32_t)RING) << 16) | kNotDone16;
+          const bool write = packed && *(lds_vu32_t *)(sp + 12) == mark_free;
+          if (write) {
+            *(lds_vu32x4_t *)sp = u32x4_t{op0, op1, op2, mark_free};
+            *(lds_vu32_t *)(sp + 12) = op3;
+            wseq += kFeeders;
+            packed = false;
+          }
+          if (asked && !packed) {
+            look_up_and_pack();
+            packed = true;
+            asked = false;
+          }
+          if (!asked && k <= klast) {
+            rec = p.rec[record(entry)];
+            asked = true;
+            entry = ahead;
+            k += kStep;
+            ahead = (uint32_t)list[min(k + kStep, klast)];
+          }
+          if (__ballot(write) == 0) __builtin_amdgcn_s_sleep(1);
+        }
+      }
+    } else {
+      // A part is ADMITTED when the relaxer has copied the previous part out of its ring slot, then moves through a fixed pipeline
+      // without ever stalling:
+      //   trip t    record requested from L2
+      //   trip t+1  placement bytes of its predecessors requested (L2), or read from LDS
+      //   trip t+2  (trip t+1 when the placement bytes are in LDS) channel delays read from LDS, op packed
+      //             and written to the ring
+      // The loop is unrolled by the pipeline depth so that the registers rotate by renaming, not by moves.
+      const uint32_t k0 = has_ops ? (uint32_t)offw[ql] : 1u;
+      const uint32_t klast = has_ops ? k0 + totalw[ql] - 1u : 0u;   // list position of the machine's last part
+      bool pending = false;
+      uint32_t admitted = 0, written = 0;
+      uint32_t aseq = (uint32_t)f;                            // index in the lane's stream of the next part to admit
+      uint32_t wseq = (uint32_t)f;                            // ... of the next part to write
+      // cursor: the next part to admit is the record at `addr`, at list position k (k > klast: the stream is exhausted);
+      // `ahead` is the entry after it in this feeder's share of the lane's stream
+      constexpr uint32_t kStep = kFeeders * SUB;
+      uint32_t k = k0 + (uint32_t)(f * SUB + sub_lane);
+      uint32_t addr = has_ops ? (uint32_t)list[min(k, klast)] : 0u;
+      uint32_t ahead = has_ops ? (uint32_t)list[min(k + kStep, klast)] : 0u;
+      struct Entry { uint4 rec; uint32_t q0, q1, q2, q3, fl; };   // fl: 1 valid
+      constexpr int kStages = PIBL ? 2 : 3;
+      Entry E[kStages];
+#pragma unroll
+      for (int i = 0; i < kStages; ++i) { E[i].rec = make_uint4(0, 0, 0, 0); E[i].q0 = E[i].q1 = E[i].q2 = E[i].q3 = 0; E[i].fl = 0; }
+
+      // The look at the relaxer's "given up" flag and the end test wait for LDS and cost a dozen instructions: once
+      // per kRounds turns of the pipeline.  Four turns where the relaxer limits (the general kind: 2 % on the MoE
+      // workload); one where the feeders do and a workgroup's last ops are waited for (3 % on the pipelines).
+      constexpr int kRounds = KIND == 0 ? 4 : 1;
+      for (uint32_t it = 0; it < p.spin_cap; it += kStages * kRounds) {
+        if (*abort_p) { k = klast + 1u; written = admitted; }   // the relaxer gave this candidate up
+        if (__ballot(!(k > klast && written == admitted)) == 0) break;
+#pragma unroll
+        for (int s_ = 0; s_ < kStages * kRounds; ++s_) {
+          const int s = s_ % kStages;
+          Entry &e0 = E[s];                             // admitted in this trip
+          Entry &e1 = E[(s + kStages - 1) % kStages];   // admitted one trip ago: its record has arrived
+          Entry &e2 = E[(s + 1) % kStages];             // the oldest: written in this trip (e1 itself when the depth is two)
+          if (kStages == 2) {
+            e1.q0 = pib(e1.rec.x & 0xFFFFu);
+            if (PR >= 2) e1.q1 = pib(e1.rec.x >> 16);
+            if (PR == 4) { e1.q2 = pib(e1.rec.y & 0xFFFFu); e1.q3 = pib(e1.rec.y >> 16); }
+          }
+          // (A) channel delays of e2
+          // (wide ops carry the machines themselves; the dummy node's machine P becomes this lane's own: no delay)
+          const uint32_t d0 = kWide ? (e2.q0 == (uint32_t)P ? (uint32_t)j : e2.q0) : commr[e2.q0 << lps];
+          const uint32_t d1 = PR < 2 ? 0u : kWide ? (e2.q1 == (uint32_t)P ? (uint32_t)j : e2.q1) : commr[e2.q1 << lps];
+          const uint32_t d2 = PR != 4 ? 0u : kWide ? (e2.q2 == (uint32_t)P ? (uint32_t)j : e2.q2) : commr[e2.q2 << lps];
+          const uint32_t d3 = PR != 4 ? 0u : kWide ? (e2.q3 == (uint32_t)P ? (uint32_t)j : e2.q3) : commr[e2.q3 << lps];
+          // (1) move the cursor past the part admitted in the previous trip and the other feeders' parts
+          // (2) the entry after it (consumed one trip later at the earliest).  Lanes whose cursor stayed
+          // keep theirs and all read the same entry instead, which costs the vector cache one line, not one per lane.
+          const bool moved = pending;
+          addr = moved ? ahead : addr;
+          k += moved ? kStep : 0u;
+          aseq += moved ? (uint32_t)kFeeders : 0u;
+          const uint32_t entry = list[moved ? min(k + kStep, klast) : 0u];
+          ahead = moved ? entry : ahead;
+          // (3) admission
+          // (measured: with two predecessors per op a branch around the read for exhausted lanes pays, 3 %; else not, 1 %)
+          lds_vu32_t *const mark_p = (lds_vu32_t *)(ring_lane + ((aseq & (uint32_t)(RING - 1)) << 10) + 12);
+          const uint32_t mark_free = ((aseq - (uint32_t)RING) << 16) | kNotDone16;
+          if (KIND >= 2) {
+            pending = (k <= klast) && *mark_p == mark_free;
+          } else {
+            const uint32_t mark = *mark_p;
+            pending = (k <= klast) & (mark == mark_free);
+          }
+          e0.fl = pending ? 1u : 0u;
+          e0.rec = p.rec[pending ? record(addr) : 0u];                 // lanes that admit nothing share one record
+          admitted += pending ? 1u : 0u;
+          // (B) placement bytes of e1's predecessors (its record was requested one trip ago)
+          if (kStages == 3) {
+            if (!(e1.fl & 1u)) e1.rec.x = e1.rec.y = (uint32_t)N | ((uint32_t)N << 16);   // nothing admitted: the dummy node's byte
+            e1.q0 = pib(e1.rec.x & 0xFFFFu);
+            if (PR >= 2) e1.q1 = pib(e1.rec.x >> 16);
+            if (PR == 4) { e1.q2 = pib(e1.rec.y & 0xFFFFu); e1.q3 = pib(e1.rec.y >> 16); }
+          }
+          // (D) pack e2 and publish it
+          if (e2.fl & 1u) {
+            const bool more = KIND == 0 && (e2.rec.z >> 31) != 0;
+            const uint32_t dst = more ? trash : kWin ? name_of(e2.rec.w >> 16) : sbase + ((e2.rec.w >> 16) << kNodeShift);
+            const uint32_t dur = e2.rec.z & 0xFFFFu;
+            lds_byte_t *const sp = ring_lane + ((wseq & (uint32_t)(RING - 1)) << 10);
+            // node ids below 32768 whenever they are shifted, so shifting both halves at once cannot carry over;
+            // the whole slot first with its free mark unchanged, then the last dword
+            const u32x4_t val = {kWin ? name_of(e2.rec.x & 0xFFFFu) | (name_of(e2.rec.x >> 16) << 16) : (e2.rec.x << kNodeShift) + base2,
+                                 kWin ? (PR == 4 ? name_of(e2.rec.y & 0xFFFFu) | (name_of(e2.rec.y >> 16) << 16) : win_dummy * 0x10001u)
+                                      : (e2.rec.y << kNodeShift) + base2,
+                                 kWide ? d0 | (d1 << 6) | (d2 << 12) | (d3 << 18) | (((e2.rec.z >> 16) & 0xFFu) << 24)
+                                       : d0 | (d1 << 8) | (d2 << 16) | (d3 << 24),
+                                 ((wseq - (uint32_t)RING) << 16) | kNotDone16};
+            *(lds_vu32x4_t *)sp = val;
+            *(lds_vu32_t *)(sp + 12) = dur | (dst << 16);
+            wseq += kFeeders;
+            ++written;
+          }
         }
       }
     }
   } else if (wave == kFeeders + 1) {
     // ------------------------------------------------------------ accountant
     // Peak of the running memory level of machine j (eqs. (17)-(19)): it depends on the order only,
-    // so one wavefront walks the order lists on its own, four operations per trip.
-    const uint16_t *list = p.ws_list + cid(cand_ok ? g : 0) * p.list_stride;
+    // so one wavefront walks the order lists on its own: a stretch of the machine's list to each of its lanes, kEight entries per
+    // trip, whose list entries were requested a trip earlier.
+    // (One lane per machine, four entries a trip and their numbers not asked for before they were needed took longer than the relaxation
+    // itself where that is short: random graph of 3001 operations on 11 machines, 95000 cycles after the relaxers had ended.)
+    const uint16_t *const list = p.ws_list + cid(cand_ok ? g : 0) * p.list_stride;
     const uint32_t vmask = (1u << p.id_bits) - 1u;
-    const int k0 = has_ops ? offw[ql] : 0;
-    const int kend = has_ops ? k0 + cntw[ql] : 0;
-    int64_t level = 0, peak = 0, base = 0;                  // level above the machine's base; base = static memory on it (eq. (16))
-    for (int k = k0; __ballot(k < kend) != 0; k += 4) {
-      uint32_t id[4];
-      int64_t m[4], wt[4];
+    constexpr int kEight = 8;
+    const int n = has_ops ? (int)totalw[ql] : 0, stretch = (n + SUB - 1) / SUB;
+    const int k0 = (has_ops ? (int)offw[ql] : 0) + min(n, sub_lane * stretch), kend = k0 + min(stretch, n - min(n, sub_lane * stretch));
+    int64_t level = 0, base = 0;                            // level above the machine's base; base = static memory on it (eq. (16))
+    uint32_t id[kEight];
+    auto entries = [&](int k) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) id[u] = (k + u < kend) ? ((uint32_t)list[k + u] & vmask) : 0u;
+      for (int u = 0; u < kEight; ++u) id[u] = list[k + u < kend ? k + u : 0];
+    };
+    entries(k0);
+    for (int k = k0; __ballot(k < kend) != 0; k += kEight) {
+      int64_t m[kEight], wt[kEight];
+      bool on[kEight];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        m[u] = p.mem_delta[id[u]];
-        wt[u] = p.weight ? p.weight[id[u]] : 0;
+      for (int u = 0; u < kEight; ++u) {
+        on[u] = k + u < kend && (KIND != 0 || id[u] <= vmask);   // (an operation counts with its first part)
+        const uint32_t v = on[u] ? id[u] : 0u;
+        m[u] = p.mem_delta[v];
+        wt[u] = p.weight ? p.weight[v] : 0;
       }
+      entries(k + kEight);
 #pragma unroll
-      for (int u = 0; u < 4; ++u)
-        if (k + u < kend) { level += m[u]; peak = max(peak, level); base += wt[u]; }   // eq. (19) along the chain
+      for (int u = 0; u < kEight; ++u)
+        if (on[u]) { level += m[u]; peak = max(peak, level); base += wt[u]; }   // eq. (19) along the chain
+    }
+    // the stretches of a machine one behind the other: a later one starts at the level the earlier ones end at
+#pragma unroll
+    for (int d = 1; d < SUB; d <<= 1) {
+      const int64_t l2 = __shfl_xor(level, d, kWave), p2 = __shfl_xor(peak, d, kWave);
+      const bool later = (sub_lane & d) != 0;
+      peak = later ? max(p2, l2 + peak) : max(peak, level + p2);
+      level += l2;
+      base += __shfl_xor(base, d, kWave);
     }
     peak += base;
     if (p.mem_limit && cand_ok && j < P && peak > p.mem_limit[j]) overb[g] = 1;   // an empty machine has peak 0
-    if (lane_on) peakw[ql] = peak;
   }
+  __syncthreads();
+  if (wave == kFeeders + 1 && lane_on && sub_lane == 0) peakw[ql] = peak;   // nobody looks at the ring any more
   __syncthreads();
 
   // ---------------------------------------------------------------- reductions and outputs (wave 0)
   if (wave == 0) {
     int32_t z = acc;
-    for (int d = 1; d < Pseg; d <<= 1) z = max(z, __shfl_xor(z, d, Pseg));
-    if (lane_on && g < ng && j < P) {
+    for (int d = 1; d < Pseg * SUB; d <<= 1) z = max(z, __shfl_xor(z, d, Pseg * SUB));
+    if (lane_on && sub_lane == 0 && g < ng && j < P) {
       const int64_t c = cid(g);
       int bits = flagw[g] | (overb[g] ? kBitOverMemory : 0);
       if (stalled || abortw[g]) {

@@ -26,7 +26,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
 sys.path.insert(0, ROOT)
 
-from paper_2503_09357_amd import workloads as W  # noqa: E402
+from paper_2503_09357_amd import _build, workloads as W  # noqa: E402
 
 SAN = ["-fsanitize=address", "-fsanitize=undefined", "-fno-sanitize-recover=undefined"]
 
@@ -54,15 +54,15 @@ def main() -> int:
         objs.append(obj)
     exe = os.path.join(tmp, "driver")
     host_san = [x for flag in SAN for x in ("-Xarch_host", flag)]
-    lib_obj, drv_obj = os.path.join(tmp, "dagsched.o"), os.path.join(tmp, "driver.o")
+    drv_obj = os.path.join(tmp, "driver.o")
     print("building (device code is compiled too: a few minutes) ...", flush=True)
-    subprocess.check_call([hipcc, "--offload-arch=gfx950", "-O1", "-g", "-std=c++17", *host_san,
-                           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-function",
-                           "-I", os.path.join(ROOT, "include"), "-c",
-                           os.path.join(ROOT, "paper_2503_09357_amd", "csrc", "dagsched.hip"), "-o", lib_obj])
+    units = []
+    for i, (source, defines) in enumerate(_build.HIP_UNITS):
+        units.append(os.path.join(tmp, "unit%d.o" % i))
+        subprocess.check_call([hipcc, "-O1", "-g", *host_san, *_build.HIP_FLAGS, *defines, "-c", os.path.join(_build.CSRC, source), "-o", units[-1]])
     subprocess.check_call([clang + "++", "-O1", "-g", "-std=c++17", *SAN, "-I", os.path.join(ROOT, "include"), "-c",
                            os.path.join(HERE, "driver.cpp"), "-o", drv_obj])
-    subprocess.check_call([hipcc, "--offload-arch=gfx950", "--hip-link", "-fno-gpu-sanitize", *SAN, lib_obj, drv_obj, *objs, "-o", exe])
+    subprocess.check_call([hipcc, "--offload-arch=gfx950", "--hip-link", "-fno-gpu-sanitize", *SAN, *units, drv_obj, *objs, "-o", exe])
     files = []
     full = {1: 1024, 2: 65536, 3: 16384, 4: 4096, 5: 1024}
     for cfg in (1, 2, 3, 4, 5):

@@ -1,0 +1,53 @@
+"""Ring kernel with several lanes per machine (as many as the candidates of a workgroup leave a wavefront, up to four), operations of
+several parts expanded into the order lists, the accountants' stretches of a machine: against the oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+from paper_2503_09357_amd import workloads as W
+from test_gpu_parity import assert_parity
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("machines,n,fanin", [
+    (1, 1, 1), (1, 130, 2), (2, 3, 1), (3, 65, 4), (4, 64, 9), (7, 333, 1), (8, 257, 14), (11, 1200, 3), (16, 515, 6), (17, 700, 2), (31, 1024, 40), (32, 2049, 9)])
+@pytest.mark.parametrize("lanes", [1, 2, 4])
+def test_lanes_per_machine(gpu_lib, machines, n, fanin, lanes):
+    """Every cell format, ring and place of the placement bytes that is built with as many lanes: machines without operations and with
+    one, lists that end in the middle of a round, cycles, malformed candidates, limits, an odd last workgroup."""
+    rng = np.random.default_rng(machines * 10000 + n)
+    per_wave = 64 // (1 << (machines - 1).bit_length())
+    if lanes > per_wave:
+        pytest.skip("a wavefront has fewer lanes to a machine")
+    g = per_wave // lanes
+    w = W.random_instance(rng, n, machines, 2 * g + 3, max_fanin=fanin, frac_arbitrary=0.25, frac_bad=0.15)
+    w.weight = rng.integers(0, 9, n).astype(np.int64)
+    w.mem_limit = rng.integers(2, 12 + 9 * n // machines, machines).astype(np.int64)
+    seen = set()
+    for bits in (16, 32):
+        for pib, ring, feeders in ((1, 4, 1), (1, 4, 2), (1, 8, 2), (1, 8, 3), (2, 8, 1), (0, 8, 2), (0, 16, 3)):
+            if pib == 2 and machines > 16:
+                continue
+            with gpu_lib.shape_defaults(cand_per_block=g, placement_mode=pib, ring_slots=ring, feeders=feeders, state_bits=bits):
+                _, info = assert_parity(gpu_lib, w, layout=(bits + pib) & 1)
+            if info["variant"] in (3, 4, 5):
+                assert (info["cand_per_block"], info["ring_slots"], info["state_bits"]) == (g, ring, bits)
+                seen.add((bits, pib, ring))
+    assert {(16, 1, 4), (16, 1, 8), (16, 0, 8), (32, 1, 8), (32, 0, 8)} <= seen, seen
+
+
+@pytest.mark.parametrize("machines,lanes", [(32, 2), (16, 4), (5, 2)])
+def test_range_stops_and_cycles(gpu_lib, machines, lanes):
+    """16-bit end times that some candidates leave: the operation that the range stops is the head's, whatever waits behind it has its
+    predecessors ended too; those candidates are evaluated again, cycles are not."""
+    rng = np.random.default_rng(77 + machines)
+    w = W.random_instance(rng, 900, machines, 61, max_fanin=2, max_dur=9, frac_arbitrary=0.3, frac_bad=0.1)
+    per_wave = 64 // (1 << (machines - 1).bit_length())
+    w.dur = (w.dur * 37 + 1).astype(np.int32)
+    z = assert_parity(gpu_lib, w)[0][0]
+    w.dur = (w.dur * (65535 / np.median(z[z > 0]))).astype(np.int32)     # about half of them beyond the range
+    with gpu_lib.shape_defaults(cand_per_block=per_wave // lanes, state_bits=16, placement_mode=1, ring_slots=8, feeders=2):
+        (z, _, _, f), info = assert_parity(gpu_lib, w)
+    assert info["variant"] == 4 and (z > 65534).any() and (z[f == 0] <= 65534).any() and (f == 1).any(), info
