@@ -102,6 +102,7 @@ struct dagsched {
   int32_t ring_G = 0, ring_sub = 1, ring_slots = 0, ring_feeders = 1, ring_kind = 0, ring_block = 256, rec_plane = 0, id_bits = 16, time_scale = 1;
   uint8_t *d_nparts = nullptr;
   int64_t list_stride = 0, pib_stride = 0;
+  bool shared_keeps_channels = false;                       // the shared placement is named and needs no missing channel
   uint8_t *ws_pib = nullptr;
   LdsLayout lds{};
   // Fallback of the optimistic 16-bit run and of the window mode: the same problem in the 32-bit form of the ring
@@ -1121,10 +1122,13 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
     if (optimistic) launch_listed(h, n_cand, pl, rk, out, stream);
   }
   // the evaluation ran with delay 0 on pairs without a channel; candidates that use one are flagged now
-  if (h->d_no_channel)
+  if (h->d_no_channel) {
     // few candidates: larger workgroups, or the chip's wavefront slots stay empty
-    hipLaunchKernelGGL(channel_flag_kernel, dim3((unsigned)n_cand), dim3(n_cand < 2048 ? 1024 : 256), channel_flag_lds(N), stream, N, h->E,
-                       h->P, h->d_edges, h->d_no_channel, pl, out);
+    const bool listed = h->shared_keeps_channels && (h->pl_stream.total || h->variant == kVariantStatic);
+    const unsigned threads = listed || n_cand < 2048 ? 1024 : 256, blocks = listed ? std::min((unsigned)n_cand, 256u) : (unsigned)n_cand;
+    hipLaunchKernelGGL(channel_flag_kernel, dim3(blocks), dim3(threads), channel_flag_lds(N), stream, N, h->E,
+                       h->P, h->d_edges, h->d_no_channel, pl, n_cand, listed ? h->d_fb_list : nullptr, listed ? h->d_fb_count : nullptr, out);
+  }
   if (!hip_ok(hipGetLastError(), "kernel launch")) return DAGSCHED_EHIP;
   return DAGSCHED_OK;
 }
@@ -1202,6 +1206,13 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   h->row_stride = ((int64_t)h->N + 31) / 32 * 32;     // 128-byte rows: no cache line shared by two candidates
   h->pib_stride = ((int64_t)h->N + 1 + 127) / 128 * 128;
   const size_t maxc = (size_t)h->max_cand;
+  if (any_missing && desc->shared_placement) {
+    const int32_t *const pi = desc->shared_placement;
+    h->shared_keeps_channels = true;
+    for (int32_t u = 0; u < h->N; ++u)
+      for (int32_t k = desc->row_ptr[u]; k < desc->row_ptr[u + 1]; ++k)
+        if ((no_channel[pi[u]] >> pi[desc->col_idx[k]]) & 1u) h->shared_keeps_channels = false;   // (no bit for a machine itself)
+  }
 
   RingPlan plan;
   StaticPlan splan;
@@ -1510,7 +1521,7 @@ int dagsched_evaluate_contended(dagsched_t *h, int32_t n_cand, const int32_t *pl
   hipLaunchKernelGGL(relax_contended_kernel, dim3((unsigned)std::min(n_cand, h->wc_grid)), dim3((unsigned)contended_threads(h->P)), contended_lds(h->P), stream, p);
   if (h->d_no_channel)
     hipLaunchKernelGGL(channel_flag_kernel, dim3((unsigned)n_cand), dim3(n_cand < 2048 ? 1024 : 256), channel_flag_lds(N), stream, N, E,
-                       h->P, h->d_edges, h->d_no_channel, pl, p.out);
+                       h->P, h->d_edges, h->d_no_channel, pl, n_cand, nullptr, nullptr, p.out);
   if (!hip_ok(hipGetLastError(), "kernel launch")) return DAGSCHED_EHIP;
   return DAGSCHED_OK;
 }
@@ -1562,7 +1573,12 @@ int launch_propose(dagsched_t *h, int32_t n_cand, const int32_t *base_placement,
   p.out_pl = placement; p.out_rk = rank; p.orders_only = orders_only;
   if (h->layout == DAGSCHED_CAND_MAJOR) { p.stride_c = h->N; p.stride_n = 1; }
   else { p.stride_c = 1; p.stride_n = n_cand; }
-  hipLaunchKernelGGL(propose_kernel, dim3((unsigned)n_cand), dim3(256), 0, stream, p);
+  // (256 neighbours of 11712 operations would leave the CUs one workgroup of 256 threads each)
+  const bool vec = h->layout == DAGSCHED_CAND_MAJOR && (h->N & 3) == 0 &&
+                   (((uintptr_t)base_placement | (uintptr_t)base_rank | (uintptr_t)placement | (uintptr_t)rank) & 15) == 0;
+  const unsigned loops = ((unsigned)h->N / (vec ? 4 : 1) + 255) / 256, split = std::max(1u, std::min(loops, 4096u / (unsigned)n_cand));
+  if (vec) hipLaunchKernelGGL(propose_kernel<true>, dim3((unsigned)n_cand, split), dim3(256), 0, stream, p);
+  else hipLaunchKernelGGL(propose_kernel<false>, dim3((unsigned)n_cand, split), dim3(256), 0, stream, p);
   if (!hip_ok(hipGetLastError(), "kernel launch")) return DAGSCHED_EHIP;
   return DAGSCHED_OK;
 }

@@ -36,7 +36,10 @@ struct ProposeParams {
 //   r0 odd:  m2 = r2 mod P; m2 == m: v is re-inserted at position r3 mod n_m of m;
 //            m2 != m: v is inserted at position r3 mod (n_m2 + 1) of m2.
 // orders_only: m2 = m whatever r2 is (the candidates keep the base's placement).
-// One workgroup per candidate; the move is the same for every thread, each thread rewrites some operations.
+// A workgroup (several for few candidates: blockIdx.y) per candidate; the move is the same for every thread, each thread rewrites some operations,
+// four at a time where rows allow 16-byte accesses (VEC).  What bounds it is what it writes: 4096 neighbours of 768 operations, 25 MB, 12.8 us with
+// 4-byte accesses.
+template <bool VEC>
 __global__ __launch_bounds__(256) void propose_kernel(ProposeParams p) {
   const int c = blockIdx.x;
   const int N = p.N;
@@ -65,8 +68,7 @@ __global__ __launch_bounds__(256) void propose_kernel(ProposeParams p) {
       }
     }
   }
-  for (int i = threadIdx.x; i < N; i += blockDim.x) {
-    int32_t pl = p.base_pl[i], rk = p.base_rk[i];
+  auto moved = [&](int i, int32_t &pl, int32_t &rk) {
     if (mode == kSwap) {
       if (i == v) rk = r + 1;
       else if (pl == m && rk == r + 1) rk = r;
@@ -81,9 +83,24 @@ __global__ __launch_bounds__(256) void propose_kernel(ProposeParams p) {
       else if (pl == m && rk > r) --rk;
       else if (pl == m2 && rk >= r_new) ++rk;
     }
-    const int64_t at = (int64_t)c * p.stride_c + (int64_t)i * p.stride_n;
-    p.out_pl[at] = pl;
-    p.out_rk[at] = rk;
+  };
+  const int first = (int)(blockIdx.y * blockDim.x + threadIdx.x), step = (int)(gridDim.y * blockDim.x);
+  if (VEC) {                                                // (candidate-major rows)
+    int4 *const out_pl = (int4 *)(p.out_pl + (int64_t)c * N), *const out_rk = (int4 *)(p.out_rk + (int64_t)c * N);
+    for (int q = first; q < N >> 2; q += step) {
+      int4 pl = ((const int4 *)p.base_pl)[q], rk = ((const int4 *)p.base_rk)[q];
+      moved(4 * q, pl.x, rk.x); moved(4 * q + 1, pl.y, rk.y); moved(4 * q + 2, pl.z, rk.z); moved(4 * q + 3, pl.w, rk.w);
+      out_pl[q] = pl;
+      out_rk[q] = rk;
+    }
+  } else {
+    for (int i = first; i < N; i += step) {
+      int32_t pl = p.base_pl[i], rk = p.base_rk[i];
+      moved(i, pl, rk);
+      const int64_t at = (int64_t)c * p.stride_c + (int64_t)i * p.stride_n;
+      p.out_pl[at] = pl;
+      p.out_rk[at] = rk;
+    }
   }
 }
 

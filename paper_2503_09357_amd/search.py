@@ -35,13 +35,13 @@ def local_search(ev, base_placement, base_rank, iterations: int, n_cand: int, se
         cand = ev.propose(pl, rk, rnd, out=cand, orders_only=orders_only)
         z, _, _, f = ev.evaluate(cand[0], cand[1], out)
         ev.select(z, f, out=best[it])
-        idx = best[it, 0:1].clamp(min=0).to(torch.int64)      # no feasible candidate cannot happen: candidate 0 is the base
+        idx = best[it, 0:1].clamp(min=0)                      # no feasible candidate cannot happen: candidate 0 is the base
         if ev.layout == CAND_MAJOR:
-            pl = cand[0].index_select(0, idx).reshape(-1).clone()
-            rk = cand[1].index_select(0, idx).reshape(-1).clone()
+            pl = cand[0].index_select(0, idx).reshape(-1)
+            rk = cand[1].index_select(0, idx).reshape(-1)
         else:
-            pl = cand[0].index_select(1, idx).reshape(-1).clone()
-            rk = cand[1].index_select(1, idx).reshape(-1).clone()
+            pl = cand[0].index_select(1, idx).reshape(-1)
+            rk = cand[1].index_select(1, idx).reshape(-1)
     history = best[:, 1].cpu().tolist() if iterations else []
     return pl, rk, history
 

@@ -223,3 +223,20 @@ def test_search_step_replays_from_a_hip_graph(gpu_lib, shared):
             zo, bo, pko, fo = oracle.Problem.of(w).evaluate(want_pl, want_rk, threads=8)
             assert (got[0].cpu().numpy() == zo).all() and (got[3].cpu().numpy() == fo).all()
             assert tuple(got[4].cpu().tolist()) == SO.select(zo, fo)
+
+
+@pytest.mark.parametrize("n,n_cand,shift", [(4, 1, 0), (4, 9000, 0), (1028, 3, 0), (1028, 3, 1), (1029, 5, 0), (2052, 4096, 0), (2052, 600, 3)])
+def test_propose_rows(gpu_lib, n, n_cand, shift):
+    """Rows of 16-byte accesses and not, by their length and by where the base lies; one to several workgroups per candidate."""
+    import torch
+    rng = np.random.default_rng(n + n_cand)
+    w = W.random_instance(rng, n, 3, 1, frac_bad=0.0, frac_arbitrary=0.0)
+    rnd = rng.integers(0, 1 << 32, size=4 * n_cand, dtype=np.uint64).astype(np.uint32)
+    base = []
+    for a in (w.placement[0], w.rank[0]):
+        base.append(torch.empty(n + shift, dtype=torch.int32, device=_dev())[shift:])
+        base[-1].copy_(torch.from_numpy(a))
+    with gpu_lib.Evaluator.for_workload(w, max_candidates=n_cand) as ev:
+        got = ev.propose(*base, torch.from_numpy(rnd.view(np.int32)).to(_dev()))
+        for a, o in zip(got, SO.propose(w.placement[0], w.rank[0], rnd, 3)):
+            assert np.array_equal(a.cpu().numpy(), o)
