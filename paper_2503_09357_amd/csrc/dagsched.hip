@@ -982,12 +982,12 @@ TransferKernel transfer_kernel_for(int lanes_per_machine) {
 }
 
 using ScheduleKernel = void (*)(ScheduleParams);
-ScheduleKernel schedule_kernel_for(const dagsched *h) {   // lanes per machine: as many as a wavefront has, at most eight
+int schedule_relaxers(const dagsched *h) { return h->Pseg == 64 ? 2 : 1; }
+ScheduleKernel schedule_kernel_for(const dagsched *h) {   // lanes per machine: as many as a wavefront has, at most four
   const bool l = h->sched_lds_cells;
-  return h->Pseg <= 8    ? (l ? schedule_kernel<8, true> : schedule_kernel<8, false>)
-         : h->Pseg == 16 ? (l ? schedule_kernel<4, true> : schedule_kernel<4, false>)
-         : h->Pseg == 32 ? (l ? schedule_kernel<2, true> : schedule_kernel<2, false>)
-                         : (l ? schedule_kernel<1, true> : schedule_kernel<1, false>);
+  return h->Pseg <= 16   ? (l ? schedule_kernel<4, true, 1> : schedule_kernel<4, false, 1>)
+         : h->Pseg == 32 ? (l ? schedule_kernel<2, true, 1> : schedule_kernel<2, false, 1>)
+                         : (l ? schedule_kernel<2, true, 2> : schedule_kernel<2, false, 2>);
 }
 
 size_t channel_flag_lds(int32_t n_nodes) {               // mask words + one byte per node
@@ -1254,10 +1254,11 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
        dev_alloc(&h->ws_cnt, (size_t)DAGSCHED_MAX_DEVICES) &&
        dev_alloc(&h->ws_sched_list, (size_t)h->row_stride) && dev_alloc(&h->ws_sched_end, (size_t)h->row_stride);
   // one schedule: the deepest rings that fit beside the end times; end times in the L2 when not even shallow ones do
-  for (const auto &[slots, lds_cells] : {std::pair<int, bool>{32, true}, {16, true}, {32, false}}) {
+  for (const auto &[slots, lds_cells] : {std::pair<int, bool>{32, true}, {16, true}, {8, true}, {32, false}}) {
+    if (slots == 8 && schedule_relaxers(h) == 1) continue;   // (16 slots of one wavefront's lanes, 8 of two)
     ScheduleParams sp{};
     sp.N = h->N; sp.P = h->P; sp.slots = slots;
-    h->sched_lds_cells = lds_cells; h->sched_slots = slots; h->sched_lds = (int32_t)schedule_lds(&sp, lds_cells);
+    h->sched_lds_cells = lds_cells; h->sched_slots = slots; h->sched_lds = (int32_t)schedule_lds(&sp, lds_cells, schedule_relaxers(h));
     if (h->sched_lds <= lds_max) break;
   }
   ok = ok && h->sched_lds <= lds_max && (h->sched_lds <= 48 * 1024 || allow_large_lds((const void *)schedule_kernel_for(h), h->device, h->sched_lds));
@@ -1615,8 +1616,8 @@ int launch_schedule(dagsched_t *h, int32_t *list_row, int32_t *end_row, const in
   p.placement = placement; p.rank = rank;
   p.list = list_row; p.cells = end_row;
   p.start = start; p.end = end; p.flag = flag;
-  const uint32_t lds = schedule_lds(&p, h->sched_lds_cells);
-  hipLaunchKernelGGL(schedule_kernel_for(h), dim3(1), dim3(kScheduleThreads), lds, stream, p);
+  const uint32_t lds = schedule_lds(&p, h->sched_lds_cells, schedule_relaxers(h));
+  hipLaunchKernelGGL(schedule_kernel_for(h), dim3(1), dim3((unsigned)schedule_threads(schedule_relaxers(h))), lds, stream, p);
   if (!hip_ok(hipGetLastError(), "kernel launch")) return DAGSCHED_EHIP;
   return DAGSCHED_OK;
 }

@@ -5,20 +5,23 @@
 // RELAXER, steps as fast as an LDS round trip allows and never touches anything but LDS, and eight HELPER wavefronts
 // look up in time what it needs (order list, predecessors, placements, delays: four dependent L2 round trips).
 //
-//   relaxer   R = min(8, 64 / P rounded up to a power of two) lanes per machine, each polling four predecessors of the
-//             machine's current operation; the lanes of a machine are combined with DPP moves, so an operation of up
-//             to 4 R predecessors is one step.  Operations with more are split into consecutive parts.
+//   relaxer   R = min(4, 64 / P rounded up to a power of two) lanes per machine (beyond 32 machines two, in two wavefronts of 32
+//             machines each, which see of each other what the end times say), which hold consecutive operations of it, each polling
+//             up to four predecessors of its own.  The end of one goes on to the next through a DPP move within the step, so that a
+//             machine runs up to R operations a step (as the ring kernel's lanes do: the head's x_acc is finite, the others' kNever or more).
+//             Operations with more predecessors are split into consecutive parts.
 //   helpers   a team of 512 / Pseg threads per machine packs the next operations of its list into the machine's ring.
 //
-// They meet at one barrier per phase of kTripsPerSlots * slots steps and hand over counts only: how many parts of a
+// They meet at one barrier per phase of 16 steps (8 with two relaxers) and hand over counts only: how many parts of a
 // machine's stream the relaxer has taken, how many the helpers have put into the ring (both kept twice, by the parity
 // of the phase, so that nobody writes what somebody still reads).  A phase is longer than the helpers' chain of loads
-// (16 steps of 210 cycles against about 2500), so the relaxer hardly ever waits.
+// (16 steps of 270 cycles against about 2500), so the relaxer hardly ever waits.
 //
-// MoE graph, 11712 operations, 32 machines: 268 us, of which 230 are 1760 steps of 311 cycles, 10 the ingest and the rest
-// phases that wait for the helpers.  The one-wavefront int32 kernel before, which polled one edge per step through the
-// L2, took 4940 us.  A step is one LDS round trip plus about 40 instructions of a lone wavefront; every predecessor
-// polled per lane costs it 25 cycles, the second half of the 32-byte ring entry 14.
+// us, while the lanes of a machine (up to eight) polled the predecessors of one operation together, and now: MoE graph, 11712 operations on
+// 32 machines 265, 212 (1760 steps of 311 cycles then); its 30-layer form on 8: 353, 132; zero-bubble pipeline, 768 on 8: 48, 19;
+// bidirectional pipeline, 6144 on 16: 146, 58; random graphs, 3001 on 11 and 6000 on 40: 66, 33 and 63, 49; layered graph, 50000 on 64,
+// end times in the L2: 752, 647 (one lane per machine there before).  The one-wavefront int32 kernel, which polled one edge per step
+// through the L2, took 4940 us for the first.
 #pragma once
 
 #include "device_common.h"
@@ -27,11 +30,13 @@ namespace dagsched_dev {
 
 constexpr int kBitNoChannel = 32;                          // (the evaluations leave this flag to a pass of its own)
 constexpr int kScheduleHelpers = 8;                        // wavefronts
-constexpr int kScheduleThreads = (2 + kScheduleHelpers) * kWave;   // relaxer, accountant, helpers
+constexpr int schedule_threads(int relaxers) { return (relaxers + 1 + kScheduleHelpers) * kWave; }   // relaxers, accountant, helpers
+// Steps of a phase: what the helpers need to bring the next operations, a thread each (beyond 32 machines they have eight threads to a machine).
+constexpr int schedule_steps(int relaxers) { return relaxers == 2 ? 8 : 16; }
 
 struct ScheduleParams {
   int32_t N, P, Pseg, n_red;
-  int32_t slots;                       // ring slots per lane: 16 or 32
+  int32_t slots;                       // ring slots per lane: 8, 16 or 32
   const int32_t *pred_ptr, *pred_idx;  // predecessor CSR of B (for the channels)
   const int32_t *red_ptr, *red_idx;    // [N + 1], [n_red] the same without the edges that other paths imply
   const int32_t *dur, *comm;           // [N], [P*P] (0 where the pair has no channel)
@@ -46,22 +51,22 @@ struct ScheduleParams {
 
 // bytes of dynamic LDS: end times, rings, delays, bookkeeping
 constexpr uint32_t kScheduleBook = 64 * 4 * 7 + 64;
-inline uint32_t schedule_lds(ScheduleParams *p, bool lds_cells) {
+inline uint32_t schedule_lds(ScheduleParams *p, bool lds_cells, int relaxers) {
   uint32_t at = lds_cells ? ((uint32_t)p->N + 2u + 3u) / 4u * 16u : 16u;
   p->o_ring = at;
-  at += (uint32_t)p->slots * kWave * 32u;
+  at += (uint32_t)p->slots * (uint32_t)(relaxers * kWave) * 32u;
   p->o_comm = at;
   at += ((uint32_t)p->P * (uint32_t)p->P + 3u) / 4u * 16u;
   p->o_book = at;
   return at + kScheduleBook;
 }
 
-// R lanes per machine; LDSC: end times in LDS, else in the scratch row (L2)
-template <int R, bool LDSC>
-__global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(ScheduleParams p) {
+// R lanes per machine, RW relaxers; LDSC: end times in LDS, else in the scratch row (L2)
+template <int R, bool LDSC, int RW>
+__global__ __launch_bounds__(schedule_threads(RW)) void schedule_kernel(ScheduleParams p) {
   extern __shared__ __align__(16) unsigned char lds[];
   lds_byte_t *const ldsb = (lds_byte_t *)lds;
-  const int tid = threadIdx.x, lane = tid & 63, T = kScheduleThreads;
+  const int tid = threadIdx.x, lane = tid & 63, T = schedule_threads(RW);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int N = p.N, P = p.P, Pseg = p.Pseg;
   constexpr uint32_t kNever = 0x80000000u;
@@ -71,13 +76,14 @@ __global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(SchedulePara
   uint32_t *const taken = (uint32_t *)(off + 64);            // [2][64] parts the relaxer has taken from the ring
   uint32_t *const fed = taken + 128;                         // [2][64] parts in the ring so far, | 0x80000000: that is all
   int32_t *const s_flag = (int32_t *)(fed + 128);
-  int32_t *const s_done = s_flag + 1;                        // [2] 1 = through, 2 = a cycle
+  int32_t *const s_done = s_flag + 1;                        // [2][2] of a relaxer: 1 = through, 2 = stuck, 3 = the bound on the phases, 0 = on its way
+  constexpr uint32_t kRow = RW * kWave * 16u;                // bytes of a ring slot of all lanes, in either plane
   uint32_t *const seen = (uint32_t *)(lds + p.o_ring);       // [N bits] ingest only
   uint32_t *const cellw = (uint32_t *)lds;                   // [N + 2] end times; N: "ended at 0", N + 1: trash
 
   // ---------------------------------------------------------------- ingest
   if (tid < 64) { cnt[tid] = 0; taken[tid] = taken[64 + tid] = fed[tid] = fed[64 + tid] = 0; }
-  if (tid == 0) { *s_flag = 0; s_done[0] = s_done[1] = 0; }
+  if (tid == 0) { *s_flag = 0; s_done[0] = s_done[1] = s_done[2] = s_done[3] = 0; }
   for (int i = tid; i < (N + 31) / 32; i += T) seen[i] = 0;
   for (int i = tid; i < P * P; i += T) comm[i] = (i / P != i % P) ? p.comm[i] : 0;
   if (LDSC) { for (int i = tid; i < N + 2; i += T) cellw[i] = i < N ? kNever : 0u; }
@@ -155,23 +161,31 @@ __global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(SchedulePara
 
   // ---------------------------------------------------------------- relaxation
   if (!bits) {
-    const int ring_mask = p.slots - 1, trips = p.slots / 2;
+    const int ring_mask = p.slots - 1;
+    // how a phase has ended: 0 it goes on, 1 through, 2 nothing moved anywhere, 3
+    auto phase_end = [&](uint32_t phase) -> int {
+      const int a = s_done[(phase & 1) * 2], b = RW == 2 ? s_done[(phase & 1) * 2 + 1] : 1;
+      return a && b ? max(a, b) : 0;
+    };
     // (every phase completes a part, or takes one, or the helpers bring one)
     const uint32_t max_phases = 4u * ((uint32_t)N + (uint32_t)p.n_red) + 64u;
     int64_t level = 0, peak = 0, base = 0;
-    if (wave == 0) {
+    if (wave < RW) {
       __builtin_amdgcn_s_setprio(3);
-      const int m = lane / R;                                // machines beyond P have no operations
-      const bool mine = lane < Pseg * R;
-      lds_byte_t *const ring_lane = ldsb + p.o_ring + (uint32_t)lane * 16u;   // two planes of [slot][lane] of 16 bytes
-      const uint32_t plane = (uint32_t)p.slots * kWave * 16u;
+      const int place = wave * kWave + lane, m = place / R, sub = place % R;   // machines beyond P have no operations
+      auto before = [](uint32_t v) -> uint32_t {             // what the lane before works out, in a ring of R
+        return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, R == 4 ? 0x93 : 0xB1, 0xF, 0xF, true);
+      };
+      const bool mine = place < Pseg * R;
+      lds_byte_t *const ring_lane = ldsb + p.o_ring + (uint32_t)place * 16u;   // two planes of [slot][lane] of 16 bytes
+      const uint32_t plane = (uint32_t)p.slots * kRow;
       // (the end times are the first thing in the workgroup's LDS, and the kernel has no static LDS: cell v is at byte 4 v)
       auto cell = [&](uint32_t v4) -> uint32_t {
         if (LDSC) return *(lds_vu32_t *)(uintptr_t)v4;
         return (v4 >> 2) < (uint32_t)N ? (uint32_t)ld_group(&p.cells[v4 >> 2]) : 0u;
       };
       const uint32_t trash = ((uint32_t)N + 1u) * 4u;
-      uint32_t t = 0, x_acc = 0;
+      uint32_t t = 0, x_acc = sub == 0 ? 0u : kNever;
       uint64_t have = 0;                                     // lanes that hold an operation
       bool all_fed = !mine;
       u32x4_t a = {(uint32_t)N * 0x10001u, (uint32_t)N * 0x10001u, 0u, trash}, d = {0u, 0u, 0u, 0u};
@@ -180,27 +194,29 @@ __global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(SchedulePara
       int idle_phases = 0;
       for (uint32_t phase = 0; ; ++phase) {
         const uint32_t f = fed[((phase + 1) & 1) * 64 + (mine ? m : 0)];
-        const uint32_t avail = mine ? f & 0x7FFFFFFFu : 0u;
+        const uint32_t avail = mine ? ((f & 0x7FFFFFFFu) + (uint32_t)(R - 1 - sub)) / R : 0u;   // parts of this lane in its ring
         all_fed = !mine || (f >> 31);
         uint64_t moved = 0;
         if (have | __ballot(t < avail)) {
           {
-            lds_byte_t *const sp = ring_lane + ((t & (uint32_t)ring_mask) << 10);
+            lds_byte_t *const sp = ring_lane + (t & (uint32_t)ring_mask) * kRow;
             na = *(lds_vu32x4_t *)sp; nd = *(lds_vu32x4_t *)(sp + plane);
           }
-          for (int i = 0; i < trips; i += 8) {
+          for (int i = 0; i < schedule_steps(RW); i += 8) {
 #pragma unroll
             for (int sub = 0; sub < 8; ++sub) {
-              uint32_t x = max(max(max(e0 + d.x, e1 + d.y), e2 + d.z), e3 + d.w);
-              // the other lanes of the machine (they hold the same operation)
-              if (R >= 2) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0xB1, 0xF, 0xF, true));    // lane ^ 1
-              if (R >= 4) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x4E, 0xF, 0xF, true));    // lane ^ 2
-              if (R >= 8) x = max(x, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x141, 0xF, 0xF, true));   // 7 - lane of eight
-              x = max(x, x_acc);
-              const uint64_t ran_m = __ballot(x < kNever) & have;
+              // (a time of kNever or more plus a delay and the durations of R operations stays below 2^32: the library accepts no
+              // problem whose times could pass INT32_MAX)
+              const uint32_t polled = max(max(max(e0 + d.x, e1 + d.y), e2 + d.z), e3 + d.w);
+              const uint32_t at = R == 1 || lane_bit(have) ? polled : kNever;
+              uint32_t b = x_acc, y = max(at, b) + a.z;
+#pragma unroll
+              for (int k = 1; k < R; ++k) { b = min(b, before(y)); y = max(at, b) + a.z; }
+              const uint64_t ran_m = R == 1 ? __ballot(y < kNever) & have : __ballot(y < kNever);
               const bool ran = lane_bit(ran_m);
-              const uint32_t y = x + a.z;
-              x_acc = ran ? y : x_acc;                       // the machine is busy until y (chain edge, eq. (7))
+              // the machine is busy until y (chain edge, eq. (7))
+              if (R == 1) x_acc = ran ? y : x_acc;
+              else { const uint32_t last = before(y); x_acc = ran ? max(x_acc, last) : b; }
               if (LDSC) *(lds_vu32_t *)(uintptr_t)(ran ? a.w : trash) = y;
               else if (ran && a.w != trash) st_group(&p.cells[a.w >> 2], (int32_t)y);
               const uint64_t take_m = (ran_m | ~have) & __ballot(t < avail);
@@ -214,30 +230,32 @@ __global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(SchedulePara
               a.z = take ? na.z : a.z; a.w = take ? na.w : a.w;
               d.x = take ? nd.x : d.x; d.y = take ? nd.y : d.y; d.z = take ? nd.z : d.z; d.w = take ? nd.w : d.w;
               t += take ? 1u : 0u;
-              lds_byte_t *const sp = ring_lane + ((t & (uint32_t)ring_mask) << 10);
+              lds_byte_t *const sp = ring_lane + (t & (uint32_t)ring_mask) * kRow;
               na = *(lds_vu32x4_t *)sp; nd = *(lds_vu32x4_t *)(sp + plane);
             }
           }
         }
-        // (the lanes of a machine agree on every count)
-        if (mine && (lane % R) == 0) taken[(phase & 1) * 64 + m] = t;
+        uint32_t next = t * R + (uint32_t)sub;                 // the first part of the machine that has not been taken
+#pragma unroll
+        for (int s = 1; s < R; s <<= 1) next = min(next, __shfl_xor(next, s, kWave));
+        if (mine && sub == 0) taken[(phase & 1) * 64 + m] = next;
         const bool held = lane_bit(have), through = !held && all_fed && t == avail;
         int done = 0;
         if (__ballot(!through) == 0) done = 1;
-        // nothing moved in a whole phase although every unfinished machine holds an operation: a cycle.  (End times in
+        // nothing moved in a whole phase although every unfinished machine holds an operation (of the other relaxer too): a cycle.  (End times in
         // the L2: seen twice, so that a store on its way is never taken for one)
         else if (moved == 0 && __ballot(!through && !held) == 0) { if (++idle_phases >= (LDSC ? 1 : 2)) done = 2; }
         else idle_phases = 0;
         if (!done && phase >= max_phases) done = 3;
-        if (lane == 0) s_done[phase & 1] = done;
+        if (lane == 0) s_done[(phase & 1) * 2 + wave] = done;
         __syncthreads();
-        if (done) {
-          if (lane == 0 && done > 1) *s_flag = done == 2 ? kBitCyclic : kBitInternal;
+        if (const int end = phase_end(phase)) {
+          if (tid == 0 && end > 1) *s_flag = end == 2 ? kBitCyclic : kBitInternal;
           break;
         }
       }
       __builtin_amdgcn_s_setprio(0);
-    } else if (wave == 1) {
+    } else if (wave == RW) {
       // accountant: peak of the running memory level (eqs. (17)-(19)), only asked for when there are limits
       int k = off[lane];
       const int kend = p.mem_limit ? k + cnt[lane] : k;
@@ -258,12 +276,12 @@ __global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(SchedulePara
       for (uint32_t phase = 0; ; ++phase) {
         walk(2);
         __syncthreads();
-        if (s_done[phase & 1]) break;
+        if (phase_end(phase)) break;
       }
       walk(N);
       if (p.mem_limit && lane < P && base + peak > p.mem_limit[lane]) atomicOr(s_flag, kBitOverMemory);
     } else {
-      const int h = tid - 2 * kWave;
+      const int h = tid - (RW + 1) * kWave;
       const int team = (kScheduleHelpers * kWave) / Pseg >= kWave ? kWave : (kScheduleHelpers * kWave) / Pseg;   // threads per machine, 8 .. 64
       const int m = h / team, i = h - m * team;
       const bool on = m < P;
@@ -274,12 +292,12 @@ __global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(SchedulePara
       uint32_t f = 0, part0 = 0;                             // parts put into the ring; parts of the operation at pos among them
       for (uint32_t phase = 0; ; ++phase) {
         const uint32_t tk = on ? taken[((phase + 1) & 1) * 64 + m] : 0u;
-        const uint32_t room = on ? (uint32_t)p.slots - (f - tk) : 0u;
+        const uint32_t room = on ? (uint32_t)p.slots * R - (f - tk) : 0u;
         const int k = pos + i;
         const bool valid = on && k < pend;
         const int v = valid ? ld_group(&p.list[k]) : 0;
         const int lo = valid ? p.red_ptr[v] : 0, hi = valid ? p.red_ptr[v + 1] : 0;
-        const uint32_t parts = valid ? (uint32_t)max(1, (hi - lo + 4 * R - 1) / (4 * R)) : 0u;
+        const uint32_t parts = valid ? (uint32_t)max(1, (hi - lo + 3) / 4) : 0u;
         const uint32_t first = i == 0 ? part0 : 0u;
         const uint32_t n_mine = parts - (valid ? first : 0u);
         // inclusive prefix over the team, from ballots of the two low bits where those are all (a shuffle is an LDS trip)
@@ -301,23 +319,20 @@ __global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(SchedulePara
         for (uint32_t q = 0; q < n_put; ++q) {
           const uint32_t part = first + q;
           const bool last = part + 1 == parts;
-          const uint32_t slot = (f + excl + q) & (uint32_t)ring_mask;
+          const uint32_t seq = f + excl + q, slot = (seq / R) & (uint32_t)ring_mask;
           const uint32_t tail_z = last ? (uint32_t)p.dur[v] : 0u, tail_w = (last ? (uint32_t)v : (uint32_t)N + 1u) * 4u;
+          uint32_t u[4], dl[4];
 #pragma unroll
-          for (int r = 0; r < R; ++r) {
-            uint32_t u[4], dl[4];
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const int kk = lo + (int)part * 4 * R + r * 4 + e;
-              u[e] = kk < hi ? (uint32_t)p.red_idx[kk] : (uint32_t)N;
-            }
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dl[e] = u[e] < (uint32_t)N ? (uint32_t)comm[p.placement[u[e]] * P + m] : 0u;
-            lds_byte_t *const sp = ldsb + p.o_ring + (slot << 10) + (uint32_t)(m * R + r) * 16u;
-            const u32x4_t wa = {u[0] | (u[1] << 16), u[2] | (u[3] << 16), tail_z, tail_w}, wd = {dl[0], dl[1], dl[2], dl[3]};
-            *(lds_vu32x4_t *)sp = wa;
-            *(lds_vu32x4_t *)(sp + (uint32_t)p.slots * kWave * 16u) = wd;
+          for (int e = 0; e < 4; ++e) {
+            const int kk = lo + (int)part * 4 + e;
+            u[e] = kk < hi ? (uint32_t)p.red_idx[kk] : (uint32_t)N;
           }
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dl[e] = u[e] < (uint32_t)N ? (uint32_t)comm[p.placement[u[e]] * P + m] : 0u;
+          lds_byte_t *const sp = ldsb + p.o_ring + slot * kRow + ((uint32_t)(m * R) + seq % R) * 16u;
+          const u32x4_t wa = {u[0] | (u[1] << 16), u[2] | (u[3] << 16), tail_z, tail_w}, wd = {dl[0], dl[1], dl[2], dl[3]};
+          *(lds_vu32x4_t *)sp = wa;
+          *(lds_vu32x4_t *)(sp + (uint32_t)p.slots * kRow) = wd;
         }
         // how far the team got: operations that are in with all their parts, and the parts of the one that is not
         const bool whole = n_put == n_mine && valid;
@@ -330,7 +345,7 @@ __global__ __launch_bounds__(kScheduleThreads) void schedule_kernel(SchedulePara
         pos += (int)n_whole;
         if (i == 0) fed[(phase & 1) * 64 + m] = f | (pos >= pend ? 0x80000000u : 0u);
         __syncthreads();
-        if (s_done[phase & 1]) break;
+        if (phase_end(phase)) break;
       }
     }
     __syncthreads();

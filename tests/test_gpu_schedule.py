@@ -1,5 +1,5 @@
-"""Start and end times of one schedule against the oracle where the kernel's split changes: lanes per machine (8 down to
-1), end times in LDS and in the L2, both ring depths, operations of many parts (more than the ring holds)."""
+"""Start and end times of one schedule against the oracle where the kernel's split changes: lanes per machine (4 or
+2), one relaxer or two, end times in LDS and in the L2, both ring depths, operations of many parts (more than the ring holds)."""
 from __future__ import annotations
 
 import numpy as np
@@ -93,3 +93,22 @@ def test_schedule_with_limits_and_missing_channels(gpu_lib, n, p):
     assert {0, oracle.FLAG_OVER_MEMORY} <= seen
     assert n == 1 or oracle.FLAG_CYCLIC in seen
     assert p == 1 or oracle.FLAG_NO_CHANNEL in seen
+
+
+@pytest.mark.parametrize("n,p,fanin", [(3, 2, 1), (65, 3, 9), (130, 16, 14), (131, 17, 5), (260, 32, 9), (90, 33, 3), (400, 40, 6), (611, 64, 20)])
+def test_orders_of_every_kind(gpu_lib, n, p, fanin):
+    """Lists that end on any lane of a machine, machines without operations, cycles through one machine and through several (of both
+    relaxers beyond 32), malformed candidates."""
+    import torch
+    rng = np.random.default_rng(n * 100 + p)
+    w = W.random_instance(rng, n, p, 24, max_fanin=fanin, frac_arbitrary=0.4, frac_bad=0.2)
+    prob = oracle.Problem.of(w)
+    seen = set()
+    with gpu_lib.Evaluator.for_workload(w, max_candidates=1, shared_placement=None) as ev:
+        for pl, rk in zip(w.placement, w.rank):
+            s, e, f = (t.cpu().numpy() for t in ev.schedule(torch.from_numpy(pl).cuda(), torch.from_numpy(rk).cuda()))
+            flag, so, eo, _, _ = prob.schedule(pl, rk)
+            assert int(f[0]) == flag
+            assert (s == so).all() and (e == eo).all() if flag == 0 else (s == -1).all() and (e == -1).all()
+            seen.add(flag)
+    assert 0 in seen and (n < 65 or 1 in seen), seen
