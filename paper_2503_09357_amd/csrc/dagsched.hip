@@ -1069,9 +1069,8 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
   const int32_t N = h->N;
   const int32_t *pl = placement, *rk = rank;
   if (h->layout == DAGSCHED_CAND_MINOR) {
-    dim3 grid((unsigned)((n_cand + 63) / 64), (unsigned)((N + 63) / 64));
-    hipLaunchKernelGGL(transpose_i32_kernel, grid, dim3(256), 0, stream, placement, h->ws_tp, (int64_t)N, (int64_t)n_cand);
-    hipLaunchKernelGGL(transpose_i32_kernel, grid, dim3(256), 0, stream, rank, h->ws_tr, (int64_t)N, (int64_t)n_cand);
+    hipLaunchKernelGGL(transpose_i32_kernel, dim3((unsigned)((n_cand + 63) / 64), (unsigned)((N + 63) / 64), 2), dim3(256), 0, stream, placement, rank, h->ws_tp,
+                       h->ws_tr, (int64_t)N, (int64_t)n_cand);
     pl = h->ws_tp;
     rk = h->ws_tr;
   }
@@ -1490,13 +1489,12 @@ int dagsched_evaluate_contended(dagsched_t *h, int32_t n_cand, const int32_t *pl
   const int32_t N = h->N, E = h->E;
   const int32_t *pl = placement, *rk = rank, *er = edge_rank;
   if (h->layout == DAGSCHED_CAND_MINOR) {
-    dim3 grid((unsigned)((n_cand + 63) / 64), (unsigned)((N + 63) / 64));
-    hipLaunchKernelGGL(transpose_i32_kernel, grid, dim3(256), 0, stream, placement, h->ws_tp, (int64_t)N, (int64_t)n_cand);
-    hipLaunchKernelGGL(transpose_i32_kernel, grid, dim3(256), 0, stream, rank, h->ws_tr, (int64_t)N, (int64_t)n_cand);
+    hipLaunchKernelGGL(transpose_i32_kernel, dim3((unsigned)((n_cand + 63) / 64), (unsigned)((N + 63) / 64), 2), dim3(256), 0, stream, placement, rank, h->ws_tp,
+                       h->ws_tr, (int64_t)N, (int64_t)n_cand);
     pl = h->ws_tp; rk = h->ws_tr;
     if (E > 0) {
       dim3 egrid((unsigned)((n_cand + 63) / 64), (unsigned)((E + 63) / 64));
-      hipLaunchKernelGGL(transpose_i32_kernel, egrid, dim3(256), 0, stream, edge_rank, h->ws_te, (int64_t)E, (int64_t)n_cand);
+      hipLaunchKernelGGL(transpose_i32_kernel, egrid, dim3(256), 0, stream, edge_rank, nullptr, h->ws_te, nullptr, (int64_t)E, (int64_t)n_cand);
       er = h->ws_te;
     }
   }

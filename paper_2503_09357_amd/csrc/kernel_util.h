@@ -5,20 +5,29 @@
 
 namespace dagsched_dev {
 
-// [rows][cols] int32 -> [cols][rows], 64x64 tiles through LDS (both sides coalesced)
-__global__ __launch_bounds__(256) void transpose_i32_kernel(const int32_t *__restrict__ in, int32_t *__restrict__ out,
-                                                             int64_t rows, int64_t cols) {
+// Two arrays [rows][cols] int32 -> [cols][rows], 64x64 tiles through LDS (both sides coalesced), one array per blockIdx.z; the sixteen
+// loads of a thread are all on their way before the first is stored.  The evaluation of 2051 candidates of 3001
+// operations: 131 us with a launch for each array and its loads one after the other, 119 with this.
+__global__ __launch_bounds__(256) void transpose_i32_kernel(const int32_t *__restrict__ in0, const int32_t *__restrict__ in1, int32_t *__restrict__ out0,
+                                                             int32_t *__restrict__ out1, int64_t rows, int64_t cols) {
   __shared__ int32_t tile[64][65];
+  const int32_t *__restrict__ const in = blockIdx.z ? in1 : in0;
+  int32_t *__restrict__ const out = blockIdx.z ? out1 : out0;
   const int64_t r0 = (int64_t)blockIdx.y * 64, c0 = (int64_t)blockIdx.x * 64;
   const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  for (int i = ty; i < 64; i += 4) {
-    int64_t r = r0 + i, cc = c0 + tx;
-    if (r < rows && cc < cols) tile[i][tx] = in[r * cols + cc];
+  int32_t x[16];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int64_t r = r0 + ty + 4 * i, c = c0 + tx;
+    x[i] = in[(r < rows ? r : rows - 1) * cols + (c < cols ? c : cols - 1)];
   }
+#pragma unroll
+  for (int i = 0; i < 16; ++i) tile[ty + 4 * i][tx] = x[i];
   __syncthreads();
-  for (int i = ty; i < 64; i += 4) {
-    int64_t cc = c0 + i, r = r0 + tx;
-    if (r < rows && cc < cols) out[cc * rows + r] = tile[tx][i];
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int64_t c = c0 + ty + 4 * i, r = r0 + tx;
+    if (r < rows && c < cols) out[c * rows + r] = tile[tx][ty + 4 * i];
   }
 }
 
