@@ -793,6 +793,12 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
       uint32_t k = k0 + (uint32_t)(f * SUB + sub_lane);
       uint32_t addr = has_ops ? (uint32_t)list[min(k, klast)] : 0u;
       uint32_t ahead = has_ops ? (uint32_t)list[min(k + kStep, klast)] : 0u;
+      // With the placement bytes in L2 the vector cache's line accesses are what bounds the CU (layered graph, window mode: its address
+      // unit busy 87 % of the time, 8.5 accesses an operation): there a lane holds the aligned block of eight entries that its next entry is in.
+      // With that here and in the accountant 953 -> 761 us for 1024 candidates of 50000 operations.
+      constexpr bool kBlocks = PIBL == 0;
+      const uint4 *const blocks = (const uint4 *)list;
+      uint4 block = kBlocks && has_ops ? blocks[min(k + kStep, klast) >> 3] : make_uint4(0, 0, 0, 0);
       struct Entry { uint4 rec; uint32_t q0, q1, q2, q3, fl; };   // fl: 1 valid
       constexpr int kStages = PIBL ? 2 : 3;
       Entry E[kStages];
@@ -827,11 +833,20 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
           // (2) the entry after it (consumed one trip later at the earliest).  Lanes whose cursor stayed
           // keep theirs and all read the same entry instead, which costs the vector cache one line, not one per lane.
           const bool moved = pending;
-          addr = moved ? ahead : addr;
-          k += moved ? kStep : 0u;
+          if (kBlocks) {
+            k += moved ? kStep : 0u;
+            const uint32_t at = min(k, klast), lo = (at & 2u) ? block.y : block.x, hi = (at & 2u) ? block.w : block.z, w = (at & 4u) ? hi : lo;
+            const uint32_t entry = (at & 1u) ? w >> 16 : w & 0xFFFFu;
+            addr = moved ? entry : addr;
+            const uint32_t then = min(k + kStep, klast) >> 3;
+            if (moved && then != at >> 3) block = blocks[then];
+          } else {
+            addr = moved ? ahead : addr;
+            k += moved ? kStep : 0u;
+            const uint32_t entry = list[moved ? min(k + kStep, klast) : 0u];
+            ahead = moved ? entry : ahead;
+          }
           aseq += moved ? (uint32_t)kFeeders : 0u;
-          const uint32_t entry = list[moved ? min(k + kStep, klast) : 0u];
-          ahead = moved ? entry : ahead;
           // (3) admission
           // (measured: with two predecessors per op a branch around the read for exhausted lanes pays, 3 %; else not, 1 %)
           lds_vu32_t *const mark_p = (lds_vu32_t *)(ring_lane + ((aseq & (uint32_t)(RING - 1)) << 10) + 12);
@@ -887,23 +902,22 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
     const int n = has_ops ? (int)totalw[ql] : 0, stretch = (n + SUB - 1) / SUB;
     const int k0 = (has_ops ? (int)offw[ql] : 0) + min(n, sub_lane * stretch), kend = k0 + min(stretch, n - min(n, sub_lane * stretch));
     int64_t level = 0, base = 0;                            // level above the machine's base; base = static memory on it (eq. (16))
-    uint32_t id[kEight];
-    auto entries = [&](int k) {
-#pragma unroll
-      for (int u = 0; u < kEight; ++u) id[u] = list[k + u < kend ? k + u : 0];
-    };
-    entries(k0);
-    for (int k = k0; __ballot(k < kend) != 0; k += kEight) {
+    // (rows of the lists are a multiple of 128 bytes: a block of eight entries is one access of the vector cache, which is what bounds
+    // the window mode)
+    const uint4 *const blocks = (const uint4 *)list;
+    uint4 block = blocks[k0 < kend ? k0 >> 3 : 0];
+    for (int k = k0 & ~7; __ballot(k < kend) != 0; k += kEight) {
       int64_t m[kEight], wt[kEight];
       bool on[kEight];
 #pragma unroll
       for (int u = 0; u < kEight; ++u) {
-        on[u] = k + u < kend && (KIND != 0 || id[u] <= vmask);   // (an operation counts with its first part)
-        const uint32_t v = on[u] ? id[u] : 0u;
+        const uint32_t w = u < 2 ? block.x : u < 4 ? block.y : u < 6 ? block.z : block.w, id = (u & 1) ? w >> 16 : w & 0xFFFFu;
+        on[u] = k + u >= k0 && k + u < kend && (KIND != 0 || id <= vmask);   // (an operation counts with its first part)
+        const uint32_t v = on[u] ? id : 0u;
         m[u] = p.mem_delta[v];
         wt[u] = p.weight ? p.weight[v] : 0;
       }
-      entries(k + kEight);
+      block = blocks[k + kEight < kend ? (k + kEight) >> 3 : 0];
 #pragma unroll
       for (int u = 0; u < kEight; ++u)
         if (on[u]) { level += m[u]; peak = max(peak, level); base += wt[u]; }   // eq. (19) along the chain
