@@ -1124,7 +1124,7 @@ int launch_evaluate(dagsched *h, int32_t n_cand, const int32_t *placement, const
   if (h->d_no_channel) {
     // few candidates: larger workgroups, or the chip's wavefront slots stay empty
     const bool listed = h->shared_keeps_channels && (h->pl_stream.total || h->variant == kVariantStatic);
-    const unsigned threads = listed || n_cand < 2048 ? 1024 : 256, blocks = listed ? std::min((unsigned)n_cand, 256u) : (unsigned)n_cand;
+    const unsigned threads = !listed && n_cand < 2048 ? 1024 : 256, blocks = listed ? std::min((unsigned)n_cand, 512u) : (unsigned)n_cand;
     hipLaunchKernelGGL(channel_flag_kernel, dim3(blocks), dim3(threads), channel_flag_lds(N), stream, N, h->E,
                        h->P, h->d_edges, h->d_no_channel, pl, n_cand, listed ? h->d_fb_list : nullptr, listed ? h->d_fb_count : nullptr, out);
   }
@@ -1565,7 +1565,7 @@ int launch_propose(dagsched_t *h, int32_t n_cand, const int32_t *base_placement,
   if (n_cand == 0) return DAGSCHED_OK;
   if (!base_placement || !base_rank || !rnd || !placement || !rank) return DAGSCHED_EINVAL;
   hipStream_t stream = (hipStream_t)hip_stream;
-  hipLaunchKernelGGL(machine_count_kernel, dim3(1), dim3(256), 0, stream, h->N, h->P, base_placement, h->ws_cnt);
+  hipLaunchKernelGGL(machine_count_kernel, dim3(1), dim3(1024), 0, stream, h->N, h->P, base_placement, h->ws_cnt);
   ProposeParams p;
   p.N = h->N; p.P = h->P; p.C = n_cand;
   p.base_pl = base_placement; p.base_rk = base_rank; p.rnd = rnd; p.cnt = h->ws_cnt;

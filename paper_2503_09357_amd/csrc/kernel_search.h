@@ -6,15 +6,25 @@
 
 namespace dagsched_dev {
 
-// operations per machine of the base schedule (placements outside [0, P) are not counted)
-__global__ __launch_bounds__(256) void machine_count_kernel(int32_t N, int32_t P, const int32_t *__restrict__ pl,
-                                                             int32_t *__restrict__ cnt) {
+// operations per machine of the base schedule (placements outside [0, P) are not counted).  One workgroup, which waits out
+// every trip to memory: sixteen loads of a thread are on their way together (11712 operations: 13.8 us with one at a time and 256 threads, 4.4 with this).
+__global__ __launch_bounds__(1024) void machine_count_kernel(int32_t N, int32_t P, const int32_t *__restrict__ pl,
+                                                              int32_t *__restrict__ cnt) {
   __shared__ int32_t h[DAGSCHED_MAX_DEVICES];
+  constexpr int kLoads = 16;
+  int32_t m[kLoads];
+  auto request = [&](int i0) {
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u) m[u] = i0 + u * 1024 < N ? pl[i0 + u * 1024] : -1;
+  };
+  request((int)threadIdx.x);
   if (threadIdx.x < DAGSCHED_MAX_DEVICES) h[threadIdx.x] = 0;
   __syncthreads();
-  for (int i = threadIdx.x; i < N; i += blockDim.x) {
-    const int32_t m = pl[i];
-    if ((uint32_t)m < (uint32_t)P) atomicAdd(&h[m], 1);
+  for (int i0 = (int)threadIdx.x; i0 < N; i0 += kLoads * 1024) {
+    if (i0 != (int)threadIdx.x) request(i0);
+#pragma unroll
+    for (int u = 0; u < kLoads; ++u)
+      if ((uint32_t)m[u] < (uint32_t)P) atomicAdd(&h[m[u]], 1);
   }
   __syncthreads();
   if (threadIdx.x < DAGSCHED_MAX_DEVICES) cnt[threadIdx.x] = h[threadIdx.x];
@@ -37,8 +47,9 @@ struct ProposeParams {
 //            m2 != m: v is inserted at position r3 mod (n_m2 + 1) of m2.
 // orders_only: m2 = m whatever r2 is (the candidates keep the base's placement).
 // A workgroup (several for few candidates: blockIdx.y) per candidate; the move is the same for every thread, each thread rewrites some operations,
-// four at a time where rows allow 16-byte accesses (VEC).  What bounds it is what it writes: 4096 neighbours of 768 operations, 25 MB, 12.8 us with
-// 4-byte accesses.
+// four at a time where rows allow 16-byte accesses (VEC).  What bounds it: what it writes, and the chain of three trips to memory in front of
+// that.  256 neighbours of 11712 operations, 24 MB: 8.6 us; 4096 of 768, 25 MB: 13 us (a wavefront to a candidate instead, its first rows requested
+// before the chain: 12.2 and 13.5).
 template <bool VEC>
 __global__ __launch_bounds__(256) void propose_kernel(ProposeParams p) {
   const int c = blockIdx.x;
