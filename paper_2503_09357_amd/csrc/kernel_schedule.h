@@ -76,7 +76,8 @@ __global__ __launch_bounds__(schedule_threads(RW)) void schedule_kernel(Schedule
   uint32_t *const taken = (uint32_t *)(off + 64);            // [2][64] parts the relaxer has taken from the ring
   uint32_t *const fed = taken + 128;                         // [2][64] parts in the ring so far, | 0x80000000: that is all
   int32_t *const s_flag = (int32_t *)(fed + 128);
-  int32_t *const s_done = s_flag + 1;                        // [2][2] of a relaxer: 1 = through, 2 = stuck, 3 = the bound on the phases, 0 = on its way
+  int32_t *const s_done = s_flag + 1;                        // [2][2] of a relaxer: 1 = through, 2 = stuck, 3 = the bound on the phases, 0 = on its way; + kMoved
+  constexpr int kMoved = 4;                                  // ... something has run in this phase, or was taken
   constexpr uint32_t kRow = RW * kWave * 16u;                // bytes of a ring slot of all lanes, in either plane
   uint32_t *const seen = (uint32_t *)(lds + p.o_ring);       // [N bits] ingest only
   uint32_t *const cellw = (uint32_t *)lds;                   // [N + 2] end times; N: "ended at 0", N + 1: trash
@@ -162,10 +163,12 @@ __global__ __launch_bounds__(schedule_threads(RW)) void schedule_kernel(Schedule
   // ---------------------------------------------------------------- relaxation
   if (!bits) {
     const int ring_mask = p.slots - 1;
-    // how a phase has ended: 0 it goes on, 1 through, 2 nothing moved anywhere, 3
+    // how a phase has ended: 0 it goes on, 1 through, 2 nothing moved anywhere, 3.  (What a stuck relaxer waits for may have run in this very
+    // phase, in the other relaxer's last step before that one was through.)
     auto phase_end = [&](uint32_t phase) -> int {
       const int a = s_done[(phase & 1) * 2], b = RW == 2 ? s_done[(phase & 1) * 2 + 1] : 1;
-      return a && b ? max(a, b) : 0;
+      const int end = (a & 3) && (b & 3) ? max(a & 3, b & 3) : 0;
+      return end == 2 && ((a | b) & kMoved) ? 0 : end;
     };
     // (every phase completes a part, or takes one, or the helpers bring one)
     const uint32_t max_phases = 4u * ((uint32_t)N + (uint32_t)p.n_red) + 64u;
@@ -242,17 +245,18 @@ __global__ __launch_bounds__(schedule_threads(RW)) void schedule_kernel(Schedule
         const bool held = lane_bit(have), through = !held && all_fed && t == avail;
         int done = 0;
         if (__ballot(!through) == 0) done = 1;
-        // nothing moved in a whole phase although every unfinished machine holds an operation (of the other relaxer too): a cycle.  (End times in
-        // the L2: seen twice, so that a store on its way is never taken for one)
+        // nothing moved in a whole phase, here and in the other relaxer, although every unfinished machine holds an operation: a cycle.  (End times in
+        // the L2: seen in two phases on end, so that a store on its way is never taken for one)
         else if (moved == 0 && __ballot(!through && !held) == 0) { if (++idle_phases >= (LDSC ? 1 : 2)) done = 2; }
         else idle_phases = 0;
         if (!done && phase >= max_phases) done = 3;
-        if (lane == 0) s_done[(phase & 1) * 2 + wave] = done;
+        if (lane == 0) s_done[(phase & 1) * 2 + wave] = done | (moved ? kMoved : 0);
         __syncthreads();
         if (const int end = phase_end(phase)) {
           if (tid == 0 && end > 1) *s_flag = end == 2 ? kBitCyclic : kBitInternal;
           break;
         }
+        if (RW == 2 && (s_done[(phase & 1) * 2 + (wave ^ 1)] & kMoved)) idle_phases = 0;
       }
       __builtin_amdgcn_s_setprio(0);
     } else if (wave == RW) {

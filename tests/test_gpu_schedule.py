@@ -1,5 +1,5 @@
 """Start and end times of one schedule against the oracle where the kernel's split changes: lanes per machine (4 or
-2), one relaxer or two, end times in LDS and in the L2, both ring depths, operations of many parts (more than the ring holds)."""
+2), one relaxer or two, end times in LDS and in the L2, every ring depth (8 slots only with two relaxers), operations of many parts (more than the ring holds)."""
 from __future__ import annotations
 
 import numpy as np
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,p,fanin,window", [
     (1, 1, 1, None), (2, 64, 1, None), (700, 1, 5, 30), (513, 8, 40, None), (514, 9, 33, 200), (640, 16, 17, 100), (641, 17, 9, 90),
-    (1300, 32, 8, 60), (1301, 33, 5, 60), (3000, 64, 12, 300), (19400, 64, 4, 400), (24000, 5, 3, 200), (28500, 31, 4, 500), (50001, 12, 4, 300)])
+    (1300, 32, 8, 60), (1301, 33, 5, 60), (3000, 64, 12, 300), (19400, 64, 4, 400), (24000, 64, 4, 400), (24000, 5, 3, 200), (28500, 31, 4, 500), (50001, 12, 4, 300)])
 def test_schedule_at_the_edges_of_its_splits(gpu_lib, n, p, fanin, window):
     import torch
     rng = np.random.default_rng(n)
@@ -112,3 +112,30 @@ def test_orders_of_every_kind(gpu_lib, n, p, fanin):
             assert (s == so).all() and (e == eo).all() if flag == 0 else (s == -1).all() and (e == -1).all()
             seen.add(flag)
     assert 0 in seen and (n < 65 or 1 in seen), seen
+
+
+@pytest.mark.parametrize("p,fillers,lengths", [(33, 0, 40), (64, 0, 40), (64, 31000, 16)])
+@pytest.mark.parametrize("upper", [True, False])
+def test_one_relaxer_ends_while_the_other_waits(gpu_lib, p, fillers, lengths, upper):
+    """Beyond 32 machines: a chain over two machines of one relaxer and an operation of the other that waits for its end, for every
+    length up to some phases; end times in LDS and (fillers in front of the chain) in the L2.  Whichever step of a phase the first relaxer's
+    last one is, the second has to see it."""
+    import torch
+    here = np.arange(32, p) if upper else np.arange(0, 32)   # the chain's half
+    one, two = (32, min(33, p - 1)) if upper else (0, 1)
+    waits = 0 if upper else p - 1
+    for k in range(1, lengths + 1):
+        n = fillers + k + 1
+        chain = fillers + np.arange(k + 1)
+        rp, ci = W.csr_from_edges(n, chain[:-1], chain[1:])
+        pl = np.concatenate([here[np.arange(fillers) % len(here)], np.where(np.arange(k) % 2, two, one), [waits]]).astype(np.int32)
+        rk = np.zeros(n, np.int32)
+        for m in np.unique(pl):
+            at = np.nonzero(pl == m)[0]
+            rk[at] = np.arange(len(at))
+        w = W.Workload("chain", p, rp, ci, np.full(n, 2, np.int32), np.full((p, p), 3, np.int32), np.zeros(n, np.int64), pl[None], rk[None])
+        flag, so, eo, _, _ = oracle.Problem.of(w).schedule(pl, rk)
+        assert flag == 0
+        with gpu_lib.Evaluator.for_workload(w, max_candidates=1, shared_placement=None) as ev:
+            s, e, f = (t.cpu().numpy() for t in ev.schedule(torch.from_numpy(pl).cuda(), torch.from_numpy(rk).cuda()))
+        assert int(f[0]) == 0 and (s == so).all() and (e == eo).all(), k
