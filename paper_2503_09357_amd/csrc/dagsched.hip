@@ -99,7 +99,7 @@ struct dagsched {
   int64_t *d_mem = nullptr, *d_weight = nullptr, *d_limit = nullptr;
   int32_t *ws_list = nullptr, *ws_end = nullptr;
   // ring kernel
-  int32_t ring_G = 0, ring_sub = 1, ring_slots = 0, ring_feeders = 1, ring_kind = 0, ring_block = 256, rec_plane = 0, id_bits = 16, time_scale = 1;
+  int32_t ring_G = 0, ring_sub = 1, ring_by_ops = 0, ring_slots = 0, ring_feeders = 1, ring_kind = 0, ring_block = 256, rec_plane = 0, id_bits = 16, time_scale = 1;
   uint8_t *d_nparts = nullptr;
   int64_t list_stride = 0, pib_stride = 0;
   bool shared_keeps_channels = false;                       // the shared placement is named and needs no missing channel
@@ -108,7 +108,7 @@ struct dagsched {
   // Fallback of the optimistic 16-bit run and of the window mode: the same problem in the 32-bit form of the ring
   // kernel (exact), launched over the list of candidates the first run left, or the pipeline kernel that stands in front of
   // it; fb_G == 0: the general kernel instead
-  int32_t fb_G = 0, fb_sub = 1, fb_slots = 0, fb_feeders = 1, fb_block = 256, fb_kind = 0;
+  int32_t fb_G = 0, fb_sub = 1, fb_by_ops = 0, fb_slots = 0, fb_feeders = 1, fb_block = 256, fb_kind = 0;
   bool ring_exact = false;                // a ring kernel is planned that takes any candidate
   bool fb_optimistic = false;             // the fallback is itself a 16-bit run with the general kernel behind it (window mode on
                                           // a problem too large for 32-bit cells)
@@ -336,7 +336,8 @@ struct RingPlan {
   LdsLayout lds{};
   std::vector<uint4> rec;
   int rec_plane = 0, id_bits = 16;
-  int64_t total_parts = 0;
+  bool by_ops = false;                                 // order lists of operations, else of op parts
+  int64_t total_parts = 0, list_row = 0;               // op parts; entries of a candidate's order lists
   std::vector<uint8_t> nparts;
   std::vector<int32_t> comm_scaled;
   // window mode: cells per candidate (0: off), the layout and workgroup size of the ingest launch
@@ -575,6 +576,7 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   const bool deep = 3 * (int64_t)levels * P > (int64_t)N;
   double best_score = -1;
   int best_wgs = 0, best_at_once = 0;
+  int64_t best_rounds = 1;
   for (int G = kWave / Pseg; G >= 1; G >>= 1) {
     if (force_g && G != force_g) continue;
     for (int pib_lds : {1, 2, 0}) {
@@ -617,7 +619,7 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
         const double rate = lanes * (ring >= 8 ? 1.0 : sub > 1 ? 0.8 : 0.7) * (pib_lds == 1 ? 1.0 : pib_lds == 2 ? 0.99 : plan.kind == 2 ? 0.85 : 0.7) *
                             (G * Pseg * sub < kWave ? 0.65 : 1.0) * (ring == 16 ? 1.001 : 1.0);
         const double score = rate / ((double)rounds * (1.0 + 0.05 * (double)(std::min<int64_t>(wgs, at_once) - 1)));
-        if (score > best_score) { best_score = score; best_wgs = wgs; best_at_once = (int)std::min<int64_t>(wgs, at_once); plan.G = G; plan.sub = sub; plan.ring = ring; plan.lds = o; }
+        if (score > best_score) { best_score = score; best_wgs = wgs; best_at_once = (int)std::min<int64_t>(wgs, at_once); best_rounds = rounds; plan.G = G; plan.sub = sub; plan.ring = ring; plan.lds = o; }
       }
     }
   }
@@ -636,6 +638,14 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   if (plan.kind == 3 && (win_log2 || wide || plan.cell32 || !built(plan.feeders))) plan.kind = 2;
   if (!force_feeders && !built(plan.feeders)) plan.feeders = 2;
   if (best_score < 0 || !built(plan.feeders)) return plan;   // shape not built
+  // Order lists of operations or of op parts (by_ops in the kernel).  Parts pay where the feeders have to keep many machines busy (few levels of B for
+  // every operation of a machine) or step through many parts, and a good deal of that again where another workgroup relaxes meanwhile; a machine of
+  // one or two operations has nothing to be fed.  Measured, lists of operations over lists of parts (us; levels * P * N / parts^2 and rounds in brackets): MoE graph on 32 machines of
+  // one micro-batch 200 / 212 (11, 2) and of eight 248 / 237 (1.4, 3), 4096 candidates each; random graphs of 1464 operations on 16 machines 101 / 110 (0.9, 1), on
+  // 64 with 7.8 parts to an operation 202 / 183 (0.35, 1); of 301 on 64 470 / 505 with 1.4 parts (5, 23); of 60 on 64 309 / 352 (12, 23).
+  plan.by_ops = plan.kind == 0 && plan.sub == 1 && !win_log2 &&
+                (N < 3 * P || (double)levels * P * N > (best_rounds >= 2 ? 1.5 : 0.8) * (double)plan.total_parts * (double)plan.total_parts);
+  plan.list_row = plan.by_ops ? N : plan.total_parts;
   // the nibble kernels start time at 255 (see the kernel), which the 16-bit range must hold as well
   // (a candidate that does not fit the window goes to the int32 kernel like one that leaves the 16-bit range: window
   // mode always runs with that kernel behind it)
@@ -1028,7 +1038,7 @@ RingParams ring_params(const dagsched *h, int32_t n_cand, const int32_t *pl, con
   p.N = N; p.P = h->P; p.Pseg = h->Pseg; p.log_pseg = ilog2(h->Pseg); p.G = h->ring_G; p.C = n_cand;
   p.optimistic = optimistic ? 1 : 0;
   p.list_stride = h->list_stride;
-  p.rec = h->d_rec; p.rec_plane = h->rec_plane; p.id_bits = h->id_bits; p.nparts = h->d_nparts; p.comm = h->d_comm_scaled; p.mem_delta = h->d_mem;
+  p.rec = h->d_rec; p.rec_plane = h->rec_plane; p.id_bits = h->id_bits; p.by_ops = h->ring_by_ops; p.nparts = h->d_nparts; p.comm = h->d_comm_scaled; p.mem_delta = h->d_mem;
   p.weight = h->d_weight; p.mem_limit = h->d_limit;
   p.sum_dur = h->sum_dur; p.time_scale = h->time_scale;
   p.placement = pl; p.rank = rk;
@@ -1052,7 +1062,7 @@ void launch_listed(dagsched *h, int32_t n_cand, const int32_t *pl, const int32_t
     RingParams p = ring_params(h, n_cand, pl, rk, out, !exact && h->fb_optimistic);
     p.cand_list = h->d_fb_list; p.cand_count = h->d_fb_count;
     if (!exact) {
-      p.G = h->fb_G; p.lds = h->fb_lds;
+      p.G = h->fb_G; p.lds = h->fb_lds; p.by_ops = h->fb_by_ops;
       p.fb_list = h->d_fb_list + h->max_cand; p.fb_count = h->d_fb_count + 1;   // (what this run leaves in its turn)
       second_list = p.fb_list; second_count = p.fb_count;
     }
@@ -1296,13 +1306,12 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   if (ok && plan.ok) {
     h->variant = !plan.exact ? kVariantRingOptimistic : plan.cell32 ? kVariantRing32 : kVariantRingExact;   // (window mode is never exact)
     h->ring_exact = plan.exact;
-    h->ring_G = plan.G; h->ring_sub = plan.sub; h->ring_slots = plan.ring; h->ring_feeders = plan.feeders; h->ring_kind = plan.kind; h->ring_block = plan.block; h->lds = plan.lds; h->time_scale = plan.scale;
+    h->ring_G = plan.G; h->ring_sub = plan.sub; h->ring_by_ops = plan.by_ops; h->ring_slots = plan.ring; h->ring_feeders = plan.feeders; h->ring_kind = plan.kind; h->ring_block = plan.block; h->lds = plan.lds; h->time_scale = plan.scale;
     h->rec_plane = plan.rec_plane; h->id_bits = plan.id_bits;
     const int64_t cap = ((int64_t)h->N + h->E + 1024) * 64;
     h->spin_cap = (uint32_t)std::min<int64_t>(cap, 0x7FFFFFFF);
-    h->list_stride = (plan.total_parts + 63) / 64 * 64;   // an entry per op part
-    ok = dev_alloc(&h->ws_list16, maxc * (size_t)h->list_stride) &&
-         (plan.lds.pib_mode != 0 || dev_alloc(&h->ws_pib, maxc * (size_t)h->pib_stride));   // only read when the placement is not in LDS
+    int64_t list_row = plan.list_row;
+    ok = plan.lds.pib_mode != 0 || dev_alloc(&h->ws_pib, maxc * (size_t)h->pib_stride);   // only read when the placement is not in LDS
     if (ok && !plan.exact) ok = dev_alloc(&h->d_fb_count, 2) && dev_alloc(&h->d_fb_list, 2 * maxc);   // (two lists)
     if (ok && !plan.exact && !plan.lds.wide) {
       // the candidates a 16-bit or window run leaves behind: 32-bit end times, a cell per operation, where that fits
@@ -1316,7 +1325,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       // (same records, part counts and delays: both plans divide by the same common factor and drop the same edges)
       if (fp.ok && fp.exact && fp.cell32 && !fp.lds.wide && fp.scale == plan.scale && fp.rec_plane == plan.rec_plane &&
           fp.id_bits == plan.id_bits && fp.rec.size() == plan.rec.size()) {
-        h->fb_G = fp.G; h->fb_sub = fp.sub; h->fb_slots = fp.ring; h->fb_feeders = fp.feeders; h->fb_block = fp.block; h->fb_lds = fp.lds; h->fb_kind = fp.kind;
+        h->fb_G = fp.G; h->fb_sub = fp.sub; h->fb_by_ops = fp.by_ops; list_row = std::max(list_row, fp.list_row); h->fb_slots = fp.ring; h->fb_feeders = fp.feeders; h->fb_block = fp.block; h->fb_lds = fp.lds; h->fb_kind = fp.kind;
         if (fp.lds.pib_mode == 0 && !h->ws_pib) ok = dev_alloc(&h->ws_pib, maxc * (size_t)h->pib_stride);
         const void *fk = (const void *)fallback_kernel(h);
         if (!fk) h->fb_G = 0;
@@ -1329,7 +1338,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
         const RingPlan gp = plan_ring(&fd, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
         if (gp.ok && !gp.cell32 && !gp.win_log2 && !gp.lds.wide && gp.scale == plan.scale && gp.rec_plane == plan.rec_plane &&
             gp.id_bits == plan.id_bits && gp.rec.size() == plan.rec.size()) {
-          h->fb_G = gp.G; h->fb_sub = gp.sub; h->fb_slots = gp.ring; h->fb_feeders = gp.feeders; h->fb_block = gp.block; h->fb_lds = gp.lds; h->fb_kind = gp.kind;
+          h->fb_G = gp.G; h->fb_sub = gp.sub; h->fb_by_ops = gp.by_ops; list_row = std::max(list_row, gp.list_row); h->fb_slots = gp.ring; h->fb_feeders = gp.feeders; h->fb_block = gp.block; h->fb_lds = gp.lds; h->fb_kind = gp.kind;
           h->fb_optimistic = !gp.exact;
           if (gp.lds.pib_mode == 0 && !h->ws_pib) ok = dev_alloc(&h->ws_pib, maxc * (size_t)h->pib_stride);
           const void *gk = (const void *)fallback_kernel(h);
@@ -1338,6 +1347,8 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
         }
       }
     }
+    h->list_stride = (list_row + 63) / 64 * 64;
+    ok = ok && dev_alloc(&h->ws_list16, maxc * (size_t)h->list_stride);
     if (ok && plan.win_log2) {
       h->lds_ingest = plan.lds_ingest; h->ingest_block = plan.ingest_block; h->win_magic = plan.win_magic;
       ok = dev_alloc(&h->ws_meta, ((maxc + plan.G - 1) / plan.G) * 4 * (size_t)kWave) &&

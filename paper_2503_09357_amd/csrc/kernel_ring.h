@@ -41,6 +41,8 @@
 // accesses in order, so a delivered last dword proves that the rest of the slot is complete.
 #pragma once
 
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace dagsched_dev {
@@ -79,6 +81,8 @@ struct RingParams {
   const uint4 *rec;                    // shared operator records (times divided by time_scale)
   int32_t rec_plane;                   // records per part plane (>= N)
   int32_t id_bits;                     // order-list entry = node | part << id_bits
+  int32_t by_ops;                      // 1: an entry is an operation, node | (parts - 1) << id_bits, whose parts the feeders step through (the
+                                       // general kind with one lane per machine)
   const uint8_t *nparts;               // [N] parts per node, or NULL when every node has one part
   const int32_t *comm;                 // [P*P] channel delays divided by time_scale (all <= 255)
   const int64_t *mem_delta;            // [N]
@@ -87,7 +91,7 @@ struct RingParams {
   int64_t sum_dur;                     // in original units
   int32_t time_scale;                  // gcd of every duration and delay
   const int32_t *placement, *rank;     // [C][N]
-  uint16_t *ws_list;                   // [C][list_stride] the machines' op parts in the order they run
+  uint16_t *ws_list;                   // [C][list_stride] the machines' op parts (by_ops: operations) in the order they run
   uint8_t *ws_pib;                     // [C][pib_stride] placement as one byte per node; entry N = P (the dummy node's machine)
   int64_t pib_stride;
   int32_t *fb_count, *fb_list;         // candidates left to the fallback (the 32-bit form of this kernel, or the general kernel)
@@ -171,6 +175,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
   const int lane = tid & 63;
   const int N = p.N, P = p.P, Pseg = p.Pseg, G = p.G;
   const int M = G * Pseg;                                   // machines of the workgroup's candidates
+  const bool by_ops = KIND == 0 && SUB == 1 && p.by_ops != 0;
   const int L = M * SUB;                                    // lanes in use per wavefront
   const int64_t c0 = (int64_t)blockIdx.x * G;
   // (a launch over a list of candidates is sized for the longest list possible: the workgroups beyond its end leave)
@@ -385,17 +390,19 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
   }
   __syncthreads();
   // Order lists to HBM, looking for unwritten slots on the way.  Feeders and accountant walk op parts, so an operation of
-  // several is several entries there: a feeder that stepped through the parts of an operation itself spent half of its
-  // instructions on that.
-  uint32_t *const row_off = (uint32_t *)(lds + o.o_scr);    // [M] start of the machine in that list (KIND 0)
-  if (KIND == 0) {
+  // several is several entries there (a feeder that steps through the parts of an operation itself spends half of its
+  // instructions on that), unless the host takes by_ops: putting the entries in place costs ingest four times a copy's
+  // instructions, 19 k cycles of a workgroup against 3.5 k (MoE graph of one micro-batch, 1464 operations, two candidates).
+  uint32_t *const row_off = (uint32_t *)(lds + o.o_scr);    // [M] start of the machine in that list (op parts)
+  if (KIND == 0 && !by_ops) {
     if (wave == 0) {
       const uint32_t start = prefix(lane < M ? cntw[lane] + (int)totalw[lane] : 0);
       if (lane < M) row_off[lane] = start;
     }
     __syncthreads();
     // some consecutive machines to a wavefront, an operation to a lane; the parts in front of a lane's are counted with ballots
-    const int n_waves = kThreads >> 6, per_cand = max(1, min(Pseg, n_waves / G)), part_bits = 16 - p.id_bits;
+    const int n_waves = kThreads >> 6, part_bits = 16 - p.id_bits;
+    const int per_cand = max(1, min(Pseg, n_waves / G));
     const uint32_t part1 = 1u << p.id_bits;
     for (int job = wave; job < ng * per_cand; job += n_waves) {
       const int gg = job / per_cand, m0 = (job % per_cand) * Pseg / per_cand, m1 = (job % per_cand + 1) * Pseg / per_cand;
@@ -418,6 +425,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
           // (an unwritten slot, whose candidate is flagged, counts as one part: nothing goes beyond the row)
           const uint32_t np1 = on && !hole ? w[u] >> p.id_bits : 0u;
           uint32_t i = to + (uint32_t)lane;
+          const uint32_t block_at = to;
           to += kWave;
           for (int k = 0; k < part_bits; ++k) {
             const uint64_t m = __ballot((np1 >> k) & 1u);
@@ -425,10 +433,31 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
             to += (uint32_t)__popcll(m) << k;
           }
           uint32_t v = w[u] & (part1 - 1u);
-          if (on) dst[i] = (uint16_t)v;
-          for (uint32_t part = 1; __ballot(np1 >= part) != 0; ++part) {
-            v += part1;
-            if (np1 >= part) dst[i + part] = (uint16_t)v;
+          if (SUB > 1 || to - block_at <= 2u * kWave) {
+            if (on) dst[i] = (uint16_t)v;
+            for (uint32_t part = 1; __ballot(np1 >= part) != 0; ++part) {
+              v += part1;
+              if (np1 >= part) dst[i + part] = (uint16_t)v;
+            }
+          } else {
+            // More than two parts to an operation on the average: runs of 8, 4, 2 and 1 entries, at any even address, a store for every bit of the
+            // number of parts and not for every part (1464 operations of up to 15 parts, four candidates: 175 k cycles, with this 55 k; with
+            // several lanes per machine not built: the MoE graph, which has no use for it, took 0.7 % longer beside it).
+            uint32_t np = on ? np1 + 1u : 0u;
+            uint16_t *out = dst + i;
+            auto run = [&](auto words) {                     // 2 * words parts
+              constexpr uint32_t kWords = decltype(words)::value;
+              uint32_t r[kWords];
+#pragma unroll
+              for (uint32_t k = 0; k < kWords; ++k) r[k] = (v + 2u * k * part1) | ((v + (2u * k + 1u) * part1) << 16);
+              __builtin_memcpy(out, r, sizeof r);
+              out += 2 * kWords;
+              v += 2u * kWords * part1;
+            };
+            for (; np >= 8u; np -= 8u) run(std::integral_constant<uint32_t, 4>());
+            if (np & 4u) run(std::integral_constant<uint32_t, 2>());
+            if (np & 2u) run(std::integral_constant<uint32_t, 1>());
+            if (np & 1u) *out = (uint16_t)v;
           }
         }
       }
@@ -448,7 +477,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
   __syncthreads();                                          // workgroup scope: the lists are read by this workgroup only
   if (tid < M) {
     totalw[tid] += (uint32_t)cntw[tid];                     // ops per machine: its operations plus their further parts
-    offw[tid] = KIND == 0 ? row_off[tid] : offw[tid] & 0xFFFFu;
+    offw[tid] = KIND == 0 && !by_ops ? row_off[tid] : offw[tid] & 0xFFFFu;
   }
   if (PHASE == 1) {                                         // the relaxation is a launch of its own
     if (tid < M) { meta[tid] = cntw[tid]; meta[kWave + tid] = (int32_t)offw[tid]; meta[2 * kWave + tid] = (int32_t)totalw[tid]; }
@@ -774,6 +803,8 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
         }
       }
     } else {
+      auto feed = [&](auto stepping) {
+      constexpr bool kStepping = decltype(stepping)::value;   // the lists hold operations (by_ops)
       // A part is ADMITTED when the relaxer has copied the previous part out of its ring slot, then moves through a fixed pipeline
       // without ever stalling:
       //   trip t    record requested from L2
@@ -782,7 +813,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
       //             and written to the ring
       // The loop is unrolled by the pipeline depth so that the registers rotate by renaming, not by moves.
       const uint32_t k0 = has_ops ? (uint32_t)offw[ql] : 1u;
-      const uint32_t klast = has_ops ? k0 + totalw[ql] - 1u : 0u;   // list position of the machine's last part
+      const uint32_t klast = has_ops ? k0 + (kStepping ? (uint32_t)cntw[ql] : totalw[ql]) - 1u : 0u;   // list position of the machine's last part (operation)
       bool pending = false;
       uint32_t admitted = 0, written = 0;
       uint32_t aseq = (uint32_t)f;                            // index in the lane's stream of the next part to admit
@@ -790,13 +821,37 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
       // cursor: the next part to admit is the record at `addr`, at list position k (k > klast: the stream is exhausted);
       // `ahead` is the entry after it in this feeder's share of the lane's stream
       constexpr uint32_t kStep = kFeeders * SUB;
-      uint32_t k = k0 + (uint32_t)(f * SUB + sub_lane);
+      uint32_t k = kStepping ? k0 : k0 + (uint32_t)(f * SUB + sub_lane);
       uint32_t addr = has_ops ? (uint32_t)list[min(k, klast)] : 0u;
       uint32_t ahead = has_ops ? (uint32_t)list[min(k + kStep, klast)] : 0u;
+      // Stepping: `addr` is the record's index and not a list entry, `rem` more parts of its operation follow, and `ids` are the entries of
+      // the next kFeeders operations (one trip moves the cursor by kFeeders parts, into at most that many operations).
+      uint32_t rem = addr >> vbits, ids[kFeeders];
+      auto look_ahead = [&](bool moved) {
+#pragma unroll
+        for (int i = 0; i < kFeeders; ++i) {
+          const uint32_t entry = list[moved ? min(k + 1u + (uint32_t)i, klast) : 0u];
+          ids[i] = moved ? entry : ids[i];
+        }
+      };
+      auto advance = [&]() {
+        const bool in_op = rem != 0;
+        addr = in_op ? addr + n_plane : ids[0] & vmask;
+        rem = in_op ? rem - 1u : ids[0] >> vbits;
+        k += in_op ? 0u : 1u;
+#pragma unroll
+        for (int i = 0; i + 1 < kFeeders; ++i) ids[i] = in_op ? ids[i] : ids[i + 1];
+      };
+      if (kStepping) {
+        addr &= vmask;
+        look_ahead(true);
+        for (int i = 0; i < f; ++i) advance();                // feeder f starts at its first own part
+        look_ahead(true);
+      }
       // With the placement bytes in L2 the vector cache's line accesses are what bounds the CU (layered graph, window mode: its address
       // unit busy 87 % of the time, 8.5 accesses an operation): there a lane holds the aligned block of eight entries that its next entry is in.
       // With that here and in the accountant 953 -> 761 us for 1024 candidates of 50000 operations.
-      constexpr bool kBlocks = PIBL == 0;
+      constexpr bool kBlocks = PIBL == 0 && !kStepping;
       const uint4 *const blocks = (const uint4 *)list;
       uint4 block = kBlocks && has_ops ? blocks[min(k + kStep, klast) >> 3] : make_uint4(0, 0, 0, 0);
       struct Entry { uint4 rec; uint32_t q0, q1, q2, q3, fl; };   // fl: 1 valid
@@ -833,7 +888,13 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
           // (2) the entry after it (consumed one trip later at the earliest).  Lanes whose cursor stayed
           // keep theirs and all read the same entry instead, which costs the vector cache one line, not one per lane.
           const bool moved = pending;
-          if (kBlocks) {
+          if (kStepping) {
+            if (moved) {
+#pragma unroll
+              for (int i = 0; i < kFeeders; ++i) advance();
+            }
+            look_ahead(moved);
+          } else if (kBlocks) {
             k += moved ? kStep : 0u;
             const uint32_t at = min(k, klast), lo = (at & 2u) ? block.y : block.x, hi = (at & 2u) ? block.w : block.z, w = (at & 4u) ? hi : lo;
             const uint32_t entry = (at & 1u) ? w >> 16 : w & 0xFFFFu;
@@ -858,7 +919,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
             pending = (k <= klast) & (mark == mark_free);
           }
           e0.fl = pending ? 1u : 0u;
-          e0.rec = p.rec[pending ? record(addr) : 0u];                 // lanes that admit nothing share one record
+          e0.rec = p.rec[pending ? (kStepping ? addr : record(addr)) : 0u];                 // lanes that admit nothing share one record
           admitted += pending ? 1u : 0u;
           // (B) placement bytes of e1's predecessors (its record was requested one trip ago)
           if (kStages == 3) {
@@ -888,6 +949,13 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
           }
         }
       }
+      };
+      if constexpr (KIND == 0 && SUB == 1) {
+        if (by_ops) feed(std::true_type());
+        else feed(std::false_type());
+      } else {
+        feed(std::false_type());
+      }
     }
   } else if (wave == kFeeders + 1) {
     // ------------------------------------------------------------ accountant
@@ -899,7 +967,7 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
     const uint16_t *const list = p.ws_list + cid(cand_ok ? g : 0) * p.list_stride;
     const uint32_t vmask = (1u << p.id_bits) - 1u;
     constexpr int kEight = 8;
-    const int n = has_ops ? (int)totalw[ql] : 0, stretch = (n + SUB - 1) / SUB;
+    const int n = has_ops ? (by_ops ? cntw[ql] : (int)totalw[ql]) : 0, stretch = (n + SUB - 1) / SUB;
     const int k0 = (has_ops ? (int)offw[ql] : 0) + min(n, sub_lane * stretch), kend = k0 + min(stretch, n - min(n, sub_lane * stretch));
     int64_t level = 0, base = 0;                            // level above the machine's base; base = static memory on it (eq. (16))
     // (rows of the lists are a multiple of 128 bytes: a block of eight entries is one access of the vector cache, which is what bounds
@@ -912,8 +980,8 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
 #pragma unroll
       for (int u = 0; u < kEight; ++u) {
         const uint32_t w = u < 2 ? block.x : u < 4 ? block.y : u < 6 ? block.z : block.w, id = (u & 1) ? w >> 16 : w & 0xFFFFu;
-        on[u] = k + u >= k0 && k + u < kend && (KIND != 0 || id <= vmask);   // (an operation counts with its first part)
-        const uint32_t v = on[u] ? id : 0u;
+        on[u] = k + u >= k0 && k + u < kend && (KIND != 0 || by_ops || id <= vmask);   // (an operation counts with its first part)
+        const uint32_t v = on[u] ? (by_ops ? id & vmask : id) : 0u;
         m[u] = p.mem_delta[v];
         wt[u] = p.weight ? p.weight[v] : 0;
       }

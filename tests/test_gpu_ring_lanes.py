@@ -51,3 +51,35 @@ def test_range_stops_and_cycles(gpu_lib, machines, lanes):
     with gpu_lib.shape_defaults(cand_per_block=per_wave // lanes, state_bits=16, placement_mode=1, ring_slots=8, feeders=2):
         (z, _, _, f), info = assert_parity(gpu_lib, w)
     assert info["variant"] == 4 and (z > 65534).any() and (z[f == 0] <= 65534).any() and (f == 1).any(), info
+
+
+@pytest.mark.parametrize("machines,n,fanin,window", [(64, 70, 9, 40), (16, 1464, 9, 25), (32, 1025, 14, 30), (3, 257, 9, None), (8, 301, 60, 100), (16, 700, 62, 90), (5, 3000, 30, 200)])
+def test_lists_of_operations_and_of_parts(gpu_lib, machines, n, fanin, window):
+    """One lane per machine, operations of up to 16 parts: lists of operations where chains are long or machines have next to nothing to do (the
+    first three), of op parts elsewhere (tests/test_host_launches.py sees which); candidates that are cyclic, have a rank twice, a rank too large,
+    a machine that is not there; several wavefronts to a candidate and several candidates to one."""
+    rng = np.random.default_rng(n + machines)
+    rp, ci = W.random_dag(rng, n, fanin, window=window)
+    per_wave = 64 // (1 << (machines - 1).bit_length())
+    pl, rk = W.list_schedules(rp, ci, machines, 3 * per_wave + 2, n)
+    for c in range(0, len(pl), 5):                           # a machine's order reversed, a rank twice, a rank too large, no such machine
+        same = np.nonzero(pl[c] == pl[c, 0])[0]
+        rk[c, same] = len(same) - 1 - rk[c, same]
+    for c in range(1, len(pl), 7):
+        v = int(rng.integers(0, n))
+        same = np.nonzero(pl[c] == pl[c, v])[0]
+        if c % 3 == 0:
+            rk[c, v] = len(same)
+        elif c % 3 == 1:
+            pl[c, v] = machines
+        else:
+            rk[c, v] = rk[c, same[0]]
+    w = W.Workload("lists", machines, rp, ci, rng.integers(1, 9, n).astype(np.int32), rng.integers(1, 5, (machines, machines)).astype(np.int32),
+                   rng.integers(-3, 4, n).astype(np.int64), pl, rk, weight=rng.integers(0, 9, n).astype(np.int64),
+                   mem_limit=np.full(machines, 12 + 9 * n // machines, np.int64))
+    for bits in (16, 32):
+        for pib, ring, feeders, block in ((1, 8, 2, 0), (1, 8, 1, 1024), (0, 8, 2, 512), (0, 16, 3, 0), (2, 8, 2, 0)):
+            if pib == 2 and machines > 16:
+                continue
+            with gpu_lib.shape_defaults(cand_per_block=per_wave, placement_mode=pib, ring_slots=ring, feeders=feeders, block_threads=block, state_bits=bits):
+                assert_parity(gpu_lib, w, layout=(bits + pib) & 1)

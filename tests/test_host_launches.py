@@ -1,5 +1,5 @@
 """What the library's host side asks of the HIP runtime, without a GPU (tests/fake_hip.c): handles that fit the memory only
-without the pipeline kernels, memory given back, grids that every launch can have."""
+without the pipeline kernels, memory given back, grids that every launch can have, what the order lists take."""
 from __future__ import annotations
 
 import ctypes
@@ -58,7 +58,24 @@ def _in_child(shim):
         got[name] = (full, make(hp, (7,), full["used"] - 1))
     got["after a refusal"] = make(problem(3, 20, 1, 20000), (7,))
     got["many"] = make(problem(5, 1, 20011, 2 ** 26), (1, 2 ** 20 + 1, 2 ** 24 + 1, 2 ** 26))
+    # entries of a candidate's order list: what 64 candidates more add to the handle (the planner's choice does not change there)
+    got["list entries"] = {}
+    for name, (machines, n, fanin, window) in LISTS.items():
+        rng = np.random.default_rng(n + machines)
+        rp, ci = W.random_dag(rng, n, fanin, window=window)
+        args = (rng.integers(1, 9, n), rng.integers(1, 5, (machines, machines)), rng.integers(-3, 4, n))
+        per_wave = 64 // (1 << (machines - 1).bit_length())
+        used = []
+        for n_cand in (64 * 256, 64 * 257):
+            hp = dagsched._HostProblem(machines, rp, ci, *args, n_cand, 0, 0, shape=dict(cand_per_block=per_wave, placement_mode=1, ring_slots=8, feeders=2, state_bits=16))
+            used.append(make(hp, ())["used"])
+        got["list entries"][name] = (used[1] - used[0]) // 128
     print(json.dumps(got))
+
+
+# (machines, operations, fan-in, window) of tests/test_gpu_ring_lanes.py
+LISTS = {"one operation to a machine": (64, 70, 9, 40), "a long chain": (16, 1464, 9, 25), "the same, odd": (32, 1025, 14, 30), "wide": (3, 257, 9, None),
+         "many parts": (8, 301, 60, 100), "more parts": (16, 700, 62, 90)}
 
 
 @pytest.fixture(scope="module")
@@ -91,6 +108,14 @@ def test_no_handle_where_nothing_is_planned_besides(seen):
 def test_a_refused_handle_leaves_no_error_behind(seen):
     """The launches of the next handle do not report that there was no memory for the one before."""
     assert seen["fused for general"][1]["rc"] == -4 and seen["after a refusal"]["calls"][0][0] == 0
+
+
+@pytest.mark.parametrize("name", list(LISTS))
+def test_order_lists_of_operations_or_of_parts(seen, name):
+    """With one lane per machine the order lists hold operations where chains are long for what a machine has to do, else op parts."""
+    n = LISTS[name][1]
+    assert (seen["list entries"][name] == (n + 63) // 64 * 64) == (name in ("one operation to a machine", "a long chain", "the same, odd"))
+    assert seen["list entries"][name] >= n
 
 
 def test_grids_of_large_batches(seen):
