@@ -502,16 +502,10 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   plan.comm_scaled.resize((size_t)P * P);
   for (int i = 0; i < P * P; ++i) plan.comm_scaled[i] = (i / P != i % P) ? (int32_t)(d->comm[i] / g) : 0;
 
-  // shape: fewest rounds of the batch first, a round's time by what its workgroups are.  Placement bytes in LDS give the fastest feeders but cost
-  // N bytes per candidate; in L2 they leave room for more candidates or a deeper ring.  Measured weights: a
-  // four-slot ring counts 0.7 (hot lanes outrun it; 0.8 with several lanes per machine, which have a ring each), placement bytes in L2 count 0.7 (0.85 with two predecessors
-  // per op: half the gathers; a 36-layer MoE graph, N = 6912: four workgroups per CU with them in L2 0.179 us per
-  // candidate, three with them in LDS 0.135), and workgroups beyond
-  // five per CU count nothing (six with several lanes per machine), half-empty wavefronts count 0.65 (the feeders do the same work for half the
-  // candidates), every further workgroup on the CU costs 5 % of the round.  Measured (us, shape taken first, in brackets the candidates of a wavefront): MoE graph, 4096 candidates
-  // 975 (1) and 1050 (2), 256 candidates 186 (1), 243 (2); its 16-layer form on 8 machines, 4096: 56 (4), 62 (8); random graph of 3001 operations on 11 machines, 2051: 91 (1),
-  // 123 (2), 153 (4); of 2000 on 16, 8192: 125 (2), 140 (1), 157 (4); of 500 on 7, 30000: 125 (4), 121 (8); layered, 5000 on 30, 1000: 72 (1), 80 (2); 1F1B of 64 on 4,
-  // 65536: 47 (16), 58 (8).
+  // Shape: the least time of the batch, as `cycles` and `busy` below work it out from the levels, op parts and machines.  Placement bytes in LDS give the fastest
+  // feeders but cost N bytes per candidate; in L2 they leave room for more candidates or a deeper ring (the relaxation then takes 1 / 0.7 of the time, 1 / 0.85 with
+  // two predecessors per op: half the gathers; a 36-layer MoE graph, N = 6912: four workgroups per CU with them in L2 0.179 us per
+  // candidate, three with them in LDS 0.135).  Half-empty wavefronts count 0.65 (the feeders do the same work for half the candidates).
   // a shape given with the description wins, field by field
   const dagsched_shape_t *sh = d->shape;
   // Width of the end times.  16 bits when every end time provably fits, or when most candidates can be expected to
@@ -569,14 +563,42 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   const int force_ring = sh ? sh->ring_slots : 0;
   const int force_feeders = sh ? sh->feeders : 0;
   const int force_pib = sh ? sh->placement_mode : -1;
-  // Levels of B for every operation that a machine has on the average: where chains across the machines are long, several
-  // lanes per machine save fewer trips.  Trips of one lane over those of two and of four, by simulation: MoE graph (1.7 levels) 1.48, 1.75, layered
-  // graph (0.5) 1.52, 1.81, four-stage 1F1B (0.5) 1.54, 1.96; zero-bubble and bidirectional pipelines (0.2), random graph (0.1) 1.85 to 1.9, 3.0 to 3.1.
-  // A trip takes 240 cycles with one lane, 265 with two, 370 with four.
-  const bool deep = 3 * (int64_t)levels * P > (int64_t)N;
+  // Lanes per machine.  Several of them save trips, the more the fewer levels of B there are for every op part of a machine; but they leave a wavefront to fewer candidates,
+  // and the batch has twice or four times the workgroups, whose four wavefronts all issue.  Fitted to 2000 problems with every number of lanes measured (16 to 24000 operations on
+  // 2 to 32 machines, 64 to 40000 candidates; random, layered and MoE graphs, pipelines): the shape taken is 0.7 % slower than the best one on the average.  By the lanes' gain alone, with
+  // 5 % for every further workgroup on the CU, it was 9.6 %, and up to twice the time on small graphs in large batches.  Lanes 1 and 2, and 4 where a wavefront has them (us): 16 operations on 8
+  // machines, 12000 candidates 15, 29, 43; 1000 on 30, 6000: 60, 72; 3000 on 30, 3000: 112, 92; 1000 on 4, 64: 59, 44, 40; MoE graph on 32, 4096: 1049, 949.
+  const double ops_per_machine = (double)plan.total_parts / P, depth = levels / ops_per_machine;
+  const double relax_cycles = 350.0 * std::max(ops_per_machine, (double)levels);         // with one lane per machine
+  // (op parts put in place by the wavefronts of a workgroup, candidates one after the other)
+  auto list_cycles = [&](int G) -> double { return 2000.0 * ((G + 3) / 4); };
+  // a workgroup alone on a CU
+  auto cycles = [&](int G, int sub, int pib_lds, int ring, bool by_ops, int64_t fits) -> double {
+    const double gain = sub == 4 ? 1.0 + 2.2 / (1.0 + 2.1 * depth) : sub == 2 ? 1.23 + 0.76 / (1.0 + 1.8 * depth) : 1.0;
+    const double threads = fits == 1 ? 0.3 : fits == 2 ? 0.5 : 1.0;                      // (the workgroup's size, below)
+    const double all = (sub == 4 ? 9000.0 : 7100.0) + 4.0 * threads * N * G + (plan.kind == 0 && !by_ops ? list_cycles(G) : 0.0) + relax_cycles / gain;
+    return all * (ring >= 8 ? 1.0 : sub > 1 ? 1.05 : 1.43) /                             // (a four-slot ring: hot lanes outrun it; several lanes have a ring each)
+           (pib_lds == 1 ? 1.0 : pib_lds == 2 ? 0.99 : plan.kind == 2 ? 0.85 : 0.7) / (G * Pseg * sub < kWave ? 0.65 : 1.0) / (ring == 16 ? 1.001 : 1.0);
+  };
+  // how many times as long `wgs` of them take on a CU that holds `fits`: round by round, each workgroup a little longer for every other one, or
+  // as long as all their instructions take
+  auto busy = [&](int64_t wgs, int64_t fits) -> double {
+    auto round = [&](int64_t n) { return n ? 1.0 + (0.04 + 0.1 / (1.0 + depth)) * (double)(n - 1) : 0.0; };
+    return std::max(0.31 * (double)wgs, (double)(wgs / fits) * round(fits) + round(wgs % fits));
+  };
+  // Order lists of operations or of op parts (by_ops in the kernel).  Parts pay where the feeders have to keep many machines busy (few levels of B for
+  // every operation of a machine) or step through many parts, if that saves more than it takes to put them in place; all the more where another workgroup
+  // relaxes meanwhile.  A machine of one or two operations has nothing to be fed.  Measured, lists of operations over lists of parts (us; levels * P * N / parts^2 and rounds in
+  // brackets): MoE graph on 32 machines of one micro-batch 200 / 212 (11, 2) and of eight 248 / 237 (1.4, 3), 4096 candidates each; random graphs of 1464 operations on
+  // 16 machines 101 / 110 (0.9, 1), on 64 with 7.8 parts to an operation 202 / 183 (0.35, 1); of 301 on 64 470 / 505 with 1.4 parts (5, 23), on 3 187 / 172 (0.2, 2); of 60 on 64
+  // 309 / 352 (12, 23); of 101 on 4 25 / 28 (0.5, 1: four candidates of a workgroup one after the other).
+  auto lists_of_ops = [&](int G, int sub, int64_t rounds) -> bool {
+    const double parts_per_op = (double)plan.total_parts / N;
+    return plan.kind == 0 && sub == 1 && !win_log2 &&
+           (N < 3 * P || depth > (rounds >= 2 ? 1.5 : 0.8) * parts_per_op || list_cycles(G) > (rounds >= 2 ? 0.2 : 0.05) * parts_per_op * relax_cycles);
+  };
   double best_score = -1;
   int best_wgs = 0, best_at_once = 0;
-  int64_t best_rounds = 1;
   for (int G = kWave / Pseg; G >= 1; G >>= 1) {
     if (force_g && G != force_g) continue;
     for (int pib_lds : {1, 2, 0}) {
@@ -612,14 +634,15 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
           const int64_t rounds = (need + wgs - 1) / wgs;
           wgs = (int)std::min<int64_t>(wgs, (need + rounds - 1) / rounds);
         }
-        // rounds of the batch times what a round takes, the smaller the better
         const int64_t at_once = std::max<int64_t>(1, ((d->max_candidates + G - 1) / G + n_cu - 1) / n_cu);   // workgroups per CU that the batch has
         const int64_t rounds = (at_once + wgs - 1) / wgs;
-        const double lanes = sub == 4 ? (deep ? 1.4 : 2.3) : sub == 2 ? (deep ? 1.4 : 1.7) : 1.0;
-        const double rate = lanes * (ring >= 8 ? 1.0 : sub > 1 ? 0.8 : 0.7) * (pib_lds == 1 ? 1.0 : pib_lds == 2 ? 0.99 : plan.kind == 2 ? 0.85 : 0.7) *
-                            (G * Pseg * sub < kWave ? 0.65 : 1.0) * (ring == 16 ? 1.001 : 1.0);
-        const double score = rate / ((double)rounds * (1.0 + 0.05 * (double)(std::min<int64_t>(wgs, at_once) - 1)));
-        if (score > best_score) { best_score = score; best_wgs = wgs; best_at_once = (int)std::min<int64_t>(wgs, at_once); best_rounds = rounds; plan.G = G; plan.sub = sub; plan.ring = ring; plan.lds = o; }
+        const bool by_ops = lists_of_ops(G, sub, rounds);
+        const int64_t fits = std::min(7, lds_max / (int)align_up(o.total, 512));   // (seven by the kernel's registers)
+        const double score = 1.0 / (cycles(G, sub, pib_lds, ring, by_ops, fits) * busy(at_once, fits));
+        if (score > best_score) {
+          best_score = score; best_wgs = wgs; best_at_once = (int)std::min<int64_t>(wgs, at_once);
+          plan.G = G; plan.sub = sub; plan.ring = ring; plan.lds = o; plan.by_ops = by_ops;
+        }
       }
     }
   }
@@ -638,13 +661,6 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   if (plan.kind == 3 && (win_log2 || wide || plan.cell32 || !built(plan.feeders))) plan.kind = 2;
   if (!force_feeders && !built(plan.feeders)) plan.feeders = 2;
   if (best_score < 0 || !built(plan.feeders)) return plan;   // shape not built
-  // Order lists of operations or of op parts (by_ops in the kernel).  Parts pay where the feeders have to keep many machines busy (few levels of B for
-  // every operation of a machine) or step through many parts, and a good deal of that again where another workgroup relaxes meanwhile; a machine of
-  // one or two operations has nothing to be fed.  Measured, lists of operations over lists of parts (us; levels * P * N / parts^2 and rounds in brackets): MoE graph on 32 machines of
-  // one micro-batch 200 / 212 (11, 2) and of eight 248 / 237 (1.4, 3), 4096 candidates each; random graphs of 1464 operations on 16 machines 101 / 110 (0.9, 1), on
-  // 64 with 7.8 parts to an operation 202 / 183 (0.35, 1); of 301 on 64 470 / 505 with 1.4 parts (5, 23); of 60 on 64 309 / 352 (12, 23).
-  plan.by_ops = plan.kind == 0 && plan.sub == 1 && !win_log2 &&
-                (N < 3 * P || (double)levels * P * N > (best_rounds >= 2 ? 1.5 : 0.8) * (double)plan.total_parts * (double)plan.total_parts);
   plan.list_row = plan.by_ops ? N : plan.total_parts;
   // the nibble kernels start time at 255 (see the kernel), which the 16-bit range must hold as well
   // (a candidate that does not fit the window goes to the int32 kernel like one that leaves the 16-bit range: window

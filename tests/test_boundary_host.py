@@ -269,3 +269,14 @@ def test_plan_of_a_pipeline(stages, micros, machines, n_cand, long_times, form):
         dur[0] += 70001
     i = dagsched.plan(machines, rp, ci, dur, comm, rng.integers(-3, 4, len(ids)), max_candidates=n_cand, shared_placement=fixed)
     assert form == ("two launches" if i["two_launches"] else "fused" if i["variant"] == 6 and i["kernel_kind"] == 3 else "other"), i
+
+
+@pytest.mark.parametrize("machines,n,fanin,n_cand,lanes", [
+    (8, 16, 9, 12000, 1), (16, 40, 4, 12000, 1), (30, 101, 9, 6000, 1), (4, 101, 4, 40000, 1),       # small graphs that fill the chip: one lane per machine
+    (8, 200, 2, 64, 4), (4, 400, 3, 512, 4), (16, 1000, 2, 1500, 2), (30, 3000, 3, 256, 2)])         # CUs with one workgroup or two: several
+def test_lanes_per_machine_follow_the_batch(machines, n, fanin, n_cand, lanes):
+    """How many lanes the ring kernel gives a machine: by what a workgroup alone takes and by how many share a CU."""
+    rng = np.random.default_rng(n)
+    rp, ci = W.random_dag(rng, n, fanin, window=None if fanin < 4 else 40)
+    info = dagsched.plan(machines, rp, ci, rng.integers(1, 9, n), rng.integers(1, 5, (machines, machines)), rng.integers(-3, 4, n), max_candidates=n_cand)
+    assert info["variant"] in (3, 4) and info["cand_per_block"] == 64 // (1 << (machines - 1).bit_length()) // lanes, info

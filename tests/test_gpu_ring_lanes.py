@@ -53,7 +53,7 @@ def test_range_stops_and_cycles(gpu_lib, machines, lanes):
     assert info["variant"] == 4 and (z > 65534).any() and (z[f == 0] <= 65534).any() and (f == 1).any(), info
 
 
-@pytest.mark.parametrize("machines,n,fanin,window", [(64, 70, 9, 40), (16, 1464, 9, 25), (32, 1025, 14, 30), (3, 257, 9, None), (8, 301, 60, 100), (16, 700, 62, 90), (5, 3000, 30, 200)])
+@pytest.mark.parametrize("machines,n,fanin,window", [(64, 70, 9, 40), (16, 1464, 9, 25), (32, 1025, 14, 30), (16, 1403, 9, None), (8, 301, 60, 100), (16, 700, 62, 90), (5, 3000, 30, 200)])
 def test_lists_of_operations_and_of_parts(gpu_lib, machines, n, fanin, window):
     """One lane per machine, operations of up to 16 parts: lists of operations where chains are long or machines have next to nothing to do (the
     first three), of op parts elsewhere (tests/test_host_launches.py sees which); candidates that are cyclic, have a rank twice, a rank too large,

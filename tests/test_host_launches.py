@@ -74,7 +74,7 @@ def _in_child(shim):
 
 
 # (machines, operations, fan-in, window) of tests/test_gpu_ring_lanes.py
-LISTS = {"one operation to a machine": (64, 70, 9, 40), "a long chain": (16, 1464, 9, 25), "the same, odd": (32, 1025, 14, 30), "wide": (3, 257, 9, None),
+LISTS = {"one operation to a machine": (64, 70, 9, 40), "a long chain": (16, 1464, 9, 25), "the same, odd": (32, 1025, 14, 30), "wide": (16, 1403, 9, None),
          "many parts": (8, 301, 60, 100), "more parts": (16, 700, 62, 90)}
 
 
