@@ -1634,7 +1634,7 @@ namespace {
 int launch_schedule(dagsched_t *h, int32_t *list_row, int32_t *end_row, const int32_t *placement, const int32_t *rank,
                     int32_t *start, int32_t *end, int32_t *flag, hipStream_t stream) {
   ScheduleParams p{};
-  p.N = h->N; p.P = h->P; p.Pseg = h->Pseg; p.n_red = h->n_red; p.slots = h->sched_slots;
+  p.N = h->N; p.P = h->P; p.Pseg = h->Pseg; p.n_red = h->n_red; p.slots = h->sched_slots; p.steps = schedule_steps(schedule_relaxers(h), h->N, h->n_red);
   p.pred_ptr = h->d_pred_ptr; p.pred_idx = h->d_pred_idx; p.red_ptr = h->d_red_ptr; p.red_idx = h->d_red_idx; p.dur = h->d_dur; p.comm = h->d_comm;
   p.no_channel = h->d_no_channel;
   p.mem_delta = h->d_mem; p.weight = h->d_weight; p.mem_limit = h->d_limit;

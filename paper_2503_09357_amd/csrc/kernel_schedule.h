@@ -12,10 +12,10 @@
 //             Operations with more predecessors are split into consecutive parts.
 //   helpers   a team of 512 / Pseg threads per machine packs the next operations of its list into the machine's ring.
 //
-// They meet at one barrier per phase of 16 steps (8 with two relaxers) and hand over counts only: how many parts of a
+// They meet at one barrier per phase of 8 to 64 steps (schedule_steps) and hand over counts only: how many parts of a
 // machine's stream the relaxer has taken, how many the helpers have put into the ring (both kept twice, by the parity
-// of the phase, so that nobody writes what somebody still reads).  A phase is longer than the helpers' chain of loads
-// (16 steps of 270 cycles against about 2500), so the relaxer hardly ever waits.
+// of the phase, so that nobody writes what somebody still reads).  16 steps of 270 cycles are longer than the helpers' chain of loads
+// (about 2500), so one relaxer hardly ever waits where operations have one part; the 8 steps of two relaxers are a little shorter than that chain.
 //
 // us, while the lanes of a machine (up to eight) polled the predecessors of one operation together, and now: MoE graph, 11712 operations on
 // 32 machines 265, 212 (1760 steps of 311 cycles then); its 30-layer form on 8: 353, 132; zero-bubble pipeline, 768 on 8: 48, 19;
@@ -24,6 +24,8 @@
 // through the L2, took 4940 us for the first.
 #pragma once
 
+#include <type_traits>
+
 #include "device_common.h"
 
 namespace dagsched_dev {
@@ -31,12 +33,19 @@ namespace dagsched_dev {
 constexpr int kBitNoChannel = 32;                          // (the evaluations leave this flag to a pass of its own)
 constexpr int kScheduleHelpers = 8;                        // wavefronts
 constexpr int schedule_threads(int relaxers) { return (relaxers + 1 + kScheduleHelpers) * kWave; }   // relaxers, accountant, helpers
-// Steps of a phase: what the helpers need to bring the next operations, a thread each (beyond 32 machines they have eight threads to a machine).
-constexpr int schedule_steps(int relaxers) { return relaxers == 2 ? 8 : 16; }
+// Steps of a phase: what the helpers need to bring the next operations, a thread each.  16; beyond 32 machines, with two relaxers, 8 unless most operations have several
+// parts; more where they have many, for a helper looks up an operation's parts a few at a time.  Random graphs, us: 24000 operations of three
+// predecessors on 64 machines, 8 steps 219; 2000 of eight on 64, 8 steps 77, 16 57; 2000 of 16 on 32, 16 steps 214, 32 152; 3000 of 16 on 64, 16 steps 137, 32 103;
+// 2000 of 40 on 8, 16 steps 775, 32 432, 64 476; 2000 of 80 on 8, 32 steps 1428, 64 1242; 3000 of 200 on 5, 32 steps 15100, 64 11550.
+inline int32_t schedule_steps(int relaxers, int32_t n_nodes, int32_t n_red) {
+  const int64_t n = n_nodes;
+  return n_red > 64 * n ? 64 : n_red > 8 * n ? 32 : relaxers == 1 || n_red > 4 * n ? 16 : 8;
+}
 
 struct ScheduleParams {
   int32_t N, P, Pseg, n_red;
   int32_t slots;                       // ring slots per lane: 8, 16 or 32
+  int32_t steps;                       // of a phase, a multiple of 8 (with one relaxer of 16)
   const int32_t *pred_ptr, *pred_idx;  // predecessor CSR of B (for the channels)
   const int32_t *red_ptr, *red_idx;    // [N + 1], [n_red] the same without the edges that other paths imply
   const int32_t *dur, *comm;           // [N], [P*P] (0 where the pair has no channel)
@@ -205,21 +214,22 @@ __global__ __launch_bounds__(schedule_threads(RW)) void schedule_kernel(Schedule
             lds_byte_t *const sp = ring_lane + (t & (uint32_t)ring_mask) * kRow;
             na = *(lds_vu32x4_t *)sp; nd = *(lds_vu32x4_t *)(sp + plane);
           }
-          for (int i = 0; i < schedule_steps(RW); i += 8) {
+          constexpr int kUnroll = RW == 1 ? 16 : 8;          // (the jump back costs 1 %)
+          for (int i = 0; i < p.steps; i += kUnroll) {
 #pragma unroll
-            for (int sub = 0; sub < 8; ++sub) {
+            for (int step = 0; step < kUnroll; ++step) {
               // (a time of kNever or more plus a delay and the durations of R operations stays below 2^32: the library accepts no
               // problem whose times could pass INT32_MAX)
               const uint32_t polled = max(max(max(e0 + d.x, e1 + d.y), e2 + d.z), e3 + d.w);
-              const uint32_t at = R == 1 || lane_bit(have) ? polled : kNever;
+              const uint32_t at = lane_bit(have) ? polled : kNever;
               uint32_t b = x_acc, y = max(at, b) + a.z;
 #pragma unroll
               for (int k = 1; k < R; ++k) { b = min(b, before(y)); y = max(at, b) + a.z; }
-              const uint64_t ran_m = R == 1 ? __ballot(y < kNever) & have : __ballot(y < kNever);
+              const uint64_t ran_m = __ballot(y < kNever);
               const bool ran = lane_bit(ran_m);
               // the machine is busy until y (chain edge, eq. (7))
-              if (R == 1) x_acc = ran ? y : x_acc;
-              else { const uint32_t last = before(y); x_acc = ran ? max(x_acc, last) : b; }
+              const uint32_t last = before(y);
+              x_acc = ran ? max(x_acc, last) : b;
               if (LDSC) *(lds_vu32_t *)(uintptr_t)(ran ? a.w : trash) = y;
               else if (ran && a.w != trash) st_group(&p.cells[a.w >> 2], (int32_t)y);
               const uint64_t take_m = (ran_m | ~have) & __ballot(t < avail);
@@ -320,23 +330,42 @@ __global__ __launch_bounds__(schedule_threads(RW)) void schedule_kernel(Schedule
         }
         const uint32_t excl = incl - n_mine;
         const uint32_t n_put = excl >= room ? 0u : min(n_mine, room - excl);
-        for (uint32_t q = 0; q < n_put; ++q) {
-          const uint32_t part = first + q;
-          const bool last = part + 1 == parts;
-          const uint32_t seq = f + excl + q, slot = (seq / R) & (uint32_t)ring_mask;
-          const uint32_t tail_z = last ? (uint32_t)p.dur[v] : 0u, tail_w = (last ? (uint32_t)v : (uint32_t)N + 1u) * 4u;
-          uint32_t u[4], dl[4];
+        // `count` parts from the q0-th on, looked up together: each is two trips to memory, one behind the other
+        auto put = [&](uint32_t q0, auto count) {
+          constexpr uint32_t kTogether = decltype(count)::value;
+          if (q0 >= n_put) return;
+          uint32_t u[kTogether][4], dl[kTogether][4];
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const int kk = lo + (int)part * 4 + e;
-            u[e] = kk < hi ? (uint32_t)p.red_idx[kk] : (uint32_t)N;
-          }
+          for (uint32_t b = 0; b < kTogether; ++b)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) dl[e] = u[e] < (uint32_t)N ? (uint32_t)comm[p.placement[u[e]] * P + m] : 0u;
-          lds_byte_t *const sp = ldsb + p.o_ring + slot * kRow + ((uint32_t)(m * R) + seq % R) * 16u;
-          const u32x4_t wa = {u[0] | (u[1] << 16), u[2] | (u[3] << 16), tail_z, tail_w}, wd = {dl[0], dl[1], dl[2], dl[3]};
-          *(lds_vu32x4_t *)sp = wa;
-          *(lds_vu32x4_t *)(sp + (uint32_t)p.slots * kRow) = wd;
+            for (int e = 0; e < 4; ++e) {
+              const int kk = lo + (int)(first + q0 + b) * 4 + e;
+              u[b][e] = kk < hi ? (uint32_t)p.red_idx[kk] : (uint32_t)N;
+            }
+#pragma unroll
+          for (uint32_t b = 0; b < kTogether; ++b)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) dl[b][e] = u[b][e] < (uint32_t)N ? (uint32_t)p.placement[u[b][e]] : 64u;
+#pragma unroll
+          for (uint32_t b = 0; b < kTogether; ++b)
+            if (q0 + b < n_put) {
+              const uint32_t part = first + q0 + b, seq = f + excl + q0 + b, slot = (seq / R) & (uint32_t)ring_mask;
+              const bool last = part + 1 == parts;
+              const uint32_t tail_z = last ? (uint32_t)p.dur[v] : 0u, tail_w = (last ? (uint32_t)v : (uint32_t)N + 1u) * 4u;
+              uint32_t d[4];
+#pragma unroll
+              for (int e = 0; e < 4; ++e) d[e] = dl[b][e] < 64u ? (uint32_t)comm[dl[b][e] * P + m] : 0u;
+              lds_byte_t *const sp = ldsb + p.o_ring + slot * kRow + ((uint32_t)(m * R) + seq % R) * 16u;
+              const u32x4_t wa = {u[b][0] | (u[b][1] << 16), u[b][2] | (u[b][3] << 16), tail_z, tail_w}, wd = {d[0], d[1], d[2], d[3]};
+              *(lds_vu32x4_t *)sp = wa;
+              *(lds_vu32x4_t *)(sp + (uint32_t)p.slots * kRow) = wd;
+            }
+        };
+        put(0, std::integral_constant<uint32_t, 1>());
+        if (__ballot(n_put > 1u) != 0) {
+          if (__ballot(n_put > 2u) == 0) put(1, std::integral_constant<uint32_t, 1>());
+          else put(1, std::integral_constant<uint32_t, 4>());
+          for (uint32_t q = 5; __ballot(n_put > q) != 0; q += 8) put(q, std::integral_constant<uint32_t, 8>());
         }
         // how far the team got: operations that are in with all their parts, and the parts of the one that is not
         const bool whole = n_put == n_mine && valid;

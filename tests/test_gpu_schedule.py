@@ -1,5 +1,6 @@
 """Start and end times of one schedule against the oracle where the kernel's split changes: lanes per machine (4 or
-2), one relaxer or two, end times in LDS and in the L2, every ring depth (8 slots only with two relaxers), operations of many parts (more than the ring holds)."""
+2), one relaxer or two, end times in LDS and in the L2, every ring depth (8 slots only with two relaxers), operations of many parts (more than the ring
+holds), phases of 8 to 64 steps."""
 from __future__ import annotations
 
 import numpy as np
@@ -13,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("n,p,fanin,window", [
     (1, 1, 1, None), (2, 64, 1, None), (700, 1, 5, 30), (513, 8, 40, None), (514, 9, 33, 200), (640, 16, 17, 100), (641, 17, 9, 90),
-    (1300, 32, 8, 60), (1301, 33, 5, 60), (3000, 64, 12, 300), (19400, 64, 4, 400), (24000, 64, 4, 400), (24000, 5, 3, 200), (28500, 31, 4, 500), (50001, 12, 4, 300)])
+    (1300, 32, 8, 60), (1301, 33, 5, 60), (400, 8, 90, 200), (401, 1, 70, 100), (700, 40, 14, 60), (301, 64, 90, 120), (3000, 64, 12, 300), (19400, 64, 4, 400), (24000, 64, 4, 400), (24000, 5, 3, 200), (28500, 31, 4, 500), (50001, 12, 4, 300)])
 def test_schedule_at_the_edges_of_its_splits(gpu_lib, n, p, fanin, window):
     import torch
     rng = np.random.default_rng(n)
