@@ -399,7 +399,7 @@ PredLists reduce_preds(const dagsched_desc_t *d, const std::vector<int32_t> &pre
 }
 
 RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_ptr, const std::vector<int32_t> &pred_idx,
-                   const PredLists &reduced, int64_t sum_dur, int lds_max, int n_cu) {
+                   const PredLists &reduced, int64_t sum_dur, int lds_max, int n_cu, bool short_lists = false) {
   RingPlan plan;
   const int N = d->n_nodes, P = d->n_devices, Pseg = next_pow2(P);
   int64_t g = 0, max_comm = 0;
@@ -568,6 +568,10 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   // 2 to 32 machines, 64 to 40000 candidates; random, layered and MoE graphs, pipelines): the shape taken is 0.7 % slower than the best one on the average.  By the lanes' gain alone, with
   // 5 % for every further workgroup on the CU, it was 9.6 %, and up to twice the time on small graphs in large batches.  Lanes 1 and 2, and 4 where a wavefront has them (us): 16 operations on 8
   // machines, 12000 candidates 15, 29, 43; 1000 on 30, 6000: 60, 72; 3000 on 30, 3000: 112, 92; 1000 on 4, 64: 59, 44, 40; MoE graph on 32, 4096: 1049, 949.
+  // Lists of op parts are up to sixteen times as long as lists of operations.  Half as long again and beyond 1 GiB for the handle, or where the caller has found no memory for
+  // them (short_lists), they are not taken, nor are several lanes per machine, which need them: what fits with lists of operations is not refused.
+  const int64_t rows_ops = ((int64_t)N + 63) / 64 * 64, rows_parts = (plan.total_parts + 63) / 64 * 64;
+  const bool parts_fit = plan.kind != 0 || rows_parts == rows_ops || (!short_lists && (2 * rows_parts <= 3 * rows_ops || 2 * rows_parts * (int64_t)d->max_candidates <= ((int64_t)1 << 30)));
   const double ops_per_machine = (double)plan.total_parts / P, depth = levels / ops_per_machine;
   const double relax_cycles = 350.0 * std::max(ops_per_machine, (double)levels);         // with one lane per machine
   // (op parts put in place by the wavefronts of a workgroup, candidates one after the other)
@@ -594,6 +598,7 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   // 309 / 352 (12, 23); of 101 on 4 25 / 28 (0.5, 1: four candidates of a workgroup one after the other).
   auto lists_of_ops = [&](int G, int sub, int64_t rounds) -> bool {
     const double parts_per_op = (double)plan.total_parts / N;
+    if (!parts_fit) return true;
     return plan.kind == 0 && sub == 1 && !win_log2 &&
            (N < 3 * P || depth > (rounds >= 2 ? 1.5 : 0.8) * parts_per_op || list_cycles(G) > (rounds >= 2 ? 0.2 : 0.05) * parts_per_op * relax_cycles);
   };
@@ -620,7 +625,7 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
               return true;
           return false;
         };
-        int sub = wide || win_log2 ? 1 : std::min(4, kWave / (G * Pseg));
+        int sub = wide || win_log2 || !parts_fit ? 1 : std::min(4, kWave / (G * Pseg));
         while (sub > 1 && !is_built(sub)) sub >>= 1;
         if (!is_built(sub)) continue;
         int wgs = std::min(sub > 1 ? 6 : 5, lds_max / (int)align_up(o.total, 512));   // beyond ~20 wavefronts the CU is issue-bound
@@ -1171,8 +1176,8 @@ extern "C" {
 
 int dagsched_validate(const dagsched_desc_t *desc) { return validate_desc(desc, nullptr, nullptr, nullptr); }
 
-int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
-  if (!out) return DAGSCHED_EINVAL;
+// short_lists: see plan_ring; *long_lists: the handle would be smaller with it
+static int create_handle(const dagsched_desc_t *caller_desc, bool short_lists, bool *long_lists, dagsched_t **out) {
   std::vector<int32_t> pred_ptr, pred_idx;
   int64_t sum_dur = 0;
   int rc = validate_desc(caller_desc, &pred_ptr, &pred_idx, &sum_dur);
@@ -1249,7 +1254,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   // (the fused form stands for the shared-placement kernel; the two launches stand in front of whatever kernel is planned besides)
   if (may_pipeline(desc)) pplan = plan_pipeline(desc, splan.fits_format, splan.ok, reduced, sum_dur, lds_max, n_cu);
   // (the ring kernel is planned behind either, unless the shared-placement kernel would evaluate without them)
-  if (!force_general && !splan.ok) plan = plan_ring(desc, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
+  if (!force_general && !splan.ok) plan = plan_ring(desc, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu, short_lists);
   const bool need_general = splan.ok || !plan.ok || !plan.exact;
 
   // the plain view of the problem is always resident: dagsched_schedule reads it
@@ -1337,7 +1342,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       fsh.window_cells = -1;
       dagsched_desc_t fd = *desc;
       fd.shape = &fsh;
-      const RingPlan fp = plan_ring(&fd, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
+      const RingPlan fp = plan_ring(&fd, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu, short_lists);
       // (same records, part counts and delays: both plans divide by the same common factor and drop the same edges)
       if (fp.ok && fp.exact && fp.cell32 && !fp.lds.wide && fp.scale == plan.scale && fp.rec_plane == plan.rec_plane &&
           fp.id_bits == plan.id_bits && fp.rec.size() == plan.rec.size()) {
@@ -1351,7 +1356,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
         // too large for that: the misses of the window go to the 16-bit kernel with a cell per operation (its own range
         // stops to a second list and the general kernel)
         fsh.state_bits = 0;
-        const RingPlan gp = plan_ring(&fd, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu);
+        const RingPlan gp = plan_ring(&fd, pred_ptr, pred_idx, reduced, sum_dur, lds_max, n_cu, short_lists);
         if (gp.ok && !gp.cell32 && !gp.win_log2 && !gp.lds.wide && gp.scale == plan.scale && gp.rec_plane == plan.rec_plane &&
             gp.id_bits == plan.id_bits && gp.rec.size() == plan.rec.size()) {
           h->fb_G = gp.G; h->fb_sub = gp.sub; h->fb_by_ops = gp.by_ops; list_row = std::max(list_row, gp.list_row); h->fb_slots = gp.ring; h->fb_feeders = gp.feeders; h->fb_block = gp.block; h->fb_lds = gp.lds; h->fb_kind = gp.kind;
@@ -1364,6 +1369,7 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
       }
     }
     h->list_stride = (list_row + 63) / 64 * 64;
+    *long_lists = h->list_stride > ((int64_t)h->N + 63) / 64 * 64;
     ok = ok && dev_alloc(&h->ws_list16, maxc * (size_t)h->list_stride);
     if (ok && plan.win_log2) {
       h->lds_ingest = plan.lds_ingest; h->ingest_block = plan.ingest_block; h->win_magic = plan.win_magic;
@@ -1496,6 +1502,17 @@ int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
   }
   *out = h;
   return DAGSCHED_OK;
+}
+
+int dagsched_create(const dagsched_desc_t *caller_desc, dagsched_t **out) {
+  if (!out) return DAGSCHED_EINVAL;
+  bool long_lists = false;
+  int rc = create_handle(caller_desc, false, &long_lists, out);
+  if (rc == DAGSCHED_ENOMEM && long_lists) {
+    g_hip_error[0] = 0;
+    rc = create_handle(caller_desc, true, &long_lists, out);
+  }
+  return rc;
 }
 
 int dagsched_evaluate(dagsched_t *h, int32_t n_cand, const int32_t *placement, const int32_t *rank, int32_t *makespan,

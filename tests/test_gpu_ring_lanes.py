@@ -5,6 +5,7 @@ from __future__ import annotations
 import numpy as np
 import pytest
 
+import oracle
 from paper_2503_09357_amd import workloads as W
 from test_gpu_parity import assert_parity
 
@@ -83,3 +84,31 @@ def test_lists_of_operations_and_of_parts(gpu_lib, machines, n, fanin, window):
                 continue
             with gpu_lib.shape_defaults(cand_per_block=per_wave, placement_mode=pib, ring_slots=ring, feeders=feeders, block_threads=block, state_bits=bits):
                 assert_parity(gpu_lib, w, layout=(bits + pib) & 1)
+
+
+@pytest.mark.parametrize("machines,width,levels,fanin,window", [(16, 50, 300, 9, True), (8, 20, 100, 30, False)])
+def test_lists_that_would_take_too_much(gpu_lib, machines, width, levels, fanin, window):
+    """Handles for batches whose lists of op parts would take more than 1 GiB: lists of operations, also in window mode (both launches of it)."""
+    rng = np.random.default_rng(width)
+    n = width * levels
+    src, dst = [], []
+    for v in range(width, n):
+        lo = max(0, v // width - 2) * width
+        for u in rng.choice(np.arange(lo, v // width * width), size=min(fanin, v // width * width - lo), replace=False):
+            src.append(u)
+            dst.append(v)
+    rp, ci = W.csr_from_edges(n, np.array(src), np.array(dst))
+    pl, rk = W.list_schedules(rp, ci, machines, 11, n)
+    same = np.nonzero(pl[3] == pl[3, 0])[0]
+    rk[3, same] = len(same) - 1 - rk[3, same]                # a cycle
+    rk[5, 7] = n                                             # a rank too large
+    w = W.Workload("long lists", machines, rp, ci, rng.integers(1, 9, n).astype(np.int32), rng.integers(1, 5, (machines, machines)).astype(np.int32),
+                   rng.integers(-3, 4, n).astype(np.int64), pl, rk)
+    for big in (11, 60000):
+        with gpu_lib.Evaluator.for_workload(w, max_candidates=big, shared_placement=None) as ev:
+            info = ev.info()
+            assert (info["window_log2"] > 0) == window and info["kernel_kind"] == 0 and info["variant"] in (3, 4), info
+            import torch
+            z, b, pk, f = (t.cpu().numpy() for t in ev.evaluate(torch.from_numpy(pl).cuda(), torch.from_numpy(rk).cuda()))
+        zo, bo, pko, fo = oracle.Problem.of(w).evaluate(pl, rk, threads=8)
+        assert (f == fo).all() and (z == zo).all() and (b == bo).all() and (pk == pko).all() and (fo != 0).sum() >= 2

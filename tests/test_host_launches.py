@@ -70,6 +70,13 @@ def _in_child(shim):
             hp = dagsched._HostProblem(machines, rp, ci, *args, n_cand, 0, 0, shape=dict(cand_per_block=per_wave, placement_mode=1, ring_slots=8, feeders=2, state_bits=16))
             used.append(make(hp, ())["used"])
         got["list entries"][name] = (used[1] - used[0]) // 128
+    # lists of op parts: without the memory for them, and where they would take more than 1 GiB
+    rng = np.random.default_rng(9)
+    rp, ci = W.random_dag(rng, 2000, 40, window=100)
+    args = (rng.integers(1, 9, 2000), rng.integers(1, 5, (8, 8)), rng.integers(-3, 4, 2000))
+    small, *more = (dagsched._HostProblem(8, rp, ci, *args, n, 0, 0) for n in (400, 2 ** 17, 2 ** 17 + 64))
+    full = make(small, (400,))
+    got["many parts"] = [full, make(small, (400,), full["used"] - 1), *(make(hp, (7,)) for hp in more)]
     print(json.dumps(got))
 
 
@@ -116,6 +123,15 @@ def test_order_lists_of_operations_or_of_parts(seen, name):
     n = LISTS[name][1]
     assert (seen["list entries"][name] == (n + 63) // 64 * 64) == (name in ("one operation to a machine", "a long chain", "the same, odd"))
     assert seen["list entries"][name] >= n
+
+
+def test_lists_of_parts_that_do_not_fit(seen):
+    """A byte less than lists of op parts take: a handle with lists of operations and one lane per machine.  Beyond 1 GiB of them nobody asks for the memory."""
+    full, short, large, larger = seen["many parts"]
+    assert (full["rc"], short["rc"], large["rc"], larger["rc"]) == (0, 0, 0, 0) and full["variant"] == short["variant"] == large["variant"]
+    assert full["used"] - short["used"] > 400 * 2 * 2000 and short["cand_per_block"] == large["cand_per_block"] == 8
+    assert (larger["used"] - large["used"]) // 64 < 2 * 2048 + 2048 and full["calls"] == short["calls"]
+    assert [x["left"] for x in seen["many parts"]] == [0, 0, 0, 0]
 
 
 def test_grids_of_large_batches(seen):
