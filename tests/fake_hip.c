@@ -1,5 +1,7 @@
 /* A HIP runtime without a GPU, for tests of what the library's host side asks of it: memory up to a budget, copies of tables, and a list of the
- * launches with their grids.  Loaded with RTLD_GLOBAL before the library, whose calls then resolve to this file. */
+ * launches with their grids and kernels' names.  Loaded with RTLD_GLOBAL before the library, whose calls then resolve to this file. */
+#define _GNU_SOURCE
+#include <dlfcn.h>
 #include <stdint.h>
 #include <stdio.h>
 #include <stdlib.h>
@@ -13,6 +15,7 @@ static struct { void *p; size_t size; } held[SLOTS];
 static size_t budget = (size_t)1 << 62, used;
 static int last, launches;
 static dim3_t grids[64], blocks[64], next_grid, next_block;
+static const void *kernels[64];
 static size_t next_lds;
 static void *next_stream;
 
@@ -20,6 +23,8 @@ void fake_budget(size_t bytes) { budget = bytes; }
 size_t fake_used(void) { return used; }
 int fake_launches(void) { const int n = launches; launches = 0; return n; }
 void fake_launch(int i, uint32_t *out) { memcpy(out, &grids[i], 12); memcpy(out + 3, &blocks[i], 12); }
+
+const char *fake_kernel(int i) { Dl_info d; return dladdr(kernels[i], &d) && d.dli_sname ? d.dli_sname : ""; }
 
 int hipMalloc(void **p, size_t size) {
   for (int i = 0; i < SLOTS; ++i)
@@ -54,9 +59,9 @@ const char *hipGetErrorString(int e) { return e == OOM ? "out of memory" : "laun
 int __hipPushCallConfiguration(dim3_t g, dim3_t b, size_t lds, void *stream) { next_grid = g; next_block = b; next_lds = lds; next_stream = stream; return OK; }
 int __hipPopCallConfiguration(dim3_t *g, dim3_t *b, size_t *lds, void **stream) { *g = next_grid; *b = next_block; *lds = next_lds; *stream = next_stream; return OK; }
 int hipLaunchKernel(const void *f, dim3_t g, dim3_t b, void **args, size_t lds, void *stream) {
-  (void)f; (void)args; (void)lds; (void)stream;
+  (void)args; (void)lds; (void)stream;
   if ((uint64_t)g.x * b.x >> 32 || (uint64_t)g.y * b.y >> 32) return last = BAD_LAUNCH;
-  if (launches < 64) { grids[launches] = g; blocks[launches] = b; }
+  if (launches < 64) { grids[launches] = g; blocks[launches] = b; kernels[launches] = f; }
   ++launches;
   return OK;
 }

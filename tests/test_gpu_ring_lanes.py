@@ -16,8 +16,9 @@ pytestmark = pytest.mark.gpu
     (1, 1, 1), (1, 130, 2), (2, 3, 1), (3, 65, 4), (4, 64, 9), (7, 333, 1), (8, 257, 14), (11, 1200, 3), (16, 515, 6), (17, 700, 2), (31, 1024, 40), (32, 2049, 9)])
 @pytest.mark.parametrize("lanes", [1, 2, 4])
 def test_lanes_per_machine(gpu_lib, machines, n, fanin, lanes):
-    """Every cell format, ring and place of the placement bytes that is built with as many lanes: machines without operations and with
-    one, lists that end in the middle of a round, cycles, malformed candidates, limits, an odd last workgroup."""
+    """Every cell format, ring and place of the placement bytes that is built with as many lanes (or with fewer: tests/test_host_launches.py sees which
+    kernel each of these launches): machines without operations and with one, lists that end in the middle of a round, cycles, malformed
+    candidates, limits, an odd last workgroup."""
     rng = np.random.default_rng(machines * 10000 + n)
     per_wave = 64 // (1 << (machines - 1).bit_length())
     if lanes > per_wave:

@@ -1,10 +1,11 @@
 """What the library's host side asks of the HIP runtime, without a GPU (tests/fake_hip.c): handles that fit the memory only
-without the pipeline kernels, memory given back, grids that every launch can have, what the order lists take."""
+without the pipeline kernels or with shorter order lists, memory given back, grids that every launch can have, the ring kernel's lanes per machine."""
 from __future__ import annotations
 
 import ctypes
 import json
 import os
+import re
 import subprocess
 import sys
 
@@ -70,6 +71,26 @@ def _in_child(shim):
             hp = dagsched._HostProblem(machines, rp, ci, *args, n_cand, 0, 0, shape=dict(cand_per_block=per_wave, placement_mode=1, ring_slots=8, feeders=2, state_bits=16))
             used.append(make(hp, ())["used"])
         got["list entries"][name] = (used[1] - used[0]) // 128
+    # the ring kernel that is launched: lanes per machine and kind, of every shape that tests/test_gpu_ring_lanes.py asks for
+    fake.fake_kernel.restype = ctypes.c_char_p
+    got["lanes"] = []
+    for machines, n, fanin in RING_PROBLEMS:
+        per_wave = 64 // (1 << (machines - 1).bit_length())
+        for lanes in (1, 2, 4):
+            if lanes > per_wave:
+                continue
+            g = per_wave // lanes
+            w = W.random_instance(np.random.default_rng(machines * 10000 + n), n, machines, 2 * g + 3, max_fanin=fanin, frac_arbitrary=0.25, frac_bad=0.15)
+            for bits in (16, 32):
+                for pib, ring, feeders in RING_SHAPES:
+                    if pib == 2 and machines > 16:
+                        continue
+                    hp = dagsched._HostProblem(machines, w.row_ptr, w.col_idx, w.dur, w.comm, w.mem_delta, w.n_cand, 0, 0, shape=dict(
+                        cand_per_block=g, placement_mode=pib, ring_slots=ring, feeders=feeders, state_bits=bits, ignore_shared_placement=1))
+                    made = make(hp, (w.n_cand,))
+                    names = [fake.fake_kernel(i).decode() for i in range(made["calls"][0][1])]
+                    of = [[int(x) for x in re.findall(r"Li(\d+)E", m)] for m in re.findall(r"relax_ring_kernelI((?:Li\d+E)+)", " ".join(names))]
+                    got["lanes"].append((lanes, bits, pib, ring, feeders, made["variant"], of))
     # lists of op parts: without the memory for them, and where they would take more than 1 GiB
     rng = np.random.default_rng(9)
     rp, ci = W.random_dag(rng, 2000, 40, window=100)
@@ -80,6 +101,9 @@ def _in_child(shim):
     print(json.dumps(got))
 
 
+# (machines, operations, fan-in) and (place of the placement bytes, slots, feeders) of test_lanes_per_machine there
+RING_PROBLEMS = [(1, 1, 1), (1, 130, 2), (2, 3, 1), (3, 65, 4), (4, 64, 9), (7, 333, 1), (8, 257, 14), (11, 1200, 3), (16, 515, 6), (17, 700, 2), (31, 1024, 40), (32, 2049, 9)]
+RING_SHAPES = [(1, 4, 1), (1, 4, 2), (1, 8, 2), (1, 8, 3), (2, 8, 1), (0, 8, 2), (0, 16, 3)]
 # (machines, operations, fan-in, window) of tests/test_gpu_ring_lanes.py
 LISTS = {"one operation to a machine": (64, 70, 9, 40), "a long chain": (16, 1464, 9, 25), "the same, odd": (32, 1025, 14, 30), "wide": (16, 1403, 9, None),
          "many parts": (8, 301, 60, 100), "more parts": (16, 700, 62, 90)}
@@ -88,7 +112,7 @@ LISTS = {"one operation to a machine": (64, 70, 9, 40), "a long chain": (16, 146
 @pytest.fixture(scope="module")
 def seen(tmp_path_factory):
     shim = str(tmp_path_factory.mktemp("fake") / "libfake_hip.so")
-    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-w", *ATTRIBUTES, os.path.join(HERE, "fake_hip.c"), "-o", shim], check=True)
+    subprocess.run(["gcc", "-O1", "-shared", "-fPIC", "-w", *ATTRIBUTES, os.path.join(HERE, "fake_hip.c"), "-o", shim, "-ldl"], check=True)
     from paper_2503_09357_amd import _build
     _build.ensure_hip()
     run = subprocess.run([sys.executable, os.path.abspath(__file__), shim], stdout=subprocess.PIPE, check=True, timeout=600)
@@ -123,6 +147,20 @@ def test_order_lists_of_operations_or_of_parts(seen, name):
     n = LISTS[name][1]
     assert (seen["list entries"][name] == (n + 63) // 64 * 64) == (name in ("one operation to a machine", "a long chain", "the same, odd"))
     assert seen["list entries"][name] >= n
+
+
+def test_the_ring_kernel_has_the_lanes_it_is_asked_for(seen):
+    """As many lanes per machine as the candidates of a workgroup leave a wavefront, where that is built: placement bytes in L2 with sixteen slots and
+    three feeders two at most, and one where no operation waits for more than one other (the kind of one predecessor has two feeders)."""
+    counted = {1: 0, 2: 0, 4: 0}
+    for lanes, bits, pib, ring, feeders, variant, kernels in seen["lanes"]:
+        if variant not in (3, 4, 5):
+            continue
+        slots, launched_feeders, _, where, kind, _, sub = kernels[0]
+        assert (slots, launched_feeders, where) == (ring, feeders, pib)
+        assert sub == (lanes if feeders < 3 else 1 if kind == 3 else min(lanes, 2)), (lanes, bits, pib, ring, feeders, kernels)
+        counted[sub] += 1
+    assert min(counted.values()) > 50, counted
 
 
 def test_lists_of_parts_that_do_not_fit(seen):
