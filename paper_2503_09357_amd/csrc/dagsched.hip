@@ -567,7 +567,7 @@ RingPlan plan_ring(const dagsched_desc_t *d, const std::vector<int32_t> &pred_pt
   // and the batch has twice or four times the workgroups, whose four wavefronts all issue.  Fitted to 2000 problems with every number of lanes measured (16 to 24000 operations on
   // 2 to 32 machines, 64 to 40000 candidates; random, layered and MoE graphs, pipelines): the shape taken is 0.7 % slower than the best one on the average.  By the lanes' gain alone, with
   // 5 % for every further workgroup on the CU, it was 9.6 %, and up to twice the time on small graphs in large batches.  Lanes 1 and 2, and 4 where a wavefront has them (us): 16 operations on 8
-  // machines, 12000 candidates 15, 29, 43; 1000 on 30, 6000: 60, 72; 3000 on 30, 3000: 112, 92; 1000 on 4, 64: 59, 44, 40; MoE graph on 32, 4096: 1049, 949.
+  // machines, 12000 candidates 15, 29, 43; 1000 on 30, 6000: 60, 72; 3000 on 30, 3000: 112, 92; 1000 on 4, 64: 60, 46, 41; MoE graph on 32, 4096: 1049, 949.
   // Lists of op parts are up to sixteen times as long as lists of operations.  Half as long again and beyond 1 GiB for the handle, or where the caller has found no memory for
   // them (short_lists), they are not taken, nor are several lanes per machine, which need them: what fits with lists of operations is not refused.
   const int64_t rows_ops = ((int64_t)N + 63) / 64 * 64, rows_parts = (plan.total_parts + 63) / 64 * 64;

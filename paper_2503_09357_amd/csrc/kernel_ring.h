@@ -1,20 +1,20 @@
 // Ring kernel: the fast evaluation path.
 //
 // Workgroup = 2 + FEEDERS wavefronts with a role, which never meet at a barrier while the schedule is being
-// relaxed (further wavefronts, if launched, only help with ingest); lane (g, j) of every wavefront stands for
-// machine j of candidate g:
+// relaxed (further wavefronts, if launched, only help with ingest); lane (g, j, i) of every wavefront is the i-th of the SUB
+// lanes of machine j of candidate g, and has a ring of its own:
 //
 //   wave 0, the RELAXER   pops compact "ops" from a per-lane ring in LDS and runs the max-plus
 //                         recurrence
 //                           s_v = max(0, e_chainpred, max_u e_u + delta(u,v)),  e_v = s_v + D^o_v
 //                         (eqs. (3),(7),(11)-(13), Sec. III) against the end-time array of its
 //                         candidate in LDS.  Its loop touches LDS only and is branch-free.
-//   waves 1..FEEDERS, the FEEDERS  walk machine j's order list, fetch the shared operator records from
+//   waves 1..FEEDERS, the FEEDERS  walk machine j's order list, every SUB-th op of it for a lane, fetch the shared operator records from
 //                         L2, look up the placement of every DAG predecessor (one byte or four bits per
 //                         node in LDS, or one byte in L2) and the channel delay (LDS), and push the
 //                         resulting op into the relaxer's ring.
-//   wave FEEDERS + 1, the ACCOUNTANT  walks the order lists and takes the peak of each machine's running
-//                         memory level (eqs. (17)-(19)), which depends on the order only.
+//   wave FEEDERS + 1, the ACCOUNTANT  walks the order lists, a stretch of the machine's to each of its lanes, and takes the peak of each
+//                         machine's running memory level (eqs. (17)-(19)), which depends on the order only.
 //
 // The feeders run ahead and absorb every global-memory latency.  A lone wavefront issues an instruction
 // every few cycles at best and waits out every LDS round trip, so the relaxer's trip is kept short and
@@ -140,9 +140,10 @@ struct RingParams {
 // is what the lane before has just worked out.  The lane whose op is the next in the order (the head) has a finite
 // x_acc, the others one of kNotDone or more; whatever waits for an op that has not run is above kNotDone as well, so
 // the test whether an op runs is the same in every lane.  MoE graph: 2040 trips of 240 cycles with one lane (of two candidates in a
-// wavefront), 1340 of 262 with two; random graph of 3001 operations on 11 machines: 510 of 290, 150 of 375 with four.  Whole evaluations, us, before and now:
-// MoE graph, 256 candidates 243, 180; 4096 1038, 977; random graph, 2051 candidates in the candidate-minor layout 238, 131; 1F1B pipeline of 64 operations, 1024 candidates
-// 13.6, 10.1.
+// wavefront), 1340 of 262 with two; random graph of 3001 operations on 11 machines: 510 of 290, 200 of 375 with four, of which 148 would do if no
+// ring were ever empty.  Whole evaluations, us, before and now:
+// MoE graph, 256 candidates 250, 175; 4096 1034, 956; random graph, 2051 candidates in the candidate-minor layout 213, 114; 1F1B pipeline of 64 operations,
+// 1024 candidates 13.3, 10.1.
 template <int RING, int FEEDERS, int HALF, int PIBL, int KIND = 0, int PHASE = 0, int SUB = 1>
 __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
   // ring_threads(FEEDERS) threads have a role while the schedule is relaxed; the host may launch more (a
@@ -804,151 +805,151 @@ __global__ __launch_bounds__(1024) void relax_ring_kernel(RingParams p) {
       }
     } else {
       auto feed = [&](auto stepping) {
-      constexpr bool kStepping = decltype(stepping)::value;   // the lists hold operations (by_ops)
-      // A part is ADMITTED when the relaxer has copied the previous part out of its ring slot, then moves through a fixed pipeline
-      // without ever stalling:
-      //   trip t    record requested from L2
-      //   trip t+1  placement bytes of its predecessors requested (L2), or read from LDS
-      //   trip t+2  (trip t+1 when the placement bytes are in LDS) channel delays read from LDS, op packed
-      //             and written to the ring
-      // The loop is unrolled by the pipeline depth so that the registers rotate by renaming, not by moves.
-      const uint32_t k0 = has_ops ? (uint32_t)offw[ql] : 1u;
-      const uint32_t klast = has_ops ? k0 + (kStepping ? (uint32_t)cntw[ql] : totalw[ql]) - 1u : 0u;   // list position of the machine's last part (operation)
-      bool pending = false;
-      uint32_t admitted = 0, written = 0;
-      uint32_t aseq = (uint32_t)f;                            // index in the lane's stream of the next part to admit
-      uint32_t wseq = (uint32_t)f;                            // ... of the next part to write
-      // cursor: the next part to admit is the record at `addr`, at list position k (k > klast: the stream is exhausted);
-      // `ahead` is the entry after it in this feeder's share of the lane's stream
-      constexpr uint32_t kStep = kFeeders * SUB;
-      uint32_t k = kStepping ? k0 : k0 + (uint32_t)(f * SUB + sub_lane);
-      uint32_t addr = has_ops ? (uint32_t)list[min(k, klast)] : 0u;
-      uint32_t ahead = has_ops ? (uint32_t)list[min(k + kStep, klast)] : 0u;
-      // Stepping: `addr` is the record's index and not a list entry, `rem` more parts of its operation follow, and `ids` are the entries of
-      // the next kFeeders operations (one trip moves the cursor by kFeeders parts, into at most that many operations).
-      uint32_t rem = addr >> vbits, ids[kFeeders];
-      auto look_ahead = [&](bool moved) {
+        constexpr bool kStepping = decltype(stepping)::value;   // the lists hold operations (by_ops)
+        // A part is ADMITTED when the relaxer has copied the previous part out of its ring slot, then moves through a fixed pipeline
+        // without ever stalling:
+        //   trip t    record requested from L2
+        //   trip t+1  placement bytes of its predecessors requested (L2), or read from LDS
+        //   trip t+2  (trip t+1 when the placement bytes are in LDS) channel delays read from LDS, op packed
+        //             and written to the ring
+        // The loop is unrolled by the pipeline depth so that the registers rotate by renaming, not by moves.
+        const uint32_t k0 = has_ops ? (uint32_t)offw[ql] : 1u;
+        const uint32_t klast = has_ops ? k0 + (kStepping ? (uint32_t)cntw[ql] : totalw[ql]) - 1u : 0u;   // list position of the machine's last part (operation)
+        bool pending = false;
+        uint32_t admitted = 0, written = 0;
+        uint32_t aseq = (uint32_t)f;                            // index in the lane's stream of the next part to admit
+        uint32_t wseq = (uint32_t)f;                            // ... of the next part to write
+        // cursor: the next part to admit is the record at `addr`, at list position k (k > klast: the stream is exhausted);
+        // `ahead` is the entry after it in this feeder's share of the lane's stream
+        constexpr uint32_t kStep = kFeeders * SUB;
+        uint32_t k = kStepping ? k0 : k0 + (uint32_t)(f * SUB + sub_lane);
+        uint32_t addr = has_ops ? (uint32_t)list[min(k, klast)] : 0u;
+        uint32_t ahead = has_ops ? (uint32_t)list[min(k + kStep, klast)] : 0u;
+        // Stepping: `addr` is the record's index and not a list entry, `rem` more parts of its operation follow, and `ids` are the entries of
+        // the next kFeeders operations (one trip moves the cursor by kFeeders parts, into at most that many operations).
+        uint32_t rem = addr >> vbits, ids[kFeeders];
+        auto look_ahead = [&](bool moved) {
 #pragma unroll
-        for (int i = 0; i < kFeeders; ++i) {
-          const uint32_t entry = list[moved ? min(k + 1u + (uint32_t)i, klast) : 0u];
-          ids[i] = moved ? entry : ids[i];
+          for (int i = 0; i < kFeeders; ++i) {
+            const uint32_t entry = list[moved ? min(k + 1u + (uint32_t)i, klast) : 0u];
+            ids[i] = moved ? entry : ids[i];
+          }
+        };
+        auto advance = [&]() {
+          const bool in_op = rem != 0;
+          addr = in_op ? addr + n_plane : ids[0] & vmask;
+          rem = in_op ? rem - 1u : ids[0] >> vbits;
+          k += in_op ? 0u : 1u;
+#pragma unroll
+          for (int i = 0; i + 1 < kFeeders; ++i) ids[i] = in_op ? ids[i] : ids[i + 1];
+        };
+        if (kStepping) {
+          addr &= vmask;
+          look_ahead(true);
+          for (int i = 0; i < f; ++i) advance();                // feeder f starts at its first own part
+          look_ahead(true);
         }
-      };
-      auto advance = [&]() {
-        const bool in_op = rem != 0;
-        addr = in_op ? addr + n_plane : ids[0] & vmask;
-        rem = in_op ? rem - 1u : ids[0] >> vbits;
-        k += in_op ? 0u : 1u;
+        // With the placement bytes in L2 the vector cache's line accesses are what bounds the CU (layered graph, window mode: its address
+        // unit busy 87 % of the time, 8.5 accesses an operation): there a lane holds the aligned block of eight entries that its next entry is in.
+        // With that here and in the accountant 953 -> 761 us for 1024 candidates of 50000 operations.
+        constexpr bool kBlocks = PIBL == 0 && !kStepping;
+        const uint4 *const blocks = (const uint4 *)list;
+        uint4 block = kBlocks && has_ops ? blocks[min(k + kStep, klast) >> 3] : make_uint4(0, 0, 0, 0);
+        struct Entry { uint4 rec; uint32_t q0, q1, q2, q3, fl; };   // fl: 1 valid
+        constexpr int kStages = PIBL ? 2 : 3;
+        Entry E[kStages];
 #pragma unroll
-        for (int i = 0; i + 1 < kFeeders; ++i) ids[i] = in_op ? ids[i] : ids[i + 1];
-      };
-      if (kStepping) {
-        addr &= vmask;
-        look_ahead(true);
-        for (int i = 0; i < f; ++i) advance();                // feeder f starts at its first own part
-        look_ahead(true);
-      }
-      // With the placement bytes in L2 the vector cache's line accesses are what bounds the CU (layered graph, window mode: its address
-      // unit busy 87 % of the time, 8.5 accesses an operation): there a lane holds the aligned block of eight entries that its next entry is in.
-      // With that here and in the accountant 953 -> 761 us for 1024 candidates of 50000 operations.
-      constexpr bool kBlocks = PIBL == 0 && !kStepping;
-      const uint4 *const blocks = (const uint4 *)list;
-      uint4 block = kBlocks && has_ops ? blocks[min(k + kStep, klast) >> 3] : make_uint4(0, 0, 0, 0);
-      struct Entry { uint4 rec; uint32_t q0, q1, q2, q3, fl; };   // fl: 1 valid
-      constexpr int kStages = PIBL ? 2 : 3;
-      Entry E[kStages];
-#pragma unroll
-      for (int i = 0; i < kStages; ++i) { E[i].rec = make_uint4(0, 0, 0, 0); E[i].q0 = E[i].q1 = E[i].q2 = E[i].q3 = 0; E[i].fl = 0; }
+        for (int i = 0; i < kStages; ++i) { E[i].rec = make_uint4(0, 0, 0, 0); E[i].q0 = E[i].q1 = E[i].q2 = E[i].q3 = 0; E[i].fl = 0; }
 
-      // The look at the relaxer's "given up" flag and the end test wait for LDS and cost a dozen instructions: once
-      // per kRounds turns of the pipeline.  Four turns where the relaxer limits (the general kind: 2 % on the MoE
-      // workload); one where the feeders do and a workgroup's last ops are waited for (3 % on the pipelines).
-      constexpr int kRounds = KIND == 0 ? 4 : 1;
-      for (uint32_t it = 0; it < p.spin_cap; it += kStages * kRounds) {
-        if (*abort_p) { k = klast + 1u; written = admitted; }   // the relaxer gave this candidate up
-        if (__ballot(!(k > klast && written == admitted)) == 0) break;
+        // The look at the relaxer's "given up" flag and the end test wait for LDS and cost a dozen instructions: once
+        // per kRounds turns of the pipeline.  Four turns where the relaxer limits (the general kind: 2 % on the MoE
+        // workload); one where the feeders do and a workgroup's last ops are waited for (3 % on the pipelines).
+        constexpr int kRounds = KIND == 0 ? 4 : 1;
+        for (uint32_t it = 0; it < p.spin_cap; it += kStages * kRounds) {
+          if (*abort_p) { k = klast + 1u; written = admitted; }   // the relaxer gave this candidate up
+          if (__ballot(!(k > klast && written == admitted)) == 0) break;
 #pragma unroll
-        for (int s_ = 0; s_ < kStages * kRounds; ++s_) {
-          const int s = s_ % kStages;
-          Entry &e0 = E[s];                             // admitted in this trip
-          Entry &e1 = E[(s + kStages - 1) % kStages];   // admitted one trip ago: its record has arrived
-          Entry &e2 = E[(s + 1) % kStages];             // the oldest: written in this trip (e1 itself when the depth is two)
-          if (kStages == 2) {
-            e1.q0 = pib(e1.rec.x & 0xFFFFu);
-            if (PR >= 2) e1.q1 = pib(e1.rec.x >> 16);
-            if (PR == 4) { e1.q2 = pib(e1.rec.y & 0xFFFFu); e1.q3 = pib(e1.rec.y >> 16); }
-          }
-          // (A) channel delays of e2
-          // (wide ops carry the machines themselves; the dummy node's machine P becomes this lane's own: no delay)
-          const uint32_t d0 = kWide ? (e2.q0 == (uint32_t)P ? (uint32_t)j : e2.q0) : commr[e2.q0 << lps];
-          const uint32_t d1 = PR < 2 ? 0u : kWide ? (e2.q1 == (uint32_t)P ? (uint32_t)j : e2.q1) : commr[e2.q1 << lps];
-          const uint32_t d2 = PR != 4 ? 0u : kWide ? (e2.q2 == (uint32_t)P ? (uint32_t)j : e2.q2) : commr[e2.q2 << lps];
-          const uint32_t d3 = PR != 4 ? 0u : kWide ? (e2.q3 == (uint32_t)P ? (uint32_t)j : e2.q3) : commr[e2.q3 << lps];
-          // (1) move the cursor past the part admitted in the previous trip and the other feeders' parts
-          // (2) the entry after it (consumed one trip later at the earliest).  Lanes whose cursor stayed
-          // keep theirs and all read the same entry instead, which costs the vector cache one line, not one per lane.
-          const bool moved = pending;
-          if (kStepping) {
-            if (moved) {
-#pragma unroll
-              for (int i = 0; i < kFeeders; ++i) advance();
+          for (int s_ = 0; s_ < kStages * kRounds; ++s_) {
+            const int s = s_ % kStages;
+            Entry &e0 = E[s];                             // admitted in this trip
+            Entry &e1 = E[(s + kStages - 1) % kStages];   // admitted one trip ago: its record has arrived
+            Entry &e2 = E[(s + 1) % kStages];             // the oldest: written in this trip (e1 itself when the depth is two)
+            if (kStages == 2) {
+              e1.q0 = pib(e1.rec.x & 0xFFFFu);
+              if (PR >= 2) e1.q1 = pib(e1.rec.x >> 16);
+              if (PR == 4) { e1.q2 = pib(e1.rec.y & 0xFFFFu); e1.q3 = pib(e1.rec.y >> 16); }
             }
-            look_ahead(moved);
-          } else if (kBlocks) {
-            k += moved ? kStep : 0u;
-            const uint32_t at = min(k, klast), lo = (at & 2u) ? block.y : block.x, hi = (at & 2u) ? block.w : block.z, w = (at & 4u) ? hi : lo;
-            const uint32_t entry = (at & 1u) ? w >> 16 : w & 0xFFFFu;
-            addr = moved ? entry : addr;
-            const uint32_t then = min(k + kStep, klast) >> 3;
-            if (moved && then != at >> 3) block = blocks[then];
-          } else {
-            addr = moved ? ahead : addr;
-            k += moved ? kStep : 0u;
-            const uint32_t entry = list[moved ? min(k + kStep, klast) : 0u];
-            ahead = moved ? entry : ahead;
-          }
-          aseq += moved ? (uint32_t)kFeeders : 0u;
-          // (3) admission
-          // (measured: with two predecessors per op a branch around the read for exhausted lanes pays, 3 %; else not, 1 %)
-          lds_vu32_t *const mark_p = (lds_vu32_t *)(ring_lane + ((aseq & (uint32_t)(RING - 1)) << 10) + 12);
-          const uint32_t mark_free = ((aseq - (uint32_t)RING) << 16) | kNotDone16;
-          if (KIND >= 2) {
-            pending = (k <= klast) && *mark_p == mark_free;
-          } else {
-            const uint32_t mark = *mark_p;
-            pending = (k <= klast) & (mark == mark_free);
-          }
-          e0.fl = pending ? 1u : 0u;
-          e0.rec = p.rec[pending ? (kStepping ? addr : record(addr)) : 0u];                 // lanes that admit nothing share one record
-          admitted += pending ? 1u : 0u;
-          // (B) placement bytes of e1's predecessors (its record was requested one trip ago)
-          if (kStages == 3) {
-            if (!(e1.fl & 1u)) e1.rec.x = e1.rec.y = (uint32_t)N | ((uint32_t)N << 16);   // nothing admitted: the dummy node's byte
-            e1.q0 = pib(e1.rec.x & 0xFFFFu);
-            if (PR >= 2) e1.q1 = pib(e1.rec.x >> 16);
-            if (PR == 4) { e1.q2 = pib(e1.rec.y & 0xFFFFu); e1.q3 = pib(e1.rec.y >> 16); }
-          }
-          // (D) pack e2 and publish it
-          if (e2.fl & 1u) {
-            const bool more = KIND == 0 && (e2.rec.z >> 31) != 0;
-            const uint32_t dst = more ? trash : kWin ? name_of(e2.rec.w >> 16) : sbase + ((e2.rec.w >> 16) << kNodeShift);
-            const uint32_t dur = e2.rec.z & 0xFFFFu;
-            lds_byte_t *const sp = ring_lane + ((wseq & (uint32_t)(RING - 1)) << 10);
-            // node ids below 32768 whenever they are shifted, so shifting both halves at once cannot carry over;
-            // the whole slot first with its free mark unchanged, then the last dword
-            const u32x4_t val = {kWin ? name_of(e2.rec.x & 0xFFFFu) | (name_of(e2.rec.x >> 16) << 16) : (e2.rec.x << kNodeShift) + base2,
-                                 kWin ? (PR == 4 ? name_of(e2.rec.y & 0xFFFFu) | (name_of(e2.rec.y >> 16) << 16) : win_dummy * 0x10001u)
-                                      : (e2.rec.y << kNodeShift) + base2,
-                                 kWide ? d0 | (d1 << 6) | (d2 << 12) | (d3 << 18) | (((e2.rec.z >> 16) & 0xFFu) << 24)
-                                       : d0 | (d1 << 8) | (d2 << 16) | (d3 << 24),
-                                 ((wseq - (uint32_t)RING) << 16) | kNotDone16};
-            *(lds_vu32x4_t *)sp = val;
-            *(lds_vu32_t *)(sp + 12) = dur | (dst << 16);
-            wseq += kFeeders;
-            ++written;
+            // (A) channel delays of e2
+            // (wide ops carry the machines themselves; the dummy node's machine P becomes this lane's own: no delay)
+            const uint32_t d0 = kWide ? (e2.q0 == (uint32_t)P ? (uint32_t)j : e2.q0) : commr[e2.q0 << lps];
+            const uint32_t d1 = PR < 2 ? 0u : kWide ? (e2.q1 == (uint32_t)P ? (uint32_t)j : e2.q1) : commr[e2.q1 << lps];
+            const uint32_t d2 = PR != 4 ? 0u : kWide ? (e2.q2 == (uint32_t)P ? (uint32_t)j : e2.q2) : commr[e2.q2 << lps];
+            const uint32_t d3 = PR != 4 ? 0u : kWide ? (e2.q3 == (uint32_t)P ? (uint32_t)j : e2.q3) : commr[e2.q3 << lps];
+            // (1) move the cursor past the part admitted in the previous trip and the other feeders' parts
+            // (2) the entry after it (consumed one trip later at the earliest).  Lanes whose cursor stayed
+            // keep theirs and all read the same entry instead, which costs the vector cache one line, not one per lane.
+            const bool moved = pending;
+            if (kStepping) {
+              if (moved) {
+#pragma unroll
+                for (int i = 0; i < kFeeders; ++i) advance();
+              }
+              look_ahead(moved);
+            } else if (kBlocks) {
+              k += moved ? kStep : 0u;
+              const uint32_t at = min(k, klast), lo = (at & 2u) ? block.y : block.x, hi = (at & 2u) ? block.w : block.z, w = (at & 4u) ? hi : lo;
+              const uint32_t entry = (at & 1u) ? w >> 16 : w & 0xFFFFu;
+              addr = moved ? entry : addr;
+              const uint32_t then = min(k + kStep, klast) >> 3;
+              if (moved && then != at >> 3) block = blocks[then];
+            } else {
+              addr = moved ? ahead : addr;
+              k += moved ? kStep : 0u;
+              const uint32_t entry = list[moved ? min(k + kStep, klast) : 0u];
+              ahead = moved ? entry : ahead;
+            }
+            aseq += moved ? (uint32_t)kFeeders : 0u;
+            // (3) admission
+            // (measured: with two predecessors per op a branch around the read for exhausted lanes pays, 3 %; else not, 1 %)
+            lds_vu32_t *const mark_p = (lds_vu32_t *)(ring_lane + ((aseq & (uint32_t)(RING - 1)) << 10) + 12);
+            const uint32_t mark_free = ((aseq - (uint32_t)RING) << 16) | kNotDone16;
+            if (KIND >= 2) {
+              pending = (k <= klast) && *mark_p == mark_free;
+            } else {
+              const uint32_t mark = *mark_p;
+              pending = (k <= klast) & (mark == mark_free);
+            }
+            e0.fl = pending ? 1u : 0u;
+            e0.rec = p.rec[pending ? (kStepping ? addr : record(addr)) : 0u];                 // lanes that admit nothing share one record
+            admitted += pending ? 1u : 0u;
+            // (B) placement bytes of e1's predecessors (its record was requested one trip ago)
+            if (kStages == 3) {
+              if (!(e1.fl & 1u)) e1.rec.x = e1.rec.y = (uint32_t)N | ((uint32_t)N << 16);   // nothing admitted: the dummy node's byte
+              e1.q0 = pib(e1.rec.x & 0xFFFFu);
+              if (PR >= 2) e1.q1 = pib(e1.rec.x >> 16);
+              if (PR == 4) { e1.q2 = pib(e1.rec.y & 0xFFFFu); e1.q3 = pib(e1.rec.y >> 16); }
+            }
+            // (D) pack e2 and publish it
+            if (e2.fl & 1u) {
+              const bool more = KIND == 0 && (e2.rec.z >> 31) != 0;
+              const uint32_t dst = more ? trash : kWin ? name_of(e2.rec.w >> 16) : sbase + ((e2.rec.w >> 16) << kNodeShift);
+              const uint32_t dur = e2.rec.z & 0xFFFFu;
+              lds_byte_t *const sp = ring_lane + ((wseq & (uint32_t)(RING - 1)) << 10);
+              // node ids below 32768 whenever they are shifted, so shifting both halves at once cannot carry over;
+              // the whole slot first with its free mark unchanged, then the last dword
+              const u32x4_t val = {kWin ? name_of(e2.rec.x & 0xFFFFu) | (name_of(e2.rec.x >> 16) << 16) : (e2.rec.x << kNodeShift) + base2,
+                                   kWin ? (PR == 4 ? name_of(e2.rec.y & 0xFFFFu) | (name_of(e2.rec.y >> 16) << 16) : win_dummy * 0x10001u)
+                                        : (e2.rec.y << kNodeShift) + base2,
+                                   kWide ? d0 | (d1 << 6) | (d2 << 12) | (d3 << 18) | (((e2.rec.z >> 16) & 0xFFu) << 24)
+                                         : d0 | (d1 << 8) | (d2 << 16) | (d3 << 24),
+                                   ((wseq - (uint32_t)RING) << 16) | kNotDone16};
+              *(lds_vu32x4_t *)sp = val;
+              *(lds_vu32_t *)(sp + 12) = dur | (dst << 16);
+              wseq += kFeeders;
+              ++written;
+            }
           }
         }
-      }
       };
       if constexpr (KIND == 0 && SUB == 1) {
         if (by_ops) feed(std::true_type());

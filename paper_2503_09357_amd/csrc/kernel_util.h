@@ -44,7 +44,7 @@ __global__ void reset_counter_kernel(int32_t *counter) {        // two words: th
 // any workgroup size that is a multiple of 64.
 // cand_list: only the candidates cand_list[0 .. *cand_count), in turn, whatever the grid.  Where the evaluation was told the placement that the
 // candidates share, and that one keeps to the channels, these are the ones that place differently: looking at all 4096 candidates of 768
-// operations took 8 us of every 78 us of a search over orders (ten steps 801 us then; 666 with this, with 16-byte accesses in the proposals and three copies
+// operations took 8 us of every 78 us of a search over orders (ten steps 801 us then; about 700 with this, with 16-byte accesses in the proposals and three copies
 // fewer around them; ten steps with 256 candidates of the MoE graph 2253 and 2087).
 __global__ __launch_bounds__(1024) void channel_flag_kernel(int32_t N, int32_t E, int32_t P,
                                                             const uint32_t *__restrict__ edges,
